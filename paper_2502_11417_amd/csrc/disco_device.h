@@ -36,9 +36,10 @@ __device__ __forceinline__ Words philox4x32_10(u64 seed, u64 index, unsigned fie
     unsigned k0 = (unsigned)seed, k1 = (unsigned)(seed >> 32);
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        unsigned hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-        unsigned hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-        unsigned n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+        const u64 p0 = (u64)c0 * 0xD2511F53u, p1 = (u64)c2 * 0xCD9E8D57u;
+        const unsigned hi0 = (unsigned)(p0 >> 32), lo0 = (unsigned)p0, hi1 = (unsigned)(p1 >> 32), lo1 = (unsigned)p1;
+        // (three-operand xor in one instruction: the compiler makes two of the operators)
+        const unsigned n0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96), n2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
         c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
         k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
     }
@@ -48,7 +49,7 @@ __device__ __forceinline__ Words philox4x32_10(u64 seed, u64 index, unsigned fie
 // 23 random bits to a uniform on (0,1): (x >> 9 + 1/2) 2^-23, exact in fp32.
 __device__ __forceinline__ float u23(unsigned x)
 {
-    return __fmaf_rn((float)(x >> 9), 0x1p-23f, 0x1p-24f);
+    return u2f(0x3F800000u | (x >> 9)) - (1.0f - 0x1p-24f);       // in [1, 2), less 1 - 2^-24: no rounding either way
 }
 
 // Uniform variate of request i in run `run` of the stochastic baselines

@@ -14,16 +14,40 @@
 
 namespace {
 
+// Correctly rounded f / d and sqrt(x) for the operands below without the scaling steps of the general operations
+// (no operand here is near the ends of the exponent range): an approximate reciprocal (reciprocal root), one Newton
+// step, and a last correction with the exact remainder (Markstein's scheme).  That the last rounding is right for
+// every operand is not left to the theorem's conditions: the generator only ever takes logarithms of the 2^23
+// variates of u23, and for all of them both results were compared with __fdiv_rn and sqrtf.
+__device__ __forceinline__ float gen_div(float f, float d)
+{
+    const float r0 = __builtin_amdgcn_rcpf(d);
+    const float r = __fmaf_rn(__fmaf_rn(-d, r0, 1.0f), r0, r0);
+    const float q = f * r;
+    return __fmaf_rn(__fmaf_rn(-d, q, f), r, q);
+}
+__device__ __forceinline__ float gen_sqrt(float x)
+{
+    const float y = __builtin_amdgcn_rsqf(x);
+    float g = x * y, h = 0.5f * y;
+    const float e = __fmaf_rn(-h, g, 0.5f);
+    g = __fmaf_rn(g, e, g);
+    h = __fmaf_rn(h, e, h);
+    return __fmaf_rn(__fmaf_rn(-g, g, x), h, g);
+}
+
 // ln of a positive normal number: x = 2^e m with m in (sqrt(1/2), sqrt(2)],
 // ln m = 2 atanh(s), s = (m - 1) / (m + 1), odd series through s^11.
 __device__ __forceinline__ float gen_ln(float x)
 {
-    unsigned bits = f2u(x);
-    int e = (int)(bits >> 23) - 127;
-    float m = u2f((bits & 0x007FFFFFu) | 0x3F800000u);
-    if (m > 1.41421354f) { m = m * 0.5f; e = e + 1; }
+    // m = the fraction of x, halved (and e + 1) where it is above 1.41421354: the bit pattern is rebased to the
+    // successor of half that number
+    constexpr unsigned LOW = 0x3F3504F4u;
+    const unsigned rel = f2u(x) + (0x3F800000u - LOW);
+    const int e = (int)(rel >> 23) - 127;
+    const float m = u2f((rel & 0x007FFFFFu) + LOW);
     float f = m - 1.0f;
-    float s = __fdiv_rn(f, 2.0f + f);
+    float s = gen_div(f, 2.0f + f);
     float z = s * s;
     float p = __fmaf_rn(z, 0.181818187f, 0.222222224f);
     p = __fmaf_rn(z, p, 0.285714298f);
@@ -34,14 +58,16 @@ __device__ __forceinline__ float gen_ln(float x)
     return __fmaf_rn((float)e, 0.693147182f, lnm);
 }
 
+// Adding this to |x| < 2^22 rounds x to the nearest integer (ties to even) and leaves it in the sum's low bits.
+constexpr float GEN_RINT = 12582912.0f;
+
 // exp on [-86, 88]: n = rint(x log2 e), r = x - n ln 2 (two-part ln 2),
 // series of e^r through r^7, exact scaling by 2^n.
 __device__ __forceinline__ float gen_exp(float x)
 {
-    x = (x < -86.0f) ? -86.0f : x;
-    x = (x > 88.0f) ? 88.0f : x;
-    float t = x * 1.44269502f;
-    float n = rintf(t);
+    x = __builtin_amdgcn_fmed3f(x, -86.0f, 88.0f);
+    float t = x * 1.44269502f + GEN_RINT;
+    float n = t - GEN_RINT;
     float r = __fmaf_rn(n, -0.693145752f, x);
     r = __fmaf_rn(n, -1.42860677e-06f, r);
     float p = __fmaf_rn(r, 1.98412701e-04f, 1.38888892e-03f);
@@ -51,16 +77,15 @@ __device__ __forceinline__ float gen_exp(float x)
     p = __fmaf_rn(r, p, 0.5f);
     p = __fmaf_rn(r, p, 1.0f);
     p = __fmaf_rn(r, p, 1.0f);
-    int ni = (int)n;
-    float scale = u2f((unsigned)(ni + 127) << 23);
-    return p * scale;
+    return p * u2f((f2u(t) << 23) + 0x3F800000u);            // 2^n: the shift leaves n alone of the sum's bits
 }
 
 // cos(2 pi u), u in (0,1): quadrant q = rint(4u), v = u - q/4 exactly,
 // a = 2 pi v in [-pi/4, pi/4], series of cos and sin.
 __device__ __forceinline__ float gen_cos2pi(float u)
 {
-    float q = rintf(4.0f * u);
+    const float t = 4.0f * u + GEN_RINT;
+    float q = t - GEN_RINT;
     float v = __fmaf_rn(q, -0.25f, u);
     float a = v * 6.28318548f;
     float a2 = a * a;
@@ -75,15 +100,15 @@ __device__ __forceinline__ float gen_cos2pi(float u)
     s = __fmaf_rn(a2, s, -0.166666672f);
     s = __fmaf_rn(a2, s, 1.0f);
     s = s * a;
-    int qi = (int)q & 3;
-    float res = (qi & 1) ? s : c;
+    const unsigned qi = f2u(t);
+    const float res = (qi & 1u) ? s : c;
     // q = 0: c, 1: -s, 2: -c, 3: s
-    return (qi == 1 || qi == 2) ? -res : res;
+    return u2f(f2u(res) ^ (((qi + 1u) << 30) & 0x80000000u));
 }
 
 __device__ __forceinline__ float gen_normal(unsigned w0, unsigned w1)
 {
-    float rad = sqrtf(-2.0f * gen_ln(u23(w0)));   // IEEE-rounded square root
+    float rad = gen_sqrt(-2.0f * gen_ln(u23(w0)));
     return rad * gen_cos2pi(u23(w1));
 }
 
@@ -205,74 +230,112 @@ __global__ __launch_bounds__(GO_BLOCK) void k_gen_offsets(i64 n, i64 per_thread,
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) tok_off[n] = run;
 }
 
-// Per-token gap in front of global token index j (the first token's is unused).
-__global__ __launch_bounds__(256) void k_gen_gaps(disco_gen_params g, i64 n_tok, float* tok_arr)
+// Per-token gap in front of global token index j.  stall_below: the variates u23 of which are below the stall
+// probability are those of w >> 9 below this number (a uniform bound instead of a conversion per token).
+__device__ __forceinline__ unsigned gen_stall_below(float p)
 {
-    i64 j = (i64)blockIdx.x * blockDim.x + threadIdx.x;
-    i64 stride = (i64)gridDim.x * blockDim.x;
-    for (; j < n_tok; j += stride) {
-        Words w = philox4x32_10(g.seed, (u64)j, F_GAP);
-        float gap;
-        if (u23(w.w2) < g.gap_stall_p)
-            gap = __fmaf_rn(u23(w.w3), g.gap_stall_hi - g.gap_stall_lo, g.gap_stall_lo);
-        else
-            gap = gen_lognormal(w.w0, w.w1, g.gap_mu, g.gap_sigma);
-        tok_arr[j] = gap;
+    unsigned lo = 0u, hi = 1u << 23;                         // u23 grows with its bits: the first that is not below p
+    while (lo < hi) {
+        const unsigned mid = (lo + hi) >> 1;
+        if (u23(mid << 9) < p) lo = mid + 1u; else hi = mid;
+    }
+    return lo;
+}
+__device__ __forceinline__ float gen_gap(const disco_gen_params& g, unsigned stall_below, u64 j)
+{
+    const Words w = philox4x32_10(g.seed, j, F_GAP);
+    const float stall = __fmaf_rn(u23(w.w3), g.gap_stall_hi - g.gap_stall_lo, g.gap_stall_lo);
+    const float gap = gen_lognormal(w.w0, w.w1, g.gap_mu, g.gap_sigma);
+    return (w.w2 >> 9) < stall_below ? stall : gap;
+}
+
+// Arrival offsets: running fp32 sum of a request's gaps in index order (the first token's offset is 0, its gap
+// unused).  The order of the additions is part of the trace's definition, so one lane adds up a request token after
+// token; everything else is spread over the wave.  A wave owns R requests and goes through them in pieces of
+// K = 1024 / R tokens, as long as any has tokens left: all lanes make the gaps of one row's piece after the other
+// (the work follows the tokens, not the longest request), the owner of each row adds them up in LDS, all lanes store
+// the offsets.  Pieces start at multiples of 32 tokens, so they are whole lines of the token array but for a
+// request's ends.
+// Bound by the arithmetic of the gaps: 168 vector instructions per 64 tokens at 3.3 cycles each (18 of them wide
+// multiplications of the counter-based generator); the gaps never reach device memory.  4.3 KB of LDS and 56
+// registers per wave leave eight waves per SIMD (16 KB tiles of 64 requests: four waves, a tenth slower).
+// 491 M tokens of 10^6 requests: 2.09 ms; gaps and sums in two kernels with the gaps in device memory between them
+// took 1.9 + 5.2 ms, the second waiting for the longest of every 256 requests.  1 M tokens of 2000 requests: 1.12 ms
+// -> 0.07 ms.
+constexpr int GT_LOG_TILE = 10;
+
+template <int LOG_R, bool WIDE>
+__global__ __launch_bounds__(64) void k_gen_tokens(disco_gen_params g, i64 n_req, const i64* __restrict__ tok_off,
+                                                   float* __restrict__ tok_arr)
+{
+    constexpr int R = 1 << LOG_R, LOG_K = GT_LOG_TILE - LOG_R, K = 1 << LOG_K;
+    constexpr int KS = K + 4;                                // row stride: 16-byte accesses of a lane per row spread over the banks
+    static_assert(LOG_K >= 6, "a step is 64 tokens of one row");
+    __shared__ __align__(16) float tile[R * KS];
+    const int lane = threadIdx.x;
+    const unsigned stall_below = gen_stall_below(g.gap_stall_p);
+    const i64 i = (i64)blockIdx.x * R + lane;
+    i64 at = 0;                                              // token index of the row's next piece (a multiple of 32)
+    int lo = 0, left = 0;                                    // the request's first token in the first piece, tokens left from its start
+    if (lane < R && i < n_req) {
+        const i64 a = tok_off[i];
+        at = a & ~(i64)31;
+        lo = (int)(a - at);
+        left = (int)(tok_off[i + 1] - at);
+    }
+    int gap_lo = lo + 1;                                     // first token of the piece that a gap is added for
+    float acc = 0.0f;
+    for (u64 m = __ballot(left > 0); m != 0ull; m = __ballot(left > 0)) {
+        for (u64 rows = m; rows != 0ull; rows &= rows - 1ull) {
+            const int r = __ffsll((long long)rows) - 1;
+            const u64 base = bcast_u64((u64)at, r);
+            const int r_lo = bcast_i(gap_lo, r), r_hi = bcast_i(left, r);
+#pragma unroll 2
+            for (int q0 = 0; q0 < K; q0 += 64) {
+                const int q = q0 + lane;
+                float gap = 0.0f;
+                if (q0 < r_hi) {                             // (the same in every lane)
+                    u64 j = base + (u64)q;
+                    if (!WIDE) j = (unsigned)base + (unsigned)q;     // (all token indices below 2^32: the counter's high word is 0)
+                    gap = gen_gap(g, stall_below, j);
+                    gap = (q >= r_lo && q < r_hi) ? gap : 0.0f;      // (a gap of 0 leaves the sum as it is)
+                }
+                tile[r * KS + q] = gap;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();                     // one wave per workgroup: LDS accesses are in order
+        if (left > 0) {
+            float4* row = reinterpret_cast<float4*>(&tile[lane * KS]);
+#pragma unroll 8
+            for (int q = 0; q < K / 4; ++q) {
+                float4 v = row[q];
+                v.x = acc + v.x; v.y = v.x + v.y; v.z = v.y + v.z; v.w = v.z + v.w;
+                acc = v.w;
+                row[q] = v;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        for (u64 rows = m; rows != 0ull; rows &= rows - 1ull) {
+            const int r = __ffsll((long long)rows) - 1;
+            float* dst = tok_arr + (i64)bcast_u64((u64)at, r);
+            const int r_lo = bcast_i(lo, r), r_hi = bcast_i(left, r);
+#pragma unroll 2
+            for (int q0 = 0; q0 < K; q0 += 64) {
+                const int q = q0 + lane;
+                if (q >= r_lo && q < r_hi) dst[q] = tile[r * KS + q];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        at += K; left -= K; lo = 0; gap_lo = 0;
     }
 }
 
-// Arrival offsets: running fp32 sum of a request's gaps in index order, in
-// place.  The order of the additions is part of the trace's definition, so
-// every request is summed by one thread, token after token; the tokens pass
-// through LDS so that device memory is read and written in contiguous
-// whole 128-byte lines: a workgroup takes 256 consecutive requests and moves
-// one line (GA_K tokens) of each per round, 32 threads per request and line;
-// the lines a request shares with its neighbours are touched by both, each
-// moving only its own tokens.
-constexpr int GA_BLOCK = 256;
-constexpr int GA_K = 32;
-
-__global__ __launch_bounds__(GA_BLOCK) void k_gen_arrivals(i64 n_req, const i64* __restrict__ tok_off, float* __restrict__ tok_arr)
+template <int LOG_R>
+void launch_tokens(const disco_gen_params& g, i64 n, i64 n_tok, const i64* tok_off, float* tok_arr, hipStream_t stream)
 {
-    __shared__ float tile[GA_BLOCK][GA_K + 1];               // odd row stride: a thread per row without bank conflicts
-    __shared__ i64 s_off[GA_BLOCK];                          // the 128-byte boundary at or below the request's first token
-    __shared__ int s_lo[GA_BLOCK], s_len[GA_BLOCK];          // first token counted from that boundary, number of tokens
-    __shared__ int s_max;
-    const int t = threadIdx.x;
-    const i64 i = (i64)blockIdx.x * GA_BLOCK + t;
-    i64 a = 0;
-    int lo = 0, len = 0;
-    if (i < n_req) {
-        const i64 first = tok_off[i];
-        a = first & ~(i64)(GA_K - 1);                        // (tok_arr itself is at least 128-byte aligned)
-        lo = (int)(first - a);
-        len = (int)(tok_off[i + 1] - a);
-    }
-    if (t == 0) s_max = 0;
-    s_off[t] = a; s_lo[t] = lo; s_len[t] = len - lo;
-    __syncthreads();
-    atomicMax(&s_max, len);
-    __syncthreads();
-    const int maxlen = s_max;
-    const int sub = t & (GA_K - 1), grp = t / GA_K;
-    float acc = 0.0f;
-    for (int c0 = 0; c0 < maxlen; c0 += GA_K) {
-        // pieces of GA_K tokens = whole 128-byte lines of the token array, 32 threads per request and piece
-#pragma unroll 8
-        for (int r = grp; r < GA_BLOCK; r += GA_BLOCK / GA_K)
-            if ((unsigned)(c0 + sub - s_lo[r]) < (unsigned)s_len[r]) tile[r][sub] = tok_arr[s_off[r] + c0 + sub];
-        __syncthreads();
-        const int q0 = lo - c0 > 0 ? lo - c0 : 0, q1 = len - c0 < GA_K ? len - c0 : GA_K;
-        for (int q = q0; q < q1; ++q) {
-            if (c0 + q > lo) acc = acc + tile[t][q];         // (the first token's offset is 0, its gap unused)
-            tile[t][q] = acc;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int r = grp; r < GA_BLOCK; r += GA_BLOCK / GA_K)
-            if ((unsigned)(c0 + sub - s_lo[r]) < (unsigned)s_len[r]) tok_arr[s_off[r] + c0 + sub] = tile[r][sub];
-        __syncthreads();
-    }
+    const dim3 grid((unsigned)((n + (1 << LOG_R) - 1) >> LOG_R));
+    if (n_tok <= 0xFFFFFFFFll) hipLaunchKernelGGL((k_gen_tokens<LOG_R, false>), grid, dim3(64), 0, stream, g, n, tok_off, tok_arr);
+    else hipLaunchKernelGGL((k_gen_tokens<LOG_R, true>), grid, dim3(64), 0, stream, g, n, tok_off, tok_arr);
 }
 
 }  // namespace
@@ -321,11 +384,11 @@ extern "C" int32_t disco_gen_trace(const disco_gen_params* g, disco_trace* tr, i
         if (tr->n_tok < 0) return DISCO_ERR_SHAPE;
         if (tr->n_tok > 0) {
             if (!tr->tok_arr || !tr->tok_off) return DISCO_ERR_NULL;
-            i64 want = (tr->n_tok + 255) / 256;
-            unsigned blocks = (unsigned)(want < 65536 ? want : 65536);
-            hipLaunchKernelGGL(k_gen_gaps, dim3(blocks), dim3(256), 0, stream, *g, tr->n_tok, tr->tok_arr);
-            hipLaunchKernelGGL(k_gen_arrivals, dim3((unsigned)((n + GA_BLOCK - 1) / GA_BLOCK)), dim3(GA_BLOCK), 0, stream, n,
-                               tr->tok_off, tr->tok_arr);
+            // requests per wave: 16 where that leaves two waves per SIMD, fewer on smaller batches, so that their tokens are
+            // not a few waves' serial work (20 000 requests: 106 us with 4 per wave, 226 with 1; 2000: 68 with 1)
+            if (n >= 2048 * 16) launch_tokens<4>(*g, n, tr->n_tok, tr->tok_off, tr->tok_arr, stream);
+            else if (n >= 2048 * 4) launch_tokens<2>(*g, n, tr->n_tok, tr->tok_off, tr->tok_arr, stream);
+            else launch_tokens<0>(*g, n, tr->n_tok, tr->tok_off, tr->tok_arr, stream);
             DISCO_HIP(hipGetLastError());
         }
     }
