@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import disco_inputs as DI
+from oracle import disco_ingest as I
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,55 @@ def test_generated_tokens(B, oracle, n_req, out_mu, out_hi, stall_p):
     assert got.n_tok == want["n_tok"]
     same_bits(got.tok_off.cpu().numpy(), want["tok_off"], "tok_off")
     same_bits(got.tok_arr.cpu().numpy(), want["tok_arr"], "tok_arr")
+
+
+# requests per wave of the ingest: 1 below 131072 requests, then 16; timestamps in pairs, or one by one where the array
+# starts off a 16-byte boundary; request lengths around the pairs and the steps of 512
+@pytest.mark.parametrize("n_req,shift", [(1, 0), (1, 1), (131_071, 0), (131_072, 1), (131_087, 0)])
+def test_ingested_offsets(B, n_req, shift):
+    print(f"ingested offsets: n_req={n_req} shift={shift}", flush=True)
+    rng = np.random.default_rng(n_req + shift)
+    n = rng.choice([0, 1, 2, 3, 7], n_req) if n_req > 1 else np.array([5])
+    long = [0, 1, 2, 127, 128, 129, 511, 512, 513, 1025]
+    for i, length in enumerate(long[:max(0, n_req - 1)]):
+        n[i * n_req // len(long)] = length
+    off = np.zeros(n_req + 1, np.int64)
+    np.cumsum(n, out=off[1:])
+    send = 1.7e9 + np.cumsum(rng.exponential(0.3, n_req))
+    tok = np.repeat(send, n) + rng.random(int(off[-1])) * 30.0
+    at = torch.zeros(len(tok) + shift, dtype=torch.float64, device="cuda")[shift:]
+    at.copy_(torch.from_numpy(tok))
+    got = B.disco_ingest_trace(torch.from_numpy(send).cuda(), at, torch.from_numpy(off).cuda(),
+                               torch.ones(n_req, dtype=torch.int32, device="cuda"))
+    first = tok[np.minimum(off[:-1], len(tok) - 1)]
+    same_bits(got.tok_arr.cpu().numpy(), (tok - np.repeat(first, n)).astype(np.float32), "tok_arr")
+    same_bits(got.output_len.cpu().numpy(), n.astype(np.int32), "output_len")
+    ttft = got.srv_ttft.cpu().numpy()
+    assert np.isnan(ttft[n == 0]).all()
+    same_bits(ttft[n > 0], (first - send).astype(np.float32)[n > 0], "srv_ttft")
+
+
+# token check: vectors of four from the first 16-byte boundary on, steps of 256 vectors; a decrease anywhere is found,
+# the steps down to the next request's first token are none
+@pytest.mark.parametrize("lengths", [[1], [3], [2, 1, 2], [1] * 9, [1023, 2, 1025], [4096, 1, 1, 300]])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_decreasing_tokens_are_found_anywhere(B, lengths, shift):
+    print(f"token check: lengths={lengths} shift={shift}", flush=True)
+    n = np.array(lengths)
+    off = np.zeros(len(n) + 1, np.int64)
+    np.cumsum(n, out=off[1:])
+    total = int(off[-1])
+    inside = np.arange(total) - np.repeat(off[:-1], n)
+    arr = (0.25 * inside).astype(np.float32)
+    buf = torch.zeros(total + shift, dtype=torch.float32, device="cuda")[shift:]
+    ones = torch.ones(len(n), dtype=torch.int32, device="cuda")
+    tr = B.Trace(n_req=len(n), n_tok=total, prompt_len=ones, output_len=torch.from_numpy(n.astype(np.int32)).cuda(),
+                 srv_ttft=ones.float(), tok_off=torch.from_numpy(off).cuda(), tok_arr=buf, dev_pre_spt_s=0.1, dev_dec_spt_s=0.1)
+    buf.copy_(torch.from_numpy(arr))
+    assert B.disco_validate_trace(tr) == 0
+    places = np.flatnonzero(inside >= 2)
+    for j in places if len(places) < 8 else [*places[:4], *places[len(places) // 2:][:2], *places[-4:]]:
+        planted = arr.copy()
+        planted[j] = np.float32(0.25 * (inside[j] - 1) - 0.125)
+        buf.copy_(torch.from_numpy(planted))
+        assert B.disco_validate_trace(tr) == B.ERR["range"], j
