@@ -42,6 +42,7 @@ namespace {
 constexpr int PP_LDS_CLS = 16;
 constexpr int PP_WORDS = DISCO_PP_NMAX / 2 + 1;              // words per class: lengths 0 .. DISCO_PP_NMAX
 constexpr int AS_BLOCK = 1024;
+constexpr int DH_LDS_BINS = 64;              // delayed-token counts below this are counted in LDS: [column][count], 16 KB
 
 __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disco_policy* __restrict__ pol, int P,
                                                         const TlSummary* __restrict__ summary,
@@ -51,6 +52,7 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
                                                         unsigned* __restrict__ dhist, int use_lds)
 {
     __shared__ unsigned cnt[PP_LDS_CLS * PP_WORDS];          // 128 KB
+    __shared__ unsigned dh[DISCO_MAX_COLS * DH_LDS_BINS];
     __shared__ unsigned s_nw[2], s_base[2];                  // [0] long requests (front of the list), [1] the others (back)
     __shared__ u64 s_cls[DISCO_MAX_CLS];
     __shared__ signed char s_slot[DISCO_MAX_CLS];
@@ -62,6 +64,7 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
     if ((int)threadIdx.x < P) spol[threadIdx.x] = pol[threadIdx.x];
     if (threadIdx.x < DISCO_MAX_CLS) { s_cls[threadIdx.x] = tl->cls_mask[threadIdx.x]; s_slot[threadIdx.x] = tl->cls_slot[threadIdx.x]; }
     for (int i = threadIdx.x; i < nlds * PP_WORDS; i += AS_BLOCK) cnt[i] = 0u;
+    for (int i = threadIdx.x; i < P * DH_LDS_BINS; i += AS_BLOCK) dh[i] = 0u;
     if (threadIdx.x < 2) s_nw[threadIdx.x] = 0u;
     __syncthreads();
     const int lane = threadIdx.x & 63;
@@ -90,8 +93,11 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
                 const int dl = kind == TL_SRV_BUF ? bs.delay_s : bs.delay_d;
                 if (m[kind] == 0ull || summary_m(me) < 0 || dl <= 0) continue;
                 const int bin = dl < DISCO_DELAY_BINS - 1 ? dl : DISCO_DELAY_BINS - 1;
-                for (u64 left = m[kind]; left != 0ull; left &= left - 1ull)
-                    atomicAdd(&dhist[(size_t)(__ffsll((long long)left) - 1) * DISCO_DELAY_BINS + bin], 1u);
+                for (u64 left = m[kind]; left != 0ull; left &= left - 1ull) {
+                    const int c = __ffsll((long long)left) - 1;
+                    if (bin < DH_LDS_BINS) atomicAdd(&dh[c * DH_LDS_BINS + bin], 1u);
+                    else atomicAdd(&dhist[(size_t)c * DISCO_DELAY_BINS + bin], 1u);
+                }
             }
         }
 #pragma unroll
@@ -152,6 +158,8 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
             if (w && !lng) list[(size_t)tr.n_req - 1 - (s_base[1] + at1 + (unsigned)__popcll(sb & below))] = (unsigned)i;
         }
     }
+    for (int i = threadIdx.x; i < P * DH_LDS_BINS; i += AS_BLOCK)
+        if (dh[i]) atomicAdd(&dhist[(size_t)(i / DH_LDS_BINS) * DISCO_DELAY_BINS + i % DH_LDS_BINS], dh[i]);
     unsigned* mine = slices + (size_t)blockIdx.x * PP_LDS_CLS * PP_WORDS;
     for (int i = threadIdx.x; i < nlds * PP_WORDS; i += AS_BLOCK) mine[i] = cnt[i];
 }

@@ -25,6 +25,11 @@
 
 namespace {
 
+// Bin counts of a slot that k_tbt_select sums up in LDS.  Tables without walked timelines (constant gaps) have room for
+// digits of 13 and 14 bits, but their 21-bit window takes two passes either way, and an unstaged slot of 8192 bins reads
+// the rows of its classes bin by bin: 10^4 requests x 16 columns 120 us with 13 bits, 28 us with 11.
+constexpr int SEL_STAGED_BITS = 11;
+
 // Prepares the next pass: prefix groups of the live slots, digit width that
 // fits, or the per-slot fallback.  All threads of a workgroup (wave_only: of
 // its first wave, the only one still running); the slots are fetched side by
@@ -81,6 +86,8 @@ __device__ void tbt_plan_next(SelState* S, int P, int nq, unsigned* s_prefix, in
             w = fit_width((long)g1 * (tl.nwalk > 0 ? tl.nwalk : 1), DISCO_TL_HIST_WORDS);
             const int wg = fit_width((long)g1 * tl.ncls, DISCO_GHIST_WORDS);
             if (wg < w) w = wg;
+            // a digit wider than the select step stages in LDS only where it saves a pass
+            if (w > SEL_STAGED_BITS && (tl.left + w - 1) / w == (tl.left + SEL_STAGED_BITS - 1) / SEL_STAGED_BITS) w = SEL_STAGED_BITS;
         }
         if (w < 1) w = 1;
         if (w > tl.left) w = tl.left;
@@ -427,6 +434,36 @@ __device__ void select_slot(SelState* S, int nq, const unsigned* ghist, int s, u
     }
 }
 
+// The same for a digit of at most SEL_NARROW_BITS bits in class mode, by one wave (lane = class): many slots side by side
+// in one workgroup.
+constexpr int SEL_NARROW_BITS = 4;
+
+__device__ void select_slot_narrow(SelState* S, int nq, const unsigned* ghist, int s)
+{
+    const TlSel& tl = S->tl;
+    const int width = tl.width, ncls = tl.ncls, lane = threadIdx.x & 63;
+    SelSlot sl = S->slot[1][s];
+    const int g = tl.slot_grp[s];
+    if (sl.done || g < 0) return;                         // uniform
+    const int col = s / nq, nbins = 1 << width;
+    static_assert(DISCO_MAX_CLS <= 64, "a lane per class");
+    const bool in = lane < ncls && ((tl.cls_mask[lane] >> col) & 1ull);
+    u64 rem = (u64)sl.k_rem;
+    int dsel = -1;
+    for (int b = 0; b < nbins && dsel < 0; ++b) {
+        const u64 c = wave_sum_u64(in ? (u64)ghist[((size_t)(g * ncls + lane) << width) | (unsigned)b] : 0ull);
+        if (rem <= c) dsel = b; else rem -= c;
+    }
+    if (lane == 0) {
+        // as in select_slot: what the window does not decide starts over on raw keys
+        if (tl.window && (dsel < 0 || (dsel == 0 && tl.left == tl.window))) S->tl.restart = 1;
+        if (dsel < 0) { dsel = nbins - 1; rem = 1; }
+        sl.k_rem = (i64)rem;
+        sl.prefix = (sl.prefix << width) | (unsigned)dsel;
+        S->slot[1][s] = sl;
+    }
+}
+
 // Step 3 (one workgroup): clear the bins that were used and plan the next pass.
 __device__ void plan_pass(SelState* S, int P, int nq, unsigned* ghist, unsigned* s_prefix, int* s_grp)
 {
@@ -495,17 +532,17 @@ __global__ __launch_bounds__(1024) void k_tbt_select(SelState* S, int P, int nq,
     __shared__ u64 wsum[DISCO_MAX_CLS];
     __shared__ int s_digit;
     __shared__ u64 s_rem;
-    __shared__ u64 binsum[2048];
+    __shared__ u64 binsum[1 << SEL_STAGED_BITS];
     if (S->tl.width <= 0) return;
-    select_slot(S, nq, ghist, blockIdx.x, wsum, &s_digit, &s_rem, binsum, 2048);
+    select_slot(S, nq, ghist, blockIdx.x, wsum, &s_digit, &s_rem, binsum, 1 << SEL_STAGED_BITS);
     if (!take_last_ticket(ticket)) return;
     plan_pass(S, P, nq, ghist, reinterpret_cast<unsigned*>(binsum), reinterpret_cast<int*>(binsum + DISCO_MAX_SLOTS));
     if (threadIdx.x == 0) *ticket = 0u;
 }
 
 // A spare pass (after the passes that normally finish the selection: needed when the window was missed or the
-// digits are narrow) in one launch: workgroups by kind walk the tokens, the one that finishes last adds the
-// analytic bins, takes every slot's digit, clears the bins and plans the next pass.  One launch per pass matters
+// digits are narrow) in one launch: every workgroup adds the analytic bins of its classes and walks its share of each kind
+// of timeline; the one that finishes last takes every slot's digit, clears the bins and plans the next pass.  One launch per pass matters
 // more here than speed: normally all of them return at once.
 __global__ __launch_bounds__(1024) void k_tbt_spare(TraceView tr, i64 n_tok, int align, const disco_policy* __restrict__ pol,
                                                     TimelineArgs a, PassGrid g)
@@ -519,22 +556,28 @@ __global__ __launch_bounds__(1024) void k_tbt_spare(TraceView tr, i64 n_tok, int
     const TlSel& tl = S->tl;
     if (tl.width <= 0) return;                          // selection finished (the same answer in every workgroup)
     const unsigned bid = blockIdx.x;
+    if (!tl.fallback)                                   // the analytic bins: a class per workgroup
+        for (int c = (int)bid; c < tl.ncls; c += (int)gridDim.x) analytic_class(S, a.ghist, a.ppcnt, a.tau, c, smem);
+    __syncthreads();
     if (tl.fallback) {
-        if (bid >= g.fast + g.buf) timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, bid - g.fast - g.buf, g.general);
-    } else if (bid < g.fast) {
+        timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, bid, g.general);
+    } else {
         HistArgs h;
         h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.pass = a.pass; h.S = a.S; h.ghist = a.ghist; h.desc = a.desc; h.list = a.list;
         tl_hist_fast_body(smem, tr, n_tok, align, h, bid, g.fast);
-    } else if (bid < g.fast + g.buf) {
-        if (*a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), bid - g.fast, g.buf);
+        __syncthreads();                                // the bins are used again
+        if (*a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), bid, g.buf);
     }
     if (!take_last_ticket(a.ticket)) return;
-    if (!tl.fallback)
-        for (int c = 0; c < tl.ncls; ++c) analytic_class(S, a.ghist, a.ppcnt, a.tau, c, smem);
     __syncthreads();
-    for (int s = 0; s < a.P * a.nq; ++s) {
-        select_slot(S, a.nq, a.ghist, s, wsum, &s_digit, &s_rem, reinterpret_cast<u64*>(smem), DISCO_TL_HIST_WORDS / 2);
+    if (!tl.fallback && tl.width <= SEL_NARROW_BITS) {
+        for (int s = threadIdx.x >> 6; s < a.P * a.nq; s += (int)blockDim.x >> 6) select_slot_narrow(S, a.nq, a.ghist, s);
         __syncthreads();
+    } else {
+        for (int s = 0; s < a.P * a.nq; ++s) {
+            select_slot(S, a.nq, a.ghist, s, wsum, &s_digit, &s_rem, reinterpret_cast<u64*>(smem), DISCO_TL_HIST_WORDS / 2);
+            __syncthreads();
+        }
     }
     plan_pass(S, a.P, a.nq, a.ghist, smem, reinterpret_cast<int*>(smem + DISCO_MAX_SLOTS));
     if (threadIdx.x == 0) *a.ticket = 0u;
@@ -573,8 +616,10 @@ void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* po
         hipLaunchKernelGGL(k_tbt_side, dim3(g.analytic + g.buf + g.general), dim3(1024), 0, stream, v, n_tok, align, pol, a, g);
         hipLaunchKernelGGL(k_tbt_select, dim3((unsigned)(a.P * a.nq)), dim3(1024), 0, stream, a.S, a.P, a.nq, a.ghist, a.ticket);
     } else {
-        // small grids: an empty launch is cheaper and a needed one merely slower
-        g.analytic = 0; g.fast = cap(64); g.buf = cap(64); g.general = cap(128);
-        hipLaunchKernelGGL(k_tbt_spare, dim3(g.fast + g.buf + g.general), dim3(1024), 0, stream, v, n_tok, align, pol, a, g);
+        // one workgroup per CU: more of them make an empty launch dearer.  (A workgroup per kind and 64 of each, all slots
+        // and analytic bins left to the last workgroup: 194 us for the one remaining bit of 10^5 requests x 12 wait
+        // columns, now 50.)
+        g.analytic = 0; g.fast = g.buf = g.general = cap(256);
+        hipLaunchKernelGGL(k_tbt_spare, dim3(g.general), dim3(1024), 0, stream, v, n_tok, align, pol, a, g);
     }
 }
