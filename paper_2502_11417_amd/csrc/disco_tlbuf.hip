@@ -18,7 +18,8 @@
 //     with the operations of the general walker (probe_handoff); a hand-off
 //     to the device whose tail is provably paced, or the end of the tokens
 //     that pass the cost test, settles the request.
-// The rest is walked one request per wave with the general walker.  With
+// Behind a hand-off to the server its tokens are walked one request per wave
+// (server_tail); the rest takes a wave per request with the general walker.  With
 // totals, the kernel is the last of the statistics pass to add into them: its
 // last workgroup turns them into the columns' accumulators (without a buffer
 // column the kernel does only that).
@@ -30,12 +31,14 @@
 namespace {
 
 constexpr int TB_BLOCK = 256;                // 4 waves
-constexpr int TB_RB = 64;                    // requests per wave batch
+constexpr int TB_RB = 64;                    // requests per wave batch, at most
+constexpr int TB_FULL = 768 * 4;              // waves the chip holds at once (3 per SIMD)
 constexpr int PROBE_TOKENS = 128;            // tokens a lane steps through before the request is left to a whole wave
 
 struct BufStatsArgs {
     float tau, kt;
     int P, G;                      // columns, columns rounded up to a power of two
+    int rb;                        // requests per wave batch
     MigPartial* totals;            // DISCO_NCOPY x 64 device-wide totals, shared with the streaming kernels; nullptr: summaries only
     disco_accum* acc;              // with totals: where the workgroup that finishes last puts the columns' totals
     unsigned* ticket;
@@ -49,8 +52,9 @@ struct BufStatsArgs {
 // use them.
 struct BufStaged { u64 cols_s, cols_d; int l, n; int m_s, m_d; int delay_s, delay_d; float M_s, M_d; };
 
-// state 0: nothing settled (the request is walked), 1: no hand-off, 2: hand-off at m with a paced tail
-struct ProbeOut { int state; int m; float M; float r0; };
+// state 0: nothing settled (the request is walked), 1: no hand-off, 2: hand-off at m with a paced tail, 3: hand-off to
+// the server at m, base = the instant its arrivals count from (server_tail walks them)
+struct ProbeOut { int state; int m; float M; float r0; float base; };
 
 typedef float Float4A __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -96,14 +100,83 @@ __device__ __forceinline__ ProbeOut probe_handoff(bool active, bool src_dev, int
             }
         }
     }
-    ProbeOut o{0, -1, 0.0f, r_first};
+    ProbeOut o{0, -1, 0.0f, r_first, 0.0f};
     if (!active) return o;
     if (m >= 0) {
-        if (!src_dev && paced_tail_proven(r_m, r_first, tm_m, g_dev, tau, (float)m, M_m)) { o.state = 2; o.m = m; o.M = M_m; }
+        if (src_dev) o = ProbeOut{3, m, M_m, r_first, r_m + tm_m};
+        else if (paced_tail_proven(r_m, r_first, tm_m, g_dev, tau, (float)m, M_m)) { o.state = 2; o.m = m; o.M = M_m; }
     } else if (tend == limit) {
         o.state = 1;
     }
     return o;
+}
+
+// The server's tokens m + 1 .. n - 1 behind a hand-off of the device at token m (one request per wave, four tokens per
+// lane and chunk): running maximum M through the last token and number of delayed tokens, with the operations of the
+// general walker on the arrivals base + (a_t - a_m), or fma(t - m, gap, base) without a token array.  A chunk in which no
+// u_t exceeds the maximum so far leaves it alone, so every slot of the chunk follows from that one value; nearly all
+// chunks are of that kind (the server is faster than the reader) and need a quarter of the walker's instructions.
+// Issue bound: 10^5 requests x 12 wait columns, 31 M tokens: k_tl_stats_buf 93 us, 160 us with the general walker for
+// these tails.
+struct TailOut { float M; int delay; };
+
+__device__ __forceinline__ void server_tail_load(const float* __restrict__ arr, i64 first, i64 n_tok, int align, int len, int lane,
+                                                 float a[4])
+{
+    const int mis = (int)((first + align) & 3);
+    a[0] = a[1] = a[2] = a[3] = 0.0f;
+    if (4 * lane - mis < len) load4(arr, first - mis + 4 * lane, n_tok, a);
+}
+
+__device__ __forceinline__ TailOut server_tail(const float* __restrict__ arr, i64 off, i64 n_tok, int align, float gap, int n, int m,
+                                               float M, float base, float a_m, float tau, int lane, const float first_chunk[4])
+{
+    const i64 first = off + m + 1;                        // the first token of the tail in the token array
+    const int len = n - 1 - m;                            // its tokens (a hand-off leaves at least one)
+    const int mis = arr ? (int)((first + align) & 3) : 0;
+    int delay = 0;
+    float nxt[4] = {first_chunk[0], first_chunk[1], first_chunk[2], first_chunk[3]};
+    for (int e0 = 0; e0 < len + mis; e0 += 256) {
+        const int j0 = e0 + 4 * lane - mis;               // tail index of this lane's first element
+        float a[4], r[4], u[4], tf[4];
+        bool val[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] = nxt[q];
+        if (arr && e0 + 256 < len + mis && j0 + 256 < len) load4(arr, first + j0 + 256, n_tok, nxt);
+        bool up = false;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int j = j0 + q;
+            val[q] = j >= 0 && j < len;
+            tf[q] = (float)(m + 1 + j);
+            const float since = a[q] - a_m;
+            const float at = arr ? base + since : __fmaf_rn((float)(j + 1), gap, base);
+            r[q] = val[q] ? at : -INFINITY;
+            u[q] = __fmaf_rn(-tf[q], tau, r[q]);
+            up = up || u[q] > M;
+        }
+        float slot[4];
+        if (__ballot(up) == 0ull) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) slot[q] = __fmaf_rn(tf[q] - 1.0f, tau, M) + tau;
+        } else {
+            float mx[4], d[4];
+            mx[0] = u[0]; mx[1] = fmaxf(mx[0], u[1]); mx[2] = fmaxf(mx[1], u[2]); mx[3] = fmaxf(mx[2], u[3]);
+            const float incl = wave_incl_max_dpp(mx[3], lane);
+            const float excl = fmaxf(wave_prev(incl, -INFINITY), M);
+            // (the delivery in front of this lane's first token has the running maximum in front of it)
+            slot[0] = __fmaf_rn(tf[0] - 1.0f, tau, excl) + tau;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) { d[q] = __fmaf_rn(tf[q], tau, fmaxf(excl, mx[q])); slot[q + 1] = d[q] + tau; }
+            M = bcast_f(fmaxf(excl, mx[3]), 63);
+        }
+        bool late[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { const float lag = r[q] - slot[q]; late[q] = val[q] && lag > 0.0f; }
+        if (__ballot(late[0] || late[1] || late[2] || late[3]))
+            delay += __popcll(__ballot(late[0])) + __popcll(__ballot(late[1])) + __popcll(__ballot(late[2])) + __popcll(__ballot(late[3]));
+    }
+    return TailOut{M, delay};
 }
 
 __global__ __launch_bounds__(TB_BLOCK) void k_tl_stats_buf(TraceView tr, i64 n_tok, int align, const disco_policy* __restrict__ pol,
@@ -126,9 +199,10 @@ __global__ __launch_bounds__(TB_BLOCK) void k_tl_stats_buf(TraceView tr, i64 n_t
     u64 acc_s_dec = 0, acc_d_dec = 0, acc_repre = 0, acc_srepre = 0, acc_delay = 0, acc_mig = 0;
     double acc_tlast = 0.0;
     const i64 nwaves = (i64)gridDim.x * (TB_BLOCK / 64);
-    const i64 nbatch = (tr.n_req + TB_RB - 1) / TB_RB;
+    const int rb = a.rb;
+    const i64 nbatch = (tr.n_req + rb - 1) / rb;
     for (i64 bt = (i64)blockIdx.x * (TB_BLOCK / 64) + wave; bt < nbatch; bt += nwaves) {
-        const Batch b = load_batch(tr, spol, P, bt * TB_RB, lane, TB_RB, a.summary);
+        const Batch b = load_batch(tr, spol, P, bt * rb, lane, rb, a.summary);
         const bool has_s = b.m[TL_SRV_BUF] != 0ull, has_d = b.m[TL_DEV_BUF] != 0ull;
         if (__ballot(has_s || has_d) == 0ull) continue;
         // lane = request.  Without a hand-off the timeline is the source's own.
@@ -144,6 +218,31 @@ __global__ __launch_bounds__(TB_BLOCK) void k_tl_stats_buf(TraceView tr, i64 n_t
                                           a.bc.dc_dev, a.bc.cp_dev, a.tau, lim_d);
         if (ps.state == 2) { m_s = ps.m; M_s = ps.M; nz_s = ps.r0 != 0.0f; }
         const bool walk_s = lim_s >= 0 && ps.state == 0, walk_d = lim_d >= 0 && pd.state == 0;
+        if (pd.state == 3) { m_d = pd.m; nz_d = pd.r0 != 0.0f; }
+        // the server's tokens behind the hand-offs of the device: a wave per request, the first chunk of the next one
+        // loaded while this one is walked
+        {
+            u64 tails = __ballot(pd.state == 3);
+            const float a_m = pd.state == 3 && tr.arr ? tr.arr[b.off + pd.m] : 0.0f;
+            float ahead[4] = {0.f, 0.f, 0.f, 0.f};
+            auto load_ahead = [&](u64 left) {
+                if (!left || !tr.arr) return;
+                const int r = __ffsll((long long)left) - 1;
+                const int m = bcast_i(pd.m, r);
+                server_tail_load(tr.arr, (i64)bcast_u64((u64)b.off, r) + m + 1, n_tok, align, bcast_i(b.n, r) - 1 - m, lane, ahead);
+            };
+            load_ahead(tails);
+            while (tails) {
+                const int rq = __ffsll((long long)tails) - 1;
+                tails &= tails - 1;
+                const float chunk[4] = {ahead[0], ahead[1], ahead[2], ahead[3]};
+                load_ahead(tails);
+                const TailOut res = server_tail(tr.arr, (i64)bcast_u64((u64)b.off, rq), n_tok, align, bcast_f(b.gap, rq),
+                                                bcast_i(b.n, rq), bcast_i(pd.m, rq), bcast_f(pd.M, rq), bcast_f(pd.base, rq),
+                                                bcast_f(a_m, rq), a.tau, lane, chunk);
+                if (lane == rq) { M_d = res.M; delay_d = res.delay; }
+            }
+        }
         // one wave per request for the rest; the first chunk of the next one is loaded while this one is walked
         u64 walkers = __ballot(walk_s || walk_d);
         float ahead[4] = {0.f, 0.f, 0.f, 0.f};
@@ -177,7 +276,7 @@ __global__ __launch_bounds__(TB_BLOCK) void k_tl_stats_buf(TraceView tr, i64 n_t
                 }
             }
         }
-        const i64 i = bt * TB_RB + lane;
+        const i64 i = bt * rb + lane;
         if (has_s || has_d)
             a.bufsum[i] = BufSummary{M_s, buf_m_enc(m_s, nz_s ? 1.0f : 0.0f), delay_s, 0, M_d, buf_m_enc(m_d, nz_d ? 1.0f : 0.0f), delay_d, 0};
         if (a.totals == nullptr) continue;
@@ -252,10 +351,15 @@ void disco_launch_tl_stats_buf(const TraceView& v, i64 n_tok, const disco_policy
     s.summary = (const TlSummary*)a.summary;
     s.bc = a.bc;
     s.buffer_flag = a.buffer_flag;
-    const i64 per_block = (i64)(TB_BLOCK / 64) * TB_RB;
+    // The requests that take a whole wave are walked one after the other within a batch: where the trace has fewer than
+    // a batch of 64 for every wave the chip holds, smaller batches share them out (10^5 requests x 12 wait
+    // columns, every hand-off walked by the general walker: 179 us with batches of 64, 161 us with 32).
+    s.rb = TB_RB;
+    while (s.rb > 4 && (v.n_req + s.rb - 1) / s.rb < TB_FULL) s.rb >>= 1;
+    const i64 per_block = (i64)(TB_BLOCK / 64) * s.rb;
     i64 b = (v.n_req + per_block - 1) / per_block;
     if (b < 1) b = 1;
-    if (b > 768) b = 768;                      // what the chip holds at once (3 waves per SIMD): every workgroup ends with a ticket
+    if (b > TB_FULL / 4) b = TB_FULL / 4;                      // what the chip holds at once (3 waves per SIMD): every workgroup ends with a ticket
     const int align = (int)(((uintptr_t)v.arr >> 2) & 3);
     hipLaunchKernelGGL(k_tl_stats_buf, dim3((unsigned)b), dim3(TB_BLOCK), 0, stream, v, n_tok, align, pol, s);
 }

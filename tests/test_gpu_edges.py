@@ -5,7 +5,8 @@ import pytest
 import torch
 
 import disco_inputs as DI
-from oracle import disco_ingest as I
+from test_gpu_buffer import slow_prefill
+from test_gpu_parity import check_migration, check_stats
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +83,14 @@ def test_decreasing_tokens_are_found_anywhere(B, lengths, shift):
         planted[j] = np.float32(0.25 * (inside[j] - 1) - 0.125)
         buf.copy_(torch.from_numpy(planted))
         assert B.disco_validate_trace(tr) == B.ERR["range"], j
+
+
+# device -> server hand-offs: batches of 4 .. 64 requests per wave, tails of 1 token to several chunks of 256 from every
+# alignment, stalls among them; twelve wait columns give the TBT digits 10 + 10 + 1 bits (the last one by the narrow select)
+@pytest.mark.parametrize("n_req,max_out,stall_p", [(1, 3, 0.0), (63, 1200, 0.05), (777, 300, 0.0), (12_289, 24, 0.02)])
+def test_server_tails_of_wait_columns(B, oracle, n_req, max_out, stall_p):
+    print(f"server tails: n_req={n_req} max_out={max_out} stall_p={stall_p}", flush=True)
+    tr = slow_prefill(DI.handmade_trace(61 + n_req, n_req, tokens=True, max_out=max_out, stall_p=stall_p), 16.0)
+    specs = [dict(mode=1, l_th=-1, w_tail=DI.f32(0.04 * j), mig_mode=2) for j in range(12)]
+    check_migration(B, oracle, tr, specs, DI.TAU, DI.KAPPA_LAG, delivered_col=None, cost=DI.COST_D)
+    check_stats(B, oracle, tr, specs, DI.COST_D, tau=DI.TAU, kappa=DI.KAPPA_LAG)
