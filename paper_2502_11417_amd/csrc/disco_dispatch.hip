@@ -32,26 +32,6 @@ struct ColTotals {
     unsigned minb, maxb;
 };
 
-__device__ __forceinline__ double acc_value(int which, const disco_cost_params& c, i64 s_pre, i64 s_dec, i64 d_pre,
-                                            i64 d_dec)
-{
-    switch (which) {
-    case DISCO_ACC_TOTAL_COST: {
-        double server = server_cost_of(c, s_pre, s_dec);
-        double energy = device_energy_of(c, d_pre, d_dec);
-        double priced = c.lambda * energy;
-        return server + priced;
-    }
-    case DISCO_ACC_SERVER_COST: return server_cost_of(c, s_pre, s_dec);
-    case DISCO_ACC_DEVICE_COST: {
-        double energy = device_energy_of(c, d_pre, d_dec);
-        return c.lambda * energy;
-    }
-    case DISCO_ACC_SERVER_PREFILL_TOK: return (double)s_pre;
-    default: return (double)d_pre;
-    }
-}
-
 // One bisection step of a search: record (parameter, accumulator), halve the
 // bracket, set the parameter of the next evaluation (after the last step: the
 // feasible end of the bracket).

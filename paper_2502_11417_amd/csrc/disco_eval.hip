@@ -895,10 +895,17 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
                     spec[j].lo >= 0.0 && spec[j].hi + 2.0 <= (double)disco_search_table_max_bins();
         if (spec[j].hi > max_hi) max_hi = spec[j].hi;
     }
+    // Waits and ramp slopes of device-constrained columns: the outcomes of a request are step functions of the
+    // parameter, a pass takes eight bisection steps (disco_search.hip).  The bounds are such that no midpoint
+    // overflows and no ramp is infinity times zero.
+    bool binned = !tabulated && !is_device_pointer(templ) && disco_search_bins_bytes(n_search) <= L.total - L.slices;
+    for (int j = 0; j < n_search && binned; ++j)
+        binned = templ[j].mode == DISCO_MODE_DEVICE_CONSTRAINED && spec[j].which_param != DISCO_PARAM_L_TH &&
+                 spec[j].lo >= -1e37 && spec[j].hi <= 1e37;
     // Otherwise every pass evaluates the next `depth` levels of each search's bisection tree as columns of their
     // own and so takes `depth` bisection steps; the recorded steps are those of the plain bisection.
     const int depth = tabulated ? 0 : disco_search_depth(n_search);
-    hipLaunchKernelGGL(k_search_init, dim3(1), dim3(64), 0, stream, t, n_search, (SearchState*)(ws + L.search),
+    if (!binned) hipLaunchKernelGGL(k_search_init, dim3(1), dim3(64), 0, stream, t, n_search, (SearchState*)(ws + L.search),
                        (disco_policy*)(ws + L.pol), (disco_policy*)(ws + L.templ), depth);
     DispFin fin;
     memset(&fin, 0, sizeof(fin));
@@ -915,6 +922,9 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
         disco_launch_search_table(v, n_search, (int)max_hi + 2, (unsigned*)(ws + L.slices), L.total - L.slices,
                                   (u64*)(ws + L.ppcnt), (u64*)((unsigned*)(ws + L.ticket) + 32),
                                   (SearchState*)(ws + L.search), (disco_policy*)(ws + L.pol), out, stream);
+    } else if (binned) {
+        disco_launch_search_bins(v, n_search, n_steps, t, *cost, ws + L.slices, (SearchState*)(ws + L.search), fin.pol_rw,
+                                 (disco_policy*)(ws + L.templ), out, stream);
     } else {
         // bisection passes only need the totals their accumulators are made of
         int need = 0;

@@ -52,6 +52,12 @@ void disco_launch_dispatch_acc(const TraceView& v, const disco_policy* pol, int 
 void disco_launch_search_table(const TraceView& v, int n_search, int nbins, unsigned* scratch, size_t scratch_bytes,
                                u64* table, u64* other, SearchState* st, disco_policy* pol, disco_search_out* sout,
                                hipStream_t stream);
+// Search of w_tail or beta over device-constrained templates (in `pol`; the answers end there too), eight steps per pass.
+// `scratch`: disco_search_bins_bytes(n_search) bytes.
+size_t disco_search_bins_bytes(int n_search);
+void disco_launch_search_bins(const TraceView& v, int n_search, int n_steps, const SpecTable& spec, const disco_cost_params& cost,
+                              void* scratch, SearchState* st, disco_policy* pol, disco_policy* templ, disco_search_out* sout,
+                              hipStream_t stream);
 int disco_search_table_max_bins(void);
 void disco_launch_len_table(const TraceView& v, int nbins, unsigned* scratch, size_t scratch_bytes, u64* table, u64* other,
                             hipStream_t stream);

@@ -39,6 +39,27 @@ __device__ __forceinline__ void search_halve(int prm, double& lo, double& hi, do
     if (prm != DISCO_PARAM_L_TH) { if (above) lo = mid; else hi = mid; }
     else if (lo < hi) { if (above) lo = mid + 1.0; else hi = mid; }
 }
+// The searched accumulator (DISCO_ACC_*) from the token totals.
+__device__ __forceinline__ double acc_value(int which, const disco_cost_params& c, i64 s_pre, i64 s_dec, i64 d_pre,
+                                            i64 d_dec)
+{
+    switch (which) {
+    case DISCO_ACC_TOTAL_COST: {
+        double server = server_cost_of(c, s_pre, s_dec);
+        double energy = device_energy_of(c, d_pre, d_dec);
+        double priced = c.lambda * energy;
+        return server + priced;
+    }
+    case DISCO_ACC_SERVER_COST: return server_cost_of(c, s_pre, s_dec);
+    case DISCO_ACC_DEVICE_COST: {
+        double energy = device_energy_of(c, d_pre, d_dec);
+        return c.lambda * energy;
+    }
+    case DISCO_ACC_SERVER_PREFILL_TOK: return (double)s_pre;
+    default: return (double)d_pre;
+    }
+}
+
 // The parameters of the next `depth` (<= 3) levels of the bisection below the bracket of `st`, as policy records
 // in heap order (node 1 = the midpoint of the bracket, node 2n = after "not above" at node n, 2n + 1 = after
 // "above"): dst[0 .. 2^depth - 1).  A search whose steps are used up gets copies of its answer.

@@ -94,3 +94,38 @@ def test_server_tails_of_wait_columns(B, oracle, n_req, max_out, stall_p):
     specs = [dict(mode=1, l_th=-1, w_tail=DI.f32(0.04 * j), mig_mode=2) for j in range(12)]
     check_migration(B, oracle, tr, specs, DI.TAU, DI.KAPPA_LAG, delivered_col=None, cost=DI.COST_D)
     check_stats(B, oracle, tr, specs, DI.COST_D, tau=DI.TAU, kappa=DI.KAPPA_LAG)
+
+
+# eight bisection steps per pass: step counts around the passes, one to several searches of both parameters at once,
+# arrays on and off 16-byte boundaries, exact ties at the searched wait, brackets that run out of floats
+@pytest.mark.parametrize("n_req,n_steps,shift", [(0, 9, 0), (1, 1, 0), (5, 8, 0), (777, 9, 1), (4099, 32, 0), (4096, 64, 3)])
+def test_wait_and_slope_searches(B, oracle, n_req, n_steps, shift):
+    print(f"wait searches: n_req={n_req} n_steps={n_steps} shift={shift}", flush=True)
+    tr = DI.handmade_trace(90 + n_req, n_req, tokens=False, ties=True)
+    tr["srv_ttft"][: n_req // 4] = np.float32(0.5)                     # the first midpoint of the bracket [0, 1]
+    total = float(tr["prompt_len"].sum(dtype=np.int64))
+    searches = [  # template, parameter, accumulator, lo, hi, target
+        (dict(mode=1, l_th=-1), B.PARAM_W_TAIL, "device_cost", 0.0, 1.0, 0.3 * DI.COST_D["cs_pre"] * total),
+        (dict(mode=1, l_th=200, l_mid=201, w_mid=DI.f32(0.1)), B.PARAM_W_TAIL, "device_prefill_tok", 0.0, 4.0, 0.4 * total),
+        (dict(mode=1, l_th=-1, beta=DI.f32(1e-3)), B.PARAM_W_TAIL, "total_cost", 0.25, 0.25, 0.0),
+        (dict(mode=1, l_th=-1), B.PARAM_W_TAIL, "server_prefill_tok", -1.0, 2.0, 0.5 * total),
+        (dict(mode=1, l_th=100, w_tail=DI.f32(0.8)), B.PARAM_BETA, "device_prefill_tok", 0.0, 0.01, 0.2 * total),
+    ]
+    dt = B.upload_trace(tr)
+    for name in ("prompt_len", "output_len", "srv_ttft", "dev_pre_spt"):
+        x = getattr(dt, name)
+        buf = torch.zeros(x.numel() + shift, dtype=x.dtype, device="cuda")[shift:]
+        buf.copy_(x)
+        setattr(dt, name, buf)
+    out = B.disco_budget_search(dt, DI.COST_D, [B.Policy(**s[0]) for s in searches],
+                                [dict(which_param=p, which_acc=acc, n_steps=n_steps, lo=lo, hi=hi, target=target)
+                                 for _, p, acc, lo, hi, target in searches])
+    so = B.search_to_host(out["out"], len(searches))
+    pol = B.policies_to_host(out["pol_out"], len(searches))
+    for j, (templ, p, acc, lo, hi, target) in enumerate(searches):
+        find = oracle.search_wait if p == B.PARAM_W_TAIL else oracle.search_slope
+        x, hp, ha = find(tr, oracle.Policy(**templ), lo, hi, n_steps, acc, DI.COST_D, target)
+        same_bits(so["hist_param"][j][:n_steps].astype(np.float32), hp, f"hist_param {j}")
+        same_bits(so["hist_acc"][j][:n_steps], ha, f"hist_acc {j}")
+        got = pol[j].w_tail if p == B.PARAM_W_TAIL else pol[j].beta
+        assert np.float32(got) == np.float32(x) == np.float32(so["param"][j]), j
