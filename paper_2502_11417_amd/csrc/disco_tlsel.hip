@@ -592,6 +592,7 @@ void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P
     i64 b = (v.n_req + CL_BLOCK - 1) / CL_BLOCK;
     if (b < 1) b = 1;
     if (b > 256) b = 256;                          // (more workgroups cost more in the merge than they save in the scan)
+    if (b < 64) b = 64;                            // small traces: the clearing (2 MB and 32 KB per column) sets the time (500 requests x 4 columns: 34 us with one workgroup, 14 us)
     b /= disco_grid_divisor();
     if (b < 1) b = 1;
     hipLaunchKernelGGL(k_tl_classify, dim3((unsigned)b), dim3(CL_BLOCK), 0, stream, v, pol, P, nq, tau,
