@@ -291,6 +291,32 @@ __device__ __forceinline__ void batch_pairs_slow(const Staged* __restrict__ st, 
     }
 }
 
+// Stochastic columns alone, full batch, every l and n below 2^24.  A request runs on one endpoint: the device's totals
+// follow from the server's and the requests' (filled in at the end of the kernel).  Bound by vector issue: 10^6 requests x
+// 64 columns of 8 runs in 40 us, 121 us with the mixed form (both modes and the draws' lane reads per pair).
+template <int G>
+__device__ __forceinline__ void batch_pairs_stoch(const Staged* __restrict__ st, const float* __restrict__ su, int ridx, int sub,
+                                                  float beta, bool inverted, ColTotals& t)
+{
+    unsigned sp = 0, dd = 0, nw = 0;
+    double ts = 0.0;
+    unsigned mn = t.minb, mx = t.maxb;
+#pragma unroll 8
+    for (int it = 0; it < G; ++it) {
+        const Staged r = st[sub * G + it];
+        const bool server = (StochStage<G, G>::get(su, ridx, sub, it) < beta) != inverted;
+        sp += server ? (unsigned)r.l : 0u;
+        dd += server ? 0u : (unsigned)r.n;
+        nw += server ? 0u : 1u;
+        const float x = server ? r.s : r.d;
+        ts += (double)x;
+        mn = min(mn, f2u(x)); mx = max(mx, f2u(x));
+    }
+    t.s_pre += sp; t.d_dec += dd; t.won += nw;
+    t.ttft_sum += ts;
+    t.minb = mn; t.maxb = mx;
+}
+
 template <int G, int MODE>
 __device__ __forceinline__ void batch_pairs_need(const Staged* __restrict__ st, int sub, int cnt, i64 base, const disco_policy& p,
                                                  int need, ColTotals& t, const StochRuns& runs, const float* su)
@@ -337,6 +363,32 @@ __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const d
     i64 b = (i64)blockIdx.x * DP_WAVES + wave;
     load_batch(b);
     const int mode = table_mode(p, colv);
+    bool one_endpoint = false;                                    // every pair runs on one endpoint
+    if (mode == 2 && all_stochastic(p, colv)) {
+        one_endpoint = true;
+        const StochRuns runs = stoch_runs(p, colv, lane);
+        if (runs.on) {
+            using Stage = StochStage<G, G>;
+            static_assert(DP_BLOCK * sizeof(Staged) + DP_WAVES * Stage::WORDS * sizeof(float) <= sizeof(smem), "variates behind the records");
+            float* su = reinterpret_cast<float*>(smem + DP_BLOCK * sizeof(Staged)) + wave * Stage::WORDS;
+            const int ridx = colv ? runs.ridx : 0;
+            const bool inverted = p.mode != DISCO_MODE_STOCH_SERVER;
+            // full batches of moderate lengths; the rest is left to the loop below
+            for (; b < nbatch && b * 64 + 64 <= tr.n_req; b += bstride) {
+                const int lv = lv_n, nv = nv_n;
+                const float sv = sv_n, dv = __fmaf_rn((float)lv, kv_n, tr.c);
+                if (__ballot(((unsigned)lv | (unsigned)nv) >= (1u << 24)) != 0ull) break;
+                load_batch(b + bstride);
+                tot_l += (u64)lv; tot_n += (u64)nv; tot_c += 1ull;
+                float u[STOCH_SHARE] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                stoch_draw(runs, b * 64 + lane, u);
+                st[lane] = Staged{lv, sv, nv, dv};
+                Stage::put(runs, u, su, lane, 0);
+                batch_pairs_stoch<G>(st, su, ridx, sub, p.beta, inverted, t);
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    }
     for (; b < nbatch; b += bstride) {
         const bool v = b * 64 + lane < tr.n_req;
         const int lv = lv_n, nv = nv_n;
@@ -392,6 +444,7 @@ __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const d
     // a column that never skips an endpoint charges it every prompt; the device is always started in Alg. 3
     if (mode == 0) { t.d_pre = tot_l; t.started = tot_c; }
     if (mode == 1) t.s_pre = tot_l;
+    if (one_endpoint) { t.d_pre = tot_l - t.s_pre; t.started = t.won; }
     __syncthreads();                          // staging no longer needed: reuse the LDS for the folds
     if (sub == 0)
         lds_put(sh, DP_BLOCK, wave * G + col,

@@ -731,9 +731,11 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
     if (rc) return rc;
     if (nq > 0) {
         unsigned char* ubytes = ws_bytes >= L.total + (size_t)v.n_req ? (unsigned char*)(ws + L.total) : nullptr;
+        // (the descriptors of the TBT selection are written after the TTFT passes)
+        u64* masks = ws_bytes >= disco_ws_full_bytes(L, v.n_req) ? (u64*)(ws + disco_ws_desc_offset(L, v.n_req)) : nullptr;
         for (int pass = 0; pass < 4; ++pass)
             disco_launch_ttft_pass(v, (const disco_policy*)(ws + L.pol), P, nq, pass, S, (unsigned*)(ws + L.slices), gh,
-                                   ubytes, stream);
+                                   ubytes, masks, stream);
         if (tl) {
             TimelineArgs a;
             memset(&a, 0, sizeof(a));

@@ -80,9 +80,10 @@ void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n,
 // One TTFT radix pass: histograms per workgroup slice (class kernel or pair kernel, decided on the device),
 // row sums, digit selection.
 // `ubytes`: n_req bytes of scratch (nullable) where the first pass leaves, per request, the number of thresholds
-// not above its prompt length for the later passes.
+// not above its prompt length for the later passes; `masks`: n_req words (nullable) where it leaves the columns that send
+// a request to the server (tables of stochastic columns).
 void disco_launch_ttft_pass(const TraceView& v, const disco_policy* pol, int P, int nq, int pass, SelState* S,
-                            unsigned* slices, unsigned* rowsum, unsigned char* ubytes, hipStream_t stream);
+                            unsigned* slices, unsigned* rowsum, unsigned char* ubytes, u64* masks, hipStream_t stream);
 void disco_launch_dispatch_mat(const TraceView& v, const disco_policy* pol, int P, uint8_t* decision, float* ttft,
                                hipStream_t stream);
 // Token timelines.  Statistics pass (a.pass = -1): streaming kernel, or the general kernel when the

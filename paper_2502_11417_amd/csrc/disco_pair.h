@@ -103,6 +103,31 @@ __device__ __forceinline__ float stoch_fetch(const StochRuns& s, const float u[S
     return x;
 }
 
+// Tables of stochastic columns alone: the variates of a batch are staged in LDS by (run, request), CH of the G requests
+// of every sub-group at a time (c-th of G / CH rounds; the area is private to the wave), and a column lane reads the one
+// of its run next to the request's record: a comparison and a selection per pair instead of STOCH_SHARE lane reads and
+// the arithmetic of the other modes.  Rows are four banks apart.
+template <int G, int CH>
+struct StochStage {
+    static constexpr int SLOTS = 64 / G * CH, STRIDE = SLOTS + 4, WORDS = STOCH_SHARE * STRIDE;
+    static __device__ __forceinline__ void put(const StochRuns& s, const float u[STOCH_SHARE], float* area, int lane, int c)
+    {
+        __builtin_amdgcn_wave_barrier();
+        if ((lane & (G - 1)) / CH == c) {
+            const int slot = lane / G * CH + (lane & (CH - 1));
+#pragma unroll
+            for (int k = 0; k < STOCH_SHARE; ++k)
+                if (k < s.R) area[k * STRIDE + slot] = u[k];
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    static __device__ __forceinline__ float get(const float* area, int ridx, int sub, int q) { return area[ridx * STRIDE + sub * CH + q]; }
+};
+__device__ __forceinline__ bool all_stochastic(const disco_policy& p, bool colv)
+{
+    return __ballot(colv && p.mode < DISCO_MODE_STOCH_SERVER) == 0ull;
+}
+
 __device__ __forceinline__ int table_mode(const disco_policy& p, bool colv)
 {
     const bool any_d = __ballot(colv && p.mode == DISCO_MODE_DEVICE_CONSTRAINED) != 0ull;

@@ -84,6 +84,8 @@ __device__ __forceinline__ void wl_append(WaveList& w, bool match, unsigned key,
                                           SelGlobal* g)
 {
     const int lane = threadIdx.x & 63;
+    const u64 m = __ballot(match);
+    if (m == 0ull) return;
     if (w.cnt + 64u > TG_SEG) {                                // wave-uniform
         unsigned base = 0u;
         if (lane == 0) base = atomicAdd(&g->n_list, w.cnt);
@@ -91,7 +93,6 @@ __device__ __forceinline__ void wl_append(WaveList& w, bool match, unsigned key,
         wl_copy(w, base, list, g);
         w.cnt = 0u;
     }
-    const u64 m = __ballot(match);
     if (match) w.seg[w.cnt + (unsigned)__popcll(m & ((1ull << lane) - 1ull))] = GEntry{key, tag};
     w.cnt += (unsigned)__popcll(m);
 }
@@ -131,13 +132,27 @@ __device__ __forceinline__ void store_slice(const unsigned* hist, int rows, int 
 
 // ------------------------------------------------------------ pair kernel --
 
+// Variates of tables of stochastic columns: 16 requests of a batch at a time (the bins leave room for no more), which
+// takes a table of more than four columns; smaller ones go the general way.  The first pass leaves every request's routing
+// (the set of columns that send it to the server) in the workspace where that has room; the later ones draw nothing and
+// take only the requests with a value whose upper bits some slot wants.  10^6 requests x 8 levels x 8 runs: 62 + 27 + 20 us
+// for the three passes, 117 + 138 + 132 us with the general evaluation of every pair.  What bounds the first one: its draws
+// (8 per request at about 100 operations, some 20 us) and the vector instructions and LDS atomic of 64 10^6 pairs.
+constexpr int VAR_MIN_G = 8;
+template <int G>
+struct VarStage {
+    static constexpr int CH = G >= VAR_MIN_G ? G / 4 : 1;
+    using Stage = StochStage<G, CH>;
+};
+constexpr size_t VAR_BYTES = DP_WAVES * VarStage<64>::Stage::WORDS * sizeof(float);
+
 // Same traversal as the fused dispatch pass; every pair whose key matches the
 // prefix of a (column, quantile) slot bumps that slot's bin.  Pass 0: one row
 // per column (all quantiles share it).
 template <int G>
 __device__ __forceinline__ void pair_body(const TraceView& tr, const disco_policy* __restrict__ pol, int P, int nq, int pass,
                                           SelState* S, unsigned* __restrict__ slices, unsigned* hist, Staged* stage,
-                                          int bid, int nblk, bool gather)
+                                          float* variates, u64* __restrict__ masks, int bid, int nblk, bool gather)
 {
     const SelGlobal g = S->g[0];
     const PassDigit dg = pass_digit(g, pass);
@@ -154,19 +169,26 @@ __device__ __forceinline__ void pair_body(const TraceView& tr, const disco_polic
     const bool colv = col < P;
     const disco_policy p = pol[colv ? col : 0];
     const StochRuns runs = stoch_runs(p, colv, lane);
+    const int ridx = runs.ridx < 0 ? 0 : runs.ridx;
+    const bool inverted = p.mode != DISCO_MODE_STOCH_SERVER;
     unsigned prefix[DISCO_MAX_Q];
-    bool live[DISCO_MAX_Q];
     bool any_live = false;
 #pragma unroll
     for (int qi = 0; qi < DISCO_MAX_Q; ++qi) {
         const bool on = colv && qi < nq;
         const SelSlot sl = S->slot[0][on ? col * nq + qi : 0];
-        prefix[qi] = sl.prefix;
-        live[qi] = on && !sl.done;
-        any_live = any_live || live[qi];
+        const bool live = on && !sl.done;
+        prefix[qi] = live ? sl.prefix : 0xFFFFFFFFu;             // keys have 31 bits: matches none
+        any_live = any_live || live;
     }
     Staged* st = stage + wave * 64;
     const i64 nbatch = (tr.n_req + 63) >> 6;
+    // later passes over routed requests: a set of the live prefixes (hashed, false members only cost time)
+    unsigned* prefixes = reinterpret_cast<unsigned*>(variates);
+    constexpr int PREFIX_BITS = 12;
+    static_assert((1 << PREFIX_BITS) / 8 <= VAR_BYTES, "the set lies where the variates do");
+    auto prefix_bit = [](unsigned hi) { return (hi * 0x9E3779B1u) >> (32 - PREFIX_BITS); };
+    auto wanted = [&](unsigned hi) { const unsigned h = prefix_bit(hi); return ((prefixes[h >> 5] >> (h & 31u)) & 1u) != 0u; };
     // the pair evaluation is specialised on the kind of table (all Alg. 3, all Alg. 2, mixed)
     auto run = [&](auto mode_c) {
         constexpr int MODE = decltype(mode_c)::value;
@@ -177,43 +199,104 @@ __device__ __forceinline__ void pair_body(const TraceView& tr, const disco_polic
             const float sv = v ? tr.s[i] : 0.0f;
             const float kv = tr.k ? (v ? tr.k[i] : 0.0f) : tr.k_s;
             const float dv = __fmaf_rn((float)lv, kv, tr.c);
-            st[lane] = Staged{lv, sv, 0, dv};
-            const int cnt = (int)((tr.n_req - b * 64 < 64) ? (tr.n_req - b * 64) : 64);
-            const bool shared = MODE == 2 && runs.on;       // stochastic columns: one draw per request and run
-            float su[STOCH_SHARE] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (shared) stoch_draw(runs, i, su);
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll 4
-            for (int it = 0; it < G; ++it) {
-                const int src = sub * G + it;
-                const Staged r = st[src];
-                const float u = shared ? stoch_fetch<G == 64>(runs, su, src) : 0.0f;
-                const PairResult e = pair_eval<MODE>(p, r.l, r.s, r.d, b * 64 + src, shared, u);
+            int cnt = (int)((tr.n_req - b * 64 < 64) ? (tr.n_req - b * 64) : 64);
+            if constexpr (MODE == 4) {
+                // only the requests with a value that some slot may want, side by side
+                const bool want = v && (wanted((f2u(sv) - g.minb) >> up) || wanted((f2u(dv) - g.minb) >> up));
+                const u64 all = __ballot(want);
+                if (want) {
+                    const u64 to_server = masks[i];
+                    st[__popcll(all & ((1ull << lane) - 1ull))] = Staged{(int)(unsigned)to_server, sv, (int)(unsigned)(to_server >> 32), dv};
+                }
+                cnt = __popcll(all);
+            } else if constexpr (MODE == 5) {
+                // (first pass: the digits of the two values)
+                st[lane] = Staged{(int)(((f2u(sv) - g.minb) >> shift) & dmask), u2f(((f2u(dv) - g.minb) >> shift) & dmask), 0, 0.0f};
+            } else {
+                st[lane] = Staged{lv, sv, 0, dv};
+            }
+            // one pair: its TTFT into the bins (or the list) of its column
+            auto count = [&](int src, float ttft) {
+                const unsigned key = f2u(ttft) - g.minb;
+                const unsigned hi = up >= 32 ? 0u : key >> up;
+                bool match = hi == prefix[0] || hi == prefix[1];
+                if (nq > 2) match = match || hi == prefix[2] || hi == prefix[3];
                 if (gather) {                            // collect the pairs that still match a slot of their column
-                    const unsigned key = f2u(e.ttft) - g.minb;
-                    const unsigned hi = key >> up;
-                    bool match = false;
-#pragma unroll
-                    for (int qi = 0; qi < DISCO_MAX_Q; ++qi) match = match || (live[qi] && hi == prefix[qi]);
                     wl_append(wl, match && src < cnt, key, 0x20000u | (unsigned)col, list, &S->g[0]);
                 } else if (src < cnt) {
-                    const unsigned key = f2u(e.ttft) - g.minb;
                     const unsigned dgt = (key >> shift) & dmask;
-                    const unsigned hi = (up >= 32) ? 0u : (key >> up);
                     if (pass == 0) {
                         if (any_live) atomicAdd(&hist[col * TH_STRIDE + dgt], 1u);
-                    } else {
+                    } else if (match) {
 #pragma unroll
                         for (int qi = 0; qi < DISCO_MAX_Q; ++qi)
-                            if (live[qi] && hi == prefix[qi]) atomicAdd(&hist[(col * nq + qi) * TH_STRIDE + dgt], 1u);
+                            if (hi == prefix[qi]) atomicAdd(&hist[(col * nq + qi) * TH_STRIDE + dgt], 1u);
                     }
+                }
+            };
+            float su[STOCH_SHARE] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if constexpr (MODE == 4) {                          // stochastic columns alone, routed by the first pass
+                __builtin_amdgcn_wave_barrier();
+                for (int r0 = 0; r0 < cnt; r0 += 64 / G) {
+                    const Staged r = st[r0 + sub];               // (the batch's 64 records; count() leaves out those from cnt on)
+                    const unsigned half = (unsigned)(col < 32 ? r.l : r.n);
+                    count(r0 + sub, (half >> (col & 31)) & 1u ? r.s : r.d);
+                }
+            } else if constexpr (MODE == 3 || MODE == 5) {      // stochastic columns alone, 5: the first pass
+                u64 to_server = 0ull;                           // of this lane's request: the columns routed to the server
+                stoch_draw(runs, i, su);
+                constexpr int CH = VarStage<G>::CH;
+                float* area = variates + wave * VarStage<G>::Stage::WORDS;
+#pragma unroll 1
+                for (int c = 0; c < G / CH; ++c) {
+                    VarStage<G>::Stage::put(runs, su, area, lane, c);
+#pragma unroll 4
+                    for (int q = 0; q < CH; ++q) {
+                        const int src = sub * G + c * CH + q;
+                        const Staged r = st[src];
+                        const bool server = (VarStage<G>::Stage::get(area, ridx, sub, q) < p.beta) != inverted;
+                        const u64 all = __ballot(server);
+                        if ((lane & (G - 1)) == c * CH + q) to_server = G == 64 ? all : (all >> (lane & ~(G - 1))) & ((1ull << (G & 63)) - 1ull);
+                        if constexpr (MODE == 3) {
+                            count(src, server ? r.s : r.d);
+                        } else {
+                            const unsigned dgt = server ? (unsigned)r.l : f2u(r.s);
+                            if (any_live && src < cnt) atomicAdd(&hist[col * TH_STRIDE + dgt], 1u);
+                        }
+                    }
+                }
+                if (masks != nullptr && pass == 0 && v) masks[i] = to_server;
+            } else {
+                const bool shared = MODE == 2 && runs.on;       // stochastic columns: one draw per request and run
+                if (shared) stoch_draw(runs, i, su);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+                for (int it = 0; it < G; ++it) {
+                    const int src = sub * G + it;
+                    const Staged r = st[src];
+                    const float u = shared ? stoch_fetch<G == 64>(runs, su, src) : 0.0f;
+                    count(src, pair_eval<MODE>(p, r.l, r.s, r.d, b * 64 + src, shared, u).ttft);
                 }
             }
             __builtin_amdgcn_wave_barrier();
         }
     };
     const int mode = table_mode(p, colv);
-    if (mode == 0) run(std::integral_constant<int, 0>{});
+    if (G >= VAR_MIN_G && mode == 2 && runs.on && all_stochastic(p, colv)) {
+        if (masks != nullptr && pass > 0) {
+            for (int w = threadIdx.x; w < (1 << PREFIX_BITS) / 32; w += DP_BLOCK) prefixes[w] = 0u;
+            __syncthreads();
+            if (wave == 0)
+#pragma unroll
+                for (int qi = 0; qi < DISCO_MAX_Q; ++qi)
+                    if (prefix[qi] != 0xFFFFFFFFu) { const unsigned h = prefix_bit(prefix[qi]); atomicOr(&prefixes[h >> 5], 1u << (h & 31u)); }
+            __syncthreads();
+            run(std::integral_constant<int, G >= VAR_MIN_G ? 4 : 2>{});
+        }
+        else if (pass == 0) run(std::integral_constant<int, G >= VAR_MIN_G ? 5 : 2>{});
+        else run(std::integral_constant<int, G >= VAR_MIN_G ? 3 : 2>{});
+    }
+    else if (mode == 0) run(std::integral_constant<int, 0>{});
     else if (mode == 1) run(std::integral_constant<int, 1>{});
     else run(std::integral_constant<int, 2>{});
     if (gather) { wl_finish(wl, list, &S->g[0]); return; }
@@ -557,18 +640,20 @@ template <int G>
 __global__ __launch_bounds__(DP_BLOCK) void k_ttft_hist(TraceView tr, const disco_policy* __restrict__ pol, int P, int nq,
                                                         int pass, SelState* S, unsigned* __restrict__ slices,
                                                         int ncls_blocks, unsigned char* __restrict__ ubytes,
-                                                        const unsigned* __restrict__ rowsum)
+                                                        const unsigned* __restrict__ rowsum, u64* __restrict__ masks)
 {
     __shared__ unsigned hist[TH_WORDS];
     __shared__ __align__(16) Staged stage[DP_BLOCK];
-    __shared__ ClsTables T;
+    // tables of the class workgroups, variates of the pair workgroups
+    __shared__ __align__(16) unsigned char shared_[sizeof(ClsTables) > VAR_BYTES ? sizeof(ClsTables) : VAR_BYTES];
+    ClsTables& T = *reinterpret_cast<ClsTables*>(shared_);
     const bool cls_block = (int)blockIdx.x < ncls_blocks;
     if (cls_block != (S->tc.on != 0)) return;
     if (pass >= 2 && S->tb.on) return;                    // the buckets finished the selection
     const bool gather = pass >= 2 && gather_on(S->g[0]);
     if (gather && pass > 2) return;                       // the list finished the selection
     if (cls_block) cls_body(tr, P, nq, pass, S, slices, hist, T, blockIdx.x, ncls_blocks, gather, ubytes, rowsum);
-    else pair_body<G>(tr, pol, P, nq, pass, S, slices, hist, stage, (int)blockIdx.x - ncls_blocks, (int)gridDim.x - ncls_blocks,
+    else pair_body<G>(tr, pol, P, nq, pass, S, slices, hist, stage, reinterpret_cast<float*>(shared_), masks, (int)blockIdx.x - ncls_blocks, (int)gridDim.x - ncls_blocks,
                       gather);
 }
 
@@ -765,16 +850,16 @@ __global__ __launch_bounds__(1024) void k_ttft_select(SelState* S, int pass, int
 
 template <int G>
 void launch_hist(const TraceView& v, const disco_policy* pol, int P, int nq, int pass, SelState* S, unsigned* slices,
-                 unsigned bp, unsigned bc, unsigned char* ubytes, const unsigned* rowsum, hipStream_t stream)
+                 unsigned bp, unsigned bc, unsigned char* ubytes, const unsigned* rowsum, u64* masks, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_ttft_hist<G>, dim3(bc + bp), dim3(DP_BLOCK), 0, stream, v, pol, P, nq, pass, S, slices, (int)bc,
-                       ubytes, rowsum);
+                       ubytes, rowsum, masks);
 }
 
 }  // namespace
 
 void disco_launch_ttft_pass(const TraceView& v, const disco_policy* pol, int P, int nq, int pass, SelState* S,
-                            unsigned* slices, unsigned* rowsum, unsigned char* ubytes, hipStream_t stream)
+                            unsigned* slices, unsigned* rowsum, unsigned char* ubytes, u64* masks, hipStream_t stream)
 {
     i64 bp = ((v.n_req + 63) / 64 + DP_WAVES - 1) / DP_WAVES;
     if (bp < 1) bp = 1;
@@ -785,13 +870,13 @@ void disco_launch_ttft_pass(const TraceView& v, const disco_policy* pol, int P, 
     int g = 1;
     while (g < P) g <<= 1;
     switch (g) {
-    case 1: launch_hist<1>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, stream); break;
-    case 2: launch_hist<2>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, stream); break;
-    case 4: launch_hist<4>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, stream); break;
-    case 8: launch_hist<8>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, stream); break;
-    case 16: launch_hist<16>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, stream); break;
-    case 32: launch_hist<32>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, stream); break;
-    default: launch_hist<64>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, stream); break;
+    case 1: launch_hist<1>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, masks, stream); break;
+    case 2: launch_hist<2>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, masks, stream); break;
+    case 4: launch_hist<4>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, masks, stream); break;
+    case 8: launch_hist<8>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, masks, stream); break;
+    case 16: launch_hist<16>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, masks, stream); break;
+    case 32: launch_hist<32>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, masks, stream); break;
+    default: launch_hist<64>(v, pol, P, nq, pass, S, slices, (unsigned)bp, (unsigned)bc, ubytes, rowsum, masks, stream); break;
     }
     const int rows_pair = pass == 0 ? P : P * nq, rows_cls = pass == 0 ? 2 * (P + 1) : P * nq;
     const int rows_max = rows_pair > rows_cls ? rows_pair : rows_cls;

@@ -6,7 +6,7 @@ import torch
 
 import disco_inputs as DI
 from test_gpu_buffer import slow_prefill
-from test_gpu_parity import check_migration, check_stats
+from test_gpu_parity import check_dispatch, check_migration, check_stats
 
 pytestmark = pytest.mark.gpu
 
@@ -129,3 +129,18 @@ def test_wait_and_slope_searches(B, oracle, n_req, n_steps, shift):
         same_bits(so["hist_acc"][j][:n_steps], ha, f"hist_acc {j}")
         got = pol[j].w_tail if p == B.PARAM_W_TAIL else pol[j].beta
         assert np.float32(got) == np.float32(x) == np.float32(so["param"][j]), j
+
+
+# tables of stochastic columns alone: the variates staged whole (dispatch) and 16 requests at a time (TTFT passes, tables
+# of more than four columns), 1 .. 8 shared runs and 9 that are not shared, ragged batches, lengths beyond 24 bits
+@pytest.mark.parametrize("n_req,levels,runs,huge", [(1, 1, 1, False), (64, 2, 2, False), (1027, 5, 1, False), (4096, 4, 8, True),
+                                                    (2049, 8, 8, False), (1999, 7, 9, False), (3000, 3, 5, True)])
+def test_tables_of_stochastic_columns(B, oracle, n_req, levels, runs, huge):
+    print(f"stochastic tables: n_req={n_req} levels={levels} runs={runs} huge={huge}", flush=True)
+    tr = DI.handmade_trace(130 + n_req, n_req, tokens=False, ties=True)
+    if huge:
+        tr["prompt_len"][n_req // 2] = (1 << 24) + 3
+    specs = [dict(mode=2 + (j & 1), beta=DI.f32((j + 1) / (levels + 1)), l_mid=17 * run) for j in range(levels) for run in range(runs)]
+    check_dispatch(B, oracle, tr, specs)
+    check_stats(B, oracle, tr, specs, DI.COST_S)
+    check_stats(B, oracle, tr, specs, DI.COST_S, ws_requests=0)         # no room for the routing: drawn again in every pass
