@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "disco_launch.h"
+#include "disco_len.h"
 #include "disco_pair.h"
 #include "disco_state.h"
 
@@ -570,11 +571,12 @@ __global__ __launch_bounds__(256) void k_dispatch_mat(TraceView tr, const disco_
 
 constexpr int LH_MAX_BINS = 32772;          // 128 KB of LDS counts: prompt lengths 0 .. 32771
 
-// Requests per prompt length, one slice of `nbins` counts per workgroup; the
-// lengths of requests outside [0, nbins) are added up in `other`.
-__global__ __launch_bounds__(DP_BLOCK) void k_len_hist(TraceView tr, int nbins, unsigned* __restrict__ slices, u64* other)
+// Requests per prompt length, one slice of `nbins` counts per workgroup, and the
+// sum of the lengths of its requests beyond the table.
+__global__ __launch_bounds__(DP_BLOCK) void k_len_hist(TraceView tr, int nbins, unsigned* __restrict__ slices, u64* __restrict__ table)
 {
     __shared__ unsigned cnt[LH_MAX_BINS];
+    __shared__ u64 wout[DP_WAVES];
     for (int i = threadIdx.x; i < nbins; i += DP_BLOCK) cnt[i] = 0u;
     __syncthreads();
     u64 out = 0;
@@ -584,15 +586,21 @@ __global__ __launch_bounds__(DP_BLOCK) void k_len_hist(TraceView tr, int nbins, 
         else if (l > 0) out += (u64)l;
     }
     out = wave_sum_u64(out);
-    if ((threadIdx.x & 63) == 0 && out) atomicAdd((unsigned long long*)other, (unsigned long long)out);
+    if ((threadIdx.x & 63) == 0) wout[threadIdx.x >> 6] = out;
     __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < DP_WAVES; ++w) out += wout[w];
+        table[nbins + blockIdx.x] = out;
+    }
     unsigned* mine = slices + (size_t)blockIdx.x * nbins;
     for (int i = threadIdx.x; i < nbins; i += DP_BLOCK) mine[i] = cnt[i];
 }
 
-// table[v] = v x (requests of length v), summed over the slices: 64 lengths
-// per workgroup, each of the 16 waves takes every sixteenth slice with four
-// loads in flight (the pass is a chain of dependent-latency loads otherwise).
+// v x (requests of length v), summed over the slices, and from these the
+// table: table[v] = prompt tokens of the lengths from v to the end of its block
+// of LEN_BLOCK.  A block per workgroup, each of the 16 waves takes every
+// sixteenth slice with four loads in flight (the pass is a chain of
+// dependent-latency loads otherwise).
 __global__ __launch_bounds__(1024) void k_len_reduce(int nbins, int nslices, const unsigned* __restrict__ slices, u64* table)
 {
     __shared__ u64 part[1024];
@@ -610,79 +618,57 @@ __global__ __launch_bounds__(1024) void k_len_reduce(int nbins, int nslices, con
     }
     part[threadIdx.x] = (a0 + a1) + (a2 + a3);
     __syncthreads();
-    if (wave == 0 && v < nbins) {
-        u64 sum = 0;
-        for (int w = 0; w < 16; ++w) sum += part[w * 64 + lane];
-        table[v] = sum * (u64)v;
+    if (wave == 0) {
+        u64 x = 0;
+        for (int w = 0; w < 16; ++w) x += part[w * 64 + lane];
+        x *= (u64)v;
+        x = wave_suffix_u64(x);
+        if (v < nbins) table[v] = x;
     }
 }
 
-// All bisection steps of search `c` from the table.
-__device__ __forceinline__ void search_from_table(int c, int nbins, const u64* table, SearchState* st_, disco_policy* pol,
-                                                  disco_search_out* sout)
+// All bisection steps of all searches from the table (one workgroup).  Sixteen lanes share a search: they read the
+// sums at the 15 midpoints that its next four steps can reach, then walk down, so that a search waits for a read of
+// device memory once per four steps.  Bound by that latency.  With the launch that set the searches up and the suffix
+// sums of the whole table gone, a sweep of 10^6 requests takes 158 -> 152 us (64 columns, 4098 lengths) and 734 -> 712 us
+// (8 columns with timelines, 32 770 lengths).
+__global__ __launch_bounds__(1024) void k_len_search(int nbins, int nslices, const u64* __restrict__ table, SpecTable t, int n_search,
+                                                     SearchState* st_, disco_policy* pol, disco_search_out* sout)
 {
-    SearchState st = st_[c];
-    disco_policy p = pol[c];
-    while (st.step < st.n_steps) {
-        const int L = p.l_th;
-        const u64 s_pre = L <= 0 ? table[0] : (L < nbins ? table[L] : table[nbins]);
-        const double A = st.which_acc == DISCO_ACC_SERVER_PREFILL_TOK ? (double)(i64)s_pre : (double)(i64)table[0];
-        search_step(st, p, A, &sout[c]);
-    }
-    st_[c] = st;
-    pol[c] = p;
-}
-
-// In place: table[L] = sum over v >= L of table[v], plus the lengths beyond
-// the table; table[nbins] = those lengths alone.  One workgroup; with
-// n_search > 0 its first threads then run the searches (thread = column).
-__global__ __launch_bounds__(1024) void k_len_suffix(int nbins, u64* table, u64* other, int n_search, SearchState* st_,
-                                                     disco_policy* pol, disco_search_out* sout)
-{
-    // Tiles of 8192 lengths from the top down: loaded coalesced into LDS, eight consecutive lengths per thread
-    // (rows padded by one element per eight against bank conflicts), suffix scan of the thread totals, stored back
-    // coalesced; `carry` = everything above the tile.
-    constexpr int TILE = 8192;
-    __shared__ u64 tile[TILE + TILE / 8];
-    __shared__ u64 part[1024];
-    __shared__ u64 carry_s;
-    const int t = threadIdx.x;
-    const u64 beyond = *other;
-    u64 carry = beyond;
-    for (int hi = nbins; hi > 0; hi -= TILE) {
-        const int lo = hi > TILE ? hi - TILE : 0, len = hi - lo;
-        for (int i = t; i < len; i += 1024) tile[i + (i >> 3)] = table[lo + i];
-        __syncthreads();
-        u64 sum = 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) if (8 * t + q < len) sum += tile[9 * t + q];
-        // suffix sums of the per-thread totals: within the wave by shuffles, across the 16 waves through LDS
-        u64 incl = sum;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const unsigned lo32 = (unsigned)__shfl_down((int)(unsigned)incl, d, 64);
-            const unsigned hi32 = (unsigned)__shfl_down((int)(unsigned)(incl >> 32), d, 64);
-            if ((t & 63) + d < 64) incl += ((u64)hi32 << 32) | lo32;
+    __shared__ LenScratch lds;
+    const LenSums A = len_sums(table, nbins, nslices, lds);
+    const int sub = threadIdx.x & 15, group = threadIdx.x & 48;
+    const bool on = (int)(threadIdx.x >> 4) < n_search;
+    const int c = on ? threadIdx.x >> 4 : 0;
+    SearchState st = t.s[c];
+    int lo = (int)st.lo, hi = (int)st.hi;
+    const u64 all = A(0);
+    disco_search_out* o = &sout[c];
+    auto halve = [](int& l, int& h, int mid, bool above) { if (l < h) { if (above) l = mid + 1; else h = mid; } };
+    while (st.step < st.n_steps) {                   // (the same number of steps in every search)
+        int l = lo, h = hi;
+        // node sub + 1 of the bisection tree in heap order: the bits behind its leading one are the steps to it
+        const int node = sub < 15 ? sub + 1 : 15;
+        for (int bit = 31 - __clz(node) - 1; bit >= 0; --bit) halve(l, h, l + (h - l) / 2, (node >> bit) & 1);
+        const int mid = l + (h - l) / 2;
+        const u64 s_pre = A(mid);
+        const double acc = st.which_acc == DISCO_ACC_SERVER_PREFILL_TOK ? (double)(i64)s_pre : (double)(i64)all;
+        int at = 1;
+        for (int d = 0; d < 4 && st.step < st.n_steps; ++d) {
+            const int m = __shfl(mid, group + at - 1, 64);
+            const double a = __shfl(acc, group + at - 1, 64);
+            if (on && sub == 0) { o->hist_param[st.step] = (double)m; o->hist_acc[st.step] = a; }
+            const bool above = a > st.target;
+            halve(lo, hi, m, above);
+            at = 2 * at + (above ? 1 : 0);
+            st.step += 1;
         }
-        if ((t & 63) == 0) part[t >> 6] = incl;     // the wave's total
-        __syncthreads();
-        u64 above = incl - sum + carry;             // the threads above this one in its wave
-        for (int w = (t >> 6) + 1; w < 16; ++w) above += part[w];
-#pragma unroll
-        for (int q = 7; q >= 0; --q)
-            if (8 * t + q < len) { above += tile[9 * t + q]; tile[9 * t + q] = above; }
-        __syncthreads();
-        for (int i = t; i < len; i += 1024) table[lo + i] = tile[i + (i >> 3)];
-        if (t == 0) carry_s = tile[0];              // all lengths from `lo` up
-        __syncthreads();
-        carry = carry_s;
-        __syncthreads();
     }
-    if (threadIdx.x == 0) { table[nbins] = beyond; *other = 0; }
-    if (n_search <= 0) return;
-    __threadfence();                                // the table is read back by other threads of this workgroup
-    __syncthreads();
-    if ((int)threadIdx.x < n_search) search_from_table(threadIdx.x, nbins, table, st_, pol, sout);
+    if (on && sub == 0) {
+        st.lo = (double)lo; st.hi = (double)hi;
+        st_[c] = st;
+        pol[c].l_th = hi;                            // the feasible end of the bracket
+    }
 }
 
 unsigned dispatch_blocks(i64 units, i64 per_block)
@@ -744,35 +730,27 @@ void disco_launch_dispatch_mat(const TraceView& v, const disco_policy* pol, int 
     hipLaunchKernelGGL(k_dispatch_mat, dim3((unsigned)b), dim3(256), 0, stream, v, pol, P, decision, ttft);
 }
 
-// table[L] = prompt tokens of the requests of length >= L for L < nbins, table[nbins] = those of longer requests
-// (see k_len_hist).  `scratch` holds the workgroup slices; *other must be zero and is zero again afterwards.
-static void launch_len_table(const TraceView& v, int nbins, unsigned* scratch, size_t scratch_bytes, u64* table, u64* other,
-                             int n_search, SearchState* st, disco_policy* pol, disco_search_out* sout, hipStream_t stream)
+// Prompt tokens by length in blocks (disco_len.h); `scratch` holds the workgroup slices.  Returns their number.
+int disco_launch_len_table(const TraceView& v, int nbins, unsigned* scratch, size_t scratch_bytes, u64* table, hipStream_t stream)
 {
     i64 blocks = (v.n_req + DP_BLOCK - 1) / DP_BLOCK;
     const i64 fit = (i64)(scratch_bytes / ((size_t)nbins * sizeof(unsigned)));
     if (blocks > fit) blocks = fit;
     if (blocks > DP_MAX_BLOCKS) blocks = DP_MAX_BLOCKS;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_len_hist, dim3((unsigned)blocks), dim3(DP_BLOCK), 0, stream, v, nbins, scratch, other);
-    hipLaunchKernelGGL(k_len_reduce, dim3((unsigned)((nbins + 63) / 64)), dim3(1024), 0, stream, nbins, (int)blocks, scratch,
-                       table);
-    hipLaunchKernelGGL(k_len_suffix, dim3(1), dim3(1024), 0, stream, nbins, table, other, n_search, st, pol, sout);
+    hipLaunchKernelGGL(k_len_hist, dim3((unsigned)blocks), dim3(DP_BLOCK), 0, stream, v, nbins, scratch, table);
+    hipLaunchKernelGGL(k_len_reduce, dim3((unsigned)((nbins + LEN_BLOCK - 1) / LEN_BLOCK)), dim3(1024), 0, stream, nbins, (int)blocks,
+                       scratch, table);
+    return (int)blocks;
 }
 
-void disco_launch_len_table(const TraceView& v, int nbins, unsigned* scratch, size_t scratch_bytes, u64* table, u64* other,
-                            hipStream_t stream)
-{
-    launch_len_table(v, nbins, scratch, scratch_bytes, table, other, 0, nullptr, nullptr, nullptr, stream);
-}
-
-// Tabulated threshold search: the table, then every bisection step of every column from it (in the kernel that
-// finishes the table).
-void disco_launch_search_table(const TraceView& v, int n_search, int nbins, unsigned* scratch, size_t scratch_bytes,
-                               u64* table, u64* other, SearchState* st, disco_policy* pol, disco_search_out* sout,
+// Tabulated threshold search: the table, then every bisection step of every column from it.
+void disco_launch_search_table(const TraceView& v, const SpecTable& spec, int n_search, int nbins, unsigned* scratch,
+                               size_t scratch_bytes, u64* table, SearchState* st, disco_policy* pol, disco_search_out* sout,
                                hipStream_t stream)
 {
-    launch_len_table(v, nbins, scratch, scratch_bytes, table, other, n_search, st, pol, sout, stream);
+    const int nslices = disco_launch_len_table(v, nbins, scratch, scratch_bytes, table, stream);
+    hipLaunchKernelGGL(k_len_search, dim3(1), dim3(1024), 0, stream, nbins, nslices, table, spec, n_search, st, pol, sout);
 }
 
 int disco_search_table_max_bins(void) { return LH_MAX_BINS; }

@@ -305,9 +305,8 @@ __global__ void k_average_runs(const disco_stats* __restrict__ in, int groups, i
 
 // ----------------------------------------------------------- search setup --
 
-// Brackets of the searches; `pol` holds their templates on entry.  depth > 0: the templates move to `templ`
-// and `pol` gets the candidate columns of the first bisection pass (2^depth - 1 per search); depth 0 (tabulated
-// threshold search): `pol` keeps one record per search with the first midpoint.
+// Brackets of the searches; `pol` holds their templates on entry.  They move to `templ` and `pol` gets the candidate
+// columns of the first bisection pass (2^depth - 1 per search).
 __global__ void k_search_init(SpecTable t, int n, SearchState* st, disco_policy* pol, disco_policy* templ, int depth)
 {
     const int c = threadIdx.x;
@@ -323,13 +322,8 @@ __global__ void k_search_init(SpecTable t, int n, SearchState* st, disco_policy*
     }
     __syncthreads();                        // all templates have been read
     if (c >= n) return;
-    if (depth > 0) {
-        templ[c] = p;
-        search_write_candidates(s, p, &pol[c * ((1 << depth) - 1)], depth);
-    } else {
-        search_set_mid(s.which_param, s.lo, s.hi, p);
-        pol[c] = p;
-    }
+    templ[c] = p;
+    search_write_candidates(s, p, &pol[c * ((1 << depth) - 1)], depth);
 }
 
 // ------------------------------------------------------------- host side --
@@ -845,7 +839,7 @@ extern "C" int32_t disco_solve_policy(const disco_trace* trace, const disco_solv
     const WsLayout L = disco_ws_layout(n);
     if (disco_solve_state_bytes() > L.ghist - L.sel) return DISCO_ERR_WORKSPACE;      // the selection state region holds it
     const TraceView v = view_of(trace);
-    disco_launch_solve(v, spec, n, ws + L.sel, (u64*)(ws + L.ppcnt), (u64*)((unsigned*)(ws + L.ticket) + 32),
+    disco_launch_solve(v, spec, n, ws + L.sel, (u64*)(ws + L.ppcnt),
                        (unsigned*)(ws + L.slices), L.total - L.slices, pol_out, out, (hipStream_t)stream_);
     DISCO_HIP(hipGetLastError());
     return DISCO_OK;
@@ -907,8 +901,9 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
     // Otherwise every pass evaluates the next `depth` levels of each search's bisection tree as columns of their
     // own and so takes `depth` bisection steps; the recorded steps are those of the plain bisection.
     const int depth = tabulated ? 0 : disco_search_depth(n_search);
-    if (!binned) hipLaunchKernelGGL(k_search_init, dim3(1), dim3(64), 0, stream, t, n_search, (SearchState*)(ws + L.search),
-                       (disco_policy*)(ws + L.pol), (disco_policy*)(ws + L.templ), depth);
+    if (!binned && !tabulated)
+        hipLaunchKernelGGL(k_search_init, dim3(1), dim3(64), 0, stream, t, n_search, (SearchState*)(ws + L.search),
+                           (disco_policy*)(ws + L.pol), (disco_policy*)(ws + L.templ), depth);
     DispFin fin;
     memset(&fin, 0, sizeof(fin));
     fin.kind = 1;
@@ -921,9 +916,8 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
     fin.templ = (const disco_policy*)(ws + L.templ);
     fin.n_search = n_search;
     if (tabulated) {
-        disco_launch_search_table(v, n_search, (int)max_hi + 2, (unsigned*)(ws + L.slices), L.total - L.slices,
-                                  (u64*)(ws + L.ppcnt), (u64*)((unsigned*)(ws + L.ticket) + 32),
-                                  (SearchState*)(ws + L.search), (disco_policy*)(ws + L.pol), out, stream);
+        disco_launch_search_table(v, t, n_search, (int)max_hi + 2, (unsigned*)(ws + L.slices), L.total - L.slices,
+                                  (u64*)(ws + L.ppcnt), fin.st, fin.pol_rw, out, stream);
     } else if (binned) {
         disco_launch_search_bins(v, n_search, n_steps, t, *cost, ws + L.slices, (SearchState*)(ws + L.search), fin.pol_rw,
                                  (disco_policy*)(ws + L.templ), out, stream);

@@ -49,8 +49,8 @@ inline int disco_search_depth(int n) { return n <= 9 ? 3 : (n <= 21 ? 2 : 1); }
 void disco_launch_dispatch_acc(const TraceView& v, const disco_policy* pol, int P, u64* part, const DispFin& fin,
                                hipStream_t stream);
 // Threshold search of server-constrained columns from a table of prompt-token sums by length.
-void disco_launch_search_table(const TraceView& v, int n_search, int nbins, unsigned* scratch, size_t scratch_bytes,
-                               u64* table, u64* other, SearchState* st, disco_policy* pol, disco_search_out* sout,
+void disco_launch_search_table(const TraceView& v, const SpecTable& spec, int n_search, int nbins, unsigned* scratch,
+                               size_t scratch_bytes, u64* table, SearchState* st, disco_policy* pol, disco_search_out* sout,
                                hipStream_t stream);
 // Search of w_tail or beta over device-constrained templates (in `pol`; the answers end there too), eight steps per pass.
 // `scratch`: disco_search_bins_bytes(n_search) bytes.
@@ -59,8 +59,7 @@ void disco_launch_search_bins(const TraceView& v, int n_search, int n_steps, con
                               void* scratch, SearchState* st, disco_policy* pol, disco_policy* templ, disco_search_out* sout,
                               hipStream_t stream);
 int disco_search_table_max_bins(void);
-void disco_launch_len_table(const TraceView& v, int nbins, unsigned* scratch, size_t scratch_bytes, u64* table, u64* other,
-                            hipStream_t stream);
+int disco_launch_len_table(const TraceView& v, int nbins, unsigned* scratch, size_t scratch_bytes, u64* table, hipStream_t stream);
 // Pairs with the buffer hand-off in class mode: their per-request summaries (a.bufsum), from the summaries of the
 // streaming walk (a.summary) and the tokens; returns at once when the staged table has no such column.
 // `totals` nullable: summaries only.
@@ -74,7 +73,7 @@ void disco_launch_fit(const void* x, int kind, i64 n, disco_lognormal_fit* fit, 
 // Closed-form policy solves (Alg. 2, Alg. 3): length table, per-column plan, multi-rank selection over the server
 // TTFTs, policy records.  `state` needs disco_solve_state_bytes() bytes.
 size_t disco_solve_state_bytes(void);
-void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n, void* state, u64* table, u64* other,
+void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n, void* state, u64* table,
                         unsigned* scratch, size_t scratch_bytes, disco_policy* pol_out, disco_solve_out* out,
                         hipStream_t stream);
 // One TTFT radix pass: histograms per workgroup slice (class kernel or pair kernel, decided on the device),

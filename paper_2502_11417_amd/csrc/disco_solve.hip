@@ -7,8 +7,8 @@
 // The distributions are the trace's own: p(l) = requests per prompt length,
 // F = empirical distribution of the server TTFT (nearest-rank inverse).  The
 // sorted sweep over the length support of the paper becomes
-//   1. the table of prompt-token mass by length and its suffix sums (the
-//      kernels of the tabulated threshold search),
+//   1. the table of prompt-token mass by length (the kernels of the tabulated
+//      threshold search),
 //   2. one thread per column that finds the last affordable length by binary
 //      search in those sums -- all budget comparisons in exact 128-bit integer
 //      arithmetic on the rational budget b and tail ratio alpha -- and the
@@ -22,6 +22,7 @@
 #include "disco_launch.h"
 #include "disco_state.h"
 #include "disco_device.h"
+#include "disco_len.h"
 
 namespace {
 
@@ -41,39 +42,42 @@ struct SolveState {
 struct SolveSpecs { disco_solve_spec s[DISCO_MAX_COLS]; };
 
 // Mass of the prompts of length <= L (tokens): total - sum over lengths > L.
-__device__ __forceinline__ u64 mass_upto(const u64* __restrict__ table, int nbins, int L)
+__device__ __forceinline__ u64 mass_upto(const LenSums& sums, u64 total, int L)
 {
-    return L < 0 ? 0ull : table[0] - table[L + 1 < nbins ? L + 1 : nbins];
+    return L < 0 ? 0ull : total - sums(L + 1);
 }
 
-// Step 2 (thread = column).
-__global__ void k_solve_plan(SolveSpecs specs, int n, i64 n_req, int nbins, const u64* __restrict__ table, SolveState* S)
+// Step 2 (thread = column, once the workgroup has added up the table's blocks).
+__global__ __launch_bounds__(1024) void k_solve_plan(SolveSpecs specs, int n, i64 n_req, int nbins, int nslices,
+                                                     const u64* __restrict__ table, SolveState* S)
 {
+    __shared__ LenScratch lds;
+    const LenSums sums = len_sums(table, nbins, nslices, lds);
     const int c = threadIdx.x;
     if (c >= n) return;
     const disco_solve_spec sp = specs.s[c];
-    const u64 total = table[0];
+    const u64 total = sums(0);
     disco_policy p;
     memset(&p, 0, sizeof(p));
     p.mode = sp.mode; p.l_th = -1; p.l_mid = -1; p.w_mid = 0.0f; p.beta = INFINITY; p.w_tail = INFINITY;
     p.mig_mode = sp.mig_mode;
     disco_solve_out o;
     memset(&o, 0, sizeof(o));
-    o.status = table[nbins] != 0ull ? 1 : 0;        // prompts longer than the table holds
+    o.status = sums.beyond != 0ull ? 1 : 0;        // prompts longer than the table holds
     o.total_tokens = (i64)total;
     SolveSlot tail{0, 0u, 0}, mid{0, 0u, 0};
     const u64 bn = (u64)sp.b_num, bd = (u64)sp.b_den, an = (u64)sp.a_num, ad = (u64)sp.a_den;
     if (sp.mode == DISCO_MODE_SERVER_CONSTRAINED) {
         // Eq. 3, discrete: the smallest L with (tokens of the prompts of length >= L) <= b x (all tokens)
         const u128 budget = (u128)bn * (u128)total;
-        int lo = 0, hi = nbins;                     // table[nbins] = lengths beyond the table
+        int lo = 0, hi = nbins;                     // sums(nbins) = lengths beyond the table
         while (lo < hi) {
             const int m = lo + (hi - lo) / 2;
-            if ((u128)table[m] * (u128)bd <= budget) hi = m; else lo = m + 1;
+            if ((u128)sums(m) * (u128)bd <= budget) hi = m; else lo = m + 1;
         }
         p.l_th = lo;
         p.beta = INFINITY; p.w_tail = INFINITY;
-        o.zero_wait_tokens = (i64)(total - table[lo]);      // tokens of the device-only prompts
+        o.zero_wait_tokens = (i64)(total - sums(lo));      // tokens of the device-only prompts
     } else {
         // Phase 1: rank of w_tail = ceil((1 - min(alpha, b)) N)
         const bool b_le_a = bn * ad <= an * bd;
@@ -89,26 +93,26 @@ __global__ void k_solve_plan(SolveSpecs specs, int n, i64 n_req, int nbins, cons
             int lo = -1, hi = nbins - 1;            // the largest L whose prefix of lengths is affordable
             while (lo < hi) {
                 const int m = lo + (hi - lo + 1) / 2;
-                if ((u128)K * (u128)mass_upto(table, nbins, m) <= avail) lo = m; else hi = m - 1;
+                if ((u128)K * (u128)mass_upto(sums, total, m) <= avail) lo = m; else hi = m - 1;
             }
-            const u64 zero_mass = mass_upto(table, nbins, lo);
+            const u64 zero_mass = mass_upto(sums, total, lo);
             // snap to the last length that occurs: the smallest L with the same mass below it
             int a = -1, z = lo;
             while (a < z) {
                 const int m = a + (z - a) / 2;
-                if (mass_upto(table, nbins, m) == zero_mass) z = m; else a = m + 1;
+                if (mass_upto(sums, total, m) == zero_mass) z = m; else a = m + 1;
             }
             p.l_th = zero_mass ? a : -1;
             o.zero_wait_tokens = (i64)zero_mass;
             // the next length that occurs gets the partial wait
             const u64 above = total - zero_mass;    // tokens of the longer prompts
-            if (above > table[nbins]) {
+            if (above > sums.beyond) {
                 int x = lo + 1, y = nbins - 1;      // smallest L > lo with mass_upto(L) > zero_mass
                 while (x < y) {
                     const int m = x + (y - x) / 2;
-                    if (mass_upto(table, nbins, m) > zero_mass) y = m; else x = m + 1;
+                    if (mass_upto(sums, total, m) > zero_mass) y = m; else x = m + 1;
                 }
-                const u64 mass_mid = mass_upto(table, nbins, x) - zero_mass;
+                const u64 mass_mid = mass_upto(sums, total, x) - zero_mass;
                 p.l_mid = x;
                 // (1 - alpha - F(w*)) mass = available left  <=>  F(w*) = (K mass - left) / (a_den b_den mass)
                 const u128 left = avail - (u128)K * (u128)zero_mass;
@@ -242,24 +246,21 @@ __global__ void k_solve_final(int n, const SolveState* S, disco_policy* pol_out,
     if (out) out[c] = S->out[c];
 }
 
-__global__ void k_solve_init(u64* other) { if (threadIdx.x == 0) *other = 0ull; }
-
 }  // namespace
 
 size_t disco_solve_state_bytes(void) { return sizeof(SolveState); }
 
-void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n, void* state, u64* table, u64* other,
+void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n, void* state, u64* table,
                         unsigned* scratch, size_t scratch_bytes, disco_policy* pol_out, disco_solve_out* out,
                         hipStream_t stream)
 {
     SolveState* S = (SolveState*)state;
     const int nbins = disco_search_table_max_bins();
-    hipLaunchKernelGGL(k_solve_init, dim3(1), dim3(64), 0, stream, other);
-    disco_launch_len_table(v, nbins, scratch, scratch_bytes, table, other, stream);
+    const int nslices = disco_launch_len_table(v, nbins, scratch, scratch_bytes, table, stream);
     SolveSpecs t;
     memset(&t, 0, sizeof(t));
     memcpy(t.s, spec, sizeof(disco_solve_spec) * (size_t)n);
-    hipLaunchKernelGGL(k_solve_plan, dim3(1), dim3(64), 0, stream, t, n, v.n_req, nbins, table, S);
+    hipLaunchKernelGGL(k_solve_plan, dim3(1), dim3(1024), 0, stream, t, n, v.n_req, nbins, nslices, table, S);
     const int nslot = 2 * n;
     i64 blocks = (v.n_req + SQ_BLOCK - 1) / SQ_BLOCK;
     const i64 fit = (i64)(scratch_bytes / (((size_t)nslot << 8) * sizeof(unsigned)));

@@ -144,3 +144,26 @@ def test_tables_of_stochastic_columns(B, oracle, n_req, levels, runs, huge):
     check_dispatch(B, oracle, tr, specs)
     check_stats(B, oracle, tr, specs, DI.COST_S)
     check_stats(B, oracle, tr, specs, DI.COST_S, ws_requests=0)         # no room for the routing: drawn again in every pass
+
+
+# tabulated threshold searches: four steps per round of table reads (step counts around the rounds), tables that end at,
+# in front of and behind a block of 64 lengths and the largest one, prompts longer than the table, 1 .. 64 searches
+@pytest.mark.parametrize("n_req,n_search,n_steps,hi", [(0, 1, 1, 0), (1, 1, 4, 1), (700, 3, 5, 61), (700, 5, 8, 62), (4097, 64, 13, 63),
+                                                       (3000, 7, 16, 1000), (5000, 33, 3, 32_770)])
+def test_tabulated_threshold_searches(B, oracle, n_req, n_search, n_steps, hi):
+    print(f"tabulated searches: n_req={n_req} n_search={n_search} n_steps={n_steps} hi={hi}", flush=True)
+    tr = DI.handmade_trace(170 + n_req, n_req, tokens=False)
+    if n_req > 1000:
+        tr["prompt_len"][::7] = np.arange(len(tr["prompt_len"][::7])) * 31 % 40_000
+    total = int(tr["prompt_len"].sum(dtype=np.int64))
+    which = ["server_prefill_tok", "device_prefill_tok"]
+    specs = [dict(which_param=B.PARAM_L_TH, which_acc=which[j % 5 == 4], n_steps=n_steps, lo=j % 2 if hi else 0, hi=hi,
+                  target=total * j / n_search) for j in range(n_search)]
+    res = B.disco_budget_search(B.upload_trace(tr), DI.COST_S, [B.Policy(mode=0, mig_mode=1)] * n_search, specs)
+    so = B.search_to_host(res["out"], n_search)
+    pol = B.policies_to_host(res["pol_out"], n_search)
+    for j, s in enumerate(specs):
+        l_th, hp, ha = oracle.search_lth(tr, oracle.Policy(mode=0), s["lo"], hi, n_steps, s["which_acc"], DI.COST_S, s["target"])
+        assert (pol[j].l_th, pol[j].mode, pol[j].mig_mode) == (l_th, 0, 1) and int(so["param"][j]) == l_th, j
+        same_bits(so["hist_param"][j][:n_steps].astype(np.int32), hp, f"hist_param {j}")
+        same_bits(so["hist_acc"][j][:n_steps], ha, f"hist_acc {j}")
