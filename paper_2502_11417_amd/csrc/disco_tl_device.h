@@ -78,25 +78,38 @@ enum { TL_DEV = 0,        // device source
 
 // The column sets of a request by kind of timeline (lane = request).  The
 // buffer hand-off (Sec. 4.3) applies when the source is the column's
-// constrained endpoint.
+// constrained endpoint.  The kind of a column is the same in every lane: it
+// branches in scalar registers to what decides the source there (the
+// operations of dispatch_pair, without the TTFT), and the source bits are
+// sorted into the sets once behind the loop.  (Every lane evaluating both
+// modes and sorting per column: the flags, classification and assignment of
+// 10^4 requests x 16 columns 60 us, now 45.)
 __device__ __forceinline__ void request_sets(const disco_policy* sp, int P, int l, float s, float d, i64 i, u64 m[TL_KINDS])
 {
-    u64 m0 = 0ull, m1 = 0ull, m2 = 0ull, m3 = 0ull, m4 = 0ull;
+    const bool race = d < s;                                  // a race that starts both at once: ties go to the server
+    u64 dev = 0ull, buffer = 0ull, lag = 0ull, dev_constrained = 0ull;
     for (int j = 0; j < P; ++j) {
-        unsigned dec; float t;
-        dispatch_pair(sp[j], l, s, d, i, dec, t);
-        const bool dev = (dec & 4u) != 0u;
-        const int mg = sp[j].mig_mode, mode = sp[j].mode;
-        const bool dev_constrained = mode == DISCO_MODE_DEVICE_CONSTRAINED || mode == DISCO_MODE_STOCH_DEVICE;
-        const bool buf = mg == DISCO_MIG_BUFFER && (dev == dev_constrained);
+        const disco_policy p = sp[j];
+        const int mode = __builtin_amdgcn_readfirstlane(p.mode), mg = __builtin_amdgcn_readfirstlane(p.mig_mode);
         const u64 bit = 1ull << j;
-        m4 |= (dev && buf) ? bit : 0ull;
-        m0 |= (dev && !buf) ? bit : 0ull;
-        m3 |= (!dev && buf) ? bit : 0ull;
-        m2 |= (!dev && !buf && mg == DISCO_MIG_LAG) ? bit : 0ull;
-        m1 |= (!dev && !buf && mg != DISCO_MIG_LAG) ? bit : 0ull;
+        bool won;
+        if (mode == DISCO_MODE_SERVER_CONSTRAINED) {
+            won = l < p.l_th || race;
+        } else {
+            disco_policy q = p;
+            q.mode = mode;
+            unsigned dec; float t;
+            dispatch_pair(q, l, s, d, i, dec, t);
+            won = (dec & 4u) != 0u;
+        }
+        dev |= won ? bit : 0ull;
+        buffer |= mg == DISCO_MIG_BUFFER ? bit : 0ull;
+        lag |= mg == DISCO_MIG_LAG ? bit : 0ull;
+        dev_constrained |= mode == DISCO_MODE_DEVICE_CONSTRAINED || mode == DISCO_MODE_STOCH_DEVICE ? bit : 0ull;
     }
-    m[TL_DEV] = m0; m[TL_SRV] = m1; m[TL_SRV_LAG] = m2; m[TL_SRV_BUF] = m3; m[TL_DEV_BUF] = m4;
+    const u64 srv = ~dev & (P < 64 ? (1ull << P) - 1ull : ~0ull), buf = buffer & ~(dev ^ dev_constrained);
+    m[TL_DEV] = dev & ~buf; m[TL_DEV_BUF] = dev & buf;
+    m[TL_SRV] = srv & ~buf & ~lag; m[TL_SRV_LAG] = srv & ~buf & lag; m[TL_SRV_BUF] = srv & buf;
 }
 
 // Pure pacing: a source whose constant gap is safely below tau (gap < 0.999 tau).
