@@ -143,9 +143,9 @@ __device__ __forceinline__ unsigned tbt_key(unsigned bits, unsigned key_lo, unsi
 // Largest digit width whose `groups` histograms fit `words` bins.
 __device__ __host__ __forceinline__ int fit_width(long groups, long words)
 {
-    int w = 0;
-    while (w < 14 && (groups << (w + 1)) <= words) ++w;
-    return w;
+    const unsigned q = (unsigned)words / (unsigned)groups;
+    const int w = q ? 31 - __builtin_clz(q) : 0;
+    return w < 14 ? w : 14;
 }
 
 }  // namespace

@@ -25,16 +25,18 @@
 
 namespace {
 
-// Bin counts of a slot that k_tbt_select sums up in LDS.  Tables without walked timelines (constant gaps) have room for
+// Bin counts of a slot that k_tbt_select sums up in registers (two per thread, the rows of eight classes in flight: 10^5
+// requests x 12 columns 19 us per step when they went through LDS four rows at a time and one thread planned the next pass,
+// now 16).  Tables without walked timelines (constant gaps) have room for
 // digits of 13 and 14 bits, but their 21-bit window takes two passes either way, and an unstaged slot of 8192 bins reads
 // the rows of its classes bin by bin: 10^4 requests x 16 columns 120 us with 13 bits, 28 us with 11.
-constexpr int SEL_STAGED_BITS = 11;
+constexpr int SEL_DIRECT_BITS = 11;
 
 // Prepares the next pass: prefix groups of the live slots, digit width that
 // fits, or the per-slot fallback.  All threads of a workgroup (wave_only: of
 // its first wave, the only one still running); the slots are fetched side by
-// side into LDS (s_prefix, s_grp: DISCO_MAX_SLOTS words each), one thread
-// groups them there.  reset: every slot starts over (empty prefix, full rank).
+// side into LDS (s_prefix, s_grp: DISCO_MAX_SLOTS words each), one wave groups
+// them.  reset: every slot starts over (empty prefix, full rank).
 __device__ void tbt_plan_next(SelState* S, int P, int nq, unsigned* s_prefix, int* s_grp, bool wave_only, bool reset)
 {
     TlSel& tl = S->tl;
@@ -47,35 +49,34 @@ __device__ void tbt_plan_next(SelState* S, int P, int nq, unsigned* s_prefix, in
         s_grp[s] = sl.done ? -2 : -1;
     }
     sync();
-    if (threadIdx.x == 0) {
-        int G = 0;
-        bool over = tl.ncls > DISCO_MAX_CLS || tl.ncls < 1;
-        unsigned gp[DISCO_MAX_GRP] = {0u, 0u, 0u, 0u};
-        for (int s = 0; s < ns; ++s) {
-            int g = -1;
-            if (s_grp[s] != -2) {
-                const unsigned prefix = s_prefix[s];
-#pragma unroll
-                for (int k = 0; k < DISCO_MAX_GRP; ++k)
-                    if (k < G && gp[k] == prefix) g = k;
-                if (g < 0) {
-                    if (G < DISCO_MAX_GRP) {
-#pragma unroll
-                        for (int k = 0; k < DISCO_MAX_GRP; ++k)
-                            if (k == G) gp[k] = prefix;
-                        g = G;
-                    } else {
-                        g = 0;         // too many distinct prefixes: the per-slot fallback does not use groups
-                    }
-                    G += 1;
-                }
-            }
-            s_grp[s] = g;
+    if (threadIdx.x < 64) {
+        // the distinct prefixes in slot order, one after the other; a lane holds slots `lane` and 64 + `lane`
+        static_assert(DISCO_MAX_SLOTS == 128, "two slots per lane");
+        const int lane = threadIdx.x;
+        const unsigned p0 = lane < ns ? s_prefix[lane] : 0u, p1 = 64 + lane < ns ? s_prefix[64 + lane] : 0u;
+        u64 todo0 = __ballot(lane < ns && s_grp[lane < ns ? lane : 0] != -2);
+        u64 todo1 = __ballot(64 + lane < ns && s_grp[64 + lane < ns ? 64 + lane : 0] != -2);
+        const bool live0 = (todo0 >> lane) & 1ull, live1 = (todo1 >> lane) & 1ull;
+        int G = 0, g0 = -1, g1 = -1;
+        while ((todo0 | todo1) != 0ull && G < DISCO_MAX_GRP) {
+            const unsigned px = todo0 ? (unsigned)bcast_i((int)p0, __ffsll((long long)todo0) - 1) : (unsigned)bcast_i((int)p1, __ffsll((long long)todo1) - 1);
+            const bool h0 = live0 && p0 == px, h1 = live1 && p1 == px;
+            if (h0) g0 = G;
+            if (h1) g1 = G;
+            todo0 &= ~__ballot(h0); todo1 &= ~__ballot(h1);
+            if (lane == 0) tl.grp_prefix[G] = px;
+            G += 1;
         }
-#pragma unroll
-        for (int k = 0; k < DISCO_MAX_GRP; ++k)
-            if (k < G) tl.grp_prefix[k] = gp[k];
+        if ((todo0 | todo1) != 0ull) {         // too many distinct prefixes: the per-slot fallback does not use groups
+            G += 1;
+            if (live0 && g0 < 0) g0 = 0;
+            if (live1 && g1 < 0) g1 = 0;
+        }
+        if (lane < ns) tl.slot_grp[lane] = g0;
+        if (64 + lane < ns) tl.slot_grp[64 + lane] = g1;
+        bool over = tl.ncls > DISCO_MAX_CLS || tl.ncls < 1;
         if (G > DISCO_MAX_GRP) over = true;
+        if (lane != 0) return;
         if (over) tl.fallback = 1;
         tl.G = G;
         int w;
@@ -87,7 +88,7 @@ __device__ void tbt_plan_next(SelState* S, int P, int nq, unsigned* s_prefix, in
             const int wg = fit_width((long)g1 * tl.ncls, DISCO_GHIST_WORDS);
             if (wg < w) w = wg;
             // a digit wider than the select step stages in LDS only where it saves a pass
-            if (w > SEL_STAGED_BITS && (tl.left + w - 1) / w == (tl.left + SEL_STAGED_BITS - 1) / SEL_STAGED_BITS) w = SEL_STAGED_BITS;
+            if (w > SEL_DIRECT_BITS && (tl.left + w - 1) / w == (tl.left + SEL_DIRECT_BITS - 1) / SEL_DIRECT_BITS) w = SEL_DIRECT_BITS;
         }
         if (w < 1) w = 1;
         if (w > tl.left) w = tl.left;
@@ -95,8 +96,6 @@ __device__ void tbt_plan_next(SelState* S, int P, int nq, unsigned* s_prefix, in
         tl.width = w;
         tl.shift = tl.left - w;
     }
-    sync();
-    for (int s = threadIdx.x; s < ns; s += nt) tl.slot_grp[s] = s_grp[s];
 }
 
 // Distinct column sets of a workgroup's requests: an open-addressing hash table in LDS (CL_SLOTS slots, far more
@@ -346,9 +345,9 @@ __device__ void analytic_class(SelState* S, unsigned* ghist, const unsigned* ppc
 // class histograms of the classes that contain the slot's column (or take the
 // slot's own histogram in the fallback), walk to the digit that holds the
 // remaining rank, extend the prefix.
-//   binsum: LDS scratch of binsum_cap words: the slot's bin counts are summed over its classes there with
-//   coalesced reads of the class rows (a thread then scans consecutive bins from LDS); wider digits and the
-//   fallback read the rows directly.
+//   binsum: LDS scratch of binsum_cap words: the bin counts of a slot with more than two bins per thread are summed over
+//   its classes there with coalesced reads of the class rows (a thread then scans consecutive bins from LDS); wider digits
+//   and the fallback read the rows directly.
 __device__ void select_slot(SelState* S, int nq, const unsigned* ghist, int s, u64* wsum /* LDS, 64 */, int* s_digit, u64* s_rem,
                             u64* binsum, int binsum_cap)
 {
@@ -362,8 +361,11 @@ __device__ void select_slot(SelState* S, int nq, const unsigned* ghist, int s, u
     const int nbins = 1 << width;
     const int per = (nbins + (int)blockDim.x - 1) / (int)blockDim.x;      // consecutive bins per thread
     const int b0 = threadIdx.x * per;
-    const bool staged = !fallback && nbins <= binsum_cap;
-    if (staged) {
+    // up to two bins per thread are summed over the classes in registers, wider digits in LDS
+    const bool direct = !fallback && per <= 2;
+    const bool staged = !fallback && !direct && nbins <= binsum_cap;
+    u64 own[2] = {0ull, 0ull};
+    if (direct || staged) {
         // the classes that contain the column (the first wave lists them in wsum[0 .. nk), nk in *s_digit), then
         // every bin is the sum over their rows: all loads independent and coalesced
         __syncthreads();
@@ -375,15 +377,32 @@ __device__ void select_slot(SelState* S, int nq, const unsigned* ghist, int s, u
         }
         __syncthreads();
         const int nk = *s_digit;
-        for (int b = threadIdx.x; b < nbins; b += (int)blockDim.x) {
-            u64 c = 0;
+        if (direct) {
+            if (b0 < nbins) {
+                const unsigned* base = ghist + ((size_t)(g * ncls) << width) + b0;
+                if (per == 2) {
+#pragma unroll 8
+                    for (int j = 0; j < nk; ++j) {
+                        const uint2 v = *reinterpret_cast<const uint2*>(base + ((size_t)wsum[j] << width));
+                        own[0] += v.x; own[1] += v.y;
+                    }
+                } else {
+#pragma unroll 8
+                    for (int j = 0; j < nk; ++j) own[0] += base[(size_t)wsum[j] << width];
+                }
+            }
+        } else {
+            for (int b = threadIdx.x; b < nbins; b += (int)blockDim.x) {
+                u64 c = 0;
 #pragma unroll 4
-            for (int j = 0; j < nk; ++j) c += ghist[((size_t)(g * ncls + (int)wsum[j]) << width) | b];
-            binsum[b] = c;
+                for (int j = 0; j < nk; ++j) c += ghist[((size_t)(g * ncls + (int)wsum[j]) << width) | b];
+                binsum[b] = c;
+            }
         }
         __syncthreads();
     }
     auto bin_count = [&](int b) -> u64 {
+        if (direct) return b == b0 ? own[0] : own[1];
         if (staged) return binsum[b];
         if (fallback) return ghist[((size_t)s << width) | b];
         u64 c = 0;
@@ -472,7 +491,8 @@ __device__ void plan_pass(SelState* S, int P, int nq, unsigned* ghist, unsigned*
     const int Gused = tl.G < DISCO_MAX_GRP ? tl.G : DISCO_MAX_GRP;
     const int words = (tl.fallback ? P * nq : Gused * tl.ncls) << width;
     __syncthreads();
-    for (int i = threadIdx.x; i < words; i += blockDim.x) ghist[i] = 0u;
+    for (int i = threadIdx.x; i < words / 4; i += blockDim.x) reinterpret_cast<uint4*>(ghist)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if ((int)threadIdx.x < words % 4) ghist[words / 4 * 4 + threadIdx.x] = 0u;      // (digits of one bit)
     __syncthreads();
     const bool restart = tl.window && tl.restart;          // the window missed a rank: all slots start over on raw keys
     const bool more = restart || tl.left - width > 0;
@@ -532,11 +552,12 @@ __global__ __launch_bounds__(1024) void k_tbt_select(SelState* S, int P, int nq,
     __shared__ u64 wsum[DISCO_MAX_CLS];
     __shared__ int s_digit;
     __shared__ u64 s_rem;
-    __shared__ u64 binsum[1 << SEL_STAGED_BITS];
+    __shared__ unsigned s_prefix[DISCO_MAX_SLOTS];
+    __shared__ int s_grp[DISCO_MAX_SLOTS];
     if (S->tl.width <= 0) return;
-    select_slot(S, nq, ghist, blockIdx.x, wsum, &s_digit, &s_rem, binsum, 1 << SEL_STAGED_BITS);
+    select_slot(S, nq, ghist, blockIdx.x, wsum, &s_digit, &s_rem, nullptr, 0);
     if (!take_last_ticket(ticket)) return;
-    plan_pass(S, P, nq, ghist, reinterpret_cast<unsigned*>(binsum), reinterpret_cast<int*>(binsum + DISCO_MAX_SLOTS));
+    plan_pass(S, P, nq, ghist, s_prefix, s_grp);
     if (threadIdx.x == 0) *ticket = 0u;
 }
 
