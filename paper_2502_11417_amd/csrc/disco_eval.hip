@@ -28,7 +28,11 @@ __host__ __device__ inline MigPartial* tl_totals(u64* totals)
 
 // Start of a selection (all threads of one workgroup): one thread per slot: rank from (num, den, M), empty
 // prefix; plan of the passes.
-struct SelInit { SelState* S; int nq; disco_quantile q[4]; const disco_accum* acc; i64 n_req; int with_tbt; };
+struct SelInit {
+    SelState* S; int nq; disco_quantile q[4]; const disco_accum* acc; i64 n_req; int with_tbt;
+    unsigned *ppcnt, *dhist;       // counts of the TBT selection, cleared in the launch that starts it
+};
+constexpr int STAGE_CLEAR = 61;    // workgroups that clear them
 
 __device__ void select_init(const SelInit& si, int which, int P, const disco_policy* pol)
 {
@@ -67,24 +71,23 @@ __device__ void select_init(const SelInit& si, int which, int P, const disco_pol
         atomicMax(&smax, acc[threadIdx.x].ttft_max_bits);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        SelGlobal g;
-        if (which == 0) {
-            g.minb = smin <= smax ? smin : 0u;
-            g.maxb = smin <= smax ? smax : 0u;
-            unsigned range = g.maxb - g.minb;
-            int left = range ? 32 - __clz(range) : 0;
-            SelPlan pl;
-            pl.npass = 0; pl.pad = 0;
-            for (int i = 0; i < DISCO_MAX_PASS; ++i) { pl.shift[i] = 0; pl.width[i] = 0; }
-            while (left > 0) {
-                int wd = left < 8 ? left : 8;
-                pl.width[pl.npass] = wd; pl.shift[pl.npass] = left - wd;
-                left -= wd; pl.npass += 1;
-            }
-            g.plan = pl;
+    if (which == 0 && threadIdx.x < DISCO_MAX_PASS) {
+        // digits of 8 bits from the top of the range's bits down
+        const unsigned lo = smin <= smax ? smin : 0u, hi = smin <= smax ? smax : 0u;
+        const int i = threadIdx.x, bits = hi != lo ? 32 - __clz(hi - lo) : 0, left = bits - 8 * i;
+        SelGlobal& g = S->g[0];
+        g.plan.width[i] = left <= 0 ? 0 : (left < 8 ? left : 8);
+        g.plan.shift[i] = left <= 8 ? 0 : left - 8;
+        if (i == 0) {
+            g.minb = lo; g.maxb = hi;
+            g.plan.npass = (bits + 7) / 8; g.plan.pad = 0;
             g.gather_bound = 0ull; g.n_list = 0u; g.gather_error = 0;
-        } else {                      // TBT: raw keys; the passes are planned on the device (TlSel)
+        }
+    }
+    if (which == 1 && threadIdx.x == 0) {
+        SelGlobal g;
+        {
+            // TBT: raw keys; the passes are planned on the device (TlSel)
             g.minb = 0u; g.maxb = 0x7FFFFFFFu;
             g.gather_bound = 0ull; g.n_list = 0u; g.gather_error = 0;
             g.plan.npass = 0; g.plan.pad = 0;
@@ -128,30 +131,21 @@ __device__ inline void reset_totals(u64* totals)
 }
 
 // With a selection state (si.S), the TTFT selection of the statistics (and, if asked, the TBT selection) is started
-// in the same launch.
-__global__ __launch_bounds__(STAGE_THREADS) void k_store_policies(PolTable t, int P, disco_policy* dst, unsigned* tickets, u64* totals,
-                                                                  SelInit si)
+// in the same launch by a workgroup of its own (one after the other in one workgroup: 10 us for 8 columns and
+// 12.5 us for 64, now 6 with the clearing and 10).
+__device__ __forceinline__ void stage_table(const disco_policy* src, int P, disco_policy* dst, unsigned* tickets, u64* totals,
+                                            const SelInit& si)
 {
-    const int i = threadIdx.x;
-    if (i < 64) {
-        if (i < P) dst[i] = t.p[i];
-        const bool any_buffer = __ballot(i < P && t.p[i < P ? i : 0].mig_mode == DISCO_MIG_BUFFER) != 0ull;
-        tickets[i] = (i == DISCO_FLAG_BUFFER && any_buffer) ? 1u : 0u;
+    if (blockIdx.x > 2) {          // (1 MB and 32 KB per column)
+        const int first = ((int)blockIdx.x - 3) * STAGE_THREADS + (int)threadIdx.x, step = ((int)gridDim.x - 3) * STAGE_THREADS;
+        for (int w = first; w < DISCO_MAX_CLS * (DISCO_PP_NMAX + 1); w += step) si.ppcnt[w] = 0u;
+        for (int w = first; w < P * DISCO_DELAY_BINS; w += step) si.dhist[w] = 0u;
+        return;
     }
-    reset_totals(totals);
-    if (si.S) {
-        __syncthreads();                       // the staged table is read back by this workgroup
-        select_init(si, 0, P, dst);
-        if (si.with_tbt) {
-            __syncthreads();
-            select_init(si, 1, P, dst);
-        }
+    if (blockIdx.x > 0) {
+        select_init(si, (int)blockIdx.x - 1, P, src);
+        return;
     }
-}
-
-__global__ __launch_bounds__(STAGE_THREADS) void k_copy_policies(const disco_policy* src, int P, disco_policy* dst, unsigned* tickets, u64* totals,
-                                                                 SelInit si)
-{
     const int i = threadIdx.x;
     if (i < 64) {
         if (i < P) dst[i] = src[i];
@@ -159,14 +153,19 @@ __global__ __launch_bounds__(STAGE_THREADS) void k_copy_policies(const disco_pol
         tickets[i] = (i == DISCO_FLAG_BUFFER && any_buffer) ? 1u : 0u;
     }
     reset_totals(totals);
-    if (si.S) {
-        __syncthreads();                       // the staged table is read back by this workgroup
-        select_init(si, 0, P, dst);
-        if (si.with_tbt) {
-            __syncthreads();
-            select_init(si, 1, P, dst);
-        }
-    }
+}
+
+__global__ __launch_bounds__(STAGE_THREADS) void k_store_policies(PolTable t, int P, disco_policy* dst, unsigned* tickets, u64* totals,
+                                                                  SelInit si)
+{
+    stage_table(t.p, P, dst, tickets, totals, si);
+}
+
+// (dst may be src: the selection's workgroup then reads what the first one writes back unchanged)
+__global__ __launch_bounds__(STAGE_THREADS) void k_copy_policies(const disco_policy* src, int P, disco_policy* dst, unsigned* tickets, u64* totals,
+                                                                 SelInit si)
+{
+    stage_table(src, P, dst, tickets, totals, si);
 }
 
 // ----------------------------------------------------------------- select --
@@ -177,102 +176,104 @@ __global__ __launch_bounds__(STAGE_THREADS) void k_copy_policies(const disco_pol
 
 // ------------------------------------------------------------ final stats --
 
-// Order statistics of the delayed tokens per migrated request (all threads of a workgroup, column c): the counts
-// by number of delayed tokens come from the first histogram pass of the timelines with a buffer hand-off;
-// migrations of the lag trigger have none and count as zeros.  Nearest rank, like the other order statistics.
-// dq[qi] keeps its value for a column without migrations.
-__device__ void delay_quantiles(int c, int nq, const disco_quantile* qs, const disco_accum* acc, const unsigned* __restrict__ dhist,
-                                u64* part /* LDS, 256 */, float* dq /* LDS */)
-{
-    constexpr int PER = DISCO_DELAY_BINS / 256;
-    const int t = threadIdx.x;
-    const i64 M = acc[c].n_migrated;
-    if (M <= 0) return;                                  // (the same answer in every thread)
-    const unsigned* row = dhist + (size_t)c * DISCO_DELAY_BINS;
-    unsigned v[PER];
-    u64 mine = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) { v[k] = row[t * PER + k]; mine += v[k]; }
-    part[t] = mine;
-    __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {                  // inclusive prefix sums of the per-thread totals
-        const u64 o = t >= d ? part[t - d] : 0;
-        __syncthreads();
-        part[t] += o;
-        __syncthreads();
-    }
-    const u64 counted = part[255];
-    const u64 zeros = (u64)M > counted ? (u64)M - counted : 0;      // hand-offs without a count: no delayed token
-    if (t == 0) v[0] += (unsigned)zeros;
-    const u64 below = t > 0 ? part[t - 1] + zeros : 0;               // migrated requests with fewer delayed tokens than t * PER
-    for (int qi = 0; qi < nq; ++qi) {
-        i64 k = ((i64)qs[qi].num * M + qs[qi].den - 1) / qs[qi].den;
-        if (k < 1) k = 1;
-        if (k > M) k = M;
-        u64 cum = below;
-#pragma unroll
-        for (int b = 0; b < PER; ++b) {
-            if (cum < (u64)k && cum + v[b] >= (u64)k) dq[qi] = (float)(t * PER + b);
-            cum += v[b];
-        }
-    }
-}
-
-// The record of a column from its accumulators and the selections' results.  With delayed-token order statistics
-// to work out (timelines and quantiles asked for): workgroup = column, 256 threads; otherwise one workgroup,
-// thread = column.
-__global__ __launch_bounds__(256) void k_stats_final(int P, int nq, i64 n_req, disco_cost_params cost, int with_tl,
+// The record of a column from its accumulators and the selections' results (workgroup = column).
+//
+// Order statistics of the delayed tokens per migrated request: the counts by number of delayed tokens come from the
+// first histogram pass of the timelines with a buffer hand-off; migrations of the lag trigger have none and count as
+// zeros.  Nearest rank, like the other order statistics; NaN for a column without migrations.
+//
+// Bound by latency: the counts, the accumulators and the slots are fetched side by side by different waves, the record is
+// put together in LDS (9 us with one thread for all but the counts, now 4 - 6).
+__global__ __launch_bounds__(256) void k_stats_final(int nq, i64 n_req, disco_cost_params cost, int with_tl,
                                                      const disco_accum* acc, const SelState* S, disco_quantile q0,
                                                      disco_quantile q1, disco_quantile q2, disco_quantile q3,
                                                      const unsigned* __restrict__ dhist, disco_stats* out)
 {
-    __shared__ u64 part[256];
+    constexpr int PER = DISCO_DELAY_BINS / 256;
+    __shared__ u64 wtot[4];
+    __shared__ i64 drank[DISCO_MAX_Q];
     __shared__ float dq[DISCO_MAX_Q];
-    const bool per_column = with_tl && nq > 0;
-    const int c = per_column ? blockIdx.x : threadIdx.x;
-    if (threadIdx.x < DISCO_MAX_Q) dq[threadIdx.x] = NAN;
-    __syncthreads();
-    if (per_column) {
-        const disco_quantile qs[4] = {q0, q1, q2, q3};
-        delay_quantiles(c, nq, qs, acc, dhist, part, dq);
-        __syncthreads();
-        if (threadIdx.x != 0) return;
-    } else if (c >= P) {
-        return;
+    __shared__ disco_stats st;
+    const int c = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const i64 migrated = with_tl ? acc[c].n_migrated : 0;
+    const bool delays = with_tl && nq > 0 && migrated > 0;
+    unsigned v[PER];
+    u64 mine = 0;
+    if (delays) {
+        const unsigned* row = dhist + (size_t)c * DISCO_DELAY_BINS;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) { v[k] = row[t * PER + k]; mine += v[k]; }
     }
-    const disco_accum a = acc[c];
-    disco_stats st;
-    memset(&st, 0, sizeof(st));
-    st.n_req = n_req;
-    st.s_pre = a.s_pre + (with_tl ? a.m_s_repre : 0);
-    st.d_pre = a.d_pre + (with_tl ? a.m_d_repre : 0);
-    st.s_dec = with_tl ? a.m_s_dec : a.s_dec;
-    st.d_dec = with_tl ? a.m_d_dec : a.d_dec;
-    st.n_dev_started = a.n_dev_started;
-    st.n_dev_win = a.n_dev_win;
-    st.n_migrated = with_tl ? a.n_migrated : 0;
-    st.tbt_count = with_tl ? a.tbt_count : 0;
-    st.mean_ttft = a.ttft_sum / (double)n_req;                       // 0/0 = NaN for an empty batch
-    st.mean_tbt = with_tl ? a.tlast_sum / (double)a.tbt_count : NAN;  // telescoped sum of gaps
-    st.mean_delay_num = (with_tl && a.n_migrated > 0) ? (double)a.delay_sum / (double)a.n_migrated : NAN;
-    st.server_cost = server_cost_of(cost, st.s_pre, st.s_dec);
-    st.device_energy = device_energy_of(cost, st.d_pre, st.d_dec);
-    st.device_cost = cost.lambda * st.device_energy;
-    st.total_cost = st.server_cost + st.device_cost;
-    for (int qi = 0; qi < DISCO_MAX_Q; ++qi) {
-        st.ttft_q[qi] = NAN; st.tbt_q[qi] = NAN; st.delay_q[qi] = dq[qi];
+    if (t < (int)(sizeof(st) / 8)) reinterpret_cast<u64*>(&st)[t] = 0ull;
+    if (t < DISCO_MAX_Q) dq[t] = NAN;
+    __syncthreads();
+    if (t == 0) {
+        const disco_accum a = acc[c];
+        st.n_req = n_req;
+        st.s_pre = a.s_pre + (with_tl ? a.m_s_repre : 0);
+        st.d_pre = a.d_pre + (with_tl ? a.m_d_repre : 0);
+        st.s_dec = with_tl ? a.m_s_dec : a.s_dec;
+        st.d_dec = with_tl ? a.m_d_dec : a.d_dec;
+        st.n_dev_started = a.n_dev_started;
+        st.n_dev_win = a.n_dev_win;
+        st.n_migrated = migrated;
+        st.tbt_count = with_tl ? a.tbt_count : 0;
+        st.mean_ttft = a.ttft_sum / (double)n_req;                       // 0/0 = NaN for an empty batch
+        st.mean_tbt = with_tl ? a.tlast_sum / (double)a.tbt_count : NAN;  // telescoped sum of gaps
+        st.mean_delay_num = (with_tl && a.n_migrated > 0) ? (double)a.delay_sum / (double)a.n_migrated : NAN;
+        st.server_cost = server_cost_of(cost, st.s_pre, st.s_dec);
+        st.device_energy = device_energy_of(cost, st.d_pre, st.d_dec);
+        st.device_cost = cost.lambda * st.device_energy;
+        st.total_cost = st.server_cost + st.device_cost;
+    }
+    if (t >= 64 && t < 64 + DISCO_MAX_Q) {
+        const int qi = t - 64;
+        float tq = NAN, bq = NAN;
         if (qi < nq) {
+            const disco_quantile q = qi == 0 ? q0 : (qi == 1 ? q1 : (qi == 2 ? q2 : q3));
             const SelSlot s0 = S->slot[0][c * nq + qi];
             st.ttft_rank[qi] = s0.rank;
-            if (s0.M > 0 && !S->g[0].gather_error) st.ttft_q[qi] = u2f(S->g[0].minb + s0.prefix);
+            if (s0.M > 0 && !S->g[0].gather_error) tq = u2f(S->g[0].minb + s0.prefix);
             if (with_tl) {
                 const SelSlot s1 = S->slot[1][c * nq + qi];
                 st.tbt_rank[qi] = s1.rank;
-                if (s1.M > 0 && !S->tl.error && S->tl.left == 0) st.tbt_q[qi] = u2f(s1.prefix + S->tl.key_lo);
+                if (s1.M > 0 && !S->tl.error && S->tl.left == 0) bq = u2f(s1.prefix + S->tl.key_lo);
+            }
+            i64 k = ((i64)q.num * migrated + q.den - 1) / q.den;
+            if (k < 1) k = 1;
+            drank[qi] = k < migrated ? k : migrated;
+        }
+        st.ttft_q[qi] = tq; st.tbt_q[qi] = bq;
+    }
+    // inclusive prefix sums of the per-thread counts
+    u64 incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned lo = (unsigned)__shfl_up((int)(unsigned)incl, d, 64), hi = (unsigned)__shfl_up((int)(unsigned)(incl >> 32), d, 64);
+        if (lane >= d) incl += ((u64)hi << 32) | lo;
+    }
+    if (lane == 63) wtot[wave] = incl;
+    __syncthreads();
+    if (delays) {
+        u64 counted = 0;
+        for (int w = 0; w < 4; ++w) { counted += wtot[w]; incl += w < wave ? wtot[w] : 0ull; }
+        const u64 zeros = (u64)migrated > counted ? (u64)migrated - counted : 0;      // hand-offs without a count: no delayed token
+        if (t == 0) v[0] += (unsigned)zeros;
+        const u64 below = t > 0 ? incl - mine + zeros : 0;               // migrated requests with fewer delayed tokens than t * PER
+        for (int qi = 0; qi < nq; ++qi) {
+            const u64 k = (u64)drank[qi];
+            u64 cum = below;
+#pragma unroll
+            for (int b = 0; b < PER; ++b) {
+                if (cum < k && cum + v[b] >= k) dq[qi] = (float)(t * PER + b);
+                cum += v[b];
             }
         }
     }
-    out[c] = st;
+    __syncthreads();
+    if (t < DISCO_MAX_Q) st.delay_q[t] = dq[t];
+    __syncthreads();
+    if (t < (int)(sizeof(st) / 8)) reinterpret_cast<u64*>(&out[c])[t] = reinterpret_cast<const u64*>(&st)[t];
 }
 
 // Mean over the runs of a group of columns: floating-point fields in fp64, summed in run order; integer
@@ -406,10 +407,11 @@ int stage_policies(const disco_policy* pol, int P, char* ws, const WsLayout& L, 
     SelInit si;
     memset(&si, 0, sizeof(si));
     if (sel) si = *sel;
+    const unsigned workgroups = !sel ? 1u : (sel->with_tbt ? 3u + STAGE_CLEAR : 2u);
     if (!pol) return DISCO_ERR_NULL;
     if (P < 1 || P > DISCO_MAX_COLS) return DISCO_ERR_SHAPE;
     if (is_device_pointer(pol)) {
-        hipLaunchKernelGGL(k_copy_policies, dim3(1), dim3(STAGE_THREADS), 0, stream, pol, P, (disco_policy*)(ws + L.pol),
+        hipLaunchKernelGGL(k_copy_policies, dim3(workgroups), dim3(STAGE_THREADS), 0, stream, pol, P, (disco_policy*)(ws + L.pol),
                            (unsigned*)(ws + L.ticket), (u64*)(ws + L.part), si);
         return DISCO_OK;
     }
@@ -418,7 +420,7 @@ int stage_policies(const disco_policy* pol, int P, char* ws, const WsLayout& L, 
     PolTable t;
     memset(&t, 0, sizeof(t));
     memcpy(t.p, pol, sizeof(disco_policy) * (size_t)P);
-    hipLaunchKernelGGL(k_store_policies, dim3(1), dim3(STAGE_THREADS), 0, stream, t, P, (disco_policy*)(ws + L.pol),
+    hipLaunchKernelGGL(k_store_policies, dim3(workgroups), dim3(STAGE_THREADS), 0, stream, t, P, (disco_policy*)(ws + L.pol),
                        (unsigned*)(ws + L.ticket), (u64*)(ws + L.part), si);
     return DISCO_OK;
 }
@@ -721,6 +723,7 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
     si.S = S; si.nq = nq; si.acc = acc; si.n_req = v.n_req;
     for (int i = 0; i < 4; ++i) si.q[i] = qs[i];
     si.with_tbt = tl != nullptr;
+    si.ppcnt = (unsigned*)(ws + L.ppcnt); si.dhist = (unsigned*)(ws + L.dhist);
     rc = stage_policies(pol, P, ws, L, stream, nq > 0 ? &si : nullptr);        // with the start of the TTFT selection
     if (rc) return rc;
     if (nq > 0) {
@@ -754,12 +757,12 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
                 disco_launch_tl_walk(v, trace->n_tok, dpol, P, a.tau, a.kt, a.wflags, a.summary, a.counter, stream);
                 disco_launch_tl_stats_buf(v, trace->n_tok, dpol, a, nullptr, stream);      // summaries only
             }
-            disco_launch_tl_classify(v, dpol, P, nq, tl->tau, a.summary, a.bufsum, S, a.ppcnt, gh, a.dhist,
+            disco_launch_tl_classify(v, dpol, P, nq, tl->tau, a.summary, a.bufsum, S,
                                      (unsigned*)(ws + L.ticket), stream);
             a.desc = (u64*)(ws + disco_ws_desc_offset(L, v.n_req));
             a.list = (unsigned*)(a.desc + v.n_req);
             disco_launch_tl_assign(v, dpol, P, a.summary, S, a.bufsum, a.desc, a.list, (unsigned*)(ws + L.slices),
-                                   L.total - L.slices, a.ppcnt, a.dhist, stream);
+                                   L.total - L.slices, a.ppcnt, gh, a.dhist, stream);
             disco_launch_pp_suffix(S, a.ppcnt, stream);
             for (int pass = 0; pass < DISCO_TBT_MAX_PASS; ++pass) {
                 a.pass = pass;
@@ -768,9 +771,8 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
             }
         }
     }
-    const bool per_column = tl && nq > 0;
-    hipLaunchKernelGGL(k_stats_final, dim3(per_column ? (unsigned)P : 1u), dim3(per_column ? 256 : 64), 0, stream, P, nq, v.n_req,
-                       *cost, tl ? 1 : 0, acc, S, qs[0], qs[1], qs[2], qs[3], (const unsigned*)(ws + L.dhist), out);
+    hipLaunchKernelGGL(k_stats_final, dim3((unsigned)P), dim3(256), 0, stream, nq, v.n_req, *cost, tl ? 1 : 0, acc, S, qs[0], qs[1],
+                       qs[2], qs[3], (const unsigned*)(ws + L.dhist), out);
     DISCO_HIP(hipGetLastError());
     return DISCO_OK;
 }

@@ -101,12 +101,12 @@ void disco_launch_tl_walk(const TraceView& v, i64 n_tok, const disco_policy* pol
 void disco_launch_timeline_general(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                    hipStream_t stream);
 void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, int nq, float tau, const void* summary,
-                              const void* bufsum, SelState* S, unsigned* ppcnt, unsigned* ghist, unsigned* dhist,
+                              const void* bufsum, SelState* S,
                               unsigned* ticket, hipStream_t stream);
 void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                hipStream_t stream);
 void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, const void* summary, SelState* S,
                             const void* bufsum, u64* desc, unsigned* list, unsigned* slices, size_t slices_bytes,
-                            unsigned* ppcnt, unsigned* dhist, hipStream_t stream);
+                            unsigned* ppcnt, unsigned* ghist, unsigned* dhist, hipStream_t stream);
 void disco_launch_pp_suffix(SelState* S, unsigned* ppcnt, hipStream_t stream);
 void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a, hipStream_t stream);

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
                                                         unsigned* __restrict__ slices, unsigned* __restrict__ ppcnt,
                                                         unsigned* __restrict__ dhist, int use_lds)
 {
-    __shared__ unsigned cnt[PP_LDS_CLS * PP_WORDS];          // 128 KB
+    __shared__ __align__(16) unsigned cnt[PP_LDS_CLS * PP_WORDS];          // 128 KB
     __shared__ unsigned dh[DISCO_MAX_COLS * DH_LDS_BINS];
     __shared__ unsigned s_nw[2], s_base[2];                  // [0] long requests (front of the list), [1] the others (back)
     __shared__ u64 s_cls[DISCO_MAX_CLS];
@@ -160,16 +160,22 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
     }
     for (int i = threadIdx.x; i < P * DH_LDS_BINS; i += AS_BLOCK)
         if (dh[i]) atomicAdd(&dhist[(size_t)(i / DH_LDS_BINS) * DISCO_DELAY_BINS + i % DH_LDS_BINS], dh[i]);
-    unsigned* mine = slices + (size_t)blockIdx.x * PP_LDS_CLS * PP_WORDS;
-    for (int i = threadIdx.x; i < nlds * PP_WORDS; i += AS_BLOCK) mine[i] = cnt[i];
+    // (whole vectors: the words behind the last class belong to rows that are not read)
+    static_assert(PP_LDS_CLS * PP_WORDS % 4 == 0, "slices of whole vectors");
+    uint4* mine = reinterpret_cast<uint4*>(slices) + (size_t)blockIdx.x * (PP_LDS_CLS * PP_WORDS / 4);
+    for (int i = threadIdx.x; 4 * i < nlds * PP_WORDS; i += AS_BLOCK) mine[i] = reinterpret_cast<const uint4*>(cnt)[i];
 }
 
 // ppcnt[c][n] += sum over the workgroup slices.  Workgroup = (class, 256 words of two lengths each); four groups
-// of threads share the slices and meet in LDS.
+// of threads share the slices and meet in LDS.  The launch also clears the device-wide bins of the histogram passes (1 MB;
+// the TTFT selection has used them before).
 __global__ __launch_bounds__(1024) void k_pp_reduce(const SelState* S, int nslices, const unsigned* __restrict__ slices,
-                                                    unsigned* __restrict__ ppcnt, int use_lds)
+                                                    unsigned* __restrict__ ppcnt, unsigned* __restrict__ ghist, int use_lds)
 {
     __shared__ unsigned part[2][1024];
+    static_assert(DISCO_GHIST_WORDS % 4 == 0, "bins of whole vectors");
+    for (unsigned i = (blockIdx.y * gridDim.x + blockIdx.x) * 1024u + threadIdx.x; i < DISCO_GHIST_WORDS / 4; i += gridDim.x * gridDim.y * 1024u)
+        reinterpret_cast<uint4*>(ghist)[i] = make_uint4(0u, 0u, 0u, 0u);
     const TlSel* tl = &S->tl;
     const int c = blockIdx.x;
     if (tl->fallback || !use_lds || c >= tl->ncls || c >= PP_LDS_CLS) return;
@@ -206,11 +212,15 @@ __global__ __launch_bounds__(TH_BLOCK, 8) void k_tl_hist(TraceView tr, i64 n_tok
 // and length.  `slices`: scratch for the workgroup slices (slices_bytes).
 void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, const void* summary, SelState* S,
                             const void* bufsum, u64* desc, unsigned* list, unsigned* slices, size_t slices_bytes,
-                            unsigned* ppcnt, unsigned* dhist, hipStream_t stream)
+                            unsigned* ppcnt, unsigned* ghist, unsigned* dhist, hipStream_t stream)
 {
     if (v.n_req <= 0) return;
     i64 b = (v.n_req + 49151) / 49152;             // at most 65535 requests per workgroup: 16-bit counts in LDS
-    if (b < 250) b = 250;                          // one workgroup per CU (128 KB of LDS each); at most 64 rounds per thread
+    // one workgroup per CU (128 KB of LDS each, at most 64 rounds per thread); fewer where every request has a thread of
+    // its own, as each workgroup writes up to 128 KB of counts (10^4 requests x 16 columns: 22 us with 250 of
+    // them, 13 with 10, and 8 -> 3 us for their sum)
+    const i64 threads = (v.n_req + AS_BLOCK - 1) / AS_BLOCK, cus = threads < 250 ? threads : 250;
+    if (b < cus) b = cus;
     const i64 fit = (i64)(slices_bytes / ((size_t)PP_LDS_CLS * PP_WORDS * sizeof(unsigned)));
     int use_lds = 1;
     // tens of millions of requests (or the testing aid that shrinks the grids): counts in device memory
@@ -218,7 +228,7 @@ void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, 
     hipLaunchKernelGGL(k_tl_assign, dim3((unsigned)b), dim3(AS_BLOCK), 0, stream, v, pol, P, (const TlSummary*)summary,
                        (const BufSummary*)bufsum, S, desc, list, slices, ppcnt, dhist, use_lds);
     hipLaunchKernelGGL(k_pp_reduce, dim3(PP_LDS_CLS, (PP_WORDS + 255) / 256), dim3(1024), 0, stream, (const SelState*)S, (int)b, (const unsigned*)slices,
-                       ppcnt, use_lds);
+                       ppcnt, ghist, use_lds);
 }
 
 void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,

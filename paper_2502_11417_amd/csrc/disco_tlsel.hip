@@ -165,22 +165,16 @@ __device__ __forceinline__ int table_compact(ClassTable& T)
 // Column sets of every request -> classes.  Every workgroup collects its distinct sets in an LDS hash table
 // and enters them (a few dozen) into a device-wide table of the same kind; the workgroup that takes the last
 // ticket compacts that table, puts the sets in ascending order (so that the class numbers do not depend on
-// timing), numbers the classes that need a token walk and plans the first histogram pass.  Also clears the length
-// counts and the device-wide bins.  The device-wide table was zeroed when the selection started (select_init, in
-// the launch that stages the policy table).
+// timing), numbers the classes that need a token walk and plans the first histogram pass.  The device-wide table was zeroed
+// when the selection started (select_init, in the launch that stages the policy table).
 __global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const disco_policy* __restrict__ pol, int P, int nq,
                                                      float tau, const TlSummary* __restrict__ summary,
-                                                     const BufSummary* __restrict__ bufsum, SelState* S,
-                                                     unsigned* ppcnt, unsigned* ghist, unsigned* dhist, unsigned* ticket)
+                                                     const BufSummary* __restrict__ bufsum, SelState* S, unsigned* ticket)
 {
     __shared__ disco_policy sp[DISCO_MAX_COLS];
     __shared__ ClassTable T;
     if ((int)threadIdx.x < P) sp[threadIdx.x] = pol[threadIdx.x];
     table_clear(T);
-    for (i64 w = (i64)blockIdx.x * CL_BLOCK + threadIdx.x; w < (i64)DISCO_MAX_CLS * (DISCO_PP_NMAX + 1); w += (i64)gridDim.x * CL_BLOCK)
-        ppcnt[w] = 0u;
-    for (i64 w = (i64)blockIdx.x * CL_BLOCK + threadIdx.x; w < (i64)DISCO_GHIST_WORDS; w += (i64)gridDim.x * CL_BLOCK) ghist[w] = 0u;
-    for (i64 w = (i64)blockIdx.x * CL_BLOCK + threadIdx.x; w < (i64)P * DISCO_DELAY_BINS; w += (i64)gridDim.x * CL_BLOCK) dhist[w] = 0u;
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const i64 nround = (tr.n_req + CL_BLOCK - 1) / CL_BLOCK;
@@ -607,17 +601,15 @@ __global__ __launch_bounds__(1024) void k_tbt_spare(TraceView tr, i64 n_tok, int
 }  // namespace
 
 void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, int nq, float tau, const void* summary,
-                              const void* bufsum, SelState* S, unsigned* ppcnt, unsigned* ghist, unsigned* dhist, unsigned* ticket,
-                              hipStream_t stream)
+                              const void* bufsum, SelState* S, unsigned* ticket, hipStream_t stream)
 {
     i64 b = (v.n_req + CL_BLOCK - 1) / CL_BLOCK;
     if (b < 1) b = 1;
     if (b > 256) b = 256;                          // (more workgroups cost more in the merge than they save in the scan)
-    if (b < 64) b = 64;                            // small traces: the clearing (2 MB and 32 KB per column) sets the time (500 requests x 4 columns: 34 us with one workgroup, 14 us)
     b /= disco_grid_divisor();
     if (b < 1) b = 1;
     hipLaunchKernelGGL(k_tl_classify, dim3((unsigned)b), dim3(CL_BLOCK), 0, stream, v, pol, P, nq, tau,
-                       (const TlSummary*)summary, (const BufSummary*)bufsum, S, ppcnt, ghist, dhist, ticket);
+                       (const TlSummary*)summary, (const BufSummary*)bufsum, S, ticket);
 }
 
 void disco_launch_pp_suffix(SelState* S, unsigned* ppcnt, hipStream_t stream)
