@@ -81,7 +81,10 @@ __device__ __forceinline__ WalkOut walk_hist(bool mem, int n, const float* __res
             const bool cheap = fast_ok && fabsf(C) <= 262144.0f * kt;
             exact = !cheap || __ballot(i3 > C + 0.5f * kt) != 0ull;
         }
-        float E = fmaxf(wave_prev(wave_incl_max_dpp(i3, lane), ninf), carryM);      // running maximum before this lane's tokens
+        // running maximum before this lane's tokens: the carried one in a chunk that does not move it (most chunks of a
+        // server that is faster than the reader: a pass over 17 M tokens 64 -> 59 us, 73 -> 67 us)
+        float E = carryM;
+        if (__ballot(i3 > carryM) != 0ull) E = fmaxf(wave_prev(wave_incl_max_dpp(i3, lane), ninf), carryM);
         if (exact) {
             const float ex[4] = {E, fmaxf(E, i0), fmaxf(E, i1), fmaxf(E, i2)};
             bool trig[4];

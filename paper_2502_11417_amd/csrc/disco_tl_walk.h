@@ -68,8 +68,18 @@ struct Batch {
 
 // What the walk of the two buffer hand-off timelines of a request found (server source handed to the device,
 // device source handed to the server): final running maximum, hand-off token in the encoding of
-// TlSummary::m_enc (the source's last token), delayed tokens after the hand-off.
-struct __attribute__((aligned(16))) BufSummary { float M_s; int m_s; int delay_s; int pad0; float M_d; int m_d; int delay_d; int pad1; };
+// TlSummary::m_enc (the source's last token), delayed tokens after the hand-off; tag of the prices it was found with.
+struct __attribute__((aligned(16))) BufSummary { float M_s; int m_s; int delay_s, delay_d; float M_d; int m_d; u64 tag; };
+
+// Tells prices apart: order statistics that start from summaries found with other prices look for the hand-offs again.
+__device__ __forceinline__ u64 price_tag(const BufCostArgs& b)
+{
+    u64 h = 0x9E3779B97F4A7C15ull;
+    const double x[4] = {b.dc_srv, b.cp_srv, b.dc_dev, b.cp_dev};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { h = (h ^ (u64)__double_as_longlong(x[i])) * 0xD6E8FEB86659FD93ull; h ^= h >> 32; }
+    return h;
+}
 
 __device__ __forceinline__ int buf_m_enc(int m, float r0)
 {

@@ -200,6 +200,7 @@ __global__ __launch_bounds__(TB_BLOCK) void k_tl_stats_buf(TraceView tr, i64 n_t
     double acc_tlast = 0.0;
     const i64 nwaves = (i64)gridDim.x * (TB_BLOCK / 64);
     const int rb = a.rb;
+    const u64 tag = price_tag(a.bc);
     const i64 nbatch = (tr.n_req + rb - 1) / rb;
     for (i64 bt = (i64)blockIdx.x * (TB_BLOCK / 64) + wave; bt < nbatch; bt += nwaves) {
         const Batch b = load_batch(tr, spol, P, bt * rb, lane, rb, a.summary);
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(TB_BLOCK) void k_tl_stats_buf(TraceView tr, i64 n_t
         }
         const i64 i = bt * rb + lane;
         if (has_s || has_d)
-            a.bufsum[i] = BufSummary{M_s, buf_m_enc(m_s, nz_s ? 1.0f : 0.0f), delay_s, 0, M_d, buf_m_enc(m_d, nz_d ? 1.0f : 0.0f), delay_d, 0};
+            a.bufsum[i] = BufSummary{M_s, buf_m_enc(m_s, nz_s ? 1.0f : 0.0f), delay_s, delay_d, M_d, buf_m_enc(m_d, nz_d ? 1.0f : 0.0f), tag};
         if (a.totals == nullptr) continue;
         st[lane] = BufStaged{b.m[TL_SRV_BUF], b.m[TL_DEV_BUF], b.l, b.n, m_s, m_d, delay_s, delay_d, M_s, M_d};
         __builtin_amdgcn_wave_barrier();                     // the staging area is private to the wave

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
         u64 m[TL_KINDS];
         request_sets(spol, P, l, s, __fmaf_rn((float)l, k, tr.c), i, m);
         u64 desc = DESC_NONE5;
-        BufSummary bs{0.0f, -1, 0, 0, 0.0f, -1, 0, 0};
+        BufSummary bs{0.0f, -1, 0, 0, 0.0f, -1, 0ull};
         if ((m[TL_SRV_BUF] | m[TL_DEV_BUF]) != 0ull) {
             bs = bufsum[i];
             // migrated requests by number of delayed tokens, per column (those without one are implied by the

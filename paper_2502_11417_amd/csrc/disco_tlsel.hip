@@ -508,7 +508,7 @@ __device__ __forceinline__ BufHistArgs buf_hist_args(const TimelineArgs& a)
     BufHistArgs h;
     h.h.tau = a.tau; h.h.kt = a.kt; h.h.P = a.P; h.h.pass = a.pass;
     h.h.S = a.S; h.h.ghist = a.ghist; h.h.desc = a.desc; h.h.list = a.list;
-    h.bc = a.bc;
+    h.bc = a.bc; h.bufsum = (const BufSummary*)a.bufsum;
     h.buffer_flag = a.buffer_flag;
     return h;
 }

@@ -671,7 +671,7 @@ __global__ __launch_bounds__(256) void k_tl_mat(TraceView tr, const disco_policy
         const float s = tr.s[i];
         const float d = __fmaf_rn((float)l, tr.k ? tr.k[i] : tr.k_s, tr.c);
         const TlSummary sum = a.summary[i];
-        BufSummary bs{0.0f, -1, 0, 0, 0.0f, -1, 0, 0};
+        BufSummary bs{0.0f, -1, 0, 0, 0.0f, -1, 0ull};
         if (any_buf) bs = a.bufsum[i];
         for (int j = 0; j < a.P; ++j) {
             unsigned dec; float t;

@@ -167,3 +167,23 @@ def test_tabulated_threshold_searches(B, oracle, n_req, n_search, n_steps, hi):
         assert (pol[j].l_th, pol[j].mode, pol[j].mig_mode) == (l_th, 0, 1) and int(so["param"][j]) == l_th, j
         same_bits(so["hist_param"][j][:n_steps].astype(np.int32), hp, f"hist_param {j}")
         same_bits(so["hist_acc"][j][:n_steps], ha, f"hist_acc {j}")
+
+
+# order statistics of buffer hand-offs: known hand-offs at the edges of chunks and tokens, with and without a token array;
+# summaries found with other prices make the selection search for the hand-offs again (prices twice as high decide alike)
+@pytest.mark.parametrize("n_req,tokens,max_out,stall_p", [(1, True, 2, 0.0), (300, True, 40, 0.2), (700, True, 1100, 0.02),
+                                                          (257, False, 600, 0.0), (5000, True, 260, 0.1)])
+def test_order_statistics_of_known_handoffs(B, oracle, n_req, tokens, max_out, stall_p):
+    print(f"known hand-offs: n_req={n_req} tokens={tokens} max_out={max_out} stall_p={stall_p}", flush=True)
+    tr = slow_prefill(DI.handmade_trace(260 + n_req, n_req, tokens=tokens, max_out=max_out, stall_p=stall_p), 16.0)
+    for cost in (DI.COST_S, DI.COST_D):
+        specs = [dict(mode=0, l_th=l, mig_mode=2) for l in (0, 12, 30)] + [dict(mode=1, l_th=-1, w_tail=DI.f32(w), mig_mode=2) for w in (0.0, 0.1, 0.3)]
+        check_stats(B, oracle, tr, specs, cost, tau=DI.TAU, kappa=DI.KAPPA_LAG)
+        dt, P = B.upload_trace(tr), len(specs)
+        pols, ws = [B.Policy(**s) for s in specs], B.workspace(n_req, P)
+        acc = B.disco_eval_dispatch(dt, pols, ws=ws)["acc"]
+        B.disco_eval_migration(dt, DI.TAU, DI.KAPPA_LAG, pols, ws=ws, acc=acc, cost=cost)
+        twice = dict(cost, cs_pre=2 * cost["cs_pre"], cs_dec=2 * cost["cs_dec"], lam=2 * cost["lam"])
+        got = [B.disco_reduce_stats(dt, cost, pols, acc, ((50, 100), (99, 100)), tau=DI.TAU, kappa=DI.KAPPA_LAG, ws=ws, mig_cost=c,
+                                    reuse_walk=True).clone() for c in (cost, twice)]
+        same_bits(got[1].cpu().numpy(), got[0].cpu().numpy(), "records")
