@@ -65,7 +65,8 @@ constexpr float GEN_RINT = 12582912.0f;
 // series of e^r through r^7, exact scaling by 2^n.
 __device__ __forceinline__ float gen_exp(float x)
 {
-    x = __builtin_amdgcn_fmed3f(x, -86.0f, 88.0f);
+    // (a NaN stays one; the median of the three in one instruction would make a bound of it)
+    x = __builtin_elementwise_minimum(__builtin_elementwise_maximum(x, -86.0f), 88.0f);
     float t = x * 1.44269502f + GEN_RINT;
     float n = t - GEN_RINT;
     float r = __fmaf_rn(n, -0.693145752f, x);
@@ -84,7 +85,7 @@ __device__ __forceinline__ float gen_exp(float x)
 // a = 2 pi v in [-pi/4, pi/4], series of cos and sin.
 __device__ __forceinline__ float gen_cos2pi(float u)
 {
-    const float t = 4.0f * u + GEN_RINT;
+    const float t = __fmaf_rn(4.0f, u, GEN_RINT);            // (4 u is exact: the same as in two operations)
     float q = t - GEN_RINT;
     float v = __fmaf_rn(q, -0.25f, u);
     float a = v * 6.28318548f;

@@ -187,3 +187,15 @@ def test_order_statistics_of_known_handoffs(B, oracle, n_req, tokens, max_out, s
         got = [B.disco_reduce_stats(dt, cost, pols, acc, ((50, 100), (99, 100)), tau=DI.TAU, kappa=DI.KAPPA_LAG, ws=ws, mig_cost=c,
                                     reuse_walk=True).clone() for c in (cost, twice)]
         same_bits(got[1].cpu().numpy(), got[0].cpu().numpy(), "records")
+
+
+# a law with a NaN parameter gives NaN times, as in the oracle's trace, and the check of the data reports them
+@pytest.mark.parametrize("law,field", [("ttft_mu", "srv_ttft"), ("tbt_mu", "srv_tbt"), ("gap_mu", "tok_arr")])
+def test_a_nan_law_is_not_hidden(B, oracle, law, field):
+    print(f"NaN law: {law}", flush=True)
+    gen = dict(DI.config(4, n_req=300, seed=5)["gen"], out_hi=90, gap_stall_p=0.1, **{law: float("nan")})
+    want, got = oracle.gen_trace(gen), B.disco_gen_trace(gen)
+    x, y = got.__dict__[field].cpu().numpy(), want[field]
+    assert np.isnan(y).any() and (np.isnan(x) == np.isnan(y)).all()
+    same_bits(x[~np.isnan(x)], y[~np.isnan(y)], field)
+    assert B.disco_validate_trace(got) == B.ERR["range"]
