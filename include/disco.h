@@ -545,10 +545,15 @@ typedef struct disco_search_out {
     disco_accum at_param;                 /* dispatch totals at the answer */
 } disco_search_out;
 
-/* Run n_search independent searches over the same trace.  In general every
- * step is one fused dispatch-and-reduce pass that evaluates all searches'
- * midpoints; the brackets are updated on the device, so there is no host
- * round trip between steps.  When every search is a length threshold of a
+/* Run n_search independent searches over the same trace.  In general a pass
+ * is one fused dispatch-and-reduce pass that evaluates the midpoints of all
+ * searches' next one to three steps; the brackets are updated on the device,
+ * so there is no host round trip between steps.  When every search is a wait
+ * or a ramp slope of a host-resident device-constrained template with
+ * -1e37 <= lo and hi <= 1e37, and the number of searches, of steps and of
+ * requests make it the faster way, a pass takes up to eight steps of each
+ * search from the changes of the requests' outcomes between the midpoints;
+ * results and recorded history are the same.  When every search is a length threshold of a
  * server-constrained template (Alg. 3) against a prompt-token accumulator,
  * with 0 <= lo and hi <= 32770, the accumulator is tabulated for every
  * threshold in one pass (Alg. 3's running totals over the sorted lengths)

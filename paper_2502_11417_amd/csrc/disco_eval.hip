@@ -893,19 +893,18 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
                     spec[j].lo >= 0.0 && spec[j].hi + 2.0 <= (double)disco_search_table_max_bins();
         if (spec[j].hi > max_hi) max_hi = spec[j].hi;
     }
+    // bisection passes only need the totals their accumulators are made of
+    int need = 0;
+    for (int j = 0; j < n_search; ++j)
+        if (spec[j].which_acc != DISCO_ACC_SERVER_PREFILL_TOK && spec[j].which_acc != DISCO_ACC_DEVICE_PREFILL_TOK) need = 1;
     // Waits and ramp slopes of device-constrained columns: the outcomes of a request are step functions of the
-    // parameter, a pass takes eight bisection steps (disco_search.hip).  The bounds are such that no midpoint
-    // overflows and no ramp is infinity times zero.
-    bool binned = !tabulated && !is_device_pointer(templ) && disco_search_bins_bytes(n_search) <= L.total - L.slices;
+    // parameter, a pass takes eight bisection steps (disco_search.hip), where that is the faster way.  The bounds are such
+    // that no midpoint overflows and no ramp is infinity times zero.
+    bool binned = !tabulated && !is_device_pointer(templ) && disco_search_bins_bytes(n_search) <= L.total - L.slices &&
+                  disco_search_bins_pays(v.n_req, n_search, n_steps, need != 0);
     for (int j = 0; j < n_search && binned; ++j)
         binned = templ[j].mode == DISCO_MODE_DEVICE_CONSTRAINED && spec[j].which_param != DISCO_PARAM_L_TH &&
                  spec[j].lo >= -1e37 && spec[j].hi <= 1e37;
-    // Otherwise every pass evaluates the next `depth` levels of each search's bisection tree as columns of their
-    // own and so takes `depth` bisection steps; the recorded steps are those of the plain bisection.
-    const int depth = tabulated ? 0 : disco_search_depth(n_search);
-    if (!binned && !tabulated)
-        hipLaunchKernelGGL(k_search_init, dim3(1), dim3(64), 0, stream, t, n_search, (SearchState*)(ws + L.search),
-                           (disco_policy*)(ws + L.pol), (disco_policy*)(ws + L.templ), depth);
     DispFin fin;
     memset(&fin, 0, sizeof(fin));
     fin.kind = 1;
@@ -924,10 +923,11 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
         disco_launch_search_bins(v, n_search, n_steps, t, *cost, ws + L.slices, (SearchState*)(ws + L.search), fin.pol_rw,
                                  (disco_policy*)(ws + L.templ), out, stream);
     } else {
-        // bisection passes only need the totals their accumulators are made of
-        int need = 0;
-        for (int j = 0; j < n_search; ++j)
-            if (spec[j].which_acc != DISCO_ACC_SERVER_PREFILL_TOK && spec[j].which_acc != DISCO_ACC_DEVICE_PREFILL_TOK) need = 1;
+        // Every pass evaluates the next `depth` levels of each search's bisection tree as columns of their own and so
+        // takes `depth` bisection steps; the recorded steps are those of the plain bisection.
+        const int depth = disco_search_depth(n_search);
+        hipLaunchKernelGGL(k_search_init, dim3(1), dim3(64), 0, stream, t, n_search, fin.st, fin.pol_rw,
+                           (disco_policy*)(ws + L.templ), depth);
         const int npass = (n_steps + depth - 1) / depth;
         fin.depth = depth;
         fin.need = need;

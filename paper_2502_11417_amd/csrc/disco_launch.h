@@ -55,6 +55,7 @@ void disco_launch_search_table(const TraceView& v, const SpecTable& spec, int n_
 // Search of w_tail or beta over device-constrained templates (in `pol`; the answers end there too), eight steps per pass.
 // `scratch`: disco_search_bins_bytes(n_search) bytes.
 size_t disco_search_bins_bytes(int n_search);
+bool disco_search_bins_pays(i64 n_req, int n_search, int n_steps, bool decode);
 void disco_launch_search_bins(const TraceView& v, int n_search, int n_steps, const SpecTable& spec, const disco_cost_params& cost,
                               void* scratch, SearchState* st, disco_policy* pol, disco_policy* templ, disco_search_out* sout,
                               hipStream_t stream);

@@ -18,7 +18,8 @@
 // Bound: the first pass by its bisections and LDS atomics (42 us for 4 10^6 requests, 1.1 TB/s), the others by the
 // latency of one read of 12-16 bytes per request (13-18 us, 2.7-3.7 TB/s out of the caches), the walks by latency
 // (6-9 us).  32 steps over 4 10^6 requests: 138 us with the evaluation at the answer; 427 us in eleven passes of three
-// steps each with seven policy columns (k_dispatch_acc<8>, 32 us a pass), which templates of other kinds still take.
+// steps each with seven policy columns (k_dispatch_acc<8>, 32 us a pass), which templates of other kinds still take, and
+// many searches at once where those passes are the faster ones (disco_search_bins_pays).
 #include <math.h>
 
 #include "disco_launch.h"
@@ -217,6 +218,30 @@ __global__ __launch_bounds__(2 * SB_CAND) void k_search_walk(SearchState* st_, c
 }
 
 }  // namespace
+
+// Whether these passes beat the fused ones, which evaluate the next one to three levels of all searches as policy columns
+// of one pass: these cost a read of the trace and two outcomes per request for every search and take eight steps, the cost
+// of a fused pass grows with its columns alone.  One and two searches: these passes (never slower by more than 8 %, 1 to 64
+// steps on 20 000 to 4 10^6 requests).  Beyond that the smaller of two estimates in microseconds, fitted to whole calls; where
+// it errs, the calls differ by a tenth at most.  These passes against the fused ones, device prompt tokens, 10^6 requests:
+//   16 searches  4 steps 120 against 87 us,  16 steps 268 / 264,  32 steps  366 / 495
+//   32 searches  4 steps 203 / 117,          16 steps 474 / 360,  32 steps  642 / 684
+//   64 searches  4 steps 372 / 169,          32 steps 1192 / 972, 64 steps 1786 / 1886
+// and 64 searches at 4 10^6 requests 747 / 256 us (one step), 4339 / 2989 (32); at 20 000 requests 41 / 42 and 112 / 498.
+// `decode`: some search's accumulator takes the output tokens too, which the fused passes then add up.
+bool disco_search_bins_pays(i64 n_req, int n_search, int n_steps, bool decode)
+{
+    if (n_search <= 2) return true;
+    const int depth = disco_search_depth(n_search);
+    int cols = 1;
+    while (cols < n_search * ((1 << depth) - 1)) cols <<= 1;
+    const double n = 1e-6 * (double)n_req;
+    const double fused = (n_steps + depth - 1) / depth * (12.0 + (decode ? 0.45 : 0.30) * n * cols);
+    const int npass = (n_steps + SB_DEPTH - 1) / SB_DEPTH, first = (n_steps + npass - 1) / npass;
+    double per_search = first <= 2 ? 2.6 : 2.0 + 0.65 * first;       // the first pass bisects, the later ones hardly
+    if (npass > 1) per_search += 5.1 + 2.3 * (npass - 2);
+    return 4.0 + 1.6 * first + 14.0 * (npass - 1) + per_search * n * n_search < fused;
+}
 
 size_t disco_search_bins_bytes(int n_search)
 {

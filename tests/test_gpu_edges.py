@@ -199,3 +199,20 @@ def test_a_nan_law_is_not_hidden(B, oracle, law, field):
     assert np.isnan(y).any() and (np.isnan(x) == np.isnan(y)).all()
     same_bits(x[~np.isnan(x)], y[~np.isnan(y)], field)
     assert B.disco_validate_trace(got) == B.ERR["range"]
+
+
+# many wait searches at once: few steps on many requests take the fused passes, the others eight steps per pass
+@pytest.mark.parametrize("n_req,n_search,n_steps", [(300_011, 10, 1), (300_011, 64, 3), (300_011, 64, 9), (900_001, 32, 4)])
+def test_many_wait_searches(B, oracle, n_req, n_search, n_steps):
+    print(f"many wait searches: n_req={n_req} n_search={n_search} n_steps={n_steps}", flush=True)
+    tr = DI.handmade_trace(410, n_req, tokens=False)
+    total = float(tr["prompt_len"].sum(dtype=np.int64))
+    specs = [dict(which_param=B.PARAM_W_TAIL, which_acc="device_prefill_tok", n_steps=n_steps, lo=0.0, hi=4.0,
+                  target=total * (j + 1) / (n_search + 2)) for j in range(n_search)]
+    out = B.disco_budget_search(B.upload_trace(tr), DI.COST_D, [B.Policy(mode=1, l_th=j - 1) for j in range(n_search)], specs)
+    so = B.search_to_host(out["out"], n_search)
+    for j in range(0, n_search, 7):
+        x, hp, ha = oracle.search_wait(tr, oracle.Policy(mode=1, l_th=j - 1), 0.0, 4.0, n_steps, "device_prefill_tok", DI.COST_D, specs[j]["target"])
+        same_bits(so["hist_param"][j][:n_steps].astype(np.float32), hp, f"hist_param {j}")
+        same_bits(so["hist_acc"][j][:n_steps], ha, f"hist_acc {j}")
+        assert np.float32(so["param"][j]) == np.float32(x), j
