@@ -266,9 +266,12 @@ int32_t disco_policy_type(const disco_cost_params* cost /*host*/, int32_t* mode 
  * for every request (the running maximum of each of its timelines and the
  * lag hand-off, 16 bytes).  A caller who passes the same workspace, untouched
  * by other calls in between except disco_reduce_stats, with the same trace,
- * policy table, tau and kappa_lag to disco_reduce_stats may set reuse_walk = 1:
- * the TBT order statistics then start from those summaries instead of walking
- * the tokens again. */
+ * policy table, tau, kappa_lag and cost to disco_reduce_stats may set
+ * reuse_walk = 1: the TBT order statistics then start from those summaries
+ * instead of walking the tokens again.  (Another cost is noticed where the
+ * table has buffer hand-offs: the order statistics are then those of
+ * reuse_walk = 0 at that cost, but all timelines are walked by the general
+ * kernel, which takes many times longer.) */
 typedef struct disco_timeline_params {
     float tau;
     float kappa_lag;

@@ -741,7 +741,7 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
             a.P = P; a.nq = nq;
             a.ticket = (unsigned*)(ws + L.ticket);
             a.S = S; a.ghist = gh;
-            a.bc = buffer_prices(tl->cost);          // the prices the statistics pass used
+            a.bc = buffer_prices(tl->cost);
             a.dhist = (unsigned*)(ws + L.dhist);
             a.buffer_flag = (unsigned*)(ws + L.ticket) + DISCO_FLAG_BUFFER;
             // column sets -> classes, then the radix passes; the digits are sized on the device and
@@ -757,7 +757,7 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
                 disco_launch_tl_walk(v, trace->n_tok, dpol, P, a.tau, a.kt, a.wflags, a.summary, a.counter, stream);
                 disco_launch_tl_stats_buf(v, trace->n_tok, dpol, a, nullptr, stream);      // summaries only
             }
-            disco_launch_tl_classify(v, dpol, P, nq, tl->tau, a.summary, a.bufsum, S,
+            disco_launch_tl_classify(v, dpol, P, nq, tl->tau, a.summary, a.bufsum, a.bc, S,
                                      (unsigned*)(ws + L.ticket), stream);
             a.desc = (u64*)(ws + disco_ws_desc_offset(L, v.n_req));
             a.list = (unsigned*)(a.desc + v.n_req);

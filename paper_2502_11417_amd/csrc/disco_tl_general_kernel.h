@@ -179,8 +179,9 @@ __device__ __forceinline__ void timeline_body(unsigned* smem, TimelineLds& lds, 
                                    lane, deliv, sink);
             }
             if (variant == 2) { res_lag = res; lag_done = true; }
-            if (hist_pass && a.pass == 0 && variant >= 3 && res.m >= 0 && ((mask >> lane) & 1ull)) {
-                // lane = column: migrated requests by number of delayed tokens
+            if (hist_pass && a.pass == 0 && variant >= 3 && res.m >= 0 && res.delay > 0 && ((mask >> lane) & 1ull)) {
+                // lane = column: migrated requests by number of delayed tokens (those without one are implied by the
+                // migration count)
                 const int bin = res.delay < DISCO_DELAY_BINS - 1 ? res.delay : DISCO_DELAY_BINS - 1;
                 atomicAdd(&a.dhist[(size_t)lane * DISCO_DELAY_BINS + bin], 1u);
             }

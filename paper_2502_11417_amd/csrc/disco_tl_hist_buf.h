@@ -12,8 +12,7 @@ constexpr int TBH_BLOCK = 1024;              // histogram workgroups: 16 waves s
 
 struct BufHistArgs {
     HistArgs h;
-    BufCostArgs bc;
-    const BufSummary* bufsum;      // the hand-offs, as the statistics of the timelines found them with the prices of their tag
+    const BufSummary* bufsum;      // the hand-offs, as the statistics of the timelines found them (k_tl_classify has checked them)
     const unsigned* buffer_flag;
 };
 
@@ -123,7 +122,6 @@ __device__ __forceinline__ void tl_hist_buf_body(unsigned* smem, const TraceView
     const int words = (h.G * nwalk) << width;
     for (int i = threadIdx.x; i < words; i += TBH_BLOCK) smem[i] = 0u;
     __syncthreads();
-    const u64 tag = price_tag(ba.bc);
     const i64 nwaves = (i64)nblk * (TBH_BLOCK / 64);
     const i64 nfront = (i64)tl->nlist, nlist = nfront + (i64)tl->nlist_back;
     i64 rb = (nlist + nwaves - 1) / nwaves;
@@ -141,7 +139,6 @@ __device__ __forceinline__ void tl_hist_buf_body(unsigned* smem, const TraceView
         float k_v = tr.k_s, gd_v = tr.g_s, gap_v = 0.0f, s_v = 0.0f;
         i64 off_v = 0;
         Handoff from_srv{-1, 0.0f, 0.0f}, from_dev{-1, 0.0f, 0.0f};
-        bool other_prices = false;
         if (desc != 0xFFFFu) {
             l_v = tr.l[il]; n_v = tr.n[il]; s_v = tr.s[il];
             if (tr.k) k_v = tr.k[il];
@@ -150,14 +147,9 @@ __device__ __forceinline__ void tl_hist_buf_body(unsigned* smem, const TraceView
             if (tr.tbt) gap_v = tr.tbt[il];
             const BufSummary bs = ba.bufsum[il];
             const int m_s = (desc & 0xFFu) != 0xFFu ? summary_m(bs.m_s) : -1, m_d = (desc >> 8) != 0xFFu ? summary_m(bs.m_d) : -1;
-            // (a hand-off leaves the target a token: others are no summaries of this trace and are not used as an index)
-            other_prices = bs.tag != tag || m_s > n_v - 2 || m_d > n_v - 2;
-            if (!other_prices) {
-                from_srv = handoff_at(false, m_s, tr.arr, off_v, l_v, s_v, k_v, tr.c, gap_v, gd_v);
-                from_dev = handoff_at(true, m_d, tr.arr, off_v, l_v, s_v, k_v, tr.c, gap_v, gd_v);
-            }
+            from_srv = handoff_at(false, m_s, tr.arr, off_v, l_v, s_v, k_v, tr.c, gap_v, gd_v);
+            from_dev = handoff_at(true, m_d, tr.arr, off_v, l_v, s_v, k_v, tr.c, gap_v, gd_v);
         }
-        const u64 search = __ballot(other_prices);
         float ahead[4] = {0.f, 0.f, 0.f, 0.f};
         auto load_ahead = [&](u64 left) {
             if (!left || !tr.arr) return;
@@ -181,15 +173,7 @@ __device__ __forceinline__ void tl_hist_buf_body(unsigned* smem, const TraceView
                 const unsigned row_base = sl << width;
                 auto sink = [&](const unsigned key[4]) { hist_keys(h, key, row_base, lane); };
                 const Handoff& v = kind ? from_dev : from_srv;
-                Handoff ho{bcast_i(v.m, rq), bcast_f(v.base, rq), bcast_f(v.a_m, rq)};
-                if ((search >> rq) & 1ull) {                 // statistics and order statistics at different prices: search again
-                    const int l = bcast_i(l_v, rq);
-                    const float s = bcast_f(s_v, rq), k = bcast_f(k_v, rq);
-                    auto none = [](const unsigned*, const bool*) {};
-                    const TimelineResult res = run_timeline(TL_SRV_BUF + kind, n, tr.arr, off, n_tok, align, gap, gd, l, k, tr.c, s, ba.bc,
-                                                            a.tau, a.kt, lane, nullptr, none);
-                    ho = handoff_at(kind != 0, res.m, tr.arr, off, l, s, k, tr.c, gap, gd);
-                }
+                const Handoff ho{bcast_i(v.m, rq), bcast_f(v.base, rq), bcast_f(v.a_m, rq)};
                 walk_hist_known(kind != 0, n, tr.arr, off, n_tok, align, chunk, gap, gd, ho, a.tau, lane, sink);
             }
         }

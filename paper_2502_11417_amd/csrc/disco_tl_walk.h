@@ -71,13 +71,13 @@ struct Batch {
 // TlSummary::m_enc (the source's last token), delayed tokens after the hand-off; tag of the prices it was found with.
 struct __attribute__((aligned(16))) BufSummary { float M_s; int m_s; int delay_s, delay_d; float M_d; int m_d; u64 tag; };
 
-// Tells prices apart: order statistics that start from summaries found with other prices look for the hand-offs again.
-__device__ __forceinline__ u64 price_tag(const BufCostArgs& b)
+// Tells prices apart: order statistics do not start from summaries that were found with other prices (k_tl_classify).
+__host__ __device__ inline u64 price_tag(const BufCostArgs& b)
 {
     u64 h = 0x9E3779B97F4A7C15ull;
     const double x[4] = {b.dc_srv, b.cp_srv, b.dc_dev, b.cp_dev};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { h = (h ^ (u64)__double_as_longlong(x[i])) * 0xD6E8FEB86659FD93ull; h ^= h >> 32; }
+    for (int i = 0; i < 4; ++i) { h = (h ^ __builtin_bit_cast(u64, x[i])) * 0xD6E8FEB86659FD93ull; h ^= h >> 32; }
     return h;
 }
 

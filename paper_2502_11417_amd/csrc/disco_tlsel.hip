@@ -167,9 +167,11 @@ __device__ __forceinline__ int table_compact(ClassTable& T)
 // ticket compacts that table, puts the sets in ascending order (so that the class numbers do not depend on
 // timing), numbers the classes that need a token walk and plans the first histogram pass.  The device-wide table was zeroed
 // when the selection started (select_init, in the launch that stages the policy table).
+// Summaries of buffer hand-offs that were found with other prices (reuse_walk) say neither which timelines are paced nor
+// where the others hand off: with any of them the general kernel walks all timelines with the prices of this call.
 __global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const disco_policy* __restrict__ pol, int P, int nq,
                                                      float tau, const TlSummary* __restrict__ summary,
-                                                     const BufSummary* __restrict__ bufsum, SelState* S, unsigned* ticket)
+                                                     const BufSummary* __restrict__ bufsum, u64 tag, SelState* S, unsigned* ticket)
 {
     __shared__ disco_policy sp[DISCO_MAX_COLS];
     __shared__ ClassTable T;
@@ -178,6 +180,7 @@ __global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const di
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const i64 nround = (tr.n_req + CL_BLOCK - 1) / CL_BLOCK;
+    bool stale = false;
     for (i64 rnd = blockIdx.x; rnd < nround; rnd += gridDim.x) {
         const i64 i = rnd * CL_BLOCK + threadIdx.x;
         if (i >= tr.n_req) continue;
@@ -192,6 +195,8 @@ __global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const di
         table_insert(T, m[TL_SRV_LAG], !timeline_is_analytic(TL_SRV_LAG, n, sm));
         if ((m[TL_SRV_BUF] | m[TL_DEV_BUF]) != 0ull) {
             const BufSummary bs = bufsum[i];
+            // (a hand-off leaves the target a token: another one is no summary of this trace and must not index its tokens)
+            stale = stale || bs.tag != tag || summary_m(bs.m_s) > n - 2 || summary_m(bs.m_d) > n - 2;
             table_insert(T, m[TL_SRV_BUF], !buf_timeline_is_analytic(TL_SRV_BUF, n, bs));
             table_insert(T, m[TL_DEV_BUF], !buf_timeline_is_analytic(TL_DEV_BUF, n, bs));
         }
@@ -217,9 +222,10 @@ __global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const di
                     h = (h + 1) & (CL_SLOTS - 1);
                 }
             }
-            if (!placed) g.goverflow = 1;
+            if (!placed) atomicOr(&g.goverflow, 1);
         }
-        if (threadIdx.x == 0 && T.overflow) g.goverflow = 1;
+        if (threadIdx.x == 0 && T.overflow) atomicOr(&g.goverflow, 1);
+        if (__ballot(stale) != 0ull && lane == 0) atomicOr(&g.goverflow, 2);
     }
     if (!take_last_ticket(ticket)) return;
     // last workgroup: the device-wide table (read where the atomics put it), compacted and put in order
@@ -230,7 +236,8 @@ __global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const di
         T.slot[threadIdx.x] = (u64)atomicCAS((unsigned long long*)&S->tl.gslot[threadIdx.x], 0ull, 0ull);
         T.walk[threadIdx.x] = atomicOr(&S->tl.gwalk[threadIdx.x], 0u);
     }
-    if (threadIdx.x == 0 && atomicOr((unsigned*)&S->tl.goverflow, 0u) != 0u) T.overflow = 1;
+    const int over = threadIdx.x == 0 ? atomicOr(&S->tl.goverflow, 0) : 0;      // bit 0: too many sets, bit 1: other prices
+    if (over != 0) T.overflow = 1;
     const int total = table_compact(T);
     if (wave != 0) return;
     // ascending order: lane e holds a set, its rank is the number of smaller ones
@@ -260,14 +267,15 @@ __global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const di
         tl.walk_mask = wm;
         tl.nwalk = __popcll(wm);
         tl.error = 0;
-        if (T.overflow) tl.fallback = 1;               // more than DISCO_MAX_CLS distinct sets: per-slot histograms
+        if (T.overflow) tl.fallback = 1;               // more than DISCO_MAX_CLS distinct sets (or other prices): per-slot histograms
         // gaps sit just above the pacing interval (down to a few thousand ulps below it after rounding): try a
         // 21-bit window of keys first
         const unsigned tb = f2u(tau);
         tl.restart = 0;
         tl.nlist = 0u;
         tl.nlist_back = 0u;
-        if (tb >= 8192u) { tl.key_lo = tb - 8192u; tl.window = 21; tl.left = 21; }
+        // (not at other prices: the passes of 128 slots would not suffice for a second start)
+        if (tb >= 8192u && (over & 2) == 0) { tl.key_lo = tb - 8192u; tl.window = 21; tl.left = 21; }
         else { tl.key_lo = 0u; tl.window = 0; tl.left = 31; }
         *ticket = 0u;
     }
@@ -508,7 +516,7 @@ __device__ __forceinline__ BufHistArgs buf_hist_args(const TimelineArgs& a)
     BufHistArgs h;
     h.h.tau = a.tau; h.h.kt = a.kt; h.h.P = a.P; h.h.pass = a.pass;
     h.h.S = a.S; h.h.ghist = a.ghist; h.h.desc = a.desc; h.h.list = a.list;
-    h.bc = a.bc; h.bufsum = (const BufSummary*)a.bufsum;
+    h.bufsum = (const BufSummary*)a.bufsum;
     h.buffer_flag = a.buffer_flag;
     return h;
 }
@@ -601,7 +609,7 @@ __global__ __launch_bounds__(1024) void k_tbt_spare(TraceView tr, i64 n_tok, int
 }  // namespace
 
 void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, int nq, float tau, const void* summary,
-                              const void* bufsum, SelState* S, unsigned* ticket, hipStream_t stream)
+                              const void* bufsum, const BufCostArgs& bc, SelState* S, unsigned* ticket, hipStream_t stream)
 {
     i64 b = (v.n_req + CL_BLOCK - 1) / CL_BLOCK;
     if (b < 1) b = 1;
@@ -609,7 +617,7 @@ void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P
     b /= disco_grid_divisor();
     if (b < 1) b = 1;
     hipLaunchKernelGGL(k_tl_classify, dim3((unsigned)b), dim3(CL_BLOCK), 0, stream, v, pol, P, nq, tau,
-                       (const TlSummary*)summary, (const BufSummary*)bufsum, S, ticket);
+                       (const TlSummary*)summary, (const BufSummary*)bufsum, price_tag(bc), S, ticket);
 }
 
 void disco_launch_pp_suffix(SelState* S, unsigned* ppcnt, hipStream_t stream)

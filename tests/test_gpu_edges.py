@@ -216,3 +216,28 @@ def test_many_wait_searches(B, oracle, n_req, n_search, n_steps):
         same_bits(so["hist_param"][j][:n_steps].astype(np.float32), hp, f"hist_param {j}")
         same_bits(so["hist_acc"][j][:n_steps], ha, f"hist_acc {j}")
         assert np.float32(so["param"][j]) == np.float32(x), j
+
+
+# order statistics with reuse_walk at prices other than those of the summaries: those of a call that walks the tokens itself
+@pytest.mark.parametrize("n_req,tokens,max_out", [(1, True, 9), (500, True, 700), (300, False, 300), (6000, True, 60)])
+def test_order_statistics_at_other_prices(B, n_req, tokens, max_out):
+    print(f"other prices: n_req={n_req} tokens={tokens} max_out={max_out}", flush=True)
+    tr = slow_prefill(DI.handmade_trace(310 + n_req, n_req, tokens=tokens, max_out=max_out, stall_p=0.1), 16.0)
+    specs = [dict(mode=0, l_th=l, mig_mode=2) for l in (0, 12, 30)] + [dict(mode=1, l_th=-1, w_tail=DI.f32(w), mig_mode=2) for w in (0.0, 0.1, 0.3)]
+    specs.append(dict(mode=0, l_th=10, mig_mode=1))
+    dt, P, pols = B.upload_trace(tr), len(specs), [B.Policy(**s) for s in specs]
+    for cost in (DI.COST_S, DI.COST_D):
+        moved = False
+        for other in (None, dict(cost, cs_pre=9 * cost["cs_pre"], e_pre=9 * cost["e_pre"]), dict(cost, cs_dec=0.7 * cost["cs_dec"]),
+                      DI.COST_D if cost is DI.COST_S else DI.COST_S):
+            ws = B.workspace(n_req, P)
+            acc = B.disco_eval_dispatch(dt, pols, ws=ws)["acc"]
+            B.disco_eval_migration(dt, DI.TAU, DI.KAPPA_LAG, pols, ws=ws, acc=acc, cost=cost)
+            args = dict(tau=DI.TAU, kappa=DI.KAPPA_LAG)
+            q = ((50, 100), (99, 100))
+            got = B.disco_reduce_stats(dt, cost, pols, acc, q, ws=ws, mig_cost=other, reuse_walk=True, **args)
+            want = B.disco_reduce_stats(dt, cost, pols, acc, q, mig_cost=other, **args)
+            same = B.disco_reduce_stats(dt, cost, pols, acc, q, mig_cost=cost, **args)
+            moved = moved or not torch.equal(want, same)
+            same_bits(got.cpu().numpy(), want.cpu().numpy(), f"records at {other}")
+        assert moved or n_req == 1
