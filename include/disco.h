@@ -615,6 +615,14 @@ int32_t disco_time_token_walk(const disco_trace* trace /*host*/, const disco_tim
                               const disco_policy* pol /*host or device*/, int32_t P, void* ws /*device*/, size_t ws_bytes,
                               int32_t reps, double* mean_ms /*host*/, double* min_ms /*host*/, void* stream);
 
+/* Testing aid: what the trace generator's division and square root give for
+ * every variate U = (w + 1/2) 2^-23, w = 0 .. 2^23 - 1 (the definition of the
+ * trace rounds both correctly).  out: device, 4 x 2^23 fp32 values, element w
+ * of each part belongs to variate w: f with U = 2^e (1 + f), f / (2 + f), the
+ * radicand x = -2 ln U, sqrt(x).  Asynchronous.  Errors: NULL, SHAPE
+ * (misaligned), HIP. */
+int32_t disco_gen_math_probe(void* out /*device*/, void* stream);
+
 /* Testing aid: from now on the grids of the dispatch pass and of the token
  * walk are divided by d (1 = the normal geometry) before launch, process-wide.
  * Integer results must not depend on it.  Errors: RANGE (d outside [1, 1024]). */

@@ -132,7 +132,7 @@ assert C.sizeof(CPolicy) == 32 and C.sizeof(CSearchSpec) == 40
 
 EXPORTS = ["disco_gen_trace", "disco_eval_dispatch", "disco_eval_dispatch_static", "disco_eval_migration", "disco_reduce_stats",
            "disco_average_runs", "disco_solve_policy", "disco_ingest_trace", "disco_fit_lognormal",
-           "disco_device_profile", "disco_budget_search", "disco_read_probe", "disco_time_token_walk", "disco_validate_trace", "disco_set_grid_divisor", "disco_policy_type", "disco_workspace_bytes", "disco_strerror", "disco_last_hip_error",
+           "disco_device_profile", "disco_budget_search", "disco_read_probe", "disco_gen_math_probe", "disco_time_token_walk", "disco_validate_trace", "disco_set_grid_divisor", "disco_policy_type", "disco_workspace_bytes", "disco_strerror", "disco_last_hip_error",
            "disco_version"]
 
 _lib.disco_strerror.restype = C.c_char_p
@@ -180,6 +180,8 @@ _lib.disco_solve_policy.argtypes = [C.POINTER(CTrace), C.POINTER(CSolveSpec), C.
                                     C.c_void_p, C.c_size_t, C.c_void_p]
 _lib.disco_read_probe.restype = C.c_int32
 _lib.disco_read_probe.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
+_lib.disco_gen_math_probe.restype = C.c_int32
+_lib.disco_gen_math_probe.argtypes = [C.c_void_p, C.c_void_p]
 _lib.disco_time_token_walk.restype = C.c_int32
 _lib.disco_time_token_walk.argtypes = [C.POINTER(CTrace), C.POINTER(CTimeline), C.POINTER(CPolicy), C.c_int32, C.c_void_p,
                                        C.c_size_t, C.c_int32, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]
@@ -564,6 +566,13 @@ def disco_read_probe(buf: torch.Tensor, out: torch.Tensor | None = None) -> torc
     if out is None:
         out = torch.zeros(64, dtype=torch.int32, device=buf.device)
     _check(_lib.disco_read_probe(buf.data_ptr(), buf.numel() * buf.element_size(), out.data_ptr(), _stream()), "disco_read_probe")
+    return out
+
+
+def disco_gen_math_probe() -> torch.Tensor:
+    """The trace generator's division and square root over all its variates: rows f, f / (2 + f), x, sqrt(x) (testing aid)."""
+    out = torch.empty((4, 1 << 23), dtype=torch.float32, device="cuda")
+    _check(_lib.disco_gen_math_probe(out.data_ptr(), _stream()), "disco_gen_math_probe")
     return out
 
 

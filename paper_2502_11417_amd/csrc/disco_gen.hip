@@ -18,7 +18,7 @@ namespace {
 // (no operand here is near the ends of the exponent range): an approximate reciprocal (reciprocal root), one Newton
 // step, and a last correction with the exact remainder (Markstein's scheme).  That the last rounding is right for
 // every operand is not left to the theorem's conditions: the generator only ever takes logarithms of the 2^23
-// variates of u23, and for all of them both results were compared with __fdiv_rn and sqrtf.
+// variates of u23, and for all of them the tests compare both results with IEEE operations (disco_gen_math_probe).
 __device__ __forceinline__ float gen_div(float f, float d)
 {
     const float r0 = __builtin_amdgcn_rcpf(d);
@@ -38,7 +38,8 @@ __device__ __forceinline__ float gen_sqrt(float x)
 
 // ln of a positive normal number: x = 2^e m with m in (sqrt(1/2), sqrt(2)],
 // ln m = 2 atanh(s), s = (m - 1) / (m + 1), odd series through s^11.
-__device__ __forceinline__ float gen_ln(float x)
+struct LnParts { float f; int e; };                      // x = 2^e (1 + f)
+__device__ __forceinline__ LnParts gen_ln_parts(float x)
 {
     // m = the fraction of x, halved (and e + 1) where it is above 1.41421354: the bit pattern is rebased to the
     // successor of half that number
@@ -46,7 +47,13 @@ __device__ __forceinline__ float gen_ln(float x)
     const unsigned rel = f2u(x) + (0x3F800000u - LOW);
     const int e = (int)(rel >> 23) - 127;
     const float m = u2f((rel & 0x007FFFFFu) + LOW);
-    float f = m - 1.0f;
+    return LnParts{m - 1.0f, e};
+}
+__device__ __forceinline__ float gen_ln(float x)
+{
+    const LnParts q = gen_ln_parts(x);
+    const float f = q.f;
+    const int e = q.e;
     float s = gen_div(f, 2.0f + f);
     float z = s * s;
     float p = __fmaf_rn(z, 0.181818187f, 0.222222224f);
@@ -111,6 +118,16 @@ __device__ __forceinline__ float gen_normal(unsigned w0, unsigned w1)
 {
     float rad = gen_sqrt(-2.0f * gen_ln(u23(w0)));
     return rad * gen_cos2pi(u23(w1));
+}
+
+// The division and the square root of every variate u23 can take: operands and results.
+__global__ __launch_bounds__(256) void k_gen_math_probe(float* __restrict__ out)
+{
+    const unsigned i = blockIdx.x * 256u + threadIdx.x;
+    constexpr unsigned N = 1u << 23;
+    const float u = u23(i << 9), f = gen_ln_parts(u).f, x = -2.0f * gen_ln(u);
+    out[i] = f; out[N + i] = gen_div(f, 2.0f + f);
+    out[2 * N + i] = x; out[3 * N + i] = gen_sqrt(x);
 }
 
 __device__ __forceinline__ float gen_lognormal(unsigned w0, unsigned w1, float mu, float sigma)
@@ -340,6 +357,15 @@ void launch_tokens(const disco_gen_params& g, i64 n, i64 n_tok, const i64* tok_o
 }
 
 }  // namespace
+
+extern "C" int32_t disco_gen_math_probe(void* out, void* stream_)
+{
+    if (!out) return DISCO_ERR_NULL;
+    if (((uintptr_t)out & 3u) != 0) return DISCO_ERR_SHAPE;
+    hipLaunchKernelGGL(k_gen_math_probe, dim3((1u << 23) / 256u), dim3(256), 0, (hipStream_t)stream_, (float*)out);
+    DISCO_HIP(hipGetLastError());
+    return DISCO_OK;
+}
 
 extern "C" int32_t disco_gen_trace(const disco_gen_params* g, disco_trace* tr, int32_t stages, void* stream_)
 {

@@ -174,6 +174,8 @@ def test_new_entry_points_reject_bad_arguments_on_the_host(B):
     assert lib.disco_read_probe(256, 1000, 256, None) == B.ERR["shape"]                         # not a multiple of 16
     assert lib.disco_read_probe(264, 1024, 256, None) == B.ERR["shape"]                         # misaligned
     assert lib.disco_read_probe(256, 0, 256, None) == 0
+    # generator's division and square root
+    assert lib.disco_gen_math_probe(None, None) == B.ERR["null"] and lib.disco_gen_math_probe(258, None) == B.ERR["shape"]
     # policy type (Alg. 1)
     assert B.disco_policy_type(DI.COST_S) == B.MODE_S and B.disco_policy_type(DI.COST_D) == B.MODE_D
     assert B.disco_policy_type(dict(DI.COST_S, lam=DI.COST_S["cs_pre"] / DI.COST_S["e_pre"])) == B.MODE_S     # equality

@@ -241,3 +241,15 @@ def test_order_statistics_at_other_prices(B, n_req, tokens, max_out):
             moved = moved or not torch.equal(want, same)
             same_bits(got.cpu().numpy(), want.cpu().numpy(), f"records at {other}")
         assert moved or n_req == 1
+
+
+# the generator's own division and square root are correctly rounded for every variate it can draw
+def test_generator_division_and_square_root(B):
+    print("generator division and square root, all variates", flush=True)
+    f, q, x, r = B.disco_gen_math_probe().cpu().numpy()
+    u = (np.arange(1 << 23, dtype=np.float64) + 0.5) * 2.0 ** -23
+    e = np.round(np.log2(u / (1.0 + f.astype(np.float64))))
+    assert (np.ldexp(1.0 + f.astype(np.float64), e.astype(int)) == u).all() and f.min() >= np.sqrt(0.5) - 1 - 1e-7 and f.max() <= np.sqrt(2.0) - 1 + 1e-7
+    assert np.abs(x + 2.0 * np.log(u)).max() <= 4e-7 * 33 and (x > 0).all()        # |2 ln u| <= 33, a few units in its last place
+    same_bits(q, f / (np.float32(2.0) + f), "f / (2 + f)")
+    same_bits(r, np.sqrt(x), "sqrt(x)")
