@@ -253,3 +253,19 @@ def test_generator_division_and_square_root(B):
     assert np.abs(x + 2.0 * np.log(u)).max() <= 4e-7 * 33 and (x > 0).all()        # |2 ln u| <= 33, a few units in its last place
     same_bits(q, f / (np.float32(2.0) + f), "f / (2 + f)")
     same_bits(r, np.sqrt(x), "sqrt(x)")
+
+
+# traces of more than 2^32 - 1 tokens (18 GB of offsets), in each form of the generator: requests around token 2^32 and at
+# both ends against the oracle, the whole array by the check of the data
+@pytest.mark.parametrize("n_req,length", [(8191, 540_000), (32_767, 135_000), (65_600, 67_001)])
+def test_more_than_2_to_the_32_tokens(B, oracle, n_req, length):
+    print(f"wide token indices: n_req={n_req} length={length}", flush=True)
+    gen = dict(DI.config(4, n_req=n_req, seed=3)["gen"], out_lo=length, out_hi=length)
+    got = B.disco_gen_trace(gen)
+    assert got.n_tok == n_req * length > 1 << 32
+    off = np.arange(n_req + 1, dtype=np.int64) * length
+    assert (got.tok_off.cpu().numpy() == off).all()
+    at = (1 << 32) // length
+    for i in (0, at - 1, at, at + 1, n_req - 1):
+        same_bits(got.tok_arr[off[i]:off[i + 1]].cpu().numpy(), oracle.gen_tokens(gen, off, i, i + 1), f"tokens of request {i}")
+    assert B.disco_validate_trace(got) == 0
