@@ -170,7 +170,7 @@ def test_tabulated_threshold_searches(B, oracle, n_req, n_search, n_steps, hi):
 
 
 # order statistics of buffer hand-offs: known hand-offs at the edges of chunks and tokens, with and without a token array;
-# summaries found with other prices make the selection search for the hand-offs again (prices twice as high decide alike)
+# summaries found with other prices leave the selection to the general kernel (prices twice as high decide alike)
 @pytest.mark.parametrize("n_req,tokens,max_out,stall_p", [(1, True, 2, 0.0), (300, True, 40, 0.2), (700, True, 1100, 0.02),
                                                           (257, False, 600, 0.0), (5000, True, 260, 0.1)])
 def test_order_statistics_of_known_handoffs(B, oracle, n_req, tokens, max_out, stall_p):

@@ -584,12 +584,20 @@ def test_stats_threshold_table_buckets_in_two_rounds(B, oracle):
     check_stats(B, oracle, tr, specs, DI.COST_S)
 
 
+def device_table(B, policies):
+    """The same policy table resident on the device."""
+    rec = np.array([(p.mode, p.l_th, p.l_mid, p.w_mid, p.beta, p.w_tail, p.mig_mode, 0) for p in policies], dtype=B.POLICY_DTYPE)
+    return B.DevicePolicies(torch.from_numpy(rec.view(np.uint8).copy()).cuda(), len(policies))
+
+
+@pytest.mark.parametrize("where", ["host", "device"])
 @pytest.mark.parametrize("n_search,n_steps", [(9, 7), (10, 5), (21, 32), (22, 3), (64, 4)])
-def test_wait_searches_side_by_side(B, oracle, n_search, n_steps):
-    """Many wait-time searches in one call: the number of searches decides how many levels of the bisection a pass
-    evaluates (three for up to 9 searches, two for up to 21, else one) and the steps need not fill the last pass;
-    the recorded history is that of the plain bisection for every one of them."""
-    print(f"search parity {n_search} searches x {n_steps} steps", flush=True)
+def test_wait_searches_side_by_side(B, oracle, n_search, n_steps, where):
+    """Many wait-time searches in one call, the recorded history is that of the plain bisection for every one of them.
+    Templates on the device take the fused passes, where the number of searches decides how many levels of the bisection a
+    pass evaluates (three for up to 9 searches, two for up to 21, else one) and the steps need not fill the last pass;
+    templates on the host take passes of up to eight steps at this size."""
+    print(f"search parity {n_search} searches x {n_steps} steps, templates on the {where}", flush=True)
     tr = DI.handmade_trace(79, 20_011, tokens=False)
     dt = B.upload_trace(tr)
     total = int(tr["prompt_len"].astype(np.int64).sum())
@@ -597,7 +605,7 @@ def test_wait_searches_side_by_side(B, oracle, n_search, n_steps):
     templ = [B.Policy(mode=1, l_th=(j % 5) * 100 - 1) for j in range(n_search)]
     specs = [dict(which_param=B.PARAM_W_TAIL, which_acc="device_prefill_tok", n_steps=n_steps, lo=0.0, hi=4.0, target=t)
              for t in targets]
-    res = B.disco_budget_search(dt, DI.COST_D, templ, specs)
+    res = B.disco_budget_search(dt, DI.COST_D, device_table(B, templ) if where == "device" else templ, specs)
     so = B.search_to_host(res["out"], n_search)
     pol = B.policies_to_host(res["pol_out"], n_search)
     for j in range(n_search):
