@@ -388,7 +388,7 @@ int32_t disco_eval_dispatch_static(const disco_trace* trace /*host*/, const disc
  * for a server target; the target's tokens arrive at r'_t = fma(t - m, g,
  * r_m + t_mig(m)) (device), fma(t - m, srv_tbt, ...) or (r_m + t_mig(m)) +
  * (tok_arr_t - tok_arr_m) (server without / with a token trace), t > m.
- * Tables with such columns run in a slower, general kernel.
+ * With `delivered` a slower, general kernel does all this.
  * acc: device, P entries, timeline block overwritten.  Asynchronous.
  * ws: disco_workspace_bytes(n_req, P) bytes (the per-request part is needed).
  * Errors: NULL, SHAPE, RANGE (tau <= 0, kappa_lag < 0), CSR (delivered

@@ -277,7 +277,7 @@ __device__ __forceinline__ float gen_gap(const disco_gen_params& g, unsigned sta
 // Bound by the arithmetic of the gaps: 168 vector instructions per 64 tokens at 3.3 cycles each (18 of them wide
 // multiplications of the counter-based generator); the gaps never reach device memory.  4.3 KB of LDS and 56
 // registers per wave leave eight waves per SIMD (16 KB tiles of 64 requests: four waves, a tenth slower).
-// 491 M tokens of 10^6 requests: 2.09 ms; gaps and sums in two kernels with the gaps in device memory between them
+// 491 M tokens of 10^6 requests: 1.75 ms; gaps and sums in two kernels with the gaps in device memory between them
 // took 1.9 + 5.2 ms, the second waiting for the longest of every 256 requests.  1 M tokens of 2000 requests: 1.12 ms
 // -> 0.07 ms.
 constexpr int GT_LOG_TILE = 10;

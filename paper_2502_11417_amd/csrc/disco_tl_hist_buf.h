@@ -37,8 +37,8 @@ __device__ __forceinline__ Handoff handoff_at(bool src_dev, int m, const float* 
 // without the scan of chunks in which the running maximum does not move.  Gaps -> sink(key[4]) as in walk_hist.
 //   src_dev  device source, the server's tokens behind the hand-off; else the other way round
 //   first    the lane's elements of the first chunk of the token window (not used without a token array)
-// Bound by vector issue.  A pass over 10^6 requests x 8 columns 74 and 87 us with the general walker, 66 and 79 us; 10^5
-// requests x 12 wait columns 28 -> 26 us.
+// Bound by vector issue.  A pass over 10^6 requests x 8 columns 74 and 87 us with the general walker, 59 and 73 us; 10^5
+// requests x 12 wait columns 28 -> 24 us.
 template <class Sink>
 __device__ __forceinline__ void walk_hist_known(bool src_dev, int n, const float* __restrict__ arr, i64 off, i64 n_tok, int align,
                                                 const float first[4], float gap, float g_dev, const Handoff& ho, float tau, int lane,

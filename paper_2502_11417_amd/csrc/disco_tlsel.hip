@@ -87,7 +87,7 @@ __device__ void tbt_plan_next(SelState* S, int P, int nq, unsigned* s_prefix, in
             w = fit_width((long)g1 * (tl.nwalk > 0 ? tl.nwalk : 1), DISCO_TL_HIST_WORDS);
             const int wg = fit_width((long)g1 * tl.ncls, DISCO_GHIST_WORDS);
             if (wg < w) w = wg;
-            // a digit wider than the select step stages in LDS only where it saves a pass
+            // a digit of more bins than the select step sums up in registers only where it saves a pass
             if (w > SEL_DIRECT_BITS && (tl.left + w - 1) / w == (tl.left + SEL_DIRECT_BITS - 1) / SEL_DIRECT_BITS) w = SEL_DIRECT_BITS;
         }
         if (w < 1) w = 1;
