@@ -278,8 +278,8 @@ __device__ __forceinline__ float gen_gap(const disco_gen_params& g, unsigned sta
 // multiplications of the counter-based generator); the gaps never reach device memory.  4.3 KB of LDS and 56
 // registers per wave leave eight waves per SIMD (16 KB tiles of 64 requests: four waves, a tenth slower).
 // 491 M tokens of 10^6 requests: 1.75 ms; gaps and sums in two kernels with the gaps in device memory between them
-// took 1.9 + 5.2 ms, the second waiting for the longest of every 256 requests.  1 M tokens of 2000 requests: 1.12 ms
-// -> 0.07 ms.
+// took 1.9 + 5.2 ms, the second waiting for the longest of every 256 requests.  1 M tokens of 2000 requests: 1.07 ms
+// -> 0.06 ms.
 constexpr int GT_LOG_TILE = 10;
 
 template <int LOG_R, bool WIDE>
@@ -301,15 +301,44 @@ __global__ __launch_bounds__(64) void k_gen_tokens(disco_gen_params g, i64 n_req
         lo = (int)(a - at);
         left = (int)(tok_off[i + 1] - at);
     }
-    int gap_lo = lo + 1;                                     // first token of the piece that a gap is added for
     float acc = 0.0f;
+    // Short requests: where all tokens of the wave's requests fit the tile, their gaps are made as one stretch instead of
+    // row by row (a row of a few tokens leaves most lanes idle: 400 000 requests of 1 to 3 tokens 82 us,
+    // now 17).
+    const i64 start = (i64)bcast_u64((u64)at, 0);
+    const u64 valid = __ballot(lane < R && i < n_req);       // (never empty)
+    const int last = 63 - __clzll((long long)valid);
+    const i64 stretch = (i64)bcast_u64((u64)(at + left), last) - start;
+    if (R > 1 && stretch <= R * K) {
+        const int lead = bcast_i(lo, 0), end = (int)stretch;
+        for (int q = lane; q - lane < end; q += 64) {
+            u64 j = (u64)start + (u64)q;
+            if (!WIDE) j = (unsigned)start + (unsigned)q;
+            tile[q] = gen_gap(g, stall_below, j);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (left > lo) {                                     // (left counts from the row's boundary, lo is its first token)
+            const int first = (int)(at - start) + lo, behind = (int)(at - start) + left;
+            tile[first] = 0.0f;
+#pragma unroll 4
+            for (int q = first + 1; q < behind; ++q) { acc = acc + tile[q]; tile[q] = acc; }
+        }
+        __builtin_amdgcn_wave_barrier();
+        for (int q = lane; q < end; q += 64)
+            if (q >= lead) tok_arr[start + q] = tile[q];
+        return;
+    }
+    int gap_lo = lo + 1;                                     // first token of the piece that a gap is added for
     for (u64 m = __ballot(left > 0); m != 0ull; m = __ballot(left > 0)) {
+        // (a lone request's last piece ends with its tokens: 8000 requests of up to 200 tokens 67 -> 20 us; with more rows a
+        // piece is short enough as it is)
+        const int len = R == 1 && bcast_i(left, 0) < K ? (bcast_i(left, 0) + 63) & ~63 : K;
         for (u64 rows = m; rows != 0ull; rows &= rows - 1ull) {
             const int r = __ffsll((long long)rows) - 1;
             const u64 base = bcast_u64((u64)at, r);
             const int r_lo = bcast_i(gap_lo, r), r_hi = bcast_i(left, r);
 #pragma unroll 2
-            for (int q0 = 0; q0 < K; q0 += 64) {
+            for (int q0 = 0; q0 < len; q0 += 64) {
                 const int q = q0 + lane;
                 float gap = 0.0f;
                 if (q0 < r_hi) {                             // (the same in every lane)
@@ -325,7 +354,7 @@ __global__ __launch_bounds__(64) void k_gen_tokens(disco_gen_params g, i64 n_req
         if (left > 0) {
             float4* row = reinterpret_cast<float4*>(&tile[lane * KS]);
 #pragma unroll 8
-            for (int q = 0; q < K / 4; ++q) {
+            for (int q = 0; q < len / 4; ++q) {
                 float4 v = row[q];
                 v.x = acc + v.x; v.y = v.x + v.y; v.z = v.y + v.z; v.w = v.z + v.w;
                 acc = v.w;
@@ -338,7 +367,7 @@ __global__ __launch_bounds__(64) void k_gen_tokens(disco_gen_params g, i64 n_req
             float* dst = tok_arr + (i64)bcast_u64((u64)at, r);
             const int r_lo = bcast_i(lo, r), r_hi = bcast_i(left, r);
 #pragma unroll 2
-            for (int q0 = 0; q0 < K; q0 += 64) {
+            for (int q0 = 0; q0 < len; q0 += 64) {
                 const int q = q0 + lane;
                 if (q >= r_lo && q < r_hi) dst[q] = tile[r * KS + q];
             }

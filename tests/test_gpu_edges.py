@@ -19,10 +19,12 @@ def same_bits(got, want, what):
 
 
 # requests per wave of the token generator: 1 below 8192 requests, 4 below 32768, then 16; pieces of 64, 256 and 1024
-# tokens from multiples of 32 on; the stall test at both ends of its range
+# tokens from multiples of 32 on, or all of a wave's requests in one stretch where they have at most 1024 tokens; the stall
+# test at both ends of its range
 @pytest.mark.parametrize("n_req,out_mu,out_hi,stall_p", [
     (1, 6.0, 1100, 0.01), (15, 6.5, 2100, 0.5), (8191, 3.0, 70, 0.01), (8192, 4.5, 600, 0.0), (8195, 3.5, 300, 1.0),
-    (32767, 3.0, 65, 0.01), (32768, 3.5, 130, 0.01), (32785, 3.5, 97, 0.25)])
+    (32767, 3.0, 65, 0.01), (32768, 3.5, 130, 0.01), (32785, 3.5, 97, 0.25),
+    (8209, 5.6, 700, 0.01), (32801, 4.2, 300, 0.02), (40_001, 0.5, 3, 0.3)])
 def test_generated_tokens(B, oracle, n_req, out_mu, out_hi, stall_p):
     print(f"generated tokens: n_req={n_req} out_mu={out_mu} out_hi={out_hi} stall_p={stall_p}", flush=True)
     gen = dict(DI.config(4, n_req=n_req, seed=n_req)["gen"], out_mu=out_mu, out_hi=out_hi, gap_stall_p=stall_p)
