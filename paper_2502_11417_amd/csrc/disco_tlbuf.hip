@@ -33,6 +33,7 @@ namespace {
 constexpr int TB_BLOCK = 256;                // 4 waves
 constexpr int TB_RB = 64;                    // requests per wave batch, at most
 constexpr int TB_FULL = 768 * 4;              // waves the chip holds at once (3 per SIMD)
+constexpr int TB_SHARE = 512 * 4;             // waves of two workgroups per CU
 constexpr int PROBE_TOKENS = 128;            // tokens a lane steps through before the request is left to a whole wave
 
 struct BufStatsArgs {
@@ -352,11 +353,14 @@ void disco_launch_tl_stats_buf(const TraceView& v, i64 n_tok, const disco_policy
     s.summary = (const TlSummary*)a.summary;
     s.bc = a.bc;
     s.buffer_flag = a.buffer_flag;
-    // The requests that take a whole wave are walked one after the other within a batch: where the trace has fewer than
-    // a batch of 64 for every wave the chip holds, smaller batches share them out (10^5 requests x 12 wait
-    // columns, every hand-off walked by the general walker: 179 us with batches of 64, 161 us with 32).
+    // The requests that take a whole wave are walked one after the other within a batch: small traces are shared out in
+    // smaller batches, as long as they take no more than two workgroups per CU (every workgroup adds its totals and ends
+    // with a device-wide release, which costs the passes that walk hardly a request).  disco_eval_migration with token
+    // lengths of workload 2, batches of 64, these, and as many as fill the chip:
+    //   10^4 requests    12 wait columns 105, 63, 66 us;  8 threshold columns 42, 45, 49
+    //   30 000 requests  12 wait columns 124, 97, 100;    8 threshold columns 51, 57, 64
     s.rb = TB_RB;
-    while (s.rb > 4 && (v.n_req + s.rb - 1) / s.rb < TB_FULL) s.rb >>= 1;
+    while (s.rb > 4 && (v.n_req + s.rb / 2 - 1) / (s.rb / 2) <= TB_SHARE) s.rb >>= 1;
     const i64 per_block = (i64)(TB_BLOCK / 64) * s.rb;
     i64 b = (v.n_req + per_block - 1) / per_block;
     if (b < 1) b = 1;

@@ -89,7 +89,8 @@ def test_decreasing_tokens_are_found_anywhere(B, lengths, shift):
 
 # device -> server hand-offs: batches of 4 .. 64 requests per wave, tails of 1 token to several chunks of 256 from every
 # alignment, stalls among them; twelve wait columns give the TBT digits 10 + 10 + 1 bits (the last one by the narrow select)
-@pytest.mark.parametrize("n_req,max_out,stall_p", [(1, 3, 0.0), (63, 1200, 0.05), (777, 300, 0.0), (12_289, 24, 0.02)])
+@pytest.mark.parametrize("n_req,max_out,stall_p", [(1, 3, 0.0), (63, 1200, 0.05), (777, 300, 0.0), (12_289, 24, 0.02),
+                                                   (4097, 60, 0.05), (20_001, 9, 0.05), (32_801, 5, 0.1)])
 def test_server_tails_of_wait_columns(B, oracle, n_req, max_out, stall_p):
     print(f"server tails: n_req={n_req} max_out={max_out} stall_p={stall_p}", flush=True)
     tr = slow_prefill(DI.handmade_trace(61 + n_req, n_req, tokens=True, max_out=max_out, stall_p=stall_p), 16.0)
