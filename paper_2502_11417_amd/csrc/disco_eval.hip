@@ -798,7 +798,7 @@ extern "C" int32_t disco_ingest_trace(const disco_raw_trace* raw, disco_trace* t
     trace->n_tok = raw->n_tok;
     trace->tok_off = const_cast<int64_t*>(raw->tok_off);
     if (raw->n_req == 0) return DISCO_OK;
-    disco_launch_ingest(raw->n_req, raw->t_send, raw->t_token, raw->tok_off, trace->srv_ttft, trace->output_len,
+    disco_launch_ingest(raw->n_req, raw->n_tok, raw->t_send, raw->t_token, raw->tok_off, trace->srv_ttft, trace->output_len,
                         trace->tok_arr, (hipStream_t)stream_);
     DISCO_HIP(hipGetLastError());
     return DISCO_OK;

@@ -28,10 +28,11 @@ constexpr int FIT_MAX_BLOCKS = 1024;
 // A wave owns R consecutive requests (their tokens are one contiguous stretch).  Lane r < R takes request r: its
 // offsets, first timestamp and per-request outputs are loaded and stored for all R at once, so the chain
 // offset -> first timestamp -> tokens is waited for once per R requests and not per request.  The tokens then pass in
-// steps of 512 per wave, all loads of a step issued before its first store; neither side is read again, so both go
-// past the caches.  Bound by device memory: 491 M tokens of 10^6 requests, 5.9 GB, in 1250 us = 4.7 TB/s (a wave per
-// request with one load in flight: 1300 us; an elementwise fp32 -> fp64 conversion of that size runs at 5.1 TB/s).
-template <int R, bool PAIR>
+// steps of 512 per wave, all loads of a step issued before its first store.  Neither side is read again here, so the
+// stores go past the caches, and so do the loads (PAST) where the timestamps do not fit the last level anyway.  Bound by
+// device memory: 491 M tokens of 10^6 requests, 5.9 GB, in 1185 us = 5.0 TB/s (a wave per request with one load in flight:
+// 1312 us; an elementwise fp32 -> fp64 conversion of that size runs at 5.1 TB/s).
+template <int R, bool PAIR, bool PAST>
 __global__ __launch_bounds__(IG_BLOCK) void k_ingest(i64 n_req, const double* __restrict__ t_send,
                                                      const double* __restrict__ t_token, const i64* __restrict__ off,
                                                      float* __restrict__ srv_ttft, int32_t* __restrict__ output_len,
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(IG_BLOCK) void k_ingest(i64 n_req, const double* __
                     d2 x[STEP];
 #pragma unroll
                     for (int q = 0; q < STEP; ++q)
-                        if (j + 64 * q < pairs) x[q] = __builtin_nontemporal_load(src + j + 64 * q);
+                        if (j + 64 * q < pairs) x[q] = PAST ? __builtin_nontemporal_load(src + j + 64 * q) : src[j + 64 * q];
 #pragma unroll
                     for (int q = 0; q < STEP; ++q)
                         if (j + 64 * q < pairs) {
@@ -145,25 +146,35 @@ const char* const kProfileNames[3] = {"Pixel 7 Pro / Bloom 1.1B", "Pixel 7 Pro /
 }  // namespace
 
 template <int R>
-static void launch_ingest(i64 n_req, const double* t_send, const double* t_token, const i64* off, float* srv_ttft,
+static void launch_ingest(i64 n_req, i64 n_tok, const double* t_send, const double* t_token, const i64* off, float* srv_ttft,
                           int32_t* output_len, float* tok_arr, hipStream_t stream)
 {
     i64 b = (n_req + R * IG_WAVES - 1) / (R * IG_WAVES);
     if (b < 1) b = 1;
     if (b > 8192) b = 8192;
     const bool pair = (((uintptr_t)t_token) & 15u) == 0 && (((uintptr_t)tok_arr) & 7u) == 0;
-    if (pair) hipLaunchKernelGGL((k_ingest<R, true>), dim3((unsigned)b), dim3(IG_BLOCK), 0, stream, n_req, t_send, t_token, off,
-                                 srv_ttft, output_len, tok_arr);
-    else hipLaunchKernelGGL((k_ingest<R, false>), dim3((unsigned)b), dim3(IG_BLOCK), 0, stream, n_req, t_send, t_token, off,
-                            srv_ttft, output_len, tok_arr);
+    // 256 MB of timestamps: the last-level cache.  9.9 M tokens 22 us with loads through it and 24 past it, 69 M tokens 163 and 153
+    const bool past = n_tok > (i64)(256 << 20) / 8;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)b), dim3(IG_BLOCK), 0, stream, n_req, t_send, t_token, off, srv_ttft, output_len, tok_arr);
+    };
+    if (!pair) go(k_ingest<R, false, false>);
+    else if (past) go(k_ingest<R, true, true>);
+    else go(k_ingest<R, true, false>);
 }
 
-void disco_launch_ingest(i64 n_req, const double* t_send, const double* t_token, const i64* off, float* srv_ttft,
+void disco_launch_ingest(i64 n_req, i64 n_tok, const double* t_send, const double* t_token, const i64* off, float* srv_ttft,
                          int32_t* output_len, float* tok_arr, hipStream_t stream)
 {
-    // groups of 16 where they still leave every wave slot of the chip (8192) one, else a wave per request
-    if (n_req >= 16 * 8192) launch_ingest<16>(n_req, t_send, t_token, off, srv_ttft, output_len, tok_arr, stream);
-    else launch_ingest<1>(n_req, t_send, t_token, off, srv_ttft, output_len, tok_arr, stream);
+    // The shorter the requests, the more of them share a wave (the wait for offsets and first timestamps is a request's own
+    // cost), as long as the waves keep half the chip's slots busy.  With 1, 2, 8 and 16 per wave: 10^6 requests of 492 tokens
+    // 1185, 1211, 1227 and 1241 us, of 215 tokens 522, 476, 498 and 516, of 71 tokens 268 with 2 and 211 with 8, of 34 tokens 333, 232, 177 and 174, of 2 tokens 207, 134,
+    // 91 and 83; 140 000 of 34 tokens 39, 28 and 24 us with 1, 2 and 8.
+    const i64 mean = n_req > 0 ? n_tok / n_req : 0;
+    if (mean < 24 && n_req >= 16 * 4096) launch_ingest<16>(n_req, n_tok, t_send, t_token, off, srv_ttft, output_len, tok_arr, stream);
+    else if (mean < 128 && n_req >= 8 * 4096) launch_ingest<8>(n_req, n_tok, t_send, t_token, off, srv_ttft, output_len, tok_arr, stream);
+    else if (mean < 256 && n_req >= 2 * 4096) launch_ingest<2>(n_req, n_tok, t_send, t_token, off, srv_ttft, output_len, tok_arr, stream);
+    else launch_ingest<1>(n_req, n_tok, t_send, t_token, off, srv_ttft, output_len, tok_arr, stream);
 }
 
 size_t disco_fit_scratch_bytes(void) { return sizeof(FitPartial) * FIT_MAX_BLOCKS; }

@@ -67,7 +67,7 @@ int disco_launch_len_table(const TraceView& v, int nbins, unsigned* scratch, siz
 void disco_launch_tl_stats_buf(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                MigPartial* totals, hipStream_t stream);
 // Recorded traces: timestamps to relative arrays; log-normal fit (`scratch`: disco_fit_scratch_bytes() bytes).
-void disco_launch_ingest(i64 n_req, const double* t_send, const double* t_token, const i64* off, float* srv_ttft,
+void disco_launch_ingest(i64 n_req, i64 n_tok, const double* t_send, const double* t_token, const i64* off, float* srv_ttft,
                          int32_t* output_len, float* tok_arr, hipStream_t stream);
 size_t disco_fit_scratch_bytes(void);
 void disco_launch_fit(const void* x, int kind, i64 n, disco_lognormal_fit* fit, void* scratch, hipStream_t stream);

@@ -35,13 +35,17 @@ def test_generated_tokens(B, oracle, n_req, out_mu, out_hi, stall_p):
     same_bits(got.tok_arr.cpu().numpy(), want["tok_arr"], "tok_arr")
 
 
-# requests per wave of the ingest: 1 below 131072 requests, then 16; timestamps in pairs, or one by one where the array
-# starts off a 16-byte boundary; request lengths around the pairs and the steps of 512
-@pytest.mark.parametrize("n_req,shift", [(1, 0), (1, 1), (131_071, 0), (131_072, 1), (131_087, 0)])
-def test_ingested_offsets(B, n_req, shift):
+# requests per wave of the ingest: 16, 8, 2 or 1 by the mean length and the number of requests; timestamps in pairs, or one
+# by one where the array starts off a 16-byte boundary; loads past the caches from 2^25 timestamps on; request lengths around
+# the pairs and the steps of 512
+@pytest.mark.parametrize("n_req,shift,about", [(1, 0, 3), (1, 1, 3), (131_071, 0, 3), (131_072, 1, 3), (131_087, 0, 3), (32_769, 0, 3), (40_007, 0, 30),
+                                               (33_001, 1, 90), (9001, 0, 150), (8193, 1, 150), (3001, 0, 400), (66_003, 0, 520), (227_007, 0, 150)])
+def test_ingested_offsets(B, n_req, shift, about):
     print(f"ingested offsets: n_req={n_req} shift={shift}", flush=True)
     rng = np.random.default_rng(n_req + shift)
     n = rng.choice([0, 1, 2, 3, 7], n_req) if n_req > 1 else np.array([5])
+    if about > 3:
+        n += rng.integers(0, 2 * about, n_req)
     long = [0, 1, 2, 127, 128, 129, 511, 512, 513, 1025]
     for i, length in enumerate(long[:max(0, n_req - 1)]):
         n[i * n_req // len(long)] = length
