@@ -79,7 +79,16 @@ __global__ __launch_bounds__(IG_BLOCK) void k_ingest(i64 n_req, const double* __
                         }
                 }
             } else {
-                for (i64 j = a + lane; j < b; j += 64) tok_arr[j] = (float)(t_token[j] - first);
+                constexpr int ONES = R >= 8 ? 1 : STEP;  // (many short requests per wave: a step covers most of them)
+                for (i64 j = a + lane; j < b; j += 64 * ONES) {
+                    double x[ONES];
+#pragma unroll
+                    for (int q = 0; q < ONES; ++q)
+                        if (j + 64 * q < b) x[q] = t_token[j + 64 * q];
+#pragma unroll
+                    for (int q = 0; q < ONES; ++q)
+                        if (j + 64 * q < b) tok_arr[j + 64 * q] = (float)(x[q] - first);
+                }
             }
         }
     }
