@@ -196,6 +196,17 @@ def test_order_statistics_of_known_handoffs(B, oracle, n_req, tokens, max_out, s
         same_bits(got[1].cpu().numpy(), got[0].cpu().numpy(), "records")
 
 
+# order statistics outside the window of keys above the pacing interval: the selection starts over on raw keys, with wide
+# digits where few classes are walked and with more than four prefixes in the end (histograms per slot)
+@pytest.mark.parametrize("n_req,max_out,P", [(1500, 90, 2), (700, 400, 5), (3000, 30, 9)])
+def test_order_statistics_on_raw_keys(B, oracle, n_req, max_out, P):
+    print(f"raw keys: n_req={n_req} max_out={max_out} P={P}", flush=True)
+    tr = DI.handmade_trace(520 + n_req, n_req, tokens=True, max_out=max_out, stall_p=0.1)
+    specs = [dict(mode=0, l_th=0, mig_mode=2), dict(mode=0, l_th=1150), dict(mode=1, l_th=0, beta=DI.f32(1e-3), w_tail=0.0, mig_mode=1)]
+    specs = (specs + [dict(mode=0, l_th=300 * j) for j in range(P)])[:P]
+    check_stats(B, oracle, tr, specs, DI.COST_S, quantiles=((0, 100), (50, 100), (99, 100), (100, 100)), tau=DI.TAU, kappa=1.0)
+
+
 # a law with a NaN parameter gives NaN times, as in the oracle's trace, and the check of the data reports them
 @pytest.mark.parametrize("law,field", [("ttft_mu", "srv_ttft"), ("tbt_mu", "srv_tbt"), ("gap_mu", "tok_arr")])
 def test_a_nan_law_is_not_hidden(B, oracle, law, field):
