@@ -240,7 +240,7 @@ bool disco_search_bins_pays(i64 n_req, int n_search, int n_steps, bool decode)
     const int npass = (n_steps + SB_DEPTH - 1) / SB_DEPTH, first = (n_steps + npass - 1) / npass;
     double per_search = first <= 2 ? 2.6 : 2.0 + 0.65 * first;       // the first pass bisects, the later ones hardly
     if (npass > 1) per_search += 5.1 + 2.3 * (npass - 2);
-    return 4.0 + 1.6 * first + 14.0 * (npass - 1) + per_search * n * n_search < fused;
+    return 4.0 + 0.08 * n_search + 1.6 * first + 14.0 * (npass - 1) + per_search * n * n_search < fused;
 }
 
 size_t disco_search_bins_bytes(int n_search)
