@@ -87,16 +87,12 @@ __device__ void tbt_plan_next(SelState* S, int P, int nq, unsigned* s_prefix, in
             w = fit_width((long)g1 * (tl.nwalk > 0 ? tl.nwalk : 1), DISCO_TL_HIST_WORDS);
             const int wg = fit_width((long)g1 * tl.ncls, DISCO_GHIST_WORDS);
             if (wg < w) w = wg;
-            // a digit of more bins than the select step sums up in registers only where it saves a pass, the later digits
-            // having room for four prefixes per class.  Not on raw keys with timelines to walk: there may be more prefixes in
-            // the end, and then every bit less here can cost another walk of everything (30 000 requests x 5 columns 1.15 ms
-            // of order statistics with 12 + 10 + 9 bits, 1.61 with 11 + 10 + 9 + 1)
-            int later = fit_width(4l * (tl.nwalk > 0 ? tl.nwalk : 1), DISCO_TL_HIST_WORDS);
-            const int later_g = fit_width(4l * tl.ncls, DISCO_GHIST_WORDS);
-            if (later_g < later) later = later_g;
-            if (later < 1) later = 1;
-            auto passes = [&](int bits) { return bits > 0 ? (bits + later - 1) / later : 0; };
-            if (w > SEL_DIRECT_BITS && (tl.window != 0 || tl.nwalk == 0) && passes(tl.left - w) == passes(tl.left - SEL_DIRECT_BITS))
+            // a digit of more bins than the select step sums up in registers only where it saves a pass.  Not on raw keys with
+            // timelines to walk: there may be more than four prefixes in the end, and then every bit less here can cost another
+            // walk of everything (30 000 requests x 5 columns 1.15 ms of order statistics with 12 + 10 + 9 bits, 1.61 with
+            // 11 + 10 + 9 + 1)
+            if (w > SEL_DIRECT_BITS && (tl.window != 0 || tl.nwalk == 0) &&
+                (tl.left + w - 1) / w == (tl.left + SEL_DIRECT_BITS - 1) / SEL_DIRECT_BITS)
                 w = SEL_DIRECT_BITS;
         }
         if (w < 1) w = 1;
