@@ -425,6 +425,44 @@ int stage_policies(const disco_policy* pol, int P, char* ws, const WsLayout& L, 
     return DISCO_OK;
 }
 
+// Dispatch totals of every column and, if asked, the per-pair outputs; `part`: device-wide totals, `ws + L.*`: scratch.
+int eval_dispatch(const TraceView& v, const disco_policy* pol, int P, const disco_pair_out* out, disco_accum* acc, char* ws,
+                  const WsLayout& L, hipStream_t stream)
+{
+    const bool pairs = out && (out->decision || out->ttft) && v.n_req > 0;
+    const bool small = disco_small(v.n_req);
+    const disco_policy* staged = (const disco_policy*)(ws + L.pol);
+    if (small && !pairs) {
+        PolTable t;
+        memset(&t, 0, sizeof(t));
+        const bool device = is_device_pointer(pol);
+        if (!device) {
+            const int rc = check_policies(pol, P);
+            if (rc) return rc;
+            memcpy(t.p, pol, sizeof(disco_policy) * (size_t)P);
+        }
+        disco_launch_small_dispatch(v, t, device ? pol : nullptr, P, acc, stream);
+    } else {
+        const int rc = stage_policies(pol, P, ws, L, stream);        // also puts the flag words and the totals at their identity
+        if (rc) return rc;
+        if (small) {
+            PolTable none;
+            memset(&none, 0, sizeof(none));
+            disco_launch_small_dispatch(v, none, staged, P, acc, stream);
+        } else {
+            DispFin fin;
+            memset(&fin, 0, sizeof(fin));
+            fin.kind = 0;
+            fin.need = 2;
+            fin.acc = acc;
+            disco_launch_dispatch_acc(v, staged, P, (u64*)(ws + L.part), fin, stream);
+        }
+        if (pairs) disco_launch_dispatch_mat(v, staged, P, out->decision, out->ttft, stream);
+    }
+    DISCO_HIP(hipGetLastError());
+    return DISCO_OK;
+}
+
 }  // namespace
 
 void disco_set_hip_error(hipError_t e, const char* what)
@@ -510,19 +548,7 @@ extern "C" int32_t disco_eval_dispatch(const disco_trace* trace, const disco_pol
     hipStream_t stream = (hipStream_t)stream_;
     char* ws = (char*)ws_;
     const WsLayout L = disco_ws_layout(P);
-    const TraceView v = view_of(trace);
-    rc = stage_policies(pol, P, ws, L, stream);
-    if (rc) return rc;
-    DispFin fin;
-    memset(&fin, 0, sizeof(fin));
-    fin.kind = 0;
-    fin.need = 2;
-    fin.acc = acc;
-    disco_launch_dispatch_acc(v, (const disco_policy*)(ws + L.pol), P, (u64*)(ws + L.part), fin, stream);
-    if (out && (out->decision || out->ttft) && v.n_req > 0)
-        disco_launch_dispatch_mat(v, (const disco_policy*)(ws + L.pol), P, out->decision, out->ttft, stream);
-    DISCO_HIP(hipGetLastError());
-    return DISCO_OK;
+    return eval_dispatch(view_of(trace), pol, P, out, acc, ws, L, stream);
 }
 
 // ---------------------------------------------------- fixed scratch area --
@@ -578,19 +604,7 @@ extern "C" int32_t disco_eval_dispatch_static(const disco_trace* trace, const di
     WsLayout L;
     memset(&L, 0, sizeof(L));
     L.pol = SS_POL; L.ticket = SS_TICKET; L.part = SS_PART; L.total = SS_BYTES;
-    const TraceView v = view_of(trace);
-    rc = stage_policies(pol, P, ws, L, stream);        // also puts the flag words and the totals at their identity
-    if (rc) return rc;
-    DispFin fin;
-    memset(&fin, 0, sizeof(fin));
-    fin.kind = 0;
-    fin.need = 2;
-    fin.acc = acc;
-    disco_launch_dispatch_acc(v, (const disco_policy*)(ws + L.pol), P, (u64*)(ws + L.part), fin, stream);
-    if (out && (out->decision || out->ttft) && v.n_req > 0)
-        disco_launch_dispatch_mat(v, (const disco_policy*)(ws + L.pol), P, out->decision, out->ttft, stream);
-    DISCO_HIP(hipGetLastError());
-    return DISCO_OK;
+    return eval_dispatch(view_of(trace), pol, P, out, acc, ws, L, stream);
 }
 
 extern "C" int32_t disco_eval_migration(const disco_trace* trace, const disco_timeline_params* tl,
@@ -730,7 +744,8 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
         unsigned char* ubytes = ws_bytes >= L.total + (size_t)v.n_req ? (unsigned char*)(ws + L.total) : nullptr;
         // (the descriptors of the TBT selection are written after the TTFT passes)
         u64* masks = ws_bytes >= disco_ws_full_bytes(L, v.n_req) ? (u64*)(ws + disco_ws_desc_offset(L, v.n_req)) : nullptr;
-        for (int pass = 0; pass < 4; ++pass)
+        if (disco_small(v.n_req)) disco_launch_small_ttft(v, (const disco_policy*)(ws + L.pol), P, nq, acc, S, stream);
+        for (int pass = 0; pass < 4 && !disco_small(v.n_req); ++pass)
             disco_launch_ttft_pass(v, (const disco_policy*)(ws + L.pol), P, nq, pass, S, (unsigned*)(ws + L.slices), gh,
                                    ubytes, masks, stream);
         if (tl) {
@@ -880,8 +895,6 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
     char* ws = (char*)ws_;
     const WsLayout L = disco_ws_layout(n_search);
     const TraceView v = view_of(trace);
-    rc = stage_policies(templ, n_search, ws, L, stream);
-    if (rc) return rc;
     // Length thresholds of server-constrained columns against a prompt-token budget: the accumulator is a
     // function of the threshold alone and is tabulated once (Alg. 3's sorted running totals); all bisection
     // steps then read the table.  Needs a host-resident template table (its modes are inspected here).
@@ -893,6 +906,22 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
                     spec[j].lo >= 0.0 && spec[j].hi + 2.0 <= (double)disco_search_table_max_bins();
         if (spec[j].hi > max_hi) max_hi = spec[j].hi;
     }
+    if (tabulated && disco_small(v.n_req) && (int)max_hi + 2 <= disco_small_search_max_bins()) {
+        rc = check_policies(templ, n_search);
+        if (rc) return rc;
+        PolTable pt;
+        SmallSearches sp;
+        memset(&pt, 0, sizeof(pt));
+        memset(&sp, 0, sizeof(sp));
+        memcpy(pt.p, templ, sizeof(disco_policy) * (size_t)n_search);
+        for (int j = 0; j < n_search; ++j)
+            sp.s[j] = SmallSearch{spec[j].target, (int)spec[j].lo, (int)spec[j].hi, spec[j].which_acc, 0};
+        disco_launch_small_search(v, pt, sp, n_search, n_steps, (int)max_hi + 2, *cost, out, pol_out, acc_out, stream);
+        DISCO_HIP(hipGetLastError());
+        return DISCO_OK;
+    }
+    rc = stage_policies(templ, n_search, ws, L, stream);
+    if (rc) return rc;
     // bisection passes only need the totals their accumulators are made of
     int need = 0;
     for (int j = 0; j < n_search; ++j)

@@ -43,6 +43,26 @@ struct DispFin {
     const disco_policy* templ;    // the searches' template records
 };
 
+// Traces of up to SMALL_REQ requests take kernels of one workgroup per policy column (disco_small.h): as many as the keys of
+// an order statistic fit LDS, and the column kernels are still the faster way there (32 000 requests, whole calls: search,
+// totals and order statistics of 64 threshold columns 100 us with the general kernels, 62 with these; of 4 88 / 52; solve,
+// totals and order statistics of 12 wait columns 157 / 82; 8 levels x 8 stochastic runs 109 / 76).  The testing aid that
+// shrinks the grids sends them through the general kernels.
+constexpr int SMALL_REQ = 32768;
+inline bool disco_small(i64 n_req) { return n_req <= SMALL_REQ && disco_grid_divisor() == 1; }
+struct SmallSearch { double target; int lo, hi, which_acc, pad; };
+struct SmallSearches { SmallSearch s[DISCO_MAX_COLS]; };
+// Table from device memory, or from `host` where `device` is null.
+void disco_launch_small_dispatch(const TraceView& v, const PolTable& host, const disco_policy* device, int P, disco_accum* acc,
+                                 hipStream_t stream);
+// Tabulated threshold searches (templates: server-constrained columns), with the evaluation at the answers.
+int disco_small_search_max_bins(void);
+void disco_launch_small_search(const TraceView& v, const PolTable& templ, const SmallSearches& sp, int n_search, int n_steps, int nbins,
+                               const disco_cost_params& cost, disco_search_out* sout, disco_policy* pol_out, disco_accum* acc,
+                               hipStream_t stream);
+void disco_launch_small_ttft(const TraceView& v, const disco_policy* pol, int P, int nq, const disco_accum* acc, SelState* S,
+                             hipStream_t stream);
+
 // Levels of the bisection tree one pass can evaluate for n searches (64 columns per pass).
 inline int disco_search_depth(int n) { return n <= 9 ? 3 : (n <= 21 ? 2 : 1); }
 

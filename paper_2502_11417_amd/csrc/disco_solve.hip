@@ -17,12 +17,14 @@
 //      passes over the bit patterns; one LDS histogram row per distinct prefix
 //      of the wanted ranks),
 //   4. one thread per column writing the policy record.
+// Small traces take all of it in one launch (k_small_solve).
 #include <string.h>
 
 #include "disco_launch.h"
 #include "disco_state.h"
 #include "disco_device.h"
 #include "disco_len.h"
+#include "disco_small.h"
 
 namespace {
 
@@ -42,30 +44,26 @@ struct SolveState {
 struct SolveSpecs { disco_solve_spec s[DISCO_MAX_COLS]; };
 
 // Mass of the prompts of length <= L (tokens): total - sum over lengths > L.
-__device__ __forceinline__ u64 mass_upto(const LenSums& sums, u64 total, int L)
+template <class Sums>
+__device__ __forceinline__ u64 mass_upto(const Sums& sums, u64 total, int L)
 {
     return L < 0 ? 0ull : total - sums(L + 1);
 }
 
-// Step 2 (thread = column, once the workgroup has added up the table's blocks).
-__global__ __launch_bounds__(1024) void k_solve_plan(SolveSpecs specs, int n, i64 n_req, int nbins, int nslices,
-                                                     const u64* __restrict__ table, SolveState* S)
+// Step 2 for one column: record and result, and the ranks of the server TTFTs that become its tail wait and its partial
+// wait (0: none).  Sums: prompt tokens of the requests of length >= L, `beyond` those of prompts longer than the table.
+template <class Sums>
+__device__ __forceinline__ void solve_column(const disco_solve_spec& sp, const Sums& sums, i64 n_req, int nbins, disco_policy& p,
+                                             disco_solve_out& o, i64& rank_tail_out, i64& rank_mid_out)
 {
-    __shared__ LenScratch lds;
-    const LenSums sums = len_sums(table, nbins, nslices, lds);
-    const int c = threadIdx.x;
-    if (c >= n) return;
-    const disco_solve_spec sp = specs.s[c];
+    rank_tail_out = 0; rank_mid_out = 0;
     const u64 total = sums(0);
-    disco_policy p;
     memset(&p, 0, sizeof(p));
     p.mode = sp.mode; p.l_th = -1; p.l_mid = -1; p.w_mid = 0.0f; p.beta = INFINITY; p.w_tail = INFINITY;
     p.mig_mode = sp.mig_mode;
-    disco_solve_out o;
     memset(&o, 0, sizeof(o));
     o.status = sums.beyond != 0ull ? 1 : 0;        // prompts longer than the table holds
     o.total_tokens = (i64)total;
-    SolveSlot tail{0, 0u, 0}, mid{0, 0u, 0};
     const u64 bn = (u64)sp.b_num, bd = (u64)sp.b_den, an = (u64)sp.a_num, ad = (u64)sp.a_den;
     if (sp.mode == DISCO_MODE_SERVER_CONSTRAINED) {
         // Eq. 3, discrete: the smallest L with (tokens of the prompts of length >= L) <= b x (all tokens)
@@ -85,7 +83,7 @@ __global__ __launch_bounds__(1024) void k_solve_plan(SolveSpecs specs, int n, i6
         i64 rank_tail = (i64)(((md - mn) * (u64)n_req + md - 1) / md);
         if (rank_tail > n_req) rank_tail = n_req;
         o.rank_tail = rank_tail;
-        tail.k_rem = rank_tail; tail.live = rank_tail > 0;
+        rank_tail_out = rank_tail > 0 ? rank_tail : 0;
         if (!b_le_a) {
             // Phase 2 in units of tokens / (a_den b_den): available = (b - alpha) total; a length costs (1 - alpha) mass
             const u128 avail = (u128)(bn * ad - an * bd) * (u128)total;
@@ -124,14 +122,24 @@ __global__ __launch_bounds__(1024) void k_solve_plan(SolveSpecs specs, int n, i6
                     if ((u128)(u64)m * den >= num) k1 = m; else k0 = m + 1;
                 }
                 o.rank_mid = k0;
-                mid.k_rem = k0; mid.live = k0 > 0;
+                rank_mid_out = k0 > 0 ? k0 : 0;
             }
         }
     }
-    S->slot[2 * c] = tail;
-    S->slot[2 * c + 1] = mid;
-    S->out[c] = o;
-    S->pol[c] = p;
+}
+
+// Step 2 (thread = column, once the workgroup has added up the table's blocks).
+__global__ __launch_bounds__(1024) void k_solve_plan(SolveSpecs specs, int n, i64 n_req, int nbins, int nslices,
+                                                     const u64* __restrict__ table, SolveState* S)
+{
+    __shared__ LenScratch lds;
+    const LenSums sums = len_sums(table, nbins, nslices, lds);
+    const int c = threadIdx.x;
+    if (c >= n) return;
+    i64 tail, mid;
+    solve_column(specs.s[c], sums, n_req, nbins, S->pol[c], S->out[c], tail, mid);
+    S->slot[2 * c] = SolveSlot{tail, 0u, tail > 0};
+    S->slot[2 * c + 1] = SolveSlot{mid, 0u, mid > 0};
 }
 
 // Step 3, histogram of one 8-bit digit.  Row r of the workgroup's LDS bins
@@ -231,6 +239,61 @@ __global__ __launch_bounds__(1024) void k_sq_select(int nslot, int nslices, cons
     }
 }
 
+// All steps in one launch for a small trace (disco_small.h), workgroup = column: the sums by length in LDS, the plan by
+// the first wave, then the server TTFTs in place of the sums and its two ranks among them.  12 columns: 21 us for 2000
+// requests and 35 for 32 000, where the twelve launches of the general solve take 75 - 80.
+union SolveLds { SmallLenLds len; RankLds rank; };
+
+__global__ __launch_bounds__(SM_BLOCK) void k_small_solve(TraceView tr, SolveSpecs specs, int nbins, disco_policy* __restrict__ pol_out,
+                                                          disco_solve_out* __restrict__ out)
+{
+    __shared__ SolveLds lds;
+    __shared__ disco_policy sp;
+    __shared__ disco_solve_out so;
+    __shared__ unsigned ranks[2], wmin[SM_WAVES], wmax[SM_WAVES];
+    const int c = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6, n = (int)tr.n_req;
+    const SmallLenSums sums = wg_len_sums(tr, nbins, lds.len);
+    if (wave == 0) {
+        disco_policy p;
+        disco_solve_out o;
+        i64 tail, mid;
+        solve_column(specs.s[c], sums, tr.n_req, nbins, p, o, tail, mid);
+        if (lane == 0) { sp = p; so = o; ranks[0] = (unsigned)tail; ranks[1] = (unsigned)mid; }
+    }
+    __syncthreads();
+    unsigned k[DISCO_MAX_Q] = {ranks[0], ranks[1], 0u, 0u}, prefix[DISCO_MAX_Q] = {0u, 0u, 0u, 0u};
+    const bool tail = k[0] != 0u, mid = k[1] != 0u;
+    if (tail || mid) {
+        unsigned lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll 1
+        for (int base = t; base < n; base += SM_BATCH * SM_BLOCK) {
+            unsigned key[SM_BATCH];
+#pragma unroll
+            for (int q = 0; q < SM_BATCH; ++q) key[q] = f2u(tr.s[base + q * SM_BLOCK < n ? base + q * SM_BLOCK : base]);
+#pragma unroll
+            for (int q = 0; q < SM_BATCH; ++q) {
+                if (base + q * SM_BLOCK < n) lds.rank.key[base + q * SM_BLOCK] = key[q];
+                lo = min(lo, key[q]); hi = max(hi, key[q]);
+            }
+        }
+        lo = wave_min_u32(lo); hi = wave_max_u32(hi);
+        if (lane == 0) { wmin[wave] = lo; wmax[wave] = hi; }
+        __syncthreads();
+        for (int w = 0; w < SM_WAVES; ++w) { lo = min(lo, wmin[w]); hi = max(hi, wmax[w]); }
+        for (int i = t; i < n; i += SM_BLOCK) lds.rank.key[i] -= lo;          // (this thread's own keys)
+        wg_select(lds.rank, n, hi > lo ? 32 - __clz(hi - lo) : 0, 2, k, prefix);
+        prefix[0] += lo; prefix[1] += lo;
+    }
+    if (t != 0) return;
+    disco_policy p = sp;
+    if (p.mode == DISCO_MODE_DEVICE_CONSTRAINED) {
+        p.w_tail = tail ? u2f(prefix[0]) : 0.0f;             // rank 0: F^-1(0) = 0
+        p.w_mid = mid ? u2f(prefix[1]) : 0.0f;
+    }
+    pol_out[c] = p;
+    if (out) out[c] = so;
+}
+
 // Step 4 (thread = column).
 __global__ void k_solve_final(int n, const SolveState* S, disco_policy* pol_out, disco_solve_out* out)
 {
@@ -256,10 +319,15 @@ void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n,
 {
     SolveState* S = (SolveState*)state;
     const int nbins = disco_search_table_max_bins();
-    const int nslices = disco_launch_len_table(v, nbins, scratch, scratch_bytes, table, stream);
     SolveSpecs t;
     memset(&t, 0, sizeof(t));
     memcpy(t.s, spec, sizeof(disco_solve_spec) * (size_t)n);
+    if (disco_small(v.n_req)) {
+        static_assert(SL_BINS >= 32772, "the table of the general solve");
+        hipLaunchKernelGGL(k_small_solve, dim3((unsigned)n), dim3(SM_BLOCK), 0, stream, v, t, nbins, pol_out, out);
+        return;
+    }
+    const int nslices = disco_launch_len_table(v, nbins, scratch, scratch_bytes, table, stream);
     hipLaunchKernelGGL(k_solve_plan, dim3(1), dim3(1024), 0, stream, t, n, v.n_req, nbins, nslices, table, S);
     const int nslot = 2 * n;
     i64 blocks = (v.n_req + SQ_BLOCK - 1) / SQ_BLOCK;

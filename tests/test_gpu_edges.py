@@ -287,3 +287,63 @@ def test_more_than_2_to_the_32_tokens(B, oracle, n_req, length):
     for i in (0, at - 1, at, at + 1, n_req - 1):
         same_bits(got.tok_arr[off[i]:off[i + 1]].cpu().numpy(), oracle.gen_tokens(gen, off, i, i + 1), f"tokens of request {i}")
     assert B.disco_validate_trace(got) == 0
+
+
+# traces of up to 32 768 requests: a workgroup per policy column takes the searches, solves, totals and TTFT order
+# statistics; the same calls with the grids shrunk go through the general kernels.  Keys of a few, of all and of no different
+# bits, a wave, a workgroup and a batch of eight strides more or less than full
+@pytest.mark.parametrize("n_req", [0, 1, 63, 1025, 8193, 20_011, 32_767, 32_768, 32_769])
+@pytest.mark.parametrize("table", ["threshold", "wait", "mixed", "ties"])
+def test_small_traces_against_the_general_kernels(B, n_req, table):
+    print(f"small traces: n_req={n_req} table={table}", flush=True)
+    tr = DI.handmade_trace(300 + n_req, n_req, tokens=False, ties=True)
+    if table == "ties":                                      # two values of the TTFT in all
+        tr["srv_ttft"][:] = np.where(np.arange(n_req) % 3, np.float32(0.5), np.float32(2.0))
+    if n_req > 2:
+        tr["prompt_len"][1], tr["prompt_len"][2] = 32_771, 40_000           # the last length of the table, one beyond it
+    dt = B.upload_trace(tr)
+    inf = float("inf")
+    pols = {"threshold": [B.Policy(mode=0, l_th=x) for x in (0, 1, 150, 150, 700, 32_771, 50_000)],
+            "wait": [B.Policy(mode=1, l_th=-1, w_tail=x) for x in (0.0, DI.f32(0.3), inf)] +
+                    [B.Policy(mode=1, l_th=90, l_mid=120, w_mid=DI.f32(0.2), beta=DI.f32(1e-3), w_tail=DI.f32(0.9))],
+            "ties": [B.Policy(mode=0, l_th=50_000), B.Policy(mode=0, l_th=0), B.Policy(mode=1, l_th=-1, w_tail=inf)],
+            "mixed": [B.Policy(mode=0, l_th=200), B.Policy(mode=1, l_th=-1, w_tail=DI.f32(0.4)),
+                      B.Policy(mode=2, beta=0.25, l_mid=3), B.Policy(mode=3, beta=0.5, l_mid=4)]}[table]
+    P = len(pols)
+    total = float(tr["prompt_len"].sum(dtype=np.int64))
+    quantiles = ((0, 100), (1, 1000), (50, 100), (100, 100))
+    ws = B.workspace(n_req, 64)
+
+    def run():
+        acc = torch.full((P * 128,), 0x5A, dtype=torch.uint8, device="cuda")
+        B.disco_eval_dispatch(dt, pols, ws=ws, acc=acc)
+        st = B.stats_to_host(B.disco_reduce_stats(dt, DI.COST_S, pols, acc, quantiles, ws=ws), P).copy()
+        out = [B.accum_to_host(acc, P).copy(), st]
+        for which in ("server_prefill_tok", "device_prefill_tok"):
+            fr = (0.0, 0.13, 0.5, 0.77, 1.0)
+            specs = [dict(which_param=B.PARAM_L_TH, which_acc=which, n_steps=17, lo=j, hi=32_770, target=f * total) for j, f in enumerate(fr)]
+            found = torch.full((len(fr) * 128,), 0x5A, dtype=torch.uint8, device="cuda")
+            r = B.disco_budget_search(dt, DI.COST_S, [B.Policy(mode=0, mig_mode=j % 3) for j in range(len(fr))], specs, ws=ws, acc=found)
+            out += [B.search_to_host(r["out"], len(fr)).copy(), r["pol_out"].cpu().numpy(), B.accum_to_host(found, len(fr)).copy()]
+        solve = [dict(mode=m, b=(b, 20), alpha=(1, 10), mig_mode=b % 3) for m in (0, 1) for b in (0, 1, 2, 7, 20)]
+        r = B.disco_solve_policy(dt, solve, ws=ws)
+        return out + [B.solve_to_host(r["out"], len(solve)).copy(), r["pol_out"].cpu().numpy()]
+
+    def same(a, b, what):
+        if a.dtype.names is None:
+            if a.dtype == np.float64 and what in ("ttft_sum", "mean_ttft"):
+                assert np.allclose(a, b, rtol=1e-12, atol=0, equal_nan=True), what       # fp64 sums in another order
+            else:
+                same_bits(a, b, what)
+        else:
+            for f in a.dtype.names:
+                same(np.ascontiguousarray(a[f]), np.ascontiguousarray(b[f]), f)
+
+    small = run()
+    try:
+        assert B._lib.disco_set_grid_divisor(2) == 0
+        general = run()
+    finally:
+        assert B._lib.disco_set_grid_divisor(1) == 0
+    for i, (a, b) in enumerate(zip(small, general)):
+        same(a, b, f"result {i}")
