@@ -31,6 +31,7 @@ __host__ __device__ inline MigPartial* tl_totals(u64* totals)
 struct SelInit {
     SelState* S; int nq; disco_quantile q[4]; const disco_accum* acc; i64 n_req; int with_tbt;
     unsigned *ppcnt, *dhist;       // counts of the TBT selection, cleared in the launch that starts it
+    unsigned* ghist;               // ... and its bins (nullable)
 };
 constexpr int STAGE_CLEAR = 61;    // workgroups that clear them
 
@@ -93,9 +94,10 @@ __device__ void select_init(const SelInit& si, int which, int P, const disco_pol
             g.plan.npass = 0; g.plan.pad = 0;
             for (int i = 0; i < DISCO_MAX_PASS; ++i) { g.plan.shift[i] = 0; g.plan.width[i] = 0; }
             TlSel& tl = S->tl;
-            tl.ncls = 0; tl.nwalk = 0; tl.walk_mask = 0ull; tl.fallback = 0; tl.error = 0; tl.left = 31; tl.shift = 0; tl.width = 0; tl.G = 0;
-            tl.key_lo = 0u; tl.window = 0; tl.restart = 0;
-            for (int i = 0; i < DISCO_MAX_GRP; ++i) tl.grp_prefix[i] = 0u;
+            tl.ncls = 0; tl.nwalk = 0; tl.walk_mask = 0ull; tl.error = 0; tl.nlist = 0u; tl.nlist_back = 0u;
+            TlPlan& start = tl.plan[0];
+            start.left = 31; start.shift = 0; start.width = 0; start.G = 0; start.window = 0; start.key_lo = 0u; start.fallback = 0; start.reset = 0;
+            for (int i = 0; i < DISCO_TBT_MAX_PASS; ++i) tl.restart[i] = 0;
         }
         S->g[which] = g;
     }
@@ -103,7 +105,6 @@ __device__ void select_init(const SelInit& si, int which, int P, const disco_pol
         for (int i = threadIdx.x; i < DISCO_MAX_CLS; i += blockDim.x) S->tl.cls_mask[i] = 0ull;
         for (int i = threadIdx.x; i < DISCO_CLS_SLOTS; i += blockDim.x) { S->tl.gslot[i] = 0ull; S->tl.gwalk[i] = 0u; }
         if (threadIdx.x == 0) S->tl.goverflow = 0;
-        for (int i = threadIdx.x; i < DISCO_MAX_SLOTS; i += blockDim.x) S->tl.slot_grp[i] = -1;
     }
     for (int s = threadIdx.x; s < P * nq; s += blockDim.x) {
         int c = s / nq, qi = s % nq;
@@ -140,6 +141,8 @@ __device__ __forceinline__ void stage_table(const disco_policy* src, int P, disc
         const int first = ((int)blockIdx.x - 3) * STAGE_THREADS + (int)threadIdx.x, step = ((int)gridDim.x - 3) * STAGE_THREADS;
         for (int w = first; w < DISCO_MAX_CLS * (DISCO_PP_NMAX + 1); w += step) si.ppcnt[w] = 0u;
         for (int w = first; w < P * DISCO_DELAY_BINS; w += step) si.dhist[w] = 0u;
+        if (si.ghist)
+            for (int w = first; w < DISCO_GHIST_WORDS / 4; w += step) reinterpret_cast<uint4*>(si.ghist)[w] = make_uint4(0u, 0u, 0u, 0u);
         return;
     }
     if (blockIdx.x > 0) {
@@ -237,7 +240,10 @@ __global__ __launch_bounds__(256) void k_stats_final(int nq, i64 n_req, disco_co
             if (with_tl) {
                 const SelSlot s1 = S->slot[1][c * nq + qi];
                 st.tbt_rank[qi] = s1.rank;
-                if (s1.M > 0 && !S->tl.error && S->tl.left == 0) bq = u2f(s1.prefix + S->tl.key_lo);
+                // (all digits decided: after the last pass, or by the one before it)
+                const TlPlan& last = S->tl.plan[DISCO_TBT_MAX_PASS];
+                const bool whole = last.left == last.width && !(last.window != 0 && S->tl.restart[DISCO_TBT_MAX_PASS - 1] != 0);
+                if (s1.M > 0 && !S->tl.error && whole) bq = u2f(s1.prefix + last.key_lo);
             }
             i64 k = ((i64)q.num * migrated + q.den - 1) / q.den;
             if (k < 1) k = 1;
@@ -738,6 +744,7 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
     for (int i = 0; i < 4; ++i) si.q[i] = qs[i];
     si.with_tbt = tl != nullptr;
     si.ppcnt = (unsigned*)(ws + L.ppcnt); si.dhist = (unsigned*)(ws + L.dhist);
+    si.ghist = disco_small(v.n_req) ? gh : nullptr;        // (the general TTFT passes use the bins in between)
     rc = stage_policies(pol, P, ws, L, stream, nq > 0 ? &si : nullptr);        // with the start of the TTFT selection
     if (rc) return rc;
     if (nq > 0) {
@@ -772,15 +779,18 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
                 disco_launch_tl_walk(v, trace->n_tok, dpol, P, a.tau, a.kt, a.wflags, a.summary, a.counter, stream);
                 disco_launch_tl_stats_buf(v, trace->n_tok, dpol, a, nullptr, stream);      // summaries only
             }
-            disco_launch_tl_classify(v, dpol, P, nq, tl->tau, a.summary, a.bufsum, a.bc, S,
-                                     (unsigned*)(ws + L.ticket), stream);
+            disco_launch_tl_classify(v, dpol, P, a.summary, a.bufsum, a.bc, S, stream);
             a.desc = (u64*)(ws + disco_ws_desc_offset(L, v.n_req));
             a.list = (unsigned*)(a.desc + v.n_req);
-            disco_launch_tl_assign(v, dpol, P, a.summary, S, a.bufsum, a.desc, a.list, (unsigned*)(ws + L.slices),
-                                   L.total - L.slices, a.ppcnt, gh, a.dhist, stream);
-            disco_launch_pp_suffix(S, a.ppcnt, stream);
+            unsigned* slices = (unsigned*)(ws + L.slices);
+            disco_launch_tl_assign(v, dpol, P, tl->tau, a.summary, S, a.bufsum, a.desc, a.list, slices, L.total - L.slices, a.ppcnt, gh,
+                                   a.dhist, stream);
             for (int pass = 0; pass < DISCO_TBT_MAX_PASS; ++pass) {
+                // the passes take turns with two sets of bins: one is counted into while the other one is cleared (the
+                // slices of the assignment have been added up by then)
                 a.pass = pass;
+                a.ghist = pass & 1 ? slices : gh;
+                a.gclear = pass & 1 ? gh : slices;
                 if (pass < DISCO_TBT_REGULAR_PASS) disco_launch_tl_hist_fast(v, trace->n_tok, dpol, a, stream);
                 disco_launch_tbt_pass(v, trace->n_tok, dpol, a, stream);
             }

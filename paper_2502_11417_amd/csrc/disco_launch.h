@@ -11,7 +11,9 @@ struct TimelineArgs {
     int P, nq, pass;          // -1: statistics pass, >= 0: TBT histogram pass
     int32_t* mig_idx; int32_t* n_src_tok; float* t_last; float* delivered; int delivered_col;
     MigPartial* part; unsigned* ticket; disco_accum* acc;
-    SelState* S; unsigned* ghist;
+    SelState* S;
+    unsigned* ghist;          // device-wide bins of the pass
+    unsigned* gclear;         // histogram passes: those of the next one, cleared in the meantime
     unsigned* ppcnt;          // pure-pacing timelines per class and length (histogram passes)
     int32_t* delay_num;       // materialised delayed-token counts (buffer hand-off), nullable
     BufCostArgs bc;           // prices of the buffer hand-off's cost test
@@ -107,8 +109,7 @@ void disco_launch_ttft_pass(const TraceView& v, const disco_policy* pol, int P, 
 void disco_launch_dispatch_mat(const TraceView& v, const disco_policy* pol, int P, uint8_t* decision, float* ttft,
                                hipStream_t stream);
 // Token timelines.  Statistics pass (a.pass = -1): streaming kernel, or the general kernel when the
-// per-token deliveries of a column are wanted.  TBT selection: classification, assignment and the "longer than"
-// counts of the analytic timelines once; then per regular pass (a.pass < DISCO_TBT_REGULAR_PASS) the walk of the
+// per-token deliveries of a column are wanted.  TBT selection: classification and assignment once; then per regular pass (a.pass < DISCO_TBT_REGULAR_PASS) the walk of the
 // streaming kinds (disco_launch_tl_hist_fast) followed by disco_launch_tbt_pass (the other histogram work of the
 // pass, the digits, the plan of the next pass); a spare pass is disco_launch_tbt_pass alone, one launch that
 // normally returns at once.
@@ -121,12 +122,11 @@ void disco_launch_tl_walk(const TraceView& v, i64 n_tok, const disco_policy* pol
                           hipEvent_t before = nullptr, hipEvent_t after = nullptr);
 void disco_launch_timeline_general(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                    hipStream_t stream);
-void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, int nq, float tau, const void* summary,
-                              const void* bufsum, const BufCostArgs& bc, SelState* S, unsigned* ticket, hipStream_t stream);
+void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, const void* summary, const void* bufsum,
+                              const BufCostArgs& bc, SelState* S, hipStream_t stream);
 void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                hipStream_t stream);
-void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, const void* summary, SelState* S,
+void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, float tau, const void* summary, SelState* S,
                             const void* bufsum, u64* desc, unsigned* list, unsigned* slices, size_t slices_bytes,
                             unsigned* ppcnt, unsigned* ghist, unsigned* dhist, hipStream_t stream);
-void disco_launch_pp_suffix(SelState* S, unsigned* ppcnt, hipStream_t stream);
 void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a, hipStream_t stream);

@@ -104,31 +104,38 @@ enum { DISCO_MAX_CLS = 64, DISCO_CLS_SLOTS = 256, DISCO_MAX_GRP = 4, DISCO_TBT_M
        DISCO_GHIST_WORDS = 262144,    // device-wide bins (1 MB)
        DISCO_PP_NMAX = 4096,          // pure-pacing timelines up to this length are histogrammed analytically
        DISCO_DELAY_BINS = 8192 };     // counts of delayed tokens per migrated request, per column (last bin: that or more)
+// Digit of one pass of the TBT selection.  It follows from the plan of the pass before, that pass's digits (the slots) and
+// whether it missed the window: every workgroup of the launch that opens a pass works it out by itself (tbt_plan), the first
+// one leaves it here for the pass's other launches and for the next plan.
+struct TlPlan {
+    int left;                      // undecided key bits
+    int shift, width;              // digit of the pass (width 0: finished)
+    int G;                         // distinct prefixes among the live slots
+    // Window mode: keys are offsets from key_lo, clamped to 2^window ("outside", never counted).  Gaps sit just
+    // above the pacing interval, so a 21-bit window above it holds the usual order statistics and two passes
+    // decide them; a rank that falls outside (or into the clamped bottom bin) restarts the selection on raw keys.
+    int window;                    // key bits of the window, 0 = raw 31-bit keys
+    unsigned key_lo;
+    int fallback;                  // 1: one histogram per (column, quantile) slot instead of per class
+    int reset;                     // the slots start over with this pass (empty prefix, full rank)
+    unsigned grp_prefix[DISCO_MAX_GRP];
+    signed char slot_grp[DISCO_MAX_SLOTS];       // prefix group of each live slot, -1 otherwise
+};
 struct TlSel {
     u64 cls_mask[DISCO_MAX_CLS];   // column set of each class, 0 = free
     u64 walk_mask;                 // classes with a timeline whose tokens have to be walked
     int ncls, nwalk;
-    int fallback;                  // 1: one histogram per (column, quantile) slot instead of per class
     int error;                     // a column set could not be placed (never expected)
-    int left;                      // undecided key bits
-    int shift, width;              // digit of the pass about to run (width 0: finished)
-    int G;                         // distinct prefixes among the live slots
-    unsigned grp_prefix[DISCO_MAX_GRP];
-    int slot_grp[DISCO_MAX_SLOTS]; // prefix group of each live slot, -1 otherwise
-    // Window mode: keys are offsets from key_lo, clamped to 2^window ("outside", never counted).  Gaps sit just
-    // above the pacing interval, so a 21-bit window above it holds the usual order statistics and two passes
-    // decide them; a rank that falls outside (or into the clamped bottom bin) restarts the selection on raw keys.
-    unsigned key_lo;
-    int window;                    // key bits of the window, 0 = raw 31-bit keys
-    int restart;
     unsigned nlist;                // requests with a timeline whose tokens are walked: entries at the front of the walk list
     unsigned nlist_back;           // ... and entries at its back (the short requests, see walk_list_entry)
-    unsigned pad2;
-    // device-wide hash table of the column sets (classification): every workgroup enters its distinct sets, the last
-    // one numbers them; zeroed when a selection starts
+    int pad;
+    TlPlan plan[DISCO_TBT_MAX_PASS + 1];         // [0]: where the selection starts; [1 + p]: pass p
+    int restart[DISCO_TBT_MAX_PASS];             // pass p missed the window
+    // device-wide hash table of the column sets (classification): every workgroup enters its distinct sets, those of
+    // the assignment number them; zeroed when a selection starts
     u64 gslot[DISCO_CLS_SLOTS];
     unsigned gwalk[DISCO_CLS_SLOTS];
-    int goverflow;
+    int goverflow;                 // bit 0: more sets than the table holds, bit 1: summaries found at other prices
     int pad3;
     signed char cls_slot[DISCO_MAX_CLS];     // row of a walked class in the workgroups' LDS histogram, -1 otherwise
     unsigned char slot_cls[DISCO_MAX_CLS];   // class of an LDS row

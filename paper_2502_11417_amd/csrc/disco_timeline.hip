@@ -13,7 +13,7 @@ __global__ __launch_bounds__(TL_BLOCK) void k_timeline(TraceView tr, i64 n_tok, 
 {
     __shared__ __align__(16) unsigned smem[DISCO_TL_HIST_WORDS];
     __shared__ TimelineLds lds;
-    timeline_body<false>(smem, lds, tr, n_tok, align, pol, a, blockIdx.x, gridDim.x);
+    timeline_body<false>(smem, lds, tr, n_tok, align, pol, a, nullptr, blockIdx.x, gridDim.x);
 }
 
 }  // namespace

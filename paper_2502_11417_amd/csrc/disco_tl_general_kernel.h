@@ -88,11 +88,11 @@ struct TimelineLds {
 
 // Workgroup `bid` of `nblk` (the statistics pass, a.pass < 0, takes the last-ticket test over the whole grid:
 // it must be called by every workgroup of the launch, bid = blockIdx.x; HIST_ONLY leaves that pass out of the
-// code).  `smem`: DISCO_TL_HIST_WORDS words of LDS.
+// code).  `smem`: DISCO_TL_HIST_WORDS words of LDS; pl: plan of a histogram pass.
 template <bool HIST_ONLY>
 __device__ __forceinline__ void timeline_body(unsigned* smem, TimelineLds& lds, const TraceView& tr, i64 n_tok, int align,
-                                              const disco_policy* __restrict__ pol, const TimelineArgs& a, unsigned bid,
-                                              unsigned nblk)
+                                              const disco_policy* __restrict__ pol, const TimelineArgs& a, const TlPlan* pl,
+                                              unsigned bid, unsigned nblk)
 {
     unsigned* sprefix = lds.sprefix;
     int* slive = lds.slive;
@@ -105,17 +105,16 @@ __device__ __forceinline__ void timeline_body(unsigned* smem, TimelineLds& lds, 
     h.hist = smem; h.shift = 0; h.width = 0; h.up = 0; h.nq = nq; h.key_lo = 0u; h.key_cap = 0xFFFFFFFFu;
     h.sprefix = sprefix; h.slive = slive;
     if (hist_pass) {
-        const TlSel* tl = &a.S->tl;
-        h.width = tl->width;
-        if (h.width <= 0 || !tl->fallback) return;     // selection finished, or class histograms (other kernel)
-        h.shift = tl->shift;
+        h.width = pl->width;
+        if (h.width <= 0 || !pl->fallback) return;     // selection finished, or class histograms (other kernel)
+        h.shift = pl->shift;
         h.up = h.shift + h.width;
-        h.key_lo = tl->key_lo; h.key_cap = tl->window ? (1u << tl->window) : 0xFFFFFFFFu;
+        h.key_lo = pl->key_lo; h.key_cap = pl->window ? (1u << pl->window) : 0xFFFFFFFFu;
         const int words = (P * nq) << h.width;
         for (int i = threadIdx.x; i < words; i += TL_BLOCK) smem[i] = 0u;
         for (int i = threadIdx.x; i < P * nq; i += TL_BLOCK) {
             const SelSlot sl = a.S->slot[1][i];
-            sprefix[i] = sl.prefix;
+            sprefix[i] = pl->reset ? 0u : sl.prefix;
             slive[i] = !sl.done;
         }
     }

@@ -105,20 +105,15 @@ __device__ __forceinline__ void walk_hist_known(bool src_dev, int n, const float
 // Workgroup `bid` of `nblk`: bytes 3 and 4 of a request's descriptor name the LDS rows of its two hand-off kinds,
 // the walk list of the selection names the requests.  `smem`: DISCO_TL_HIST_WORDS words of LDS.
 __device__ __forceinline__ void tl_hist_buf_body(unsigned* smem, const TraceView& tr, i64 n_tok, int align, const BufHistArgs& ba,
-                                                 unsigned bid, unsigned nblk)
+                                                 const TlPlan& pl, unsigned bid, unsigned nblk)
 {
     const HistArgs& a = ba.h;
     const TlSel* tl = &a.S->tl;
-    const int width = tl->width;
-    if (*ba.buffer_flag == 0u || width <= 0 || tl->fallback) return;
+    const int width = __builtin_amdgcn_readfirstlane(pl.width);
+    if (*ba.buffer_flag == 0u || width <= 0 || pl.fallback) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ncls = tl->ncls, nwalk = tl->nwalk;
-    HistCtx h;
-    h.hist = smem; h.width = width; h.shift = tl->shift; h.up = h.shift + width;
-    h.G = tl->G < DISCO_MAX_GRP ? tl->G : DISCO_MAX_GRP;
-    h.stride = (unsigned)nwalk << width;
-    h.key_lo = tl->key_lo; h.key_cap = tl->window ? (1u << tl->window) : 0xFFFFFFFFu;
-    for (int k = 0; k < DISCO_MAX_GRP; ++k) h.grp_prefix[k] = tl->grp_prefix[k];
+    const HistCtx h = hist_ctx(smem, pl, nwalk);
     const int words = (h.G * nwalk) << width;
     for (int i = threadIdx.x; i < words; i += TBH_BLOCK) smem[i] = 0u;
     __syncthreads();

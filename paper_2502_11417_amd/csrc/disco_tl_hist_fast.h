@@ -9,6 +9,102 @@ namespace {
 
 constexpr int TH_BLOCK = 1024;               // histogram workgroups: 16 waves share 64 KB of bins
 
+// ------------------------------------------------------------------ plan ---
+
+// Bin counts of a slot that k_tbt_select sums up in registers (two per thread, the rows of eight classes in flight).  Tables
+// without walked timelines (constant gaps) have room for digits of 13 and 14 bits, but their 21-bit window takes two
+// passes either way, and an unstaged slot of 8192 bins reads the rows of its classes bin by bin: 10^4 requests x 16 columns
+// 120 us with 13 bits, 28 us with 11.
+constexpr int SEL_DIRECT_BITS = 11;
+
+// The plan of a pass (first wave of a workgroup; `out` in LDS): prefix groups of the live slots, digit width that fits, or
+// the per-slot fallback.  Every workgroup of the launch that opens a pass does this, some 2 us beside its other start-up; the
+// last workgroup of the pass before did it behind a ticket, with the bins still to clear: 10 us of an 18 us launch.
+__device__ __forceinline__ void tbt_plan(const SelState* S, int pass, int P, int nq, TlPlan& out)
+{
+    static_assert(DISCO_MAX_SLOTS == 128, "two slots per lane");
+    const TlSel& tl = S->tl;
+    const TlPlan& prev = tl.plan[pass];
+    const int lane = threadIdx.x & 63, ns = P * nq;
+    const int ncls = tl.ncls, nwalk = tl.nwalk;
+    unsigned p0 = 0u, p1 = 0u;
+    bool live0 = false, live1 = false;
+    if (lane < ns) { p0 = S->slot[1][lane].prefix; live0 = !S->slot[1][lane].done; }
+    if (64 + lane < ns) { p1 = S->slot[1][64 + lane].prefix; live1 = !S->slot[1][64 + lane].done; }
+    int left = prev.left, window = prev.window, reset = 0;
+    unsigned key_lo = prev.key_lo;
+    bool done = false;
+    if (pass > 0) {
+        done = prev.width <= 0;
+        if (!done && window != 0 && tl.restart[pass - 1] != 0) {       // the window missed a rank: all slots start over on raw keys
+            window = 0; key_lo = 0u; left = 31; reset = 1;
+            p0 = p1 = 0u;
+        } else if (!done) {
+            left -= prev.width;
+            done = left == 0;
+        }
+    }
+    // the distinct prefixes in slot order, one after the other; a lane holds slots `lane` and 64 + `lane`
+    u64 todo0 = __ballot(live0), todo1 = __ballot(live1);
+    int G = 0, g0 = -1, g1 = -1;
+    unsigned grp[DISCO_MAX_GRP] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int k = 0; k < DISCO_MAX_GRP; ++k) {
+        if ((todo0 | todo1) == 0ull) break;
+        const unsigned px = todo0 ? (unsigned)bcast_i((int)p0, __ffsll((long long)todo0) - 1) : (unsigned)bcast_i((int)p1, __ffsll((long long)todo1) - 1);
+        const bool h0 = live0 && p0 == px, h1 = live1 && p1 == px;
+        if (h0) g0 = k;
+        if (h1) g1 = k;
+        todo0 &= ~__ballot(h0); todo1 &= ~__ballot(h1);
+        grp[k] = px;
+        G = k + 1;
+    }
+    int fallback = prev.fallback;
+    if ((todo0 | todo1) != 0ull) {             // too many distinct prefixes: the per-slot fallback does not use groups
+        fallback = 1;
+        G += 1;
+        if (live0 && g0 < 0) g0 = 0;
+        if (live1 && g1 < 0) g1 = 0;
+    }
+    if (ncls > DISCO_MAX_CLS || ncls < 1) fallback = 1;
+    int w;
+    if (fallback) {
+        w = fit_width(ns, DISCO_TL_HIST_WORDS);
+    } else {
+        const int gn = G > 0 ? G : 1;
+        w = fit_width((long)gn * (nwalk > 0 ? nwalk : 1), DISCO_TL_HIST_WORDS);
+        const int wg = fit_width((long)gn * ncls, DISCO_GHIST_WORDS);
+        if (wg < w) w = wg;
+        // a digit of more bins than the select step sums up in registers only where it saves a pass.  Not on raw keys with
+        // timelines to walk: there may be more than four prefixes in the end, and then every bit less here can cost another
+        // walk of everything (30 000 requests x 5 columns 1.15 ms of order statistics with 12 + 10 + 9 bits, 1.61 with
+        // 11 + 10 + 9 + 1)
+        if (w > SEL_DIRECT_BITS && (window != 0 || nwalk == 0) && (left + w - 1) / w == (left + SEL_DIRECT_BITS - 1) / SEL_DIRECT_BITS)
+            w = SEL_DIRECT_BITS;
+    }
+    if (w < 1) w = 1;
+    if (w > left) w = left;
+    if (G == 0 || done) w = 0;                 // nothing left to select
+    if (lane == 0) {
+        out.left = left; out.shift = left - w; out.width = w; out.G = G; out.window = window; out.key_lo = key_lo;
+        out.fallback = fallback; out.reset = reset;
+#pragma unroll
+        for (int k = 0; k < DISCO_MAX_GRP; ++k) out.grp_prefix[k] = grp[k];
+    }
+    out.slot_grp[lane] = (signed char)g0;
+    out.slot_grp[64 + lane] = (signed char)g1;
+}
+
+// All threads of a workgroup of the launch that opens the pass; the first workgroup leaves the plan to the others.
+__device__ __forceinline__ void tbt_open_pass(SelState* S, int pass, int P, int nq, TlPlan& plan)
+{
+    if (threadIdx.x < 64) tbt_plan(S, pass, P, nq, plan);
+    __syncthreads();
+    static_assert(sizeof(TlPlan) % 4 == 0, "copied in words");
+    if (blockIdx.x == 0 && threadIdx.x < sizeof(TlPlan) / 4)
+        reinterpret_cast<unsigned*>(&S->tl.plan[pass + 1])[threadIdx.x] = reinterpret_cast<const unsigned*>(&plan)[threadIdx.x];
+}
+
 struct WalkOut { int m; float M; };          // hand-off index (-1 none), running maximum over all tokens
 
 // Histogram walk of one request and source: the delivery of every token and
@@ -154,19 +250,14 @@ constexpr unsigned DESC_NONE = 0xFFFFFFu;
 // timelines have tokens to walk (few: the others were counted analytically once) and the walk list names their
 // requests.  `smem`: DISCO_TL_HIST_WORDS words of LDS.
 __device__ __forceinline__ void tl_hist_fast_body(unsigned* smem, const TraceView& tr, i64 n_tok, int align, const HistArgs& a,
-                                                  unsigned bid, unsigned nblk)
+                                                  const TlPlan& pl, unsigned bid, unsigned nblk)
 {
     const TlSel* tl = &a.S->tl;
-    const int width = tl->width;
-    if (width <= 0 || tl->fallback) return;       // selection finished, or per-slot histograms (other kernel)
+    const int width = __builtin_amdgcn_readfirstlane(pl.width);
+    if (width <= 0 || pl.fallback) return;        // selection finished, or per-slot histograms (other kernel)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ncls = tl->ncls, nwalk = tl->nwalk;
-    HistCtx h;
-    h.hist = smem; h.width = width; h.shift = tl->shift; h.up = h.shift + width;
-    h.G = tl->G < DISCO_MAX_GRP ? tl->G : DISCO_MAX_GRP;
-    h.stride = (unsigned)nwalk << width;
-    h.key_lo = tl->key_lo; h.key_cap = tl->window ? (1u << tl->window) : 0xFFFFFFFFu;
-    for (int k = 0; k < DISCO_MAX_GRP; ++k) h.grp_prefix[k] = tl->grp_prefix[k];
+    const HistCtx h = hist_ctx(smem, pl, nwalk);
     const int words = (h.G * nwalk) << width;
     for (int i = threadIdx.x; i < words; i += TH_BLOCK) smem[i] = 0u;
     __syncthreads();

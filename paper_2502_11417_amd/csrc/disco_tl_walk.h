@@ -159,7 +159,7 @@ inline int tl_batch(i64 n_req, i64 waves)
 
 struct HistArgs {
     float tau, kt;
-    int P, pass;
+    int P, nq, pass;
     SelState* S;
     unsigned* ghist;
     const u64* desc;               // per request: LDS rows of its timelines that have tokens to walk (one byte per kind)
@@ -174,6 +174,22 @@ struct HistCtx {
     unsigned stride;               // words per prefix group = nwalk << width
     unsigned grp_prefix[DISCO_MAX_GRP];
 };
+
+// From a plan in LDS or device memory into scalar registers (read as they are from LDS, its fields took vector registers the
+// walk needs: a pass over 17 M tokens 74 us instead of 60).
+__device__ __forceinline__ HistCtx hist_ctx(unsigned* hist, const TlPlan& pl, int nwalk)
+{
+    auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    HistCtx h;
+    h.hist = hist; h.width = uni(pl.width); h.shift = uni(pl.shift); h.up = h.shift + h.width;
+    const int G = uni(pl.G), window = uni(pl.window);
+    h.G = G < DISCO_MAX_GRP ? G : DISCO_MAX_GRP;
+    h.stride = (unsigned)nwalk << h.width;
+    h.key_lo = (unsigned)uni((int)pl.key_lo); h.key_cap = window ? (1u << window) : 0xFFFFFFFFu;
+#pragma unroll
+    for (int k = 0; k < DISCO_MAX_GRP; ++k) h.grp_prefix[k] = (unsigned)uni((int)pl.grp_prefix[k]);
+    return h;
+}
 
 // The walk list of the TBT selection: requests with 3 or more 256-token chunks are entered from the front, the
 // others from the back of an array of `cap` slots.  The histogram kernels deal entry v to wave v mod W, so the long

@@ -44,7 +44,67 @@ constexpr int PP_WORDS = DISCO_PP_NMAX / 2 + 1;              // words per class:
 constexpr int AS_BLOCK = 1024;
 constexpr int DH_LDS_BINS = 64;              // delayed-token counts below this are counted in LDS: [column][count], 16 KB
 
-__global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disco_policy* __restrict__ pol, int P,
+// The classes from the device-wide table of column sets, in ascending order (so that their numbers do not depend on
+// timing), and the rows of those with tokens to walk in the workgroups' LDS histograms, in class order.
+struct ClassList {
+    u64 mask[DISCO_MAX_CLS];                   // 0: none
+    u64 found[DISCO_MAX_CLS];
+    unsigned char walk[DISCO_MAX_CLS], found_walk[DISCO_MAX_CLS];
+    signed char slot[DISCO_MAX_CLS];           // LDS row of a walked class, -1 otherwise
+    unsigned cnt[DISCO_CLS_SLOTS / 64];
+    int total;
+};
+
+// All threads.
+__device__ __forceinline__ void list_classes(const TlSel& tl, ClassList& L)
+{
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    u64 v = 0ull;
+    unsigned w = 0u;
+    if (t < DISCO_CLS_SLOTS) { v = tl.gslot[t]; w = tl.gwalk[t]; }
+    const u64 occ = __ballot(v != 0ull);
+    if (t < DISCO_CLS_SLOTS && lane == 0) L.cnt[wave] = (unsigned)__popcll(occ);
+    if (t < DISCO_MAX_CLS) { L.mask[t] = 0ull; L.walk[t] = 0; }
+    __syncthreads();
+    int before = 0, total = 0;
+    for (int k = 0; k < DISCO_CLS_SLOTS / 64; ++k) { const int c = (int)L.cnt[k]; before += k < wave ? c : 0; total += c; }
+    if (v != 0ull) {
+        const int at = before + __popcll(occ & ((1ull << lane) - 1ull));
+        if (at < DISCO_MAX_CLS) { L.found[at] = v; L.found_walk[at] = w != 0u; }
+    }
+    if (t == 0) L.total = total;
+    __syncthreads();
+    const int n = total < DISCO_MAX_CLS ? total : DISCO_MAX_CLS;
+    if (t < n) {
+        const u64 mine = L.found[t];
+        int rank = 0;
+#pragma unroll 8
+        for (int k = 0; k < n; ++k) rank += L.found[k] < mine ? 1 : 0;
+        L.mask[rank] = mine; L.walk[rank] = L.found_walk[t];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const u64 wm = __ballot(L.walk[lane] != 0);
+        L.slot[lane] = L.walk[lane] ? (signed char)__popcll(wm & ((1ull << lane) - 1ull)) : (signed char)-1;
+    }
+    __syncthreads();
+}
+
+// The counter `idx` (-1: none) of every lane plus one; the one of the first lane that has any is added to once for all
+// lanes that share it (requests of one length).
+__device__ __forceinline__ void count_shared(unsigned* __restrict__ counters, int idx, int lane)
+{
+    const u64 any = __ballot(idx >= 0);
+    if (!any) return;
+    const int leader = __ffsll((long long)any) - 1;
+    const int i0 = bcast_i(idx, leader);
+    const u64 same = __ballot(idx == i0);
+    if (lane == leader) atomicAdd(&counters[i0], (unsigned)__popcll(same));
+    if (idx >= 0 && idx != i0) atomicAdd(&counters[idx], 1u);
+}
+
+// use_lds = 0: counts in device memory (small traces: a slice per workgroup and their sum cost more than the few atomics).
+__global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disco_policy* __restrict__ pol, int P, float tau,
                                                         const TlSummary* __restrict__ summary,
                                                         const BufSummary* __restrict__ bufsum, SelState* S,
                                                         u64* __restrict__ desc_out, unsigned* __restrict__ list,
@@ -54,15 +114,33 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
     __shared__ __align__(16) unsigned cnt[PP_LDS_CLS * PP_WORDS];          // 128 KB
     __shared__ unsigned dh[DISCO_MAX_COLS * DH_LDS_BINS];
     __shared__ unsigned s_nw[2], s_base[2];                  // [0] long requests (front of the list), [1] the others (back)
-    __shared__ u64 s_cls[DISCO_MAX_CLS];
-    __shared__ signed char s_slot[DISCO_MAX_CLS];
+    __shared__ ClassList cl;
     __shared__ disco_policy spol[DISCO_MAX_COLS];
-    const TlSel* tl = &S->tl;
-    if (tl->fallback) return;                                // per-slot histograms: the general kernel walks everything
-    const int ncls = tl->ncls;
-    const int nlds = use_lds ? (ncls < PP_LDS_CLS ? ncls : PP_LDS_CLS) : 0;
     if ((int)threadIdx.x < P) spol[threadIdx.x] = pol[threadIdx.x];
-    if (threadIdx.x < DISCO_MAX_CLS) { s_cls[threadIdx.x] = tl->cls_mask[threadIdx.x]; s_slot[threadIdx.x] = tl->cls_slot[threadIdx.x]; }
+    list_classes(S->tl, cl);
+    const int over = S->tl.goverflow;                        // bit 0: too many sets, bit 1: summaries found at other prices
+    const bool fallback = cl.total > DISCO_MAX_CLS || over != 0;
+    const int ncls = fallback ? DISCO_MAX_CLS : (cl.total > 0 ? cl.total : 1);
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        // for the passes; gaps sit just above the pacing interval (down to a few thousand ulps below it after rounding): a
+        // 21-bit window of keys is tried first (not at other prices: the passes of 128 slots would not suffice for a second start)
+        const int lane = threadIdx.x;
+        TlSel& g = S->tl;
+        const u64 wm = __ballot(cl.walk[lane] != 0);
+        g.cls_mask[lane] = cl.mask[lane];
+        g.cls_slot[lane] = cl.slot[lane];
+        if (cl.walk[lane]) g.slot_cls[cl.slot[lane]] = (unsigned char)lane;
+        if (lane == 0) {
+            const unsigned tb = f2u(tau);
+            const bool window = tb >= 8192u && (over & 2) == 0;
+            g.ncls = ncls; g.walk_mask = wm; g.nwalk = __popcll(wm);
+            TlPlan& start = g.plan[0];
+            start.window = window ? 21 : 0; start.left = window ? 21 : 31; start.key_lo = window ? tb - 8192u : 0u;
+            start.fallback = fallback ? 1 : 0;
+        }
+    }
+    if (fallback) return;                                    // per-slot histograms: the general kernel walks everything
+    const int nlds = use_lds ? (ncls < PP_LDS_CLS ? ncls : PP_LDS_CLS) : 0;
     for (int i = threadIdx.x; i < nlds * PP_WORDS; i += AS_BLOCK) cnt[i] = 0u;
     for (int i = threadIdx.x; i < P * DH_LDS_BINS; i += AS_BLOCK) dh[i] = 0u;
     if (threadIdx.x < 2) s_nw[threadIdx.x] = 0u;
@@ -102,17 +180,22 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
         }
 #pragma unroll
         for (int kind = 0; kind < TL_KINDS; ++kind) {
-            if (m[kind] == 0ull) continue;
-            const int c = cls_find(s_cls, ncls, m[kind]);
-            if (c < 0) { S->tl.error = 1; continue; }        // a set the classification did not see: never expected
-            if (kind < TL_SRV_BUF ? timeline_is_analytic(kind, n, sm) : buf_timeline_is_analytic(kind, n, bs)) {
-                if (c < nlds) atomicAdd(&cnt[c * PP_WORDS + (n >> 1)], 1u << (16 * (n & 1)));
-                else atomicAdd(&ppcnt[(size_t)c * (DISCO_PP_NMAX + 1) + n], 1u);
-            } else {
-                const int sl = s_slot[c];
-                if (sl < 0) { S->tl.error = 1; continue; }
-                desc = (desc & ~(0xFFull << (8 * kind))) | ((u64)(unsigned)sl << (8 * kind));
+            int direct = -1;                                 // counter in device memory
+            if (m[kind] != 0ull) {
+                const int c = cls_find(cl.mask, ncls, m[kind]);
+                const int sl = c >= 0 ? cl.slot[c] : -1;
+                if (c < 0) {
+                    S->tl.error = 1;                         // a set the classification did not see: never expected
+                } else if (kind < TL_SRV_BUF ? timeline_is_analytic(kind, n, sm) : buf_timeline_is_analytic(kind, n, bs)) {
+                    if (c < nlds) atomicAdd(&cnt[c * PP_WORDS + (n >> 1)], 1u << (16 * (n & 1)));
+                    else direct = c * (DISCO_PP_NMAX + 1) + n;
+                } else if (sl < 0) {
+                    S->tl.error = 1;
+                } else {
+                    desc = (desc & ~(0xFFull << (8 * kind))) | ((u64)(unsigned)sl << (8 * kind));
+                }
             }
+            if (nlds < ncls) count_shared(ppcnt, direct, lane);
         }
         desc_out[i] = desc;
         const bool walk = desc != DESC_NONE5, lng = n >= WALK_LONG_TOKENS;
@@ -178,7 +261,7 @@ __global__ __launch_bounds__(1024) void k_pp_reduce(const SelState* S, int nslic
         reinterpret_cast<uint4*>(ghist)[i] = make_uint4(0u, 0u, 0u, 0u);
     const TlSel* tl = &S->tl;
     const int c = blockIdx.x;
-    if (tl->fallback || !use_lds || c >= tl->ncls || c >= PP_LDS_CLS) return;
+    if (tl->plan[0].fallback || !use_lds || c >= tl->ncls || c >= PP_LDS_CLS) return;
     const int w = blockIdx.y * 256 + (threadIdx.x & 255), grp = threadIdx.x >> 8;
     unsigned even = 0u, odd = 0u;
     if (w < PP_WORDS) {
@@ -198,19 +281,21 @@ __global__ __launch_bounds__(1024) void k_pp_reduce(const SelState* S, int nslic
     }
 }
 
-// One histogram pass over the walk list (regular passes; the spare passes run the same body in the kernel that
+// Plan of a regular pass and its histogram over the walk list (the spare passes run the same body in the kernel that
 // also advances the selection).
 __global__ __launch_bounds__(TH_BLOCK, 8) void k_tl_hist(TraceView tr, i64 n_tok, int align, HistArgs a)
 {
     __shared__ __align__(16) unsigned smem[DISCO_TL_HIST_WORDS];
-    tl_hist_fast_body(smem, tr, n_tok, align, a, blockIdx.x, gridDim.x);
+    __shared__ TlPlan plan;
+    tbt_open_pass(a.S, a.pass, a.P, a.nq, plan);
+    tl_hist_fast_body(smem, tr, n_tok, align, a, plan, blockIdx.x, gridDim.x);
 }
 
 }  // namespace
 
 // Once per selection, after the classification: descriptors of all requests, analytic timelines counted per class
 // and length.  `slices`: scratch for the workgroup slices (slices_bytes).
-void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, const void* summary, SelState* S,
+void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, float tau, const void* summary, SelState* S,
                             const void* bufsum, u64* desc, unsigned* list, unsigned* slices, size_t slices_bytes,
                             unsigned* ppcnt, unsigned* ghist, unsigned* dhist, hipStream_t stream)
 {
@@ -225,8 +310,11 @@ void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, 
     int use_lds = 1;
     // tens of millions of requests (or the testing aid that shrinks the grids): counts in device memory
     if (b > fit || disco_grid_divisor() > 1) { b = (v.n_req + 65535) / 65536; use_lds = 0; }
-    hipLaunchKernelGGL(k_tl_assign, dim3((unsigned)b), dim3(AS_BLOCK), 0, stream, v, pol, P, (const TlSummary*)summary,
+    const bool small = disco_small(v.n_req);
+    if (small) use_lds = 0;
+    hipLaunchKernelGGL(k_tl_assign, dim3((unsigned)b), dim3(AS_BLOCK), 0, stream, v, pol, P, tau, (const TlSummary*)summary,
                        (const BufSummary*)bufsum, S, desc, list, slices, ppcnt, dhist, use_lds);
+    if (small) return;                             // (their bins are cleared in the launch that stages the policy table)
     hipLaunchKernelGGL(k_pp_reduce, dim3(PP_LDS_CLS, (PP_WORDS + 255) / 256), dim3(1024), 0, stream, (const SelState*)S, (int)b, (const unsigned*)slices,
                        ppcnt, ghist, use_lds);
 }
@@ -237,7 +325,7 @@ void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy
     (void)pol;
     HistArgs h;
     memset(&h, 0, sizeof(h));
-    h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.pass = a.pass;
+    h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass;
     h.S = a.S; h.ghist = a.ghist;
     h.desc = a.desc; h.list = a.list;
     i64 b = (v.n_req + TH_BLOCK / 64 - 1) / (TH_BLOCK / 64);      // at most one request per wave

@@ -10,12 +10,11 @@
 // round(t tau) - round((t-1) tau) for every one of them, so counting the
 // timelines per class and length gives their histogram.
 //
-// Launches of a selection: classification, assignment (other file), the
-// "longer than" counts; per regular pass the walk of the streaming kinds
+// Launches of a selection: classification, assignment (other file); per
+// regular pass the plan of its digit and the walk of the streaming kinds
 // (other file), k_tbt_side (analytic bins, buffer hand-off timelines,
 // per-slot histograms: workgroups by kind) and k_tbt_select (one workgroup
-// per slot; the last one plans the next pass); per spare pass k_tbt_spare
-// alone.  A launch that finds the selection finished returns at once, which
+// per slot); per spare pass k_tbt_spare alone.  A launch that finds the selection finished returns at once, which
 // still costs about 2 us on the device: hence few launches.
 #include <string.h>
 
@@ -24,84 +23,6 @@
 #include "disco_tl_hist_fast.h"
 
 namespace {
-
-// Bin counts of a slot that k_tbt_select sums up in registers (two per thread, the rows of eight classes in flight: 10^5
-// requests x 12 columns 19 us per step when they went through LDS four rows at a time and one thread planned the next pass,
-// now 16).  Tables without walked timelines (constant gaps) have room for
-// digits of 13 and 14 bits, but their 21-bit window takes two passes either way, and an unstaged slot of 8192 bins reads
-// the rows of its classes bin by bin: 10^4 requests x 16 columns 120 us with 13 bits, 28 us with 11.
-constexpr int SEL_DIRECT_BITS = 11;
-
-// Prepares the next pass: prefix groups of the live slots, digit width that
-// fits, or the per-slot fallback.  All threads of a workgroup (wave_only: of
-// its first wave, the only one still running); the slots are fetched side by
-// side into LDS (s_prefix, s_grp: DISCO_MAX_SLOTS words each), one wave groups
-// them.  reset: every slot starts over (empty prefix, full rank).
-__device__ void tbt_plan_next(SelState* S, int P, int nq, unsigned* s_prefix, int* s_grp, bool wave_only, bool reset)
-{
-    TlSel& tl = S->tl;
-    const int ns = P * nq, nt = wave_only ? 64 : (int)blockDim.x;
-    auto sync = [&]() { if (wave_only) __builtin_amdgcn_wave_barrier(); else __syncthreads(); };
-    for (int s = threadIdx.x; s < ns; s += nt) {
-        SelSlot sl = S->slot[1][s];
-        if (reset) { sl.prefix = 0u; sl.k_rem = sl.rank; S->slot[1][s] = sl; }
-        s_prefix[s] = sl.prefix;
-        s_grp[s] = sl.done ? -2 : -1;
-    }
-    sync();
-    if (threadIdx.x < 64) {
-        // the distinct prefixes in slot order, one after the other; a lane holds slots `lane` and 64 + `lane`
-        static_assert(DISCO_MAX_SLOTS == 128, "two slots per lane");
-        const int lane = threadIdx.x;
-        const unsigned p0 = lane < ns ? s_prefix[lane] : 0u, p1 = 64 + lane < ns ? s_prefix[64 + lane] : 0u;
-        u64 todo0 = __ballot(lane < ns && s_grp[lane < ns ? lane : 0] != -2);
-        u64 todo1 = __ballot(64 + lane < ns && s_grp[64 + lane < ns ? 64 + lane : 0] != -2);
-        const bool live0 = (todo0 >> lane) & 1ull, live1 = (todo1 >> lane) & 1ull;
-        int G = 0, g0 = -1, g1 = -1;
-        while ((todo0 | todo1) != 0ull && G < DISCO_MAX_GRP) {
-            const unsigned px = todo0 ? (unsigned)bcast_i((int)p0, __ffsll((long long)todo0) - 1) : (unsigned)bcast_i((int)p1, __ffsll((long long)todo1) - 1);
-            const bool h0 = live0 && p0 == px, h1 = live1 && p1 == px;
-            if (h0) g0 = G;
-            if (h1) g1 = G;
-            todo0 &= ~__ballot(h0); todo1 &= ~__ballot(h1);
-            if (lane == 0) tl.grp_prefix[G] = px;
-            G += 1;
-        }
-        if ((todo0 | todo1) != 0ull) {         // too many distinct prefixes: the per-slot fallback does not use groups
-            G += 1;
-            if (live0 && g0 < 0) g0 = 0;
-            if (live1 && g1 < 0) g1 = 0;
-        }
-        if (lane < ns) tl.slot_grp[lane] = g0;
-        if (64 + lane < ns) tl.slot_grp[64 + lane] = g1;
-        bool over = tl.ncls > DISCO_MAX_CLS || tl.ncls < 1;
-        if (G > DISCO_MAX_GRP) over = true;
-        if (lane != 0) return;
-        if (over) tl.fallback = 1;
-        tl.G = G;
-        int w;
-        if (over || tl.fallback) {
-            w = fit_width(P * nq, DISCO_TL_HIST_WORDS);
-        } else {
-            const int g1 = G > 0 ? G : 1;
-            w = fit_width((long)g1 * (tl.nwalk > 0 ? tl.nwalk : 1), DISCO_TL_HIST_WORDS);
-            const int wg = fit_width((long)g1 * tl.ncls, DISCO_GHIST_WORDS);
-            if (wg < w) w = wg;
-            // a digit of more bins than the select step sums up in registers only where it saves a pass.  Not on raw keys with
-            // timelines to walk: there may be more than four prefixes in the end, and then every bit less here can cost another
-            // walk of everything (30 000 requests x 5 columns 1.15 ms of order statistics with 12 + 10 + 9 bits, 1.61 with
-            // 11 + 10 + 9 + 1)
-            if (w > SEL_DIRECT_BITS && (tl.window != 0 || tl.nwalk == 0) &&
-                (tl.left + w - 1) / w == (tl.left + SEL_DIRECT_BITS - 1) / SEL_DIRECT_BITS)
-                w = SEL_DIRECT_BITS;
-        }
-        if (w < 1) w = 1;
-        if (w > tl.left) w = tl.left;
-        if (G == 0) w = 0;                 // nothing left to select
-        tl.width = w;
-        tl.shift = tl.left - w;
-    }
-}
 
 // Distinct column sets of a workgroup's requests: an open-addressing hash table in LDS (CL_SLOTS slots, far more
 // than the DISCO_MAX_CLS sets a class-mode selection can hold).  A lane looks its set up with one LDS read in the
@@ -116,8 +37,6 @@ struct ClassTable {
     unsigned long long dense_walk;
     unsigned wave_cnt[CL_BLOCK / 64];
     int overflow;
-    unsigned plan_prefix[DISCO_MAX_SLOTS];     // scratch of the first plan (tbt_plan_next)
-    int plan_grp[DISCO_MAX_SLOTS];
 };
 
 __device__ __forceinline__ void table_clear(ClassTable& T)
@@ -167,23 +86,22 @@ __device__ __forceinline__ int table_compact(ClassTable& T)
     return total < DISCO_MAX_CLS ? total : DISCO_MAX_CLS;
 }
 
-// Column sets of every request -> classes.  Every workgroup collects its distinct sets in an LDS hash table
-// and enters them (a few dozen) into a device-wide table of the same kind; the workgroup that takes the last
-// ticket compacts that table, puts the sets in ascending order (so that the class numbers do not depend on
-// timing), numbers the classes that need a token walk and plans the first histogram pass.  The device-wide table was zeroed
-// when the selection started (select_init, in the launch that stages the policy table).
+// Column sets of every request.  Every workgroup collects its distinct sets in an LDS hash table and enters them
+// (a few dozen) into a device-wide table of the same kind, from which every workgroup of the assignment numbers them as
+// classes (a last workgroup that did so behind a ticket took half of this launch).  The device-wide table was zeroed when the
+// selection started (select_init, in the launch that stages the policy table).
 // Summaries of buffer hand-offs that were found with other prices (reuse_walk) say neither which timelines are paced nor
 // where the others hand off: with any of them the general kernel walks all timelines with the prices of this call.
-__global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const disco_policy* __restrict__ pol, int P, int nq,
-                                                     float tau, const TlSummary* __restrict__ summary,
-                                                     const BufSummary* __restrict__ bufsum, u64 tag, SelState* S, unsigned* ticket)
+__global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const disco_policy* __restrict__ pol, int P,
+                                                     const TlSummary* __restrict__ summary,
+                                                     const BufSummary* __restrict__ bufsum, u64 tag, SelState* S)
 {
     __shared__ disco_policy sp[DISCO_MAX_COLS];
     __shared__ ClassTable T;
     if ((int)threadIdx.x < P) sp[threadIdx.x] = pol[threadIdx.x];
     table_clear(T);
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
     const i64 nround = (tr.n_req + CL_BLOCK - 1) / CL_BLOCK;
     bool stale = false;
     for (i64 rnd = blockIdx.x; rnd < nround; rnd += gridDim.x) {
@@ -232,68 +150,11 @@ __global__ __launch_bounds__(CL_BLOCK) void k_tl_classify(TraceView tr, const di
         if (threadIdx.x == 0 && T.overflow) atomicOr(&g.goverflow, 1);
         if (__ballot(stale) != 0ull && lane == 0) atomicOr(&g.goverflow, 2);
     }
-    if (!take_last_ticket(ticket)) return;
-    // last workgroup: the device-wide table (read where the atomics put it), compacted and put in order
-    __syncthreads();
-    table_clear(T);
-    __syncthreads();
-    if (threadIdx.x < CL_SLOTS) {
-        T.slot[threadIdx.x] = (u64)atomicCAS((unsigned long long*)&S->tl.gslot[threadIdx.x], 0ull, 0ull);
-        T.walk[threadIdx.x] = atomicOr(&S->tl.gwalk[threadIdx.x], 0u);
-    }
-    const int over = threadIdx.x == 0 ? atomicOr(&S->tl.goverflow, 0) : 0;      // bit 0: too many sets, bit 1: other prices
-    if (over != 0) T.overflow = 1;
-    const int total = table_compact(T);
-    if (wave != 0) return;
-    // ascending order: lane e holds a set, its rank is the number of smaller ones
-    const u64 v = lane < total ? T.dense[lane] : ~0ull;
-    int rank = 0;
-    for (int j = 0; j < total; ++j) rank += bcast_u64(v, j) < v ? 1 : 0;
-    TlSel& tl = S->tl;
-    tl.cls_mask[lane < total ? rank : lane] = lane < total ? v : 0ull;
-    // walk mask in the new numbering: bit `rank` of the lanes whose set is walked
-    u64 wm = 0ull;
-    for (int j = 0; j < total; ++j) {
-        const int rj = bcast_i(rank, j);
-        if ((T.dense_walk >> j) & 1ull) wm |= 1ull << rj;
-    }
-    {
-        // rows of the walked classes in the workgroups' LDS histogram, in class order
-        const bool wl = (wm >> lane) & 1ull;
-        const int row = __popcll(wm & ((1ull << lane) - 1ull));
-        tl.cls_slot[lane] = wl ? (signed char)row : (signed char)-1;
-        u64 t = wm;                                          // class of row `lane`: the lane-th walked class
-        for (int q = 0; q < lane && t != 0ull; ++q) t &= t - 1ull;
-        tl.slot_cls[lane] = t != 0ull ? (unsigned char)(__ffsll((long long)t) - 1) : (unsigned char)0;
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (lane == 0) {
-        tl.ncls = total > 0 ? total : 1;
-        tl.walk_mask = wm;
-        tl.nwalk = __popcll(wm);
-        tl.error = 0;
-        if (T.overflow) tl.fallback = 1;               // more than DISCO_MAX_CLS distinct sets (or other prices): per-slot histograms
-        // gaps sit just above the pacing interval (down to a few thousand ulps below it after rounding): try a
-        // 21-bit window of keys first
-        const unsigned tb = f2u(tau);
-        tl.restart = 0;
-        tl.nlist = 0u;
-        tl.nlist_back = 0u;
-        // (not at other prices: the passes of 128 slots would not suffice for a second start)
-        if (tb >= 8192u && (over & 2) == 0) { tl.key_lo = tb - 8192u; tl.window = 21; tl.left = 21; }
-        else { tl.key_lo = 0u; tl.window = 0; tl.left = 31; }
-        *ticket = 0u;
-    }
-    __builtin_amdgcn_wave_barrier();
-    tbt_plan_next(S, P, nq, T.plan_prefix, T.plan_grp, true, false);
 }
 
-// Per class: counts by length -> number of timelines longer than t (in place).
-__global__ __launch_bounds__(1024) void k_pp_suffix(SelState* S, unsigned* ppcnt)
+// Of one class: counts by length -> number of timelines longer than t, in place (all threads; `part`: 1024 words of LDS).
+__device__ void longer_than(unsigned* row, unsigned* part)
 {
-    __shared__ unsigned part[1024];
-    if (S->tl.fallback || (int)blockIdx.x >= S->tl.ncls) return;
-    unsigned* row = ppcnt + (size_t)blockIdx.x * (DISCO_PP_NMAX + 1);
     constexpr int PER = (DISCO_PP_NMAX + 1 + 1023) / 1024;
     const int t0 = threadIdx.x * PER;
     unsigned v[PER];
@@ -312,33 +173,35 @@ __global__ __launch_bounds__(1024) void k_pp_suffix(SelState* S, unsigned* ppcnt
         if (t0 + q <= DISCO_PP_NMAX) row[t0 + q] = above;                         // timelines with n > t0 + q
         above += v[q];
     }
+    __threadfence_block();                          // (the workgroup reads the row it has written)
+    __syncthreads();
 }
 
 // Step 1 of a TBT pass (all threads of a workgroup, class c; beside the
 // workgroups that walk tokens, hence atomic adds): add the analytic bins of
-// the class's pure-pacing timelines to its device-wide rows.  ppcnt[c][t] timelines of class c have a token t, and the
-// gap in front of it is the same number for all of them.
-__device__ void analytic_class(SelState* S, unsigned* ghist, const unsigned* ppcnt, float tau, int c, unsigned* lds)
+// the class's pure-pacing timelines to its device-wide rows.  ppcnt[c][t] timelines of class c have a token t (the first
+// pass makes that of the counts by length), and the gap in front of it is the same number for all of them.
+__device__ void analytic_class(const TlPlan& pl, int ncls, int pass, unsigned* ghist, unsigned* ppcnt, float tau, int c, unsigned* lds)
 {
-    const TlSel& tl = S->tl;
-    const int width = tl.width, ncls = tl.ncls;
-    const unsigned* row = ppcnt + (size_t)c * (DISCO_PP_NMAX + 1);
+    const int width = pl.width;
+    unsigned* row = ppcnt + (size_t)c * (DISCO_PP_NMAX + 1);
+    if (pass == 0) longer_than(row, lds);
     if (row[0] == 0u) return;                             // no pure-pacing timeline in this class (uniform)
-    const int Gused = tl.G < DISCO_MAX_GRP ? tl.G : DISCO_MAX_GRP;
+    const int Gused = pl.G < DISCO_MAX_GRP ? pl.G : DISCO_MAX_GRP;
     const unsigned dmask = (1u << width) - 1u;
     const int words = Gused << width;
-    const int shift = tl.shift, up = tl.shift + width;
-    const unsigned key_cap = tl.window ? (1u << tl.window) : 0xFFFFFFFFu;
+    const int shift = pl.shift, up = pl.shift + width;
+    const unsigned key_cap = pl.window ? (1u << pl.window) : 0xFFFFFFFFu;
     __syncthreads();
     for (int i = threadIdx.x; i < words; i += blockDim.x) lds[i] = 0u;
     __syncthreads();
     for (int t = 1 + (int)threadIdx.x; t < DISCO_PP_NMAX; t += blockDim.x) {
         const unsigned cnt = row[t];
         if (!cnt) continue;
-        const unsigned key = tbt_key(f2u((float)t * tau - (float)(t - 1) * tau), tl.key_lo, key_cap);
+        const unsigned key = tbt_key(f2u((float)t * tau - (float)(t - 1) * tau), pl.key_lo, key_cap);
         const unsigned hi = key >> up;                     // clamped keys match no prefix
         int g = -1;
-        for (int k = 0; k < Gused; ++k) g = (hi == tl.grp_prefix[k] && g < 0) ? k : g;
+        for (int k = 0; k < Gused; ++k) g = (hi == pl.grp_prefix[k] && g < 0) ? k : g;
         if (g >= 0) atomicAdd(&lds[((unsigned)g << width) | ((key >> shift) & dmask)], cnt);
     }
     __syncthreads();
@@ -355,14 +218,15 @@ __device__ void analytic_class(SelState* S, unsigned* ghist, const unsigned* ppc
 //   binsum: LDS scratch of binsum_cap words: the bin counts of a slot with more than two bins per thread are summed over
 //   its classes there with coalesced reads of the class rows (a thread then scans consecutive bins from LDS); wider digits
 //   and the fallback read the rows directly.
-__device__ void select_slot(SelState* S, int nq, const unsigned* ghist, int s, u64* wsum /* LDS, 64 */, int* s_digit, u64* s_rem,
-                            u64* binsum, int binsum_cap)
+__device__ void select_slot(SelState* S, const TlPlan& pl, int pass, int nq, const unsigned* ghist, int s, u64* wsum /* LDS, 64 */,
+                            int* s_digit, u64* s_rem, u64* binsum, int binsum_cap)
 {
     const TlSel& tl = S->tl;
-    const int width = tl.width, ncls = tl.ncls, fallback = tl.fallback;
+    const int width = pl.width, ncls = tl.ncls, fallback = pl.fallback;
     SelSlot sl = S->slot[1][s];
-    const int g = tl.slot_grp[s];
+    const int g = pl.slot_grp[s];
     if (sl.done || g < 0) return;                         // uniform
+    if (pl.reset) { sl.prefix = 0u; sl.k_rem = sl.rank; }
     const int col = s / nq;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nbins = 1 << width;
@@ -452,7 +316,7 @@ __device__ void select_slot(SelState* S, int nq, const unsigned* ghist, int s, u
         u64 rem = *s_rem;
         // window mode: a rank beyond the counted keys, or in the bottom bin (which also holds the keys below the
         // window), is not decided here -> start over on raw keys.  Raw keys: the rank is always found.
-        if (tl.window && (dsel < 0 || (dsel == 0 && tl.left == tl.window))) S->tl.restart = 1;
+        if (pl.window && (dsel < 0 || (dsel == 0 && pl.left == pl.window))) S->tl.restart[pass] = 1;
         if (dsel < 0) { dsel = nbins - 1; rem = 1; }
         sl.k_rem = (i64)rem;
         sl.prefix = (sl.prefix << width) | (unsigned)dsel;
@@ -464,13 +328,14 @@ __device__ void select_slot(SelState* S, int nq, const unsigned* ghist, int s, u
 // in one workgroup.
 constexpr int SEL_NARROW_BITS = 4;
 
-__device__ void select_slot_narrow(SelState* S, int nq, const unsigned* ghist, int s)
+__device__ void select_slot_narrow(SelState* S, const TlPlan& pl, int pass, int nq, const unsigned* ghist, int s)
 {
     const TlSel& tl = S->tl;
-    const int width = tl.width, ncls = tl.ncls, lane = threadIdx.x & 63;
+    const int width = pl.width, ncls = tl.ncls, lane = threadIdx.x & 63;
     SelSlot sl = S->slot[1][s];
-    const int g = tl.slot_grp[s];
+    const int g = pl.slot_grp[s];
     if (sl.done || g < 0) return;                         // uniform
+    if (pl.reset) { sl.prefix = 0u; sl.k_rem = sl.rank; }
     const int col = s / nq, nbins = 1 << width;
     static_assert(DISCO_MAX_CLS <= 64, "a lane per class");
     const bool in = lane < ncls && ((tl.cls_mask[lane] >> col) & 1ull);
@@ -482,7 +347,7 @@ __device__ void select_slot_narrow(SelState* S, int nq, const unsigned* ghist, i
     }
     if (lane == 0) {
         // as in select_slot: what the window does not decide starts over on raw keys
-        if (tl.window && (dsel < 0 || (dsel == 0 && tl.left == tl.window))) S->tl.restart = 1;
+        if (pl.window && (dsel < 0 || (dsel == 0 && pl.left == pl.window))) S->tl.restart[pass] = 1;
         if (dsel < 0) { dsel = nbins - 1; rem = 1; }
         sl.k_rem = (i64)rem;
         sl.prefix = (sl.prefix << width) | (unsigned)dsel;
@@ -490,27 +355,17 @@ __device__ void select_slot_narrow(SelState* S, int nq, const unsigned* ghist, i
     }
 }
 
-// Step 3 (one workgroup): clear the bins that were used and plan the next pass.
-__device__ void plan_pass(SelState* S, int P, int nq, unsigned* ghist, unsigned* s_prefix, int* s_grp)
+// Words of the device-wide bins a pass uses.
+__device__ __forceinline__ int bins_used(const TlPlan& pl, int ncls, int ns)
 {
-    TlSel& tl = S->tl;
-    const int width = tl.width;
-    const int Gused = tl.G < DISCO_MAX_GRP ? tl.G : DISCO_MAX_GRP;
-    const int words = (tl.fallback ? P * nq : Gused * tl.ncls) << width;
-    __syncthreads();
-    for (int i = threadIdx.x; i < words / 4; i += blockDim.x) reinterpret_cast<uint4*>(ghist)[i] = make_uint4(0u, 0u, 0u, 0u);
-    if ((int)threadIdx.x < words % 4) ghist[words / 4 * 4 + threadIdx.x] = 0u;      // (digits of one bit)
-    __syncthreads();
-    const bool restart = tl.window && tl.restart;          // the window missed a rank: all slots start over on raw keys
-    const bool more = restart || tl.left - width > 0;
-    __syncthreads();                                       // (every thread has read the state thread 0 now changes)
-    if (threadIdx.x == 0) {
-        if (restart) { tl.window = 0; tl.key_lo = 0u; tl.restart = 0; tl.left = 31; }
-        else if (more) tl.left -= width;
-        else { tl.left = 0; tl.width = 0; tl.G = 0; }
-    }
-    __syncthreads();
-    if (more) tbt_plan_next(S, P, nq, s_prefix, s_grp, false, restart);
+    const int Gused = pl.G < DISCO_MAX_GRP ? pl.G : DISCO_MAX_GRP;
+    return pl.width <= 0 ? 0 : (pl.fallback ? ns : Gused * ncls) << pl.width;
+}
+// The bins of the next pass back to zero (thread t of nt): what the pass before this one used, all of them before the second.
+__device__ __forceinline__ void clear_next_bins(const SelState* S, int pass, int ns, unsigned* bins, int t, int nt)
+{
+    const int words = pass > 0 ? bins_used(S->tl.plan[pass], S->tl.ncls, ns) : DISCO_GHIST_WORDS;
+    for (int i = t; i < (words + 3) / 4; i += nt) reinterpret_cast<uint4*>(bins)[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // Workgroups of the launches below, by what they run.
@@ -519,7 +374,7 @@ struct PassGrid { unsigned analytic, fast, buf, general; };
 __device__ __forceinline__ BufHistArgs buf_hist_args(const TimelineArgs& a)
 {
     BufHistArgs h;
-    h.h.tau = a.tau; h.h.kt = a.kt; h.h.P = a.P; h.h.pass = a.pass;
+    h.h.tau = a.tau; h.h.kt = a.kt; h.h.P = a.P; h.h.nq = a.nq; h.h.pass = a.pass;
     h.h.S = a.S; h.h.ghist = a.ghist; h.h.desc = a.desc; h.h.list = a.list;
     h.bufsum = (const BufSummary*)a.bufsum;
     h.buffer_flag = a.buffer_flag;
@@ -537,40 +392,41 @@ __global__ __launch_bounds__(1024) void k_tbt_side(TraceView tr, i64 n_tok, int 
 {
     __shared__ __align__(16) unsigned smem[DISCO_TL_HIST_WORDS];
     __shared__ TimelineLds lds;
-    const TlSel& tl = a.S->tl;
-    if (tl.width <= 0) return;                          // selection finished
+    const TlPlan& pl = a.S->tl.plan[a.pass + 1];        // (left by the launch that opened the pass)
+    if (pl.width <= 0) return;                          // selection finished
     unsigned bid = blockIdx.x;
     if (bid < g.analytic) {
-        if (!tl.fallback && (int)bid < tl.ncls) analytic_class(a.S, a.ghist, a.ppcnt, a.tau, (int)bid, smem);
+        const int ncls = a.S->tl.ncls;
+        if (!pl.fallback && (int)bid < ncls) analytic_class(pl, ncls, a.pass, a.ghist, a.ppcnt, a.tau, (int)bid, smem);
         return;
     }
     bid -= g.analytic;
     if (bid < g.buf) {
-        if (!tl.fallback && *a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), bid, g.buf);
+        if (!pl.fallback && *a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), pl, bid, g.buf);
         return;
     }
     bid -= g.buf;
-    if (tl.fallback) timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, bid, g.general);
+    if (pl.fallback) timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, &pl, bid, g.general);
 }
 
-// Workgroup = slot: the digit of the slot; the workgroup that finishes last clears the bins and plans the next pass.
-__global__ __launch_bounds__(1024) void k_tbt_select(SelState* S, int P, int nq, unsigned* ghist, unsigned* ticket)
+// Workgroup = slot: the digit of the slot; SEL_CLEAR workgroups behind them clear the bins of the next pass.
+constexpr int SEL_CLEAR = DISCO_GHIST_WORDS / 4 / 1024;
+__global__ __launch_bounds__(1024) void k_tbt_select(SelState* S, int pass, int P, int nq, const unsigned* __restrict__ ghist,
+                                                     unsigned* __restrict__ next)
 {
     __shared__ u64 wsum[DISCO_MAX_CLS];
     __shared__ int s_digit;
     __shared__ u64 s_rem;
-    __shared__ unsigned s_prefix[DISCO_MAX_SLOTS];
-    __shared__ int s_grp[DISCO_MAX_SLOTS];
-    if (S->tl.width <= 0) return;
-    select_slot(S, nq, ghist, blockIdx.x, wsum, &s_digit, &s_rem, nullptr, 0);
-    if (!take_last_ticket(ticket)) return;
-    plan_pass(S, P, nq, ghist, s_prefix, s_grp);
-    if (threadIdx.x == 0) *ticket = 0u;
+    const TlPlan& pl = S->tl.plan[pass + 1];
+    if (pl.width <= 0) return;
+    const int ns = P * nq;
+    if ((int)blockIdx.x < ns) select_slot(S, pl, pass, nq, ghist, blockIdx.x, wsum, &s_digit, &s_rem, nullptr, 0);
+    else clear_next_bins(S, pass, ns, next, ((int)blockIdx.x - ns) * 1024 + (int)threadIdx.x, SEL_CLEAR * 1024);
 }
 
 // A spare pass (after the passes that normally finish the selection: needed when the window was missed or the
 // digits are narrow) in one launch: every workgroup adds the analytic bins of its classes and walks its share of each kind
-// of timeline; the one that finishes last takes every slot's digit, clears the bins and plans the next pass.  One launch per pass matters
+// of timeline; the one that finishes last takes every slot's digit and clears the next pass's bins.  One launch per pass matters
 // more here than speed: normally all of them return at once.
 __global__ __launch_bounds__(1024) void k_tbt_spare(TraceView tr, i64 n_tok, int align, const disco_policy* __restrict__ pol,
                                                     TimelineArgs a, PassGrid g)
@@ -580,54 +436,51 @@ __global__ __launch_bounds__(1024) void k_tbt_spare(TraceView tr, i64 n_tok, int
     __shared__ u64 wsum[DISCO_MAX_CLS];
     __shared__ int s_digit;
     __shared__ u64 s_rem;
+    __shared__ TlPlan pl;
     SelState* S = a.S;
     const TlSel& tl = S->tl;
-    if (tl.width <= 0) return;                          // selection finished (the same answer in every workgroup)
+    tbt_open_pass(S, a.pass, a.P, a.nq, pl);
+    if (pl.width <= 0) return;                          // selection finished (the same answer in every workgroup)
     const unsigned bid = blockIdx.x;
-    if (!tl.fallback)                                   // the analytic bins: a class per workgroup
-        for (int c = (int)bid; c < tl.ncls; c += (int)gridDim.x) analytic_class(S, a.ghist, a.ppcnt, a.tau, c, smem);
+    if (!pl.fallback)                                   // the analytic bins: a class per workgroup
+        for (int c = (int)bid; c < tl.ncls; c += (int)gridDim.x) analytic_class(pl, tl.ncls, a.pass, a.ghist, a.ppcnt, a.tau, c, smem);
     __syncthreads();
-    if (tl.fallback) {
-        timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, bid, g.general);
+    if (pl.fallback) {
+        timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, &pl, bid, g.general);
     } else {
         HistArgs h;
-        h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.pass = a.pass; h.S = a.S; h.ghist = a.ghist; h.desc = a.desc; h.list = a.list;
-        tl_hist_fast_body(smem, tr, n_tok, align, h, bid, g.fast);
+        h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass; h.S = a.S; h.ghist = a.ghist; h.desc = a.desc; h.list = a.list;
+        tl_hist_fast_body(smem, tr, n_tok, align, h, pl, bid, g.fast);
         __syncthreads();                                // the bins are used again
-        if (*a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), bid, g.buf);
+        if (*a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), pl, bid, g.buf);
     }
     if (!take_last_ticket(a.ticket)) return;
     __syncthreads();
-    if (!tl.fallback && tl.width <= SEL_NARROW_BITS) {
-        for (int s = threadIdx.x >> 6; s < a.P * a.nq; s += (int)blockDim.x >> 6) select_slot_narrow(S, a.nq, a.ghist, s);
+    if (!pl.fallback && pl.width <= SEL_NARROW_BITS) {
+        for (int s = threadIdx.x >> 6; s < a.P * a.nq; s += (int)blockDim.x >> 6) select_slot_narrow(S, pl, a.pass, a.nq, a.ghist, s);
         __syncthreads();
     } else {
         for (int s = 0; s < a.P * a.nq; ++s) {
-            select_slot(S, a.nq, a.ghist, s, wsum, &s_digit, &s_rem, reinterpret_cast<u64*>(smem), DISCO_TL_HIST_WORDS / 2);
+            select_slot(S, pl, a.pass, a.nq, a.ghist, s, wsum, &s_digit, &s_rem, reinterpret_cast<u64*>(smem), DISCO_TL_HIST_WORDS / 2);
             __syncthreads();
         }
     }
-    plan_pass(S, a.P, a.nq, a.ghist, smem, reinterpret_cast<int*>(smem + DISCO_MAX_SLOTS));
+    clear_next_bins(S, a.pass, a.P * a.nq, a.gclear, (int)threadIdx.x, (int)blockDim.x);
     if (threadIdx.x == 0) *a.ticket = 0u;
 }
 
 }  // namespace
 
-void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, int nq, float tau, const void* summary,
-                              const void* bufsum, const BufCostArgs& bc, SelState* S, unsigned* ticket, hipStream_t stream)
+void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, const void* summary, const void* bufsum,
+                              const BufCostArgs& bc, SelState* S, hipStream_t stream)
 {
     i64 b = (v.n_req + CL_BLOCK - 1) / CL_BLOCK;
     if (b < 1) b = 1;
     if (b > 256) b = 256;                          // (more workgroups cost more in the merge than they save in the scan)
     b /= disco_grid_divisor();
     if (b < 1) b = 1;
-    hipLaunchKernelGGL(k_tl_classify, dim3((unsigned)b), dim3(CL_BLOCK), 0, stream, v, pol, P, nq, tau,
-                       (const TlSummary*)summary, (const BufSummary*)bufsum, price_tag(bc), S, ticket);
-}
-
-void disco_launch_pp_suffix(SelState* S, unsigned* ppcnt, hipStream_t stream)
-{
-    hipLaunchKernelGGL(k_pp_suffix, dim3(DISCO_MAX_CLS), dim3(1024), 0, stream, S, ppcnt);
+    hipLaunchKernelGGL(k_tl_classify, dim3((unsigned)b), dim3(CL_BLOCK), 0, stream, v, pol, P, (const TlSummary*)summary,
+                       (const BufSummary*)bufsum, price_tag(bc), S);
 }
 
 // One pass of the TBT selection over everything but the streaming kinds' walk in the regular passes (that walk:
@@ -641,7 +494,8 @@ void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* po
     if (a.pass < DISCO_TBT_REGULAR_PASS) {
         g.analytic = DISCO_MAX_CLS; g.fast = 0; g.buf = cap(512); g.general = cap(512);
         hipLaunchKernelGGL(k_tbt_side, dim3(g.analytic + g.buf + g.general), dim3(1024), 0, stream, v, n_tok, align, pol, a, g);
-        hipLaunchKernelGGL(k_tbt_select, dim3((unsigned)(a.P * a.nq)), dim3(1024), 0, stream, a.S, a.P, a.nq, a.ghist, a.ticket);
+        hipLaunchKernelGGL(k_tbt_select, dim3((unsigned)(a.P * a.nq + SEL_CLEAR)), dim3(1024), 0, stream, a.S, a.pass, a.P, a.nq, a.ghist,
+                           a.gclear);
     } else {
         // one workgroup per CU: more of them make an empty launch dearer.  (A workgroup per kind and 64 of each, all slots
         // and analytic bins left to the last workgroup: 194 us for the one remaining bit of 10^5 requests x 12 wait

@@ -347,3 +347,18 @@ def test_small_traces_against_the_general_kernels(B, n_req, table):
         assert B._lib.disco_set_grid_divisor(1) == 0
     for i, (a, b) in enumerate(zip(small, general)):
         same(a, b, f"result {i}")
+
+
+# TBT order statistics: analytic timelines of a small trace are counted in device memory, those of one length once per wave;
+# one more request than the small ones takes the counts in LDS; ranks that leave the window of keys start over on raw keys
+@pytest.mark.parametrize("n_req,length,tau", [(1, 2, 0.2), (65, 37, 0.2), (1500, 1, 0.2), (2049, 4097, 0.2), (2049, 4096, 0.2), (3000, 0, 0.02), (32_769, 5, 0.2)])
+def test_analytic_timelines_of_small_traces(B, oracle, n_req, length, tau):
+    print(f"analytic timelines: n_req={n_req} length={length} tau={tau}", flush=True)
+    tr = DI.handmade_trace(400 + n_req, n_req, tokens=False, max_out=60)
+    if length:
+        tr["output_len"][:] = length
+        tr["output_len"][:: 7] = 3
+        tr["tok_off"][1:] = np.cumsum(tr["output_len"])
+        tr["n_tok"] = int(tr["tok_off"][-1])
+    specs = [dict(mode=0, l_th=x, mig_mode=1) for x in (0, 400, 1500, 5000)] + [dict(mode=1, l_th=-1, w_tail=DI.f32(0.3), mig_mode=0)]
+    check_stats(B, oracle, tr, specs, DI.COST_S, tau=DI.f32(tau), kappa=DI.KAPPA_LAG, quantiles=((1, 100), (50, 100), (99, 100)))
