@@ -431,6 +431,17 @@ int stage_policies(const disco_policy* pol, int P, char* ws, const WsLayout& L, 
     return DISCO_OK;
 }
 
+// The table of a call as the kernels of small traces take it: `host` filled in and validated, or *device set.
+int small_table(const disco_policy* pol, int P, PolTable& host, const disco_policy** device)
+{
+    memset(&host, 0, sizeof(host));
+    *device = nullptr;
+    if (is_device_pointer(pol)) { *device = pol; return DISCO_OK; }
+    const int rc = check_policies(pol, P);
+    if (rc == DISCO_OK) memcpy(host.p, pol, sizeof(disco_policy) * (size_t)P);
+    return rc;
+}
+
 // Dispatch totals of every column and, if asked, the per-pair outputs; `part`: device-wide totals, `ws + L.*`: scratch.
 int eval_dispatch(const TraceView& v, const disco_policy* pol, int P, const disco_pair_out* out, disco_accum* acc, char* ws,
                   const WsLayout& L, hipStream_t stream)
@@ -440,14 +451,10 @@ int eval_dispatch(const TraceView& v, const disco_policy* pol, int P, const disc
     const disco_policy* staged = (const disco_policy*)(ws + L.pol);
     if (small && !pairs) {
         PolTable t;
-        memset(&t, 0, sizeof(t));
-        const bool device = is_device_pointer(pol);
-        if (!device) {
-            const int rc = check_policies(pol, P);
-            if (rc) return rc;
-            memcpy(t.p, pol, sizeof(disco_policy) * (size_t)P);
-        }
-        disco_launch_small_dispatch(v, t, device ? pol : nullptr, P, acc, stream);
+        const disco_policy* device;
+        const int rc = small_table(pol, P, t, &device);
+        if (rc) return rc;
+        disco_launch_small_dispatch(v, t, device, P, acc, stream);
     } else {
         const int rc = stage_policies(pol, P, ws, L, stream);        // also puts the flag words and the totals at their identity
         if (rc) return rc;
@@ -633,7 +640,10 @@ extern "C" int32_t disco_eval_migration(const disco_trace* trace, const disco_ti
     if (!(out && out->delivered) && ws_bytes < disco_ws_full_bytes(L, trace->n_req)) return DISCO_ERR_WORKSPACE;
     TraceView v = view_of(trace);
     if (out && out->delivered) v.off = trace->tok_off;      // offsets index `delivered` even without tok_arr
-    rc = stage_policies(pol, P, ws, L, stream);
+    const bool small = disco_small(v.n_req) && !(out && out->delivered);
+    PolTable host;
+    const disco_policy* device = nullptr;
+    rc = small ? small_table(pol, P, host, &device) : stage_policies(pol, P, ws, L, stream);
     if (rc) return rc;
     TimelineArgs a;
     memset(&a, 0, sizeof(a));
@@ -661,7 +671,11 @@ extern "C" int32_t disco_eval_migration(const disco_trace* trace, const disco_ti
         a.summary = ws + disco_ws_summary_offset(L, v.n_req);
         a.counter = (unsigned*)(ws + L.wcount);
         a.bufsum = ws + disco_ws_bufsum_offset(L, v.n_req);
-        disco_launch_tl_stats_fast(v, trace->n_tok, (const disco_policy*)(ws + L.pol), a,
+        if (small)
+            disco_launch_small_stats(v, trace->n_tok, host, device, (disco_policy*)(ws + L.pol), (unsigned*)(ws + L.ticket), a,
+                                     tl_totals((u64*)(ws + L.part)), stream);
+        else
+            disco_launch_tl_stats_fast(v, trace->n_tok, (const disco_policy*)(ws + L.pol), a,
                                    tl_totals((u64*)(ws + L.part)), stream);
     }
     DISCO_HIP(hipGetLastError());
@@ -776,7 +790,13 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
             a.counter = (unsigned*)(ws + L.wcount);
             a.bufsum = ws + disco_ws_bufsum_offset(L, v.n_req);
             if (!tl->reuse_walk) {
-                disco_launch_tl_walk(v, trace->n_tok, dpol, P, a.tau, a.kt, a.wflags, a.summary, a.counter, stream);
+                if (disco_small(v.n_req)) {
+                    PolTable none;
+                    memset(&none, 0, sizeof(none));
+                    disco_launch_small_walk(v, trace->n_tok, none, dpol, P, a.tau, a.kt, a.summary, nullptr, nullptr, nullptr, stream);
+                } else {
+                    disco_launch_tl_walk(v, trace->n_tok, dpol, P, a.tau, a.kt, a.wflags, a.summary, a.counter, stream);
+                }
                 disco_launch_tl_stats_buf(v, trace->n_tok, dpol, a, nullptr, stream);      // summaries only
             }
             disco_launch_tl_classify(v, dpol, P, a.summary, a.bufsum, a.bc, S, stream);

@@ -120,6 +120,12 @@ void disco_launch_tl_stats_fast(const TraceView& v, i64 n_tok, const disco_polic
 void disco_launch_tl_walk(const TraceView& v, i64 n_tok, const disco_policy* pol, int P, float tau, float kt,
                           unsigned char* wflags, void* summary, unsigned* counter, hipStream_t stream,
                           hipEvent_t before = nullptr, hipEvent_t after = nullptr);
+// The same for a small trace, and the statistics pass of one: the policy table (from device memory, or `host` where `device` is
+// null) is staged and the totals are cleared in the first launch (staged, tickets, totals: not written if null).
+void disco_launch_small_walk(const TraceView& v, i64 n_tok, const PolTable& host, const disco_policy* device, int P, float tau, float kt,
+                             void* summary, disco_policy* staged, unsigned* tickets, MigPartial* totals, hipStream_t stream);
+void disco_launch_small_stats(const TraceView& v, i64 n_tok, const PolTable& host, const disco_policy* device, disco_policy* staged,
+                              unsigned* tickets, const TimelineArgs& a, MigPartial* totals, hipStream_t stream);
 void disco_launch_timeline_general(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                    hipStream_t stream);
 void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, const void* summary, const void* bufsum,

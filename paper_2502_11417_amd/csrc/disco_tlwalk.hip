@@ -24,6 +24,7 @@
 //   k_tl_accum   lane = column: per-column totals from the summaries (the pairs with a buffer hand-off are
 //                added by the kernel that settles those hand-offs)
 //   k_tl_mat     optional per-pair outputs from the summaries
+// Small traces take the flags and all walks in one launch (k_small_walk) and the totals in another (k_small_accum).
 #include <string.h>
 
 #include "disco_tl_walk.h"
@@ -43,6 +44,19 @@ constexpr int TW_NV = 1;                     // 16-byte vectors per lane and ite
 __device__ __forceinline__ int window_lead(const float* first) { return (int)(((uintptr_t)first >> 2) & 31u); }
 
 
+// The walk flags of a request with the column sets m.
+__device__ __forceinline__ unsigned walks_needed(const u64 m[TL_KINDS], bool mem, float gap, float gd, float tau)
+{
+    const bool srv_closed = pure_pacing(!mem, gap, tau);
+    unsigned f = 0;
+    if (m[TL_SRV_LAG] != 0ull && !srv_closed) f |= WF_LAG;
+    // (a buffer hand-off timeline that never hands off is the source's own timeline: the kernel of those
+    // pairs takes its final maximum from here instead of walking it)
+    if ((m[TL_SRV] | m[TL_SRV_BUF]) != 0ull && !srv_closed) f |= WF_PLAIN;
+    if ((m[TL_DEV] | m[TL_DEV_BUF]) != 0ull && !pure_pacing(true, gd, tau)) f |= WF_DEV;
+    return f;
+}
+
 __global__ __launch_bounds__(256) void k_tl_flags(TraceView tr, i64 n_tok, const disco_policy* __restrict__ pol, int P, float tau,
                                                   unsigned char* __restrict__ wflags, unsigned* __restrict__ counters, int ncounters)
 {
@@ -60,13 +74,7 @@ __global__ __launch_bounds__(256) void k_tl_flags(TraceView tr, i64 n_tok, const
         const float gap = tr.tbt ? tr.tbt[i] : 0.0f;
         u64 m[TL_KINDS];
         request_sets(sp, P, l, s, __fmaf_rn((float)l, k, tr.c), i, m);
-        const bool srv_closed = pure_pacing(!mem, gap, tau);
-        unsigned f = 0;
-        if (m[TL_SRV_LAG] != 0ull && !srv_closed) f |= WF_LAG;
-        // (a buffer hand-off timeline that never hands off is the source's own timeline: the kernel of those
-        // pairs takes its final maximum from here instead of walking it)
-        if ((m[TL_SRV] | m[TL_SRV_BUF]) != 0ull && !srv_closed) f |= WF_PLAIN;
-        if ((m[TL_DEV] | m[TL_DEV_BUF]) != 0ull && !pure_pacing(true, gd, tau)) f |= WF_DEV;
+        unsigned f = walks_needed(m, mem, gap, gd, tau);
         // the streaming walk loads 16 bytes per lane without bounds checks, from the 128-byte boundary at or below
         // the request's first token: the requests at the very ends of the token array, where such a load could
         // leave it, are left to the general walker
@@ -459,88 +467,138 @@ __global__ __launch_bounds__(TW_BLOCK) void k_tl_walk(TraceView tr, i64 n_tok, W
     }
 }
 
-// Everything the streaming walk leaves: requests it flagged WF_REDO (the lag trigger may fire: exact evaluation,
-// and a second walk without hand-off where columns without hand-off share the request), server sources with a
+// Row maxima of a wave's walks: slot 0 server walk, 1 server walk without hand-off beside a hand-off that fired, 2 device
+// source; one row per request of the batch.
+constexpr int WR_RB = 64;                                    // requests per wave and round
+typedef float WalkRows[3][WR_RB][4];
+
+// The walks of a wave's batch (lane = request `il` = first + lane with the flags f; srv: its server source is walked here),
+// one request and source at a time with the general walker: the lag trigger is evaluated exactly, and a second walk without
+// hand-off made where columns without one share a request that hands off.  s: the lane's summary, its fields of the walked
+// kinds set.
+template <int NV>
+__device__ __forceinline__ void walk_batch(const TraceView& tr, i64 n_tok, i64 first, i64 il, unsigned f, bool srv, float tau, float kt,
+                                           const LagConst& lc, WalkRows& rows, TlSummary& s)
+{
+    const int lane = threadIdx.x & 63;
+    const float lane4f = (float)(4 * lane);
+    const bool mem = tr.arr != nullptr;
+    u64 todo0 = __ballot(srv), todo1 = 0ull;
+    u64 todo2 = __ballot((f & WF_DEV) != 0u);
+    int n_v = 1;
+    i64 off_v = 0;
+    float gap_v = 0.0f;
+    if (srv || (f & WF_DEV) != 0u) {
+        n_v = tr.n[il];
+        if (tr.off) off_v = tr.off[il];
+        if (!mem && tr.tbt) gap_v = tr.tbt[il];
+    }
+    int m_enc = -1;                                          // lane = request
+    bool two = false;                                        // a second server walk was needed
+    while ((todo0 | todo1 | todo2) != 0ull) {
+        const int slot = todo0 ? 0 : (todo1 ? 1 : 2);
+        const u64 td = todo0 ? todo0 : (todo1 ? todo1 : todo2);
+        const int rq = __ffsll((long long)td) - 1;
+        if (slot == 0) todo0 &= todo0 - 1; else if (slot == 1) todo1 &= todo1 - 1; else todo2 &= todo2 - 1;
+        const int n = bcast_i(n_v, rq);
+        const unsigned fr = (unsigned)bcast_i((int)f, rq);
+        const i64 off = (i64)bcast_u64((u64)off_v, rq);
+        const bool job_mem = mem && slot < 2;
+        const bool lag = slot == 0 && (fr & WF_LAG) != 0u;
+        float gap = 0.0f;
+        if (slot == 2) gap = tr.g ? tr.g[first + rq] : tr.g_s;
+        else if (!mem) gap = bcast_f(gap_v, rq);
+        float now[NV][4];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) { now[v][0] = now[v][1] = now[v][2] = now[v][3] = 0.0f; }
+        if (job_mem) load_span<NV>(tr.arr, off + 4 * lane, 4 * lane, n, n_tok, off + n + 3 <= n_tok, now);
+        const WalkRes w = walk_request<NV>(tr, job_mem, first + rq, n, off, n_tok, now, gap, lag, tau, kt, lc, lane, lane4f);
+        put_rows(w.Mlane, rows[slot][rq], lane);
+        if (slot == 0) {
+            const bool nz = w.C != 0.0f;
+            const int enc = w.m >= 0 ? (w.m | (nz ? (1 << 30) : 0)) : (nz ? -2 : -1);
+            m_enc = lane == rq ? enc : m_enc;
+            if (w.m >= 0 && (fr & WF_PLAIN) != 0u) todo1 |= 1ull << rq;           // columns without hand-off share the request
+        } else if (slot == 1) {
+            two = lane == rq ? true : two;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();                         // the row maxima were written by other lanes of this wave
+    auto rowmax = [&](int slot) {
+        const float4 x = *reinterpret_cast<const float4*>(rows[slot][lane]);
+        return fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w));
+    };
+    if (srv) {
+        s.M_lag = rowmax(0);
+        s.m_enc = m_enc;
+        s.M_plain = two ? rowmax(1) : s.M_lag;
+    }
+    if (f & WF_DEV) s.M_dev = rowmax(2);
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Everything the streaming walk leaves: requests it flagged WF_REDO (the lag trigger may fire), server sources with a
 // constant gap that is not pure pacing (no token array), and device sources that are not pure pacing.  Few
 // requests; one wave per request and job with the general walker.  `streamed`: the streaming walk has run (else
 // every server job is done here).
 __global__ __launch_bounds__(TW_BLOCK) void k_tl_walk_rest(TraceView tr, i64 n_tok, WalkArgs a, int streamed)
 {
-    // row maxima per wave, slot (0 server walk, 1 server walk without hand-off beside a hand-off that fired,
-    // 2 device source) and request of the batch
-    constexpr int WR_RB = 64;                                // requests per wave and round: one flag byte per lane
-    __shared__ __align__(16) float red[TW_WAVES][3][WR_RB][4];
+    __shared__ __align__(16) WalkRows rows[TW_WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float lane4f = (float)(4 * lane);
     const float tau = a.tau, kt = a.kt;
     const LagConst lc{262144.0f * (kt / tau), 262144.0f * kt, kt >= tau * 0.0009765625f};
-    const bool mem = tr.arr != nullptr;
-    float (*myred)[WR_RB][4] = red[wave];
     const i64 nbatch = (tr.n_req + WR_RB - 1) / WR_RB;
     for (i64 bt = (i64)blockIdx.x * TW_WAVES + wave; bt < nbatch; bt += (i64)gridDim.x * TW_WAVES) {
         const i64 first = bt * WR_RB;
         const i64 il = first + lane;
-        const bool valid = il < tr.n_req;
-        const unsigned f = valid ? a.wflags[il] : 0u;
+        const unsigned f = il < tr.n_req ? a.wflags[il] : 0u;
         const bool srv_here = (f & (WF_LAG | WF_PLAIN)) != 0u && (!streamed || (f & WF_REDO) != 0u);
-        u64 todo0 = __ballot(srv_here), todo1 = 0ull;
-        u64 todo2 = __ballot((f & WF_DEV) != 0u);
-        if ((todo0 | todo2) == 0ull) continue;               // (almost every batch)
-        int n_v = 1;
-        i64 off_v = 0;
-        float gap_v = 0.0f;
-        if (srv_here || (f & WF_DEV) != 0u) {
-            n_v = tr.n[il];
-            if (tr.off) off_v = tr.off[il];
-            if (!mem && tr.tbt) gap_v = tr.tbt[il];
-        }
-        int m_enc = -1;                                      // lane = request
-        bool two = false;                                    // a second server walk was needed
-        while ((todo0 | todo1 | todo2) != 0ull) {
-            const int slot = todo0 ? 0 : (todo1 ? 1 : 2);
-            const u64 td = todo0 ? todo0 : (todo1 ? todo1 : todo2);
-            const int rq = __ffsll((long long)td) - 1;
-            if (slot == 0) todo0 &= todo0 - 1; else if (slot == 1) todo1 &= todo1 - 1; else todo2 &= todo2 - 1;
-            const int n = bcast_i(n_v, rq);
-            const unsigned fr = (unsigned)bcast_i((int)f, rq);
-            const i64 off = (i64)bcast_u64((u64)off_v, rq);
-            const bool job_mem = mem && slot < 2;
-            const bool lag = slot == 0 && (fr & WF_LAG) != 0u;
-            float gap = 0.0f;
-            if (slot == 2) gap = tr.g ? tr.g[first + rq] : tr.g_s;
-            else if (!mem) gap = bcast_f(gap_v, rq);
-            float now[TW_NV][4];
-#pragma unroll
-            for (int v = 0; v < TW_NV; ++v) { now[v][0] = now[v][1] = now[v][2] = now[v][3] = 0.0f; }
-            if (job_mem) load_span<TW_NV>(tr.arr, off + 4 * lane, 4 * lane, n, n_tok, off + n + 3 <= n_tok, now);
-            const WalkRes w = walk_request<TW_NV>(tr, job_mem, first + rq, n, off, n_tok, now, gap, lag, tau, kt, lc, lane, lane4f);
-            put_rows(w.Mlane, myred[slot][rq], lane);
-            if (slot == 0) {
-                const bool nz = w.C != 0.0f;
-                const int enc = w.m >= 0 ? (w.m | (nz ? (1 << 30) : 0)) : (nz ? -2 : -1);
-                m_enc = lane == rq ? enc : m_enc;
-                if (w.m >= 0 && (fr & WF_PLAIN) != 0u) todo1 |= 1ull << rq;       // columns without hand-off share the request
-            } else if (slot == 1) {
-                two = lane == rq ? true : two;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();                     // the row maxima were written by other lanes of this wave
-        if (srv_here || (f & WF_DEV) != 0u) {
-            auto rowmax = [&](int slot) {
-                const float4 x = *reinterpret_cast<const float4*>(myred[slot][lane]);
-                return fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w));
-            };
-            TlSummary s = a.summary[il];                     // what the streaming walk left (all zero / none without it)
-            if (srv_here) {
-                s.M_lag = rowmax(0);
-                s.m_enc = m_enc;
-                s.M_plain = two ? rowmax(1) : s.M_lag;
-            }
-            if (f & WF_DEV) s.M_dev = rowmax(2);
-            a.summary[il] = s;
-        }
-        __builtin_amdgcn_wave_barrier();
+        const bool any = srv_here || (f & WF_DEV) != 0u;
+        if (__ballot(any) == 0ull) continue;                 // (almost every batch)
+        TlSummary s{0.0f, -1, 0.0f, 0.0f};
+        if (any) s = a.summary[il];                          // what the streaming walk left (all zero / none without it)
+        walk_batch<TW_NV>(tr, n_tok, first, il, f, srv_here, tau, kt, lc, rows[wave], s);
+        if (any) a.summary[il] = s;
     }
+}
+
+// Small traces (disco_small): the policy table staged, the flags, and every walk with the exact walker, in one launch of a
+// few requests per wave.  What counts there is the longest request's walk: 512 tokens per iteration.
+constexpr int SW_NV = 2;
+
+__global__ __launch_bounds__(TW_BLOCK) void k_small_walk(TraceView tr, i64 n_tok, PolTable host, const disco_policy* __restrict__ device,
+                                                         int P, int rb, float tau, float kt, TlSummary* __restrict__ summary,
+                                                         disco_policy* __restrict__ staged, unsigned* __restrict__ tickets,
+                                                         u64* __restrict__ totals)
+{
+    __shared__ disco_policy sp[DISCO_MAX_COLS];
+    __shared__ __align__(16) WalkRows rows[TW_WAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if ((int)threadIdx.x < P) sp[threadIdx.x] = device ? device[threadIdx.x] : host.p[threadIdx.x];
+    __syncthreads();
+    if (blockIdx.x == 0 && wave == 0 && staged != nullptr) {          // as the launch that stages the table elsewhere
+        const bool any_buffer = __ballot(lane < P && sp[lane < P ? lane : 0].mig_mode == DISCO_MIG_BUFFER) != 0ull;
+        if (lane < P) staged[lane] = sp[lane];
+        tickets[lane] = (lane == DISCO_FLAG_BUFFER && any_buffer) ? 1u : 0u;
+    }
+    if (totals != nullptr)
+        for (unsigned w = blockIdx.x * (unsigned)TW_BLOCK + threadIdx.x; w < DISCO_NCOPY * 64 * sizeof(MigPartial) / 8; w += gridDim.x * (unsigned)TW_BLOCK)
+            totals[w] = 0ull;
+    const LagConst lc{262144.0f * (kt / tau), 262144.0f * kt, kt >= tau * 0.0009765625f};
+    const i64 first = ((i64)blockIdx.x * TW_WAVES + wave) * rb, il = first + lane;
+    if (first >= tr.n_req) return;
+    const bool valid = lane < rb && il < tr.n_req;
+    unsigned f = 0u;
+    if (valid) {
+        const int l = tr.l[il];
+        const float s = tr.s[il], gd = tr.g ? tr.g[il] : tr.g_s, gap = tr.tbt ? tr.tbt[il] : 0.0f;
+        u64 m[TL_KINDS];
+        request_sets(sp, P, l, s, __fmaf_rn((float)l, tr.k ? tr.k[il] : tr.k_s, tr.c), il, m);
+        f = walks_needed(m, tr.arr != nullptr, gap, gd, tau);
+    }
+    TlSummary s{0.0f, -1, 0.0f, 0.0f};
+    walk_batch<SW_NV>(tr, n_tok, first, il, f, (f & (WF_LAG | WF_PLAIN)) != 0u, tau, kt, lc, rows[wave], s);
+    if (valid) summary[il] = s;
 }
 
 // Summaries of a trace without a token array: nothing streamed, every field at its closed-form value.
@@ -646,6 +704,82 @@ __global__ __launch_bounds__(TA_BLOCK) void k_tl_accum(TraceView tr, const disco
     }
 }
 
+// Small traces, workgroup = column: the totals of all its pairs, those with a buffer hand-off included, straight into its
+// accumulator.  Up to SA_REQ requests: 5 us for 500, 22 for 32 000, where k_tl_accum takes 12 and a last workgroup that folds
+// the totals 4.
+constexpr int SA_REQ = 16384;
+__global__ __launch_bounds__(TA_BLOCK) void k_small_accum(TraceView tr, const disco_policy* __restrict__ pol, float tau,
+                                                          const TlSummary* __restrict__ summary, const BufSummary* __restrict__ bufsum,
+                                                          disco_accum* __restrict__ acc)
+{
+    __shared__ u64 part[8][TA_WAVES];
+    const int c = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6, n_req = (int)tr.n_req;
+    const disco_policy p = pol[c];
+    const bool dev_constrained = p.mode == DISCO_MODE_DEVICE_CONSTRAINED || p.mode == DISCO_MODE_STOCH_DEVICE;
+    const bool may_lag = p.mig_mode == DISCO_MIG_LAG, may_buf = p.mig_mode == DISCO_MIG_BUFFER;
+    // tokens from the server and from the device, device and server re-prefill, hand-offs, TBT values, delayed tokens
+    u64 x[7] = {0, 0, 0, 0, 0, 0, 0};
+    double tlast = 0.0;
+    constexpr int B = 4;                                     // strides whose loads are in flight together
+#pragma unroll 1
+    for (int base = t; base < n_req; base += B * TA_BLOCK) {
+        int l[B], n[B], m_s[B], m_d[B], delay_s[B], delay_d[B];
+        float s[B], k[B], M_s[B], M_d[B];
+        TlSummary sum[B];
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+            const int i = base + q * TA_BLOCK, at = i < n_req ? i : base;
+            l[q] = tr.l[at]; n[q] = tr.n[at]; s[q] = tr.s[at]; k[q] = tr.k ? tr.k[at] : tr.k_s;
+            sum[q] = summary[at];
+            m_s[q] = m_d[q] = -1; delay_s[q] = delay_d[q] = 0; M_s[q] = M_d[q] = 0.0f;
+            if (may_buf) {
+                // (written for the requests with such a pair alone, and read for no other)
+                const BufSummary* b = &bufsum[at];
+                M_s[q] = b->M_s; m_s[q] = b->m_s; delay_s[q] = b->delay_s; delay_d[q] = b->delay_d; M_d[q] = b->M_d; m_d[q] = b->m_d;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+            const int i = base + q * TA_BLOCK;
+            if (i >= n_req) continue;
+            unsigned dec; float ttft;
+            dispatch_pair(p, l[q], s[q], __fmaf_rn((float)l[q], k[q], tr.c), i, dec, ttft);
+            const bool dev = (dec & 4u) != 0u, buf = may_buf && dev == dev_constrained, lag = !dev && may_lag;
+            // first token of the other endpoint, -1: no hand-off
+            int m = lag ? summary_m(sum[q].m_enc) : -1;
+            float M = dev ? sum[q].M_dev : (lag ? sum[q].M_lag : sum[q].M_plain);
+            if (buf) {
+                const int last = summary_m(dev ? m_d[q] : m_s[q]);
+                m = last >= 0 ? last + 1 : -1;
+                M = dev ? M_d[q] : M_s[q];
+                if (last >= 0) x[6] += (u64)(dev ? delay_d[q] : delay_s[q]);
+            }
+            const u64 src = (u64)(m >= 0 ? m : n[q]), all = (u64)n[q];
+            x[0] += dev ? all - src : src;
+            x[1] += dev ? src : all - src;
+            const u64 again = m >= 0 ? (u64)l[q] + src : 0ull;
+            x[2] += dev ? 0ull : again;
+            x[3] += dev ? again : 0ull;
+            x[4] += m >= 0 ? 1ull : 0ull;
+            x[5] += (u64)(n[q] - 1);
+            tlast += (double)__fmaf_rn((float)(n[q] - 1), tau, M);
+        }
+    }
+#pragma unroll
+    for (int f = 0; f < 7; ++f) { const u64 v = wave_sum_u64(x[f]); if (lane == 0) part[f][wave] = v; }
+    tlast = wave_sum_f64(tlast);
+    if (lane == 0) part[7][wave] = (u64)__double_as_longlong(tlast);
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int f = 0; f < 7; ++f) x[f] = wave_sum_u64(lane < TA_WAVES ? part[f][lane] : 0ull);
+    tlast = wave_sum_f64(lane < TA_WAVES ? __longlong_as_double((long long)part[7][lane]) : 0.0);
+    if (lane != 0) return;
+    disco_accum* o = &acc[c];
+    o->m_s_dec = (i64)x[0]; o->m_d_dec = (i64)x[1]; o->m_d_repre = (i64)x[2]; o->m_s_repre = (i64)x[3];
+    o->n_migrated = (i64)x[4]; o->tbt_count = (i64)x[5]; o->delay_sum = (i64)x[6]; o->tlast_sum = tlast;
+}
+
 // ----------------------------------------------------- per-pair outputs ----
 
 struct MatArgs {
@@ -740,36 +874,72 @@ void disco_launch_tl_walk(const TraceView& v, i64 n_tok, const disco_policy* pol
     hipLaunchKernelGGL(k_tl_walk_rest, dim3((unsigned)rb_), dim3(TW_BLOCK), 0, stream, v, n_tok, w, mem ? 1 : 0);
 }
 
+void disco_launch_small_walk(const TraceView& v, i64 n_tok, const PolTable& host, const disco_policy* device, int P, float tau, float kt,
+                             void* summary, disco_policy* staged, unsigned* tickets, MigPartial* totals, hipStream_t stream)
+{
+    // one request per wave as long as they take no more than eight workgroups per CU
+    int rb = 1;
+    while ((v.n_req + (i64)TW_WAVES * rb - 1) / ((i64)TW_WAVES * rb) > 2048) rb <<= 1;
+    i64 b = (v.n_req + (i64)TW_WAVES * rb - 1) / ((i64)TW_WAVES * rb);
+    if (b < 1) b = 1;
+    hipLaunchKernelGGL(k_small_walk, dim3((unsigned)b), dim3(TW_BLOCK), 0, stream, v, n_tok, host, device, P, rb, tau, kt,
+                       (TlSummary*)summary, staged, tickets, (u64*)totals);
+}
+
+static void launch_accum(const TraceView& v, const disco_policy* pol, const TimelineArgs& a, MigPartial* totals, hipStream_t stream)
+{
+    if (v.n_req <= 0) return;
+    AccumArgs c;
+    memset(&c, 0, sizeof(c));
+    c.tau = a.tau; c.P = a.P;
+    c.G = 1;
+    while (c.G < a.P) c.G <<= 1;
+    c.summary = (const TlSummary*)a.summary;
+    c.totals = totals;
+    i64 b = ((v.n_req + 63) / 64 + TA_WAVES - 1) / TA_WAVES;
+    if (b > 256) b = 256;
+    b /= disco_grid_divisor();
+    if (b < 1) b = 1;
+    hipLaunchKernelGGL(k_tl_accum, dim3((unsigned)b), dim3(TA_BLOCK), 0, stream, v, pol, c);
+}
+
+static void launch_mat(const TraceView& v, const disco_policy* pol, const TimelineArgs& a, hipStream_t stream)
+{
+    if (v.n_req <= 0 || !(a.mig_idx || a.n_src_tok || a.t_last || a.delay_num)) return;
+    MatArgs m;
+    memset(&m, 0, sizeof(m));
+    m.tau = a.tau; m.P = a.P; m.summary = (const TlSummary*)a.summary;
+    m.bufsum = (const BufSummary*)a.bufsum; m.buffer_flag = a.buffer_flag;
+    m.mig_idx = a.mig_idx; m.n_src_tok = a.n_src_tok; m.t_last = a.t_last; m.delay_num = a.delay_num;
+    i64 mb = (v.n_req + 255) / 256;
+    if (mb > 4096) mb = 4096;
+    hipLaunchKernelGGL(k_tl_mat, dim3((unsigned)mb), dim3(256), 0, stream, v, pol, m);
+}
+
+void disco_launch_small_stats(const TraceView& v, i64 n_tok, const PolTable& host, const disco_policy* device, disco_policy* staged,
+                              unsigned* tickets, const TimelineArgs& a, MigPartial* totals, hipStream_t stream)
+{
+    const bool by_column = v.n_req <= SA_REQ;
+    disco_launch_small_walk(v, n_tok, host, device, a.P, a.tau, a.kt, a.summary, staged, tickets, by_column ? nullptr : totals, stream);
+    if (by_column) {
+        bool buffer = device != nullptr;               // (a table on the device may have such a column)
+        for (int j = 0; j < a.P && !buffer; ++j) buffer = host.p[j].mig_mode == DISCO_MIG_BUFFER;
+        if (buffer) disco_launch_tl_stats_buf(v, n_tok, staged, a, nullptr, stream);
+        hipLaunchKernelGGL(k_small_accum, dim3((unsigned)a.P), dim3(TA_BLOCK), 0, stream, v, staged, a.tau, (const TlSummary*)a.summary,
+                           (const BufSummary*)a.bufsum, a.acc);
+    } else {
+        launch_accum(v, staged, a, totals, stream);
+        disco_launch_tl_stats_buf(v, n_tok, staged, a, totals, stream);
+    }
+    launch_mat(v, staged, a, stream);
+}
+
 void disco_launch_tl_stats_fast(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                 MigPartial* totals, hipStream_t stream)
 {
     disco_launch_tl_walk(v, n_tok, pol, a.P, a.tau, a.kt, a.wflags, a.summary, a.counter, stream, nullptr, nullptr);
-    if (v.n_req > 0) {
-        AccumArgs c;
-        memset(&c, 0, sizeof(c));
-        c.tau = a.tau; c.P = a.P;
-        c.G = 1;
-        while (c.G < a.P) c.G <<= 1;
-        c.summary = (const TlSummary*)a.summary;
-        c.totals = totals;
-        i64 b = ((v.n_req + 63) / 64 + TA_WAVES - 1) / TA_WAVES;
-        if (b > 256) b = 256;
-        b /= disco_grid_divisor();
-        if (b < 1) b = 1;
-        hipLaunchKernelGGL(k_tl_accum, dim3((unsigned)b), dim3(TA_BLOCK), 0, stream, v, pol, c);
-    }
+    launch_accum(v, pol, a, totals, stream);
     // the pairs with a buffer hand-off, if any; its last workgroup turns the totals into the accumulators
     disco_launch_tl_stats_buf(v, n_tok, pol, a, totals, stream);
-    if (v.n_req > 0) {
-        if (a.mig_idx || a.n_src_tok || a.t_last || a.delay_num) {
-            MatArgs m;
-            memset(&m, 0, sizeof(m));
-            m.tau = a.tau; m.P = a.P; m.summary = (const TlSummary*)a.summary;
-            m.bufsum = (const BufSummary*)a.bufsum; m.buffer_flag = a.buffer_flag;
-            m.mig_idx = a.mig_idx; m.n_src_tok = a.n_src_tok; m.t_last = a.t_last; m.delay_num = a.delay_num;
-            i64 mb = (v.n_req + 255) / 256;
-            if (mb > 4096) mb = 4096;
-            hipLaunchKernelGGL(k_tl_mat, dim3((unsigned)mb), dim3(256), 0, stream, v, pol, m);
-        }
-    }
+    launch_mat(v, pol, a, stream);
 }

@@ -362,3 +362,17 @@ def test_analytic_timelines_of_small_traces(B, oracle, n_req, length, tau):
         tr["n_tok"] = int(tr["tok_off"][-1])
     specs = [dict(mode=0, l_th=x, mig_mode=1) for x in (0, 400, 1500, 5000)] + [dict(mode=1, l_th=-1, w_tail=DI.f32(0.3), mig_mode=0)]
     check_stats(B, oracle, tr, specs, DI.COST_S, tau=DI.f32(tau), kappa=DI.KAPPA_LAG, quantiles=((1, 100), (50, 100), (99, 100)))
+
+
+# token timelines of small traces: flags and exact walks in one launch, totals by column up to 16 384 requests and by workgroup
+# beyond, every kind of hand-off; from 32 769 on the streaming walk
+@pytest.mark.parametrize("n_req,max_out,tokens", [(0, 5, True), (1, 3, True), (3, 2100, True), (8195, 30, True), (16_384, 12, False), (16_385, 12, True),
+                                                  (32_768, 6, False), (32_769, 6, True)])
+def test_timelines_of_small_traces(B, oracle, n_req, max_out, tokens):
+    print(f"timelines of small traces: n_req={n_req} max_out={max_out} tokens={tokens}", flush=True)
+    tr = slow_prefill(DI.handmade_trace(500 + n_req, n_req, tokens=tokens, max_out=max_out, stall_p=0.05), 16.0)
+    for mode in (0, 1):
+        specs = [dict(mode=mode, l_th=x, w_tail=DI.f32(0.05 * j), mig_mode=j % 3) for j, x in enumerate((-1, 300, 900, 1500, 2900))]
+        cost = DI.COST_D if mode else DI.COST_S
+        check_migration(B, oracle, tr, specs, DI.TAU, DI.KAPPA_LAG, delivered_col=None, cost=cost)
+        check_stats(B, oracle, tr, specs, cost, tau=DI.TAU, kappa=DI.KAPPA_LAG)
