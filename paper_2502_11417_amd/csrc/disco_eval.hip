@@ -94,7 +94,7 @@ __device__ void select_init(const SelInit& si, int which, int P, const disco_pol
             g.plan.npass = 0; g.plan.pad = 0;
             for (int i = 0; i < DISCO_MAX_PASS; ++i) { g.plan.shift[i] = 0; g.plan.width[i] = 0; }
             TlSel& tl = S->tl;
-            tl.ncls = 0; tl.nwalk = 0; tl.walk_mask = 0ull; tl.error = 0; tl.nlist = 0u; tl.nlist_back = 0u;
+            tl.ncls = 0; tl.nwalk = 0; tl.walk_mask = 0ull; tl.error = 0; tl.nlist = 0u; tl.nlist_back = 0u; tl.left_fast = 0u; tl.left_buf = 0u;
             TlPlan& start = tl.plan[0];
             start.left = 31; start.shift = 0; start.width = 0; start.G = 0; start.window = 0; start.key_lo = 0u; start.fallback = 0; start.reset = 0;
             for (int i = 0; i < DISCO_TBT_MAX_PASS; ++i) tl.restart[i] = 0;
@@ -805,9 +805,11 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
             unsigned* slices = (unsigned*)(ws + L.slices);
             disco_launch_tl_assign(v, dpol, P, tl->tau, a.summary, S, a.bufsum, a.desc, a.list, slices, L.total - L.slices, a.ppcnt, gh,
                                    a.dhist, stream);
+            // (the slices of the assignment have been added up by then; the second set of bins lies in front of the pools)
+            const size_t bins = DISCO_GHIST_WORDS * sizeof(unsigned);
+            disco_launch_tl_runs(v, trace->n_tok, a, ws + L.slices + bins, L.total - L.slices - bins, stream);
             for (int pass = 0; pass < DISCO_TBT_MAX_PASS; ++pass) {
-                // the passes take turns with two sets of bins: one is counted into while the other one is cleared (the
-                // slices of the assignment have been added up by then)
+                // the passes take turns with two sets of bins: one is counted into while the other one is cleared
                 a.pass = pass;
                 a.ghist = pass & 1 ? slices : gh;
                 a.gclear = pass & 1 ? gh : slices;

@@ -6,6 +6,12 @@
 // source handing off to the device, _dev: device source handing off to the server.
 struct BufCostArgs { double dc_srv, cp_srv, dc_dev, cp_dev; };
 
+// Gaps counted per value: pool b (`cap` entries, the first one its header: entries written, 0) is filled by workgroup b of the
+// launch that makes the runs and read by every pass.  An entry: bit pattern of the gap, number of such gaps in the low
+// RUN_COUNT_BITS bits of the other word, above them the LDS row of the timeline.
+constexpr int RUN_COUNT_BITS = 26;
+struct RunPool { uint2* pool; unsigned cap; int n; };
+
 struct TimelineArgs {
     float tau, kt;            // pacing interval, kappa_lag * tau
     int P, nq, pass;          // -1: statistics pass, >= 0: TBT histogram pass
@@ -25,6 +31,7 @@ struct TimelineArgs {
     u64* desc;                     // per request: LDS rows of its timelines with tokens to walk, one byte per kind (histogram passes)
     void* bufsum;                  // BufSummary per request: what the walk of its buffer hand-off timelines found
     unsigned* list;                // the requests that have such a timeline, one word each (histogram passes)
+    RunPool runs;                  // gaps of the timelines that need no walk (histogram passes)
 };
 
 // How the last workgroup of a dispatch pass hands on the column totals.
@@ -135,4 +142,7 @@ void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy
 void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, float tau, const void* summary, SelState* S,
                             const void* bufsum, u64* desc, unsigned* list, unsigned* slices, size_t slices_bytes,
                             unsigned* ppcnt, unsigned* ghist, unsigned* dhist, hipStream_t stream);
+// After the assignment: the gaps of the listed timelines into pools in `scratch`, as far as they fit (a.runs on return); their
+// descriptors then name them no more.
+void disco_launch_tl_runs(const TraceView& v, i64 n_tok, TimelineArgs& a, void* scratch, size_t scratch_bytes, hipStream_t stream);
 void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a, hipStream_t stream);

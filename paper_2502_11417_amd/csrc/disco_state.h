@@ -128,7 +128,7 @@ struct TlSel {
     int error;                     // a column set could not be placed (never expected)
     unsigned nlist;                // requests with a timeline whose tokens are walked: entries at the front of the walk list
     unsigned nlist_back;           // ... and entries at its back (the short requests, see walk_list_entry)
-    int pad;
+    unsigned left_fast, left_buf;  // listed timelines whose tokens the passes walk: streaming kinds, buffer hand-off kinds
     TlPlan plan[DISCO_TBT_MAX_PASS + 1];         // [0]: where the selection starts; [1 + p]: pass p
     int restart[DISCO_TBT_MAX_PASS];             // pass p missed the window
     // device-wide hash table of the column sets (classification): every workgroup enters its distinct sets, those of

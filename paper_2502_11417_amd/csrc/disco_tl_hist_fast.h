@@ -8,6 +8,7 @@
 namespace {
 
 constexpr int TH_BLOCK = 1024;               // histogram workgroups: 16 waves share 64 KB of bins
+constexpr unsigned HIST_POOL_BLOCKS = 128;   // (512: 18 and 23 us for the two passes of 10^6 requests x 8 columns, 128: 13 and 14)
 
 // ------------------------------------------------------------------ plan ---
 
@@ -246,14 +247,18 @@ __device__ __forceinline__ void load_first(const float* __restrict__ arr, i64 of
 constexpr u64 DESC_NONE5 = 0xFFFFFFFFFFull;
 constexpr unsigned DESC_NONE = 0xFFFFFFu;
 
-// One histogram pass of the class-mode TBT selection, workgroup `bid` of `nblk`: the descriptors say which
-// timelines have tokens to walk (few: the others were counted analytically once) and the walk list names their
+// One histogram pass of the class-mode TBT selection, workgroup `bid` of `nblk`: the gaps of the pools, then the timelines
+// that have tokens to walk (few: those whose gaps fill no pool, disco_tl_runs.h), by the descriptors; the walk list names their
 // requests.  `smem`: DISCO_TL_HIST_WORDS words of LDS.
 __device__ __forceinline__ void tl_hist_fast_body(unsigned* smem, const TraceView& tr, i64 n_tok, int align, const HistArgs& a,
                                                   const TlPlan& pl, unsigned bid, unsigned nblk)
 {
     const TlSel* tl = &a.S->tl;
     const int width = __builtin_amdgcn_readfirstlane(pl.width);
+    // (a pass over the pools alone takes fewer workgroups: each one clears its bins and adds them to the device-wide ones)
+    const bool walks = tl->left_fast != 0u;
+    if (!walks && nblk > HIST_POOL_BLOCKS) nblk = HIST_POOL_BLOCKS;
+    if (bid >= nblk) return;
     if (width <= 0 || pl.fallback) return;        // selection finished, or per-slot histograms (other kernel)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ncls = tl->ncls, nwalk = tl->nwalk;
@@ -261,11 +266,12 @@ __device__ __forceinline__ void tl_hist_fast_body(unsigned* smem, const TraceVie
     const int words = (h.G * nwalk) << width;
     for (int i = threadIdx.x; i < words; i += TH_BLOCK) smem[i] = 0u;
     __syncthreads();
+    hist_runs(h, a.runs, bid, nblk);
     const float tau = a.tau, kt = a.kt;
     const bool mem = tr.arr != nullptr;
     // the walk list is shared out in batches of rb entries (lane = entry) so that every wave gets some
     const i64 nwaves = (i64)nblk * (TH_BLOCK / 64);
-    const i64 nfront = (i64)tl->nlist, nlist = nfront + (i64)tl->nlist_back;
+    const i64 nfront = (i64)tl->nlist, nlist = walks ? nfront + (i64)tl->nlist_back : 0;
     i64 rb = (nlist + nwaves - 1) / nwaves;
     rb = rb < 1 ? 1 : (rb > 64 ? 64 : rb);
     // wave w of a round takes the entries w, w + W, ... (lane = which of them), W = waves x rounds needed

@@ -164,6 +164,7 @@ struct HistArgs {
     unsigned* ghist;
     const u64* desc;               // per request: LDS rows of its timelines that have tokens to walk (one byte per kind)
     const unsigned* list;          // requests with such a timeline (see walk_list_entry)
+    RunPool runs;                  // gaps of the timelines that need no walk in the passes (disco_tl_runs.h)
 };
 
 // Digit of this pass and the rows of the LDS histogram.
@@ -241,6 +242,33 @@ __device__ __forceinline__ void hist_keys(const HistCtx& h, const unsigned key[4
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         if (pend[q]) atomicAdd(&h.hist[idx[q]], 1u);
+}
+
+__device__ __forceinline__ void hist_count(const HistCtx& h, unsigned row_base, unsigned gap_bits, unsigned count)
+{
+    const unsigned kq = tbt_key(gap_bits, h.key_lo, h.key_cap), hi = kq >> h.up;
+    unsigned g = 0;
+    bool hit = hi == h.grp_prefix[0];
+#pragma unroll
+    for (int k = 1; k < DISCO_MAX_GRP; ++k) {
+        const bool hk = k < h.G && hi == h.grp_prefix[k] && !hit;
+        g = hk ? (unsigned)k : g;
+        hit = hit || hk;
+    }
+    if (hit && count) atomicAdd(&h.hist[g * h.stride + row_base + ((kq >> h.shift) & ((1u << h.width) - 1u))], count);
+}
+
+// The pools of workgroup `bid` of `nblk` into the LDS histogram.
+__device__ __forceinline__ void hist_runs(const HistCtx& h, const RunPool& r, unsigned bid, unsigned nblk)
+{
+    for (unsigned b = bid; b < (unsigned)r.n; b += nblk) {
+        const uint2* mine = r.pool + (size_t)b * r.cap;
+        const unsigned cnt = mine[0].x;
+        for (unsigned i = 1u + threadIdx.x; i <= cnt; i += blockDim.x) {
+            const uint2 e = mine[i];
+            hist_count(h, (e.y >> RUN_COUNT_BITS) << h.width, e.x, e.y & ((1u << RUN_COUNT_BITS) - 1u));
+        }
+    }
 }
 
 }  // namespace

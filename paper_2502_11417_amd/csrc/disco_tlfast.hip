@@ -7,7 +7,9 @@
 //                the others get their histogram row into the request's
 //                descriptor and the request into the walk list
 //   k_pp_reduce  per-workgroup count slices -> counts per class and length
-//   k_tl_hist    one pass over the walk list (workgroup body and walker in
+//   k_tl_runs    the listed timelines' gaps, counted per value once
+//                (disco_tl_runs.h)
+//   k_tl_hist    one pass over these and what is left of the walk list (workgroup body and walker in
 //                disco_tl_hist_fast.h): a wave walks one request at a time in
 //                chunks of 256 tokens, four consecutive tokens per lane (one
 //                16-byte load per lane and chunk, the next chunk's load
@@ -31,7 +33,7 @@
 // only picks the timeline of its dispatch winner.
 #include <string.h>
 
-#include "disco_tl_hist_fast.h"
+#include "disco_tl_runs.h"
 
 namespace {
 
@@ -123,7 +125,10 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
     const int ncls = fallback ? DISCO_MAX_CLS : (cl.total > 0 ? cl.total : 1);
     if (blockIdx.x == 0 && threadIdx.x < 64) {
         // for the passes; gaps sit just above the pacing interval (down to a few thousand ulps below it after rounding): a
-        // 21-bit window of keys is tried first (not at other prices: the passes of 128 slots would not suffice for a second start)
+        // window of keys is tried first (not at other prices: the passes of 128 slots would not suffice for a second start), 21
+        // bits or as many as two digits have if the LDS rows of the walked classes leave room for digits of less than 11 bits.
+        // (A third walk for the last bit of 12 wait columns: 49 us of 570 with 10^5 requests, 64 of 400 with 30 000; a rank
+        // beyond the shorter window costs a pass more than one beyond the longer.)
         const int lane = threadIdx.x;
         TlSel& g = S->tl;
         const u64 wm = __ballot(cl.walk[lane] != 0);
@@ -132,10 +137,12 @@ __global__ __launch_bounds__(AS_BLOCK) void k_tl_assign(TraceView tr, const disc
         if (cl.walk[lane]) g.slot_cls[cl.slot[lane]] = (unsigned char)lane;
         if (lane == 0) {
             const unsigned tb = f2u(tau);
-            const bool window = tb >= 8192u && (over & 2) == 0;
-            g.ncls = ncls; g.walk_mask = wm; g.nwalk = __popcll(wm);
+            const int nwalk = __popcll(wm);
+            const int wl = fit_width(nwalk > 0 ? nwalk : 1, DISCO_TL_HIST_WORDS), wg = fit_width(ncls, DISCO_GHIST_WORDS);
+            const int two = 2 * (wl < wg ? wl : wg), window = tb < 8192u || (over & 2) != 0 ? 0 : (two < 21 ? two : 21);
+            g.ncls = ncls; g.walk_mask = wm; g.nwalk = nwalk;
             TlPlan& start = g.plan[0];
-            start.window = window ? 21 : 0; start.left = window ? 21 : 31; start.key_lo = window ? tb - 8192u : 0u;
+            start.window = window; start.left = window ? window : 31; start.key_lo = window ? tb - 8192u : 0u;
             start.fallback = fallback ? 1 : 0;
         }
     }
@@ -281,6 +288,98 @@ __global__ __launch_bounds__(1024) void k_pp_reduce(const SelState* S, int nslic
     }
 }
 
+// The gaps of the listed timelines, per value, into the workgroup's pool; the descriptors then name those alone that are left to
+// the passes.  List entries are dealt as in the passes.  Bound by vector issue (some 800 instructions per request): 56 us for the
+// 17 M tokens of 35 000 requests with lag hand-offs (10^6 requests x 8 columns), 43 with buffer hand-offs, after which a pass
+// takes 13 us; walked token by token a pass took 59 and 69 us.  10^5 requests x 12 wait columns: 26 us, and 18 instead of 45 a pass.
+constexpr int TR_BLOCK = 512, TR_WAVES = TR_BLOCK / 64;
+constexpr int TR_MAX_BLOCKS = 768;           // what the chip holds at once (six waves per SIMD)
+
+__global__ __launch_bounds__(TR_BLOCK, 6) void k_tl_runs(TraceView tr, i64 n_tok, int align, float tau, float kt, SelState* S,
+                                                      u64* __restrict__ desc_rw, const unsigned* __restrict__ list,
+                                                      const TlSummary* __restrict__ summary, const BufSummary* __restrict__ bufsum, RunPool runs)
+{
+    __shared__ __align__(16) RunLds rl[TR_WAVES];
+    __shared__ unsigned used;
+    TlSel& tl = S->tl;
+    uint2* pool = runs.pool + (size_t)blockIdx.x * runs.cap;
+    if (threadIdx.x == 0) used = 0u;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const i64 nfront = (i64)tl.nlist, nlist = tl.plan[0].fallback ? 0 : nfront + (i64)tl.nlist_back;
+    const i64 nwaves = (i64)gridDim.x * (TR_WAVES);
+    i64 rb = (nlist + nwaves - 1) / nwaves;
+    rb = rb < 1 ? 1 : (rb > 64 ? 64 : rb);
+    const i64 nround = (nlist + rb * nwaves - 1) / (rb * nwaves);
+    for (i64 rnd = 0; rnd < nround; ++rnd) {
+        const i64 j = rnd * rb * nwaves + (i64)blockIdx.x * (TR_WAVES) + wave + (i64)lane * nwaves;
+        const bool mine = lane < rb && j < nlist;
+        const i64 i = mine ? (i64)walk_list_entry(list, tr.n_req, nfront, j) : 0;
+        const u64 desc = mine ? desc_rw[i] & DESC_NONE5 : DESC_NONE5;
+        u64 left = desc;
+        int l_v = 0, n_v = 1, m_v = -1;
+        float k_v = tr.k_s, gd_v = tr.g_s, gap_v = 0.0f;
+        i64 off_v = 0;
+        Handoff from_srv{-1, 0.0f, 0.0f}, from_dev{-1, 0.0f, 0.0f};
+        if (mine) {
+            l_v = tr.l[i]; n_v = tr.n[i];
+            if (tr.k) k_v = tr.k[i];
+            if (tr.g) gd_v = tr.g[i];
+            if (tr.off) off_v = tr.off[i];
+            if (tr.tbt) gap_v = tr.tbt[i];
+            if (((desc >> (8 * TL_SRV_LAG)) & 0xFFull) != 0xFFull) m_v = summary_m(summary[i].m_enc);
+            const bool sb = ((desc >> (8 * TL_SRV_BUF)) & 0xFFull) != 0xFFull, db = ((desc >> (8 * TL_DEV_BUF)) & 0xFFull) != 0xFFull;
+            if (sb || db) {
+                const BufSummary bs = bufsum[i];
+                const float s_ttft = tr.s[i];
+                from_srv = handoff_at(false, sb ? summary_m(bs.m_s) : -1, tr.arr, off_v, l_v, s_ttft, k_v, tr.c, gap_v, gd_v);
+                from_dev = handoff_at(true, db ? summary_m(bs.m_d) : -1, tr.arr, off_v, l_v, s_ttft, k_v, tr.c, gap_v, gd_v);
+            }
+        }
+        u64 walkers = __ballot(mine && paced_ok(tau, n_v));
+        // requests that read the token array: all but those of the device's own timeline alone
+        const u64 memw = tr.arr != nullptr ? __ballot((desc >> 8) != (DESC_NONE5 >> 8)) : 0ull;
+        float ahead[4] = {0.f, 0.f, 0.f, 0.f};
+        auto load_ahead = [&](u64 todo) {
+            if (!todo) return;
+            const int r = __ffsll((long long)todo) - 1;
+            if ((memw >> r) & 1ull) load_first(tr.arr, (i64)bcast_u64((u64)off_v, r), bcast_i(n_v, r), n_tok, align, lane, ahead);
+        };
+        load_ahead(walkers);
+        while (walkers) {
+            const int rq = __ffsll((long long)walkers) - 1;
+            walkers &= walkers - 1;
+            const u64 dsc = bcast_u64(desc, rq);
+            const int n = bcast_i(n_v, rq), l = bcast_i(l_v, rq);
+            const float gd = bcast_f(gd_v, rq), gap = bcast_f(gap_v, rq), k = bcast_f(k_v, rq);
+            const i64 off = tr.arr ? (i64)bcast_u64((u64)off_v, rq) : 0;
+            const float chunk[4] = {ahead[0], ahead[1], ahead[2], ahead[3]};
+            load_ahead(walkers);                             // the next request's first chunk, while this one is walked
+#pragma unroll 1
+            for (int kind = 0; kind < TL_KINDS; ++kind) {
+                const unsigned row = (unsigned)(dsc >> (8 * kind)) & 0xFFu;
+                if (row == 0xFFu) continue;
+                const Handoff& v = kind == TL_DEV_BUF ? from_dev : from_srv;
+                const Handoff ho{0, bcast_f(v.base, rq), bcast_f(v.a_m, rq)};
+                // first token of the target
+                const int last = kind >= TL_SRV_BUF ? bcast_i(v.m, rq) : (kind == TL_SRV_LAG ? bcast_i(m_v, rq) - 1 : -2);
+                const int m = last >= 0 ? last + 1 : 0x7FFFFFFF;
+                int ns, n1;
+                if (walk_runs(rl[wave], ns, n1, kind, n, tr.arr, off, n_tok, align, chunk, gap, gd, l, k, tr.c, m, ho, tau, kt, lane) &&
+                    emit_runs(rl[wave], ns, n1, row, tau, pool, runs.cap, &used, lane))
+                    left |= lane == rq ? 0xFFull << (8 * kind) : 0ull;
+            }
+        }
+        if (mine && left != desc) desc_rw[i] = left;
+        constexpr u64 FAST = 0xFFFFFFull;                    // the streaming kinds' bytes
+        const u64 lf = __ballot((left & FAST) != FAST), lb = __ballot((left | FAST) != DESC_NONE5);
+        if (lane == 0 && lf != 0ull) atomicAdd(&tl.left_fast, (unsigned)__popcll(lf));
+        if (lane == 0 && lb != 0ull) atomicAdd(&tl.left_buf, (unsigned)__popcll(lb));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) pool[0] = make_uint2(used < runs.cap ? used : runs.cap - 1u, 0u);
+}
+
 // Plan of a regular pass and its histogram over the walk list (the spare passes run the same body in the kernel that
 // also advances the selection).
 __global__ __launch_bounds__(TH_BLOCK, 8) void k_tl_hist(TraceView tr, i64 n_tok, int align, HistArgs a)
@@ -319,6 +418,30 @@ void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, 
                        ppcnt, ghist, use_lds);
 }
 
+static unsigned hist_blocks(i64 n_req)
+{
+    i64 b = (n_req + TH_BLOCK / 64 - 1) / (TH_BLOCK / 64);        // at most one request per wave
+    if (b < 1) b = 1;
+    if (b > 512) b = 512;                                          // two resident workgroups per CU
+    b /= disco_grid_divisor();
+    return (unsigned)(b < 1 ? 1 : b);
+}
+
+void disco_launch_tl_runs(const TraceView& v, i64 n_tok, TimelineArgs& a, void* scratch, size_t scratch_bytes, hipStream_t stream)
+{
+    i64 b = (v.n_req + TR_WAVES - 1) / TR_WAVES;                   // at most one request per wave
+    if (b < 1) b = 1;
+    if (b > TR_MAX_BLOCKS) b = TR_MAX_BLOCKS;
+    b /= disco_grid_divisor();
+    if (b < 1) b = 1;
+    a.runs.pool = (uint2*)scratch;
+    a.runs.cap = (unsigned)(scratch_bytes / sizeof(uint2) / (size_t)b);
+    a.runs.n = (int)b;
+    const int align = (int)(((uintptr_t)v.arr >> 2) & 3);
+    hipLaunchKernelGGL(k_tl_runs, dim3((unsigned)b), dim3(TR_BLOCK), 0, stream, v, n_tok, align, a.tau, a.kt, a.S, a.desc, a.list,
+                       (const TlSummary*)a.summary, (const BufSummary*)a.bufsum, a.runs);
+}
+
 void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                hipStream_t stream)
 {
@@ -328,11 +451,7 @@ void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy
     h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass;
     h.S = a.S; h.ghist = a.ghist;
     h.desc = a.desc; h.list = a.list;
-    i64 b = (v.n_req + TH_BLOCK / 64 - 1) / (TH_BLOCK / 64);      // at most one request per wave
-    if (b < 1) b = 1;
-    if (b > 512) b = 512;                                          // two resident workgroups per CU
-    b /= disco_grid_divisor();
-    if (b < 1) b = 1;
+    h.runs = a.runs;
     const int align = (int)(((uintptr_t)v.arr >> 2) & 3);
-    hipLaunchKernelGGL(k_tl_hist, dim3((unsigned)b), dim3(TH_BLOCK), 0, stream, v, n_tok, align, h);
+    hipLaunchKernelGGL(k_tl_hist, dim3(hist_blocks(v.n_req)), dim3(TH_BLOCK), 0, stream, v, n_tok, align, h);
 }

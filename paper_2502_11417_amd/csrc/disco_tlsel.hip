@@ -375,7 +375,7 @@ __device__ __forceinline__ BufHistArgs buf_hist_args(const TimelineArgs& a)
 {
     BufHistArgs h;
     h.h.tau = a.tau; h.h.kt = a.kt; h.h.P = a.P; h.h.nq = a.nq; h.h.pass = a.pass;
-    h.h.S = a.S; h.h.ghist = a.ghist; h.h.desc = a.desc; h.h.list = a.list;
+    h.h.S = a.S; h.h.ghist = a.ghist; h.h.desc = a.desc; h.h.list = a.list; h.h.runs = a.runs;
     h.bufsum = (const BufSummary*)a.bufsum;
     h.buffer_flag = a.buffer_flag;
     return h;
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(1024) void k_tbt_spare(TraceView tr, i64 n_tok, int
         timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, &pl, bid, g.general);
     } else {
         HistArgs h;
-        h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass; h.S = a.S; h.ghist = a.ghist; h.desc = a.desc; h.list = a.list;
+        h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass; h.S = a.S; h.ghist = a.ghist; h.desc = a.desc; h.list = a.list; h.runs = a.runs;
         tl_hist_fast_body(smem, tr, n_tok, align, h, pl, bid, g.fast);
         __syncthreads();                                // the bins are used again
         if (*a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), pl, bid, g.buf);

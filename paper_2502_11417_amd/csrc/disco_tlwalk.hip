@@ -33,7 +33,7 @@ namespace {
 
 constexpr int TW_BLOCK = 256;                // 4 waves
 constexpr int TW_WAVES = TW_BLOCK / 64;
-constexpr int TW_NV = 1;                     // 16-byte vectors per lane and iteration of the general walker
+constexpr int TW_NV = 1;                     // 16-byte vectors per lane and iteration of the general walker (2 here: 50 us instead of 42 for the 35 000 requests of workload 4)
 
 // ---------------------------------------------------------------- flags ----
 

@@ -376,3 +376,43 @@ def test_timelines_of_small_traces(B, oracle, n_req, max_out, tokens):
         cost = DI.COST_D if mode else DI.COST_S
         check_migration(B, oracle, tr, specs, DI.TAU, DI.KAPPA_LAG, delivered_col=None, cost=cost)
         check_stats(B, oracle, tr, specs, cost, tau=DI.TAU, kappa=DI.KAPPA_LAG)
+
+
+# stretches of tokens that do not move the running maximum are counted by binade of the delivery: pacing intervals whose ratio to
+# the spacing of the floats is an integer or not, maxima on and off half spacings, stretches over one to twenty binades, more
+# of them in a request than wait together, stalls on both sides of a chunk's ends
+@pytest.mark.parametrize("tau", [0.25, 0.2, 0.15, 0.1875, 3.0, 0.0009765625, 1.25e-4])
+@pytest.mark.parametrize("every", [0, 255, 256, 512, 700])
+def test_stretches_of_paced_tokens(B, oracle, tau, every):
+    print(f"paced stretches: tau={tau} every={every}", flush=True)
+    tau = DI.f32(tau)
+    n = np.array([1, 2, 3, 255, 256, 257, 258, 511, 513, 1025, 3000, 5000, 17_001, 25_000])
+    n_req = len(n)
+    tr = DI.handmade_trace(600, n_req, tokens=True, max_out=2)
+    tr["output_len"] = n.astype(np.int32)
+    tr["prompt_len"][:] = 2000
+    tr["srv_ttft"][:] = np.float32(0.1)
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    arr = np.zeros(int(off[-1]), np.float32)
+    for i in range(n_req):
+        t = np.arange(n[i])
+        late = 0.5 * tau * (1 + i) if i % 2 else 0.37 * tau + 0.01 * i          # a first move of the maximum, dyadic or not
+        step = np.where(t >= 2, late, 0.0)
+        if every:
+            step = step + (t // every) * tau * every * (0.75 if i % 3 else 1.03) * (t >= every)
+        arr[off[i]:off[i + 1]] = np.maximum.accumulate((t * (0.25 * tau) + step)).astype(np.float32)
+        arr[off[i]] = 0.0
+    tr.update(n_tok=len(arr), tok_off=off, tok_arr=arr)
+    specs = [dict(mode=0, l_th=0, mig_mode=0), dict(mode=0, l_th=0, mig_mode=1), dict(mode=0, l_th=0, mig_mode=2), dict(mode=0, l_th=5000, mig_mode=0)]
+    check_stats(B, oracle, tr, specs, DI.COST_S, tau=tau, kappa=1e6, quantiles=((1, 100), (50, 100), (90, 100), (999, 1000)))
+    check_stats(B, oracle, tr, specs, DI.COST_S, tau=tau, kappa=DI.KAPPA_LAG, quantiles=((50, 100), (99, 100)))
+
+
+# more gaps than the pools hold: timelines whose entries are taken back are walked in the passes, next to those that fit
+def test_gaps_beyond_the_pools(B, oracle):
+    print("gaps beyond the pools", flush=True)
+    gen = dict(DI.config(4, n_req=600_000, seed=9)["gen"], out_mu=3.4, out_hi=60, gap_stall_p=0.3)
+    tr = oracle.gen_trace(gen)
+    assert tr["n_tok"] * 4 < 1 << 30
+    specs = [dict(mode=0, l_th=0, mig_mode=0), dict(mode=0, l_th=0, mig_mode=1)]
+    check_stats(B, oracle, tr, specs, DI.COST_S, tau=DI.TAU, kappa=DI.KAPPA_LAG)
