@@ -15,160 +15,24 @@
 
 #include <mutex>
 
+#include "disco_final.h"
 #include "disco_launch.h"
+#include "disco_stage.h"
 #include "disco_state.h"
 
 namespace {
 
-// The timeline totals follow the dispatch totals in the same workspace region.
-__host__ __device__ inline MigPartial* tl_totals(u64* totals)
-{
-    return reinterpret_cast<MigPartial*>(totals + DISCO_NCOPY * 64 * 8);
-}
-
-// Start of a selection (all threads of one workgroup): one thread per slot: rank from (num, den, M), empty
-// prefix; plan of the passes.
-struct SelInit {
-    SelState* S; int nq; disco_quantile q[4]; const disco_accum* acc; i64 n_req; int with_tbt;
-    unsigned *ppcnt, *dhist;       // counts of the TBT selection, cleared in the launch that starts it
-    unsigned* ghist;               // ... and its bins (nullable)
-};
-constexpr int STAGE_CLEAR = 61;    // workgroups that clear them
-
-__device__ void select_init(const SelInit& si, int which, int P, const disco_policy* pol)
-{
-    SelState* S = si.S;
-    const int nq = si.nq;
-    const disco_accum* acc = si.acc;
-    const i64 n_req = si.n_req;
-    const disco_quantile qs[4] = {si.q[0], si.q[1], si.q[2], si.q[3]};
-    __shared__ unsigned smin, smax;
-    __shared__ int all_thresholds;
-    if (threadIdx.x == 0) { smin = 0xFFFFFFFFu; smax = 0u; all_thresholds = 1; }
-    __syncthreads();
-    if (which == 0) {
-        // a table of length-threshold columns (Alg. 3) is selected by classes: thresholds in ascending order
-        const int t = threadIdx.x;
-        __shared__ int lth_s[DISCO_MAX_COLS];
-        if (t < P) {
-            if (pol[t].mode != DISCO_MODE_SERVER_CONSTRAINED) all_thresholds = 0;
-            lth_s[t] = pol[t].l_th;
-        }
-        __syncthreads();
-        if (t < P) {
-            const int lth = lth_s[t];
-            int rank = 0;
-            for (int k = 0; k < P; ++k) rank += (lth_s[k] < lth || (lth_s[k] == lth && k < t)) ? 1 : 0;
-            S->tc.sorted_lth[rank] = lth;
-            S->tc.col_of_pos[rank] = (unsigned char)t;
-            S->tc.pos_of_col[t] = (unsigned char)rank;
-        }
-        __syncthreads();
-        if (t == 0) { S->tc.on = all_thresholds; S->tb.on = 0; S->tb.pad = 0; }
-        if (t < DISCO_MAX_SLOTS) { S->tb.fill[t] = 0u; S->tb.of_slot[t] = -1; }
-    }
-    if (which == 0 && (int)threadIdx.x < P) {
-        atomicMin(&smin, acc[threadIdx.x].ttft_min_bits);
-        atomicMax(&smax, acc[threadIdx.x].ttft_max_bits);
-    }
-    __syncthreads();
-    if (which == 0 && threadIdx.x < DISCO_MAX_PASS) {
-        // digits of 8 bits from the top of the range's bits down
-        const unsigned lo = smin <= smax ? smin : 0u, hi = smin <= smax ? smax : 0u;
-        const int i = threadIdx.x, bits = hi != lo ? 32 - __clz(hi - lo) : 0, left = bits - 8 * i;
-        SelGlobal& g = S->g[0];
-        g.plan.width[i] = left <= 0 ? 0 : (left < 8 ? left : 8);
-        g.plan.shift[i] = left <= 8 ? 0 : left - 8;
-        if (i == 0) {
-            g.minb = lo; g.maxb = hi;
-            g.plan.npass = (bits + 7) / 8; g.plan.pad = 0;
-            g.gather_bound = 0ull; g.n_list = 0u; g.gather_error = 0;
-        }
-    }
-    if (which == 1 && threadIdx.x == 0) {
-        SelGlobal g;
-        {
-            // TBT: raw keys; the passes are planned on the device (TlSel)
-            g.minb = 0u; g.maxb = 0x7FFFFFFFu;
-            g.gather_bound = 0ull; g.n_list = 0u; g.gather_error = 0;
-            g.plan.npass = 0; g.plan.pad = 0;
-            for (int i = 0; i < DISCO_MAX_PASS; ++i) { g.plan.shift[i] = 0; g.plan.width[i] = 0; }
-            TlSel& tl = S->tl;
-            tl.ncls = 0; tl.nwalk = 0; tl.walk_mask = 0ull; tl.error = 0; tl.nlist = 0u; tl.nlist_back = 0u; tl.left_fast = 0u; tl.left_buf = 0u;
-            TlPlan& start = tl.plan[0];
-            start.left = 31; start.shift = 0; start.width = 0; start.G = 0; start.window = 0; start.key_lo = 0u; start.fallback = 0; start.reset = 0;
-            for (int i = 0; i < DISCO_TBT_MAX_PASS; ++i) tl.restart[i] = 0;
-        }
-        S->g[which] = g;
-    }
-    if (which == 1) {
-        for (int i = threadIdx.x; i < DISCO_MAX_CLS; i += blockDim.x) S->tl.cls_mask[i] = 0ull;
-        for (int i = threadIdx.x; i < DISCO_CLS_SLOTS; i += blockDim.x) { S->tl.gslot[i] = 0ull; S->tl.gwalk[i] = 0u; }
-        if (threadIdx.x == 0) S->tl.goverflow = 0;
-    }
-    for (int s = threadIdx.x; s < P * nq; s += blockDim.x) {
-        int c = s / nq, qi = s % nq;
-        i64 M = which ? acc[c].tbt_count : n_req;
-        SelSlot sl;
-        sl.M = M;
-        i64 k = M > 0 ? ((i64)qs[qi].num * M + qs[qi].den - 1) / qs[qi].den : 0;
-        if (M > 0 && k < 1) k = 1;
-        if (k > M) k = M;
-        sl.rank = k; sl.k_rem = k; sl.prefix = 0u; sl.done = (M <= 0);
-        S->slot[which][s] = sl;
-    }
-}
-
-
-// Staging of the policy table (wave 0); all 1024 threads also put the tickets and the per-column totals that
-// the workgroups of a pass add into at their identity: the dispatch totals (8 words per column and copy,
-// word-major; word 7 = {min bits, max bits}) and, behind them, the timeline totals (all zero).
-constexpr int STAGE_THREADS = 1024;
-__device__ inline void reset_totals(u64* totals)
-{
-    constexpr int DISP_WORDS = 8 * DISCO_NCOPY * 64, TL_WORDS = DISCO_NCOPY * 64 * (int)(sizeof(MigPartial) / 8);
-    for (int w = threadIdx.x; w < DISP_WORDS + TL_WORDS; w += STAGE_THREADS)
-        totals[w] = (w >= 7 * DISCO_NCOPY * 64 && w < DISP_WORDS) ? 0x00000000FFFFFFFFull : 0ull;
-}
-
-// With a selection state (si.S), the TTFT selection of the statistics (and, if asked, the TBT selection) is started
-// in the same launch by a workgroup of its own (one after the other in one workgroup: 10 us for 8 columns and
-// 12.5 us for 64, now 6 with the clearing and 10).
-__device__ __forceinline__ void stage_table(const disco_policy* src, int P, disco_policy* dst, unsigned* tickets, u64* totals,
-                                            const SelInit& si)
-{
-    if (blockIdx.x > 2) {          // (1 MB and 32 KB per column)
-        const int first = ((int)blockIdx.x - 3) * STAGE_THREADS + (int)threadIdx.x, step = ((int)gridDim.x - 3) * STAGE_THREADS;
-        for (int w = first; w < DISCO_MAX_CLS * (DISCO_PP_NMAX + 1); w += step) si.ppcnt[w] = 0u;
-        for (int w = first; w < P * DISCO_DELAY_BINS; w += step) si.dhist[w] = 0u;
-        if (si.ghist)
-            for (int w = first; w < DISCO_GHIST_WORDS / 4; w += step) reinterpret_cast<uint4*>(si.ghist)[w] = make_uint4(0u, 0u, 0u, 0u);
-        return;
-    }
-    if (blockIdx.x > 0) {
-        select_init(si, (int)blockIdx.x - 1, P, src);
-        return;
-    }
-    const int i = threadIdx.x;
-    if (i < 64) {
-        if (i < P) dst[i] = src[i];
-        const bool any_buffer = __ballot(i < P && src[i < P ? i : 0].mig_mode == DISCO_MIG_BUFFER) != 0ull;
-        tickets[i] = (i == DISCO_FLAG_BUFFER && any_buffer) ? 1u : 0u;
-    }
-    reset_totals(totals);
-}
-
 __global__ __launch_bounds__(STAGE_THREADS) void k_store_policies(PolTable t, int P, disco_policy* dst, unsigned* tickets, u64* totals,
                                                                   SelInit si)
 {
-    stage_table(t.p, P, dst, tickets, totals, si);
+    stage_table(t.p, P, dst, tickets, totals, si, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // (dst may be src: the selection's workgroup then reads what the first one writes back unchanged)
 __global__ __launch_bounds__(STAGE_THREADS) void k_copy_policies(const disco_policy* src, int P, disco_policy* dst, unsigned* tickets, u64* totals,
                                                                  SelInit si)
 {
-    stage_table(src, P, dst, tickets, totals, si);
+    stage_table(src, P, dst, tickets, totals, si, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // ----------------------------------------------------------------- select --
@@ -179,107 +43,10 @@ __global__ __launch_bounds__(STAGE_THREADS) void k_copy_policies(const disco_pol
 
 // ------------------------------------------------------------ final stats --
 
-// The record of a column from its accumulators and the selections' results (workgroup = column).
-//
-// Order statistics of the delayed tokens per migrated request: the counts by number of delayed tokens come from the
-// first histogram pass of the timelines with a buffer hand-off; migrations of the lag trigger have none and count as
-// zeros.  Nearest rank, like the other order statistics; NaN for a column without migrations.
-//
-// Bound by latency: the counts, the accumulators and the slots are fetched side by side by different waves, the record is
-// put together in LDS (9 us with one thread for all but the counts, now 4 - 6).
-__global__ __launch_bounds__(256) void k_stats_final(int nq, i64 n_req, disco_cost_params cost, int with_tl,
-                                                     const disco_accum* acc, const SelState* S, disco_quantile q0,
-                                                     disco_quantile q1, disco_quantile q2, disco_quantile q3,
-                                                     const unsigned* __restrict__ dhist, disco_stats* out)
+__global__ __launch_bounds__(FINAL_THREADS) void k_stats_final(FinalArgs f)
 {
-    constexpr int PER = DISCO_DELAY_BINS / 256;
-    __shared__ u64 wtot[4];
-    __shared__ i64 drank[DISCO_MAX_Q];
-    __shared__ float dq[DISCO_MAX_Q];
-    __shared__ disco_stats st;
-    const int c = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const i64 migrated = with_tl ? acc[c].n_migrated : 0;
-    const bool delays = with_tl && nq > 0 && migrated > 0;
-    unsigned v[PER];
-    u64 mine = 0;
-    if (delays) {
-        const unsigned* row = dhist + (size_t)c * DISCO_DELAY_BINS;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) { v[k] = row[t * PER + k]; mine += v[k]; }
-    }
-    if (t < (int)(sizeof(st) / 8)) reinterpret_cast<u64*>(&st)[t] = 0ull;
-    if (t < DISCO_MAX_Q) dq[t] = NAN;
-    __syncthreads();
-    if (t == 0) {
-        const disco_accum a = acc[c];
-        st.n_req = n_req;
-        st.s_pre = a.s_pre + (with_tl ? a.m_s_repre : 0);
-        st.d_pre = a.d_pre + (with_tl ? a.m_d_repre : 0);
-        st.s_dec = with_tl ? a.m_s_dec : a.s_dec;
-        st.d_dec = with_tl ? a.m_d_dec : a.d_dec;
-        st.n_dev_started = a.n_dev_started;
-        st.n_dev_win = a.n_dev_win;
-        st.n_migrated = migrated;
-        st.tbt_count = with_tl ? a.tbt_count : 0;
-        st.mean_ttft = a.ttft_sum / (double)n_req;                       // 0/0 = NaN for an empty batch
-        st.mean_tbt = with_tl ? a.tlast_sum / (double)a.tbt_count : NAN;  // telescoped sum of gaps
-        st.mean_delay_num = (with_tl && a.n_migrated > 0) ? (double)a.delay_sum / (double)a.n_migrated : NAN;
-        st.server_cost = server_cost_of(cost, st.s_pre, st.s_dec);
-        st.device_energy = device_energy_of(cost, st.d_pre, st.d_dec);
-        st.device_cost = cost.lambda * st.device_energy;
-        st.total_cost = st.server_cost + st.device_cost;
-    }
-    if (t >= 64 && t < 64 + DISCO_MAX_Q) {
-        const int qi = t - 64;
-        float tq = NAN, bq = NAN;
-        if (qi < nq) {
-            const disco_quantile q = qi == 0 ? q0 : (qi == 1 ? q1 : (qi == 2 ? q2 : q3));
-            const SelSlot s0 = S->slot[0][c * nq + qi];
-            st.ttft_rank[qi] = s0.rank;
-            if (s0.M > 0 && !S->g[0].gather_error) tq = u2f(S->g[0].minb + s0.prefix);
-            if (with_tl) {
-                const SelSlot s1 = S->slot[1][c * nq + qi];
-                st.tbt_rank[qi] = s1.rank;
-                // (all digits decided: after the last pass, or by the one before it)
-                const TlPlan& last = S->tl.plan[DISCO_TBT_MAX_PASS];
-                const bool whole = last.left == last.width && !(last.window != 0 && S->tl.restart[DISCO_TBT_MAX_PASS - 1] != 0);
-                if (s1.M > 0 && !S->tl.error && whole) bq = u2f(s1.prefix + last.key_lo);
-            }
-            i64 k = ((i64)q.num * migrated + q.den - 1) / q.den;
-            if (k < 1) k = 1;
-            drank[qi] = k < migrated ? k : migrated;
-        }
-        st.ttft_q[qi] = tq; st.tbt_q[qi] = bq;
-    }
-    // inclusive prefix sums of the per-thread counts
-    u64 incl = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned lo = (unsigned)__shfl_up((int)(unsigned)incl, d, 64), hi = (unsigned)__shfl_up((int)(unsigned)(incl >> 32), d, 64);
-        if (lane >= d) incl += ((u64)hi << 32) | lo;
-    }
-    if (lane == 63) wtot[wave] = incl;
-    __syncthreads();
-    if (delays) {
-        u64 counted = 0;
-        for (int w = 0; w < 4; ++w) { counted += wtot[w]; incl += w < wave ? wtot[w] : 0ull; }
-        const u64 zeros = (u64)migrated > counted ? (u64)migrated - counted : 0;      // hand-offs without a count: no delayed token
-        if (t == 0) v[0] += (unsigned)zeros;
-        const u64 below = t > 0 ? incl - mine + zeros : 0;               // migrated requests with fewer delayed tokens than t * PER
-        for (int qi = 0; qi < nq; ++qi) {
-            const u64 k = (u64)drank[qi];
-            u64 cum = below;
-#pragma unroll
-            for (int b = 0; b < PER; ++b) {
-                if (cum < k && cum + v[b] >= k) dq[qi] = (float)(t * PER + b);
-                cum += v[b];
-            }
-        }
-    }
-    __syncthreads();
-    if (t < DISCO_MAX_Q) st.delay_q[t] = dq[t];
-    __syncthreads();
-    if (t < (int)(sizeof(st) / 8)) reinterpret_cast<u64*>(&out[c])[t] = reinterpret_cast<const u64*>(&st)[t];
+    __shared__ FinalLds lds;
+    stats_final((int)blockIdx.x, f, lds, f.tbt ? &f.S->tl.plan[DISCO_TBT_MAX_PASS] : nullptr);
 }
 
 // Mean over the runs of a group of columns: floating-point fields in fp64, summed in run order; integer
@@ -759,14 +526,28 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
     si.with_tbt = tl != nullptr;
     si.ppcnt = (unsigned*)(ws + L.ppcnt); si.dhist = (unsigned*)(ws + L.dhist);
     si.ghist = disco_small(v.n_req) ? gh : nullptr;        // (the general TTFT passes use the bins in between)
-    rc = stage_policies(pol, P, ws, L, stream, nq > 0 ? &si : nullptr);        // with the start of the TTFT selection
-    if (rc) return rc;
+    FinalArgs fin;
+    memset(&fin, 0, sizeof(fin));
+    fin.nq = nq; fin.with_tl = tl ? 1 : 0; fin.tbt = tl && nq > 0 ? 1 : 0; fin.n_req = v.n_req; fin.cost = *cost;
+    for (int i = 0; i < DISCO_MAX_Q; ++i) fin.q[i] = qs[i];
+    fin.acc = acc; fin.S = S; fin.dhist = (const unsigned*)(ws + L.dhist); fin.out = out;
+    const bool small = nq > 0 && disco_small(v.n_req);
+    if (small) {
+        // staging, the starts of the selections and the whole TTFT selection, without timelines the records as well
+        PolTable host;
+        const disco_policy* device;
+        rc = small_table(pol, P, host, &device);
+        if (rc) return rc;
+        disco_launch_small_begin(v, host, device, P, (disco_policy*)(ws + L.pol), (unsigned*)(ws + L.ticket), si, fin, stream);
+    } else {
+        rc = stage_policies(pol, P, ws, L, stream, nq > 0 ? &si : nullptr);        // with the start of the TTFT selection
+        if (rc) return rc;
+    }
     if (nq > 0) {
         unsigned char* ubytes = ws_bytes >= L.total + (size_t)v.n_req ? (unsigned char*)(ws + L.total) : nullptr;
         // (the descriptors of the TBT selection are written after the TTFT passes)
         u64* masks = ws_bytes >= disco_ws_full_bytes(L, v.n_req) ? (u64*)(ws + disco_ws_desc_offset(L, v.n_req)) : nullptr;
-        if (disco_small(v.n_req)) disco_launch_small_ttft(v, (const disco_policy*)(ws + L.pol), P, nq, acc, S, stream);
-        for (int pass = 0; pass < 4 && !disco_small(v.n_req); ++pass)
+        for (int pass = 0; !small && pass < disco_ttft_passes(v.n_req, P, nq); ++pass)
             disco_launch_ttft_pass(v, (const disco_policy*)(ws + L.pol), P, nq, pass, S, (unsigned*)(ws + L.slices), gh,
                                    ubytes, masks, stream);
         if (tl) {
@@ -813,13 +594,15 @@ extern "C" int32_t disco_reduce_stats(const disco_trace* trace, const disco_cost
                 a.pass = pass;
                 a.ghist = pass & 1 ? slices : gh;
                 a.gclear = pass & 1 ? gh : slices;
-                if (pass < DISCO_TBT_REGULAR_PASS) disco_launch_tl_hist_fast(v, trace->n_tok, dpol, a, stream);
-                disco_launch_tbt_pass(v, trace->n_tok, dpol, a, stream);
+                disco_launch_tbt_pass(v, trace->n_tok, dpol, a, fin, stream);       // (the last one makes the records)
             }
         }
     }
-    hipLaunchKernelGGL(k_stats_final, dim3((unsigned)P), dim3(256), 0, stream, nq, v.n_req, *cost, tl ? 1 : 0, acc, S, qs[0], qs[1],
-                       qs[2], qs[3], (const unsigned*)(ws + L.dhist), out);
+    if (fin.tbt || small) {
+        DISCO_HIP(hipGetLastError());
+        return DISCO_OK;
+    }
+    hipLaunchKernelGGL(k_stats_final, dim3((unsigned)P), dim3(FINAL_THREADS), 0, stream, fin);
     DISCO_HIP(hipGetLastError());
     return DISCO_OK;
 }

@@ -12,6 +12,25 @@ struct BufCostArgs { double dc_srv, cp_srv, dc_dev, cp_dev; };
 constexpr int RUN_COUNT_BITS = 26;
 struct RunPool { uint2* pool; unsigned cap; int n; };
 
+// Start of the order-statistic selections (disco_stage.h).
+struct SelInit {
+    SelState* S; int nq; disco_quantile q[4]; const disco_accum* acc; i64 n_req; int with_tbt;
+    unsigned *ppcnt, *dhist;       // counts of the TBT selection, cleared in the launch that starts it
+    unsigned* ghist;               // ... and its bins (nullable)
+};
+
+// What the result records are made from (disco_final.h).
+struct FinalArgs {
+    int nq, with_tl, tbt;          // tbt: there was a TBT selection
+    i64 n_req;
+    disco_cost_params cost;
+    disco_quantile q[DISCO_MAX_Q];
+    const disco_accum* acc;
+    const SelState* S;
+    const unsigned* dhist;
+    disco_stats* out;
+};
+
 struct TimelineArgs {
     float tau, kt;            // pacing interval, kappa_lag * tau
     int P, nq, pass;          // -1: statistics pass, >= 0: TBT histogram pass
@@ -69,8 +88,10 @@ int disco_small_search_max_bins(void);
 void disco_launch_small_search(const TraceView& v, const PolTable& templ, const SmallSearches& sp, int n_search, int n_steps, int nbins,
                                const disco_cost_params& cost, disco_search_out* sout, disco_policy* pol_out, disco_accum* acc,
                                hipStream_t stream);
-void disco_launch_small_ttft(const TraceView& v, const disco_policy* pol, int P, int nq, const disco_accum* acc, SelState* S,
-                             hipStream_t stream);
+// Statistics of a small trace: TTFT order statistics; with timelines (fin.with_tl) also the staging of the table and the start of
+// the TBT selection, without them the records.
+void disco_launch_small_begin(const TraceView& v, const PolTable& host, const disco_policy* device, int P, disco_policy* staged,
+                              unsigned* tickets, const SelInit& si, const FinalArgs& fin, hipStream_t stream);
 
 // Levels of the bisection tree one pass can evaluate for n searches (64 columns per pass).
 inline int disco_search_depth(int n) { return n <= 9 ? 3 : (n <= 21 ? 2 : 1); }
@@ -111,6 +132,7 @@ void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n,
 // `ubytes`: n_req bytes of scratch (nullable) where the first pass leaves, per request, the number of thresholds
 // not above its prompt length for the later passes; `masks`: n_req words (nullable) where it leaves the columns that send
 // a request to the server (tables of stochastic columns).
+int disco_ttft_passes(i64 n_req, int P, int nq);
 void disco_launch_ttft_pass(const TraceView& v, const disco_policy* pol, int P, int nq, int pass, SelState* S,
                             unsigned* slices, unsigned* rowsum, unsigned char* ubytes, u64* masks, hipStream_t stream);
 void disco_launch_dispatch_mat(const TraceView& v, const disco_policy* pol, int P, uint8_t* decision, float* ttft,
@@ -137,12 +159,11 @@ void disco_launch_timeline_general(const TraceView& v, i64 n_tok, const disco_po
                                    hipStream_t stream);
 void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P, const void* summary, const void* bufsum,
                               const BufCostArgs& bc, SelState* S, hipStream_t stream);
-void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
-                               hipStream_t stream);
 void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, float tau, const void* summary, SelState* S,
                             const void* bufsum, u64* desc, unsigned* list, unsigned* slices, size_t slices_bytes,
                             unsigned* ppcnt, unsigned* ghist, unsigned* dhist, hipStream_t stream);
 // After the assignment: the gaps of the listed timelines into pools in `scratch`, as far as they fit (a.runs on return); their
 // descriptors then name them no more.
 void disco_launch_tl_runs(const TraceView& v, i64 n_tok, TimelineArgs& a, void* scratch, size_t scratch_bytes, hipStream_t stream);
-void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a, hipStream_t stream);
+void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a, const FinalArgs& fin,
+                           hipStream_t stream);

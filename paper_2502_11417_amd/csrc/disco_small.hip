@@ -1,8 +1,11 @@
 // Dispatch totals, tabulated threshold search and TTFT order statistics of
 // small traces (disco_small.h): one launch each, workgroup = policy column.
+#include <math.h>
 #include <string.h>
 
+#include "disco_final.h"
 #include "disco_small.h"
+#include "disco_stage.h"
 
 namespace {
 
@@ -58,25 +61,48 @@ __global__ __launch_bounds__(SM_BLOCK) void k_small_search(TraceView tr, PolTabl
 
 // The column's TTFTs as keys in LDS, then its quantiles.  (The general selection is nine launches: one for each digit's
 // histograms, their sums and choices, and the passes that only the device can rule out: 45 - 60 us; here 6 us for 500
-// requests, 15 for 16 000, 24 for 32 000.)
-__global__ __launch_bounds__(SM_BLOCK) void k_small_ttft(TraceView tr, const disco_policy* __restrict__ pol, int nq,
-                                                         const disco_accum* __restrict__ acc, SelState* S)
+// requests, 15 for 16 000, 24 for 32 000.)  Without timelines the column's record follows at once (with_tl = 0); with
+// them the workgroups behind the columns stage the table and start the TBT selection.
+struct SmallBeginLds { RankLds rank; FinalLds fin; TtftFound found; };
+
+__global__ __launch_bounds__(SM_BLOCK) void k_small_begin(TraceView tr, PolTable host, const disco_policy* __restrict__ device, int P,
+                                                          disco_policy* __restrict__ staged, unsigned* __restrict__ tickets, SelInit si,
+                                                          FinalArgs fin)
 {
-    __shared__ RankLds lds;
-    const int c = blockIdx.x, n = (int)tr.n_req;
-    const disco_policy p = pol[c];
-    const unsigned lo = acc[c].ttft_min_bits, hi = acc[c].ttft_max_bits, base = S->g[0].minb;
-    unsigned k[DISCO_MAX_Q] = {0u, 0u, 0u, 0u}, prefix[DISCO_MAX_Q];
+    __shared__ SmallBeginLds lds;
+    const int c = blockIdx.x, n = (int)tr.n_req, nq = si.nq;
+    SelState* S = si.S;
+    if (c >= P) {
+        // 0 the table, 1 start of the TBT selection, the others clear; no start of the TTFT selection
+        static_assert(STAGE_THREADS == SM_BLOCK, "the kinds of workgroup share a launch");
+        const int bid = c - P;
+        stage_table(device ? device : host.p, P, staged, tickets, nullptr, si, bid > 0 ? bid + 1 : 0, (int)gridDim.x - P + 1);
+        return;
+    }
+    const disco_policy p = device ? device[c] : host.p[c];
+    const unsigned lo = si.acc[c].ttft_min_bits, hi = si.acc[c].ttft_max_bits;
+    unsigned k[DISCO_MAX_Q] = {0u, 0u, 0u, 0u}, prefix[DISCO_MAX_Q] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int q = 0; q < DISCO_MAX_Q; ++q)
-        if (q < nq) k[q] = (unsigned)S->slot[0][c * nq + q].rank;
-    if (n <= 0) return;
-    for_outcomes<false>(tr, p, [&](int i, int, int, const PairResult& e) { lds.key[i] = f2u(e.ttft) - lo; });
-    wg_select(lds, n, hi > lo ? 32 - __clz(hi - lo) : 0, nq, k, prefix);
-    if (threadIdx.x == 0)
+        if (q < nq) k[q] = (unsigned)nearest_rank(si.q[q], tr.n_req);
+    unsigned rank[DISCO_MAX_Q] = {k[0], k[1], k[2], k[3]};
+    if (n > 0) {
+        for_outcomes<false>(tr, p, [&](int i, int, int, const PairResult& e) { lds.rank.key[i] = f2u(e.ttft) - lo; });
+        wg_select(lds.rank, n, hi > lo ? 32 - __clz(hi - lo) : 0, nq, k, prefix);
+    }
+    if (threadIdx.x == 0) {
+        if (c == 0) { S->g[0].minb = 0u; S->g[0].gather_error = 0; }
 #pragma unroll
         for (int q = 0; q < DISCO_MAX_Q; ++q)
-            if (q < nq) S->slot[0][c * nq + q].prefix = prefix[q] + (lo - base);
+            if (q < nq) {
+                lds.found.rank[q] = (i64)rank[q];
+                lds.found.q[q] = n > 0 ? u2f(prefix[q] + lo) : NAN;
+                if (fin.with_tl) S->slot[0][c * nq + q] = SelSlot{prefix[q] + lo, n <= 0, 1, (i64)rank[q], tr.n_req};
+            }
+    }
+    if (fin.with_tl) return;
+    __syncthreads();
+    stats_final(c, fin, lds.fin, nullptr, &lds.found);
 }
 
 }  // namespace
@@ -97,8 +123,9 @@ void disco_launch_small_search(const TraceView& v, const PolTable& templ, const 
                        pol_out, acc);
 }
 
-void disco_launch_small_ttft(const TraceView& v, const disco_policy* pol, int P, int nq, const disco_accum* acc, SelState* S,
-                             hipStream_t stream)
+void disco_launch_small_begin(const TraceView& v, const PolTable& host, const disco_policy* device, int P, disco_policy* staged,
+                              unsigned* tickets, const SelInit& si, const FinalArgs& fin, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_small_ttft, dim3((unsigned)P), dim3(SM_BLOCK), 0, stream, v, pol, nq, acc, S);
+    const unsigned others = fin.with_tl ? 2u + STAGE_CLEAR : 0u;
+    hipLaunchKernelGGL(k_small_begin, dim3((unsigned)P + others), dim3(SM_BLOCK), 0, stream, v, host, device, P, staged, tickets, si, fin);
 }

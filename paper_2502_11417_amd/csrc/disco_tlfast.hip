@@ -380,16 +380,6 @@ __global__ __launch_bounds__(TR_BLOCK, 6) void k_tl_runs(TraceView tr, i64 n_tok
     if (threadIdx.x == 0) pool[0] = make_uint2(used < runs.cap ? used : runs.cap - 1u, 0u);
 }
 
-// Plan of a regular pass and its histogram over the walk list (the spare passes run the same body in the kernel that
-// also advances the selection).
-__global__ __launch_bounds__(TH_BLOCK, 8) void k_tl_hist(TraceView tr, i64 n_tok, int align, HistArgs a)
-{
-    __shared__ __align__(16) unsigned smem[DISCO_TL_HIST_WORDS];
-    __shared__ TlPlan plan;
-    tbt_open_pass(a.S, a.pass, a.P, a.nq, plan);
-    tl_hist_fast_body(smem, tr, n_tok, align, a, plan, blockIdx.x, gridDim.x);
-}
-
 }  // namespace
 
 // Once per selection, after the classification: descriptors of all requests, analytic timelines counted per class
@@ -418,15 +408,6 @@ void disco_launch_tl_assign(const TraceView& v, const disco_policy* pol, int P, 
                        ppcnt, ghist, use_lds);
 }
 
-static unsigned hist_blocks(i64 n_req)
-{
-    i64 b = (n_req + TH_BLOCK / 64 - 1) / (TH_BLOCK / 64);        // at most one request per wave
-    if (b < 1) b = 1;
-    if (b > 512) b = 512;                                          // two resident workgroups per CU
-    b /= disco_grid_divisor();
-    return (unsigned)(b < 1 ? 1 : b);
-}
-
 void disco_launch_tl_runs(const TraceView& v, i64 n_tok, TimelineArgs& a, void* scratch, size_t scratch_bytes, hipStream_t stream)
 {
     i64 b = (v.n_req + TR_WAVES - 1) / TR_WAVES;                   // at most one request per wave
@@ -440,18 +421,4 @@ void disco_launch_tl_runs(const TraceView& v, i64 n_tok, TimelineArgs& a, void* 
     const int align = (int)(((uintptr_t)v.arr >> 2) & 3);
     hipLaunchKernelGGL(k_tl_runs, dim3((unsigned)b), dim3(TR_BLOCK), 0, stream, v, n_tok, align, a.tau, a.kt, a.S, a.desc, a.list,
                        (const TlSummary*)a.summary, (const BufSummary*)a.bufsum, a.runs);
-}
-
-void disco_launch_tl_hist_fast(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
-                               hipStream_t stream)
-{
-    (void)pol;
-    HistArgs h;
-    memset(&h, 0, sizeof(h));
-    h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass;
-    h.S = a.S; h.ghist = a.ghist;
-    h.desc = a.desc; h.list = a.list;
-    h.runs = a.runs;
-    const int align = (int)(((uintptr_t)v.arr >> 2) & 3);
-    hipLaunchKernelGGL(k_tl_hist, dim3(hist_blocks(v.n_req)), dim3(TH_BLOCK), 0, stream, v, n_tok, align, h);
 }

@@ -10,14 +10,14 @@
 // round(t tau) - round((t-1) tau) for every one of them, so counting the
 // timelines per class and length gives their histogram.
 //
-// Launches of a selection: classification, assignment (other file); per
-// regular pass the plan of its digit and the walk of the streaming kinds
-// (other file), k_tbt_side (analytic bins, buffer hand-off timelines,
-// per-slot histograms: workgroups by kind) and k_tbt_select (one workgroup
-// per slot); per spare pass k_tbt_spare alone.  A launch that finds the selection finished returns at once, which
+// Launches of a selection: classification, assignment and the gap pools
+// (other file); per regular pass k_tbt_pass (plan, analytic bins, pools,
+// timelines left to be walked: workgroups by kind) and k_tbt_select (one
+// workgroup per slot); per spare pass k_tbt_pass alone.  A launch that finds the selection finished returns at once, which
 // still costs about 2 us on the device: hence few launches.
 #include <string.h>
 
+#include "disco_final.h"
 #include "disco_tl_general_kernel.h"
 #include "disco_tl_hist_buf.h"
 #include "disco_tl_hist_fast.h"
@@ -368,9 +368,6 @@ __device__ __forceinline__ void clear_next_bins(const SelState* S, int pass, int
     for (int i = t; i < (words + 3) / 4; i += nt) reinterpret_cast<uint4*>(bins)[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// Workgroups of the launches below, by what they run.
-struct PassGrid { unsigned analytic, fast, buf, general; };
-
 __device__ __forceinline__ BufHistArgs buf_hist_args(const TimelineArgs& a)
 {
     BufHistArgs h;
@@ -382,32 +379,6 @@ __device__ __forceinline__ BufHistArgs buf_hist_args(const TimelineArgs& a)
 }
 
 static_assert(TH_BLOCK == 1024 && TBH_BLOCK == 1024 && TL_BLOCK == 1024, "the kinds of workgroup share launches");
-
-// A regular pass, everything but the streaming kinds' walk (which has a kernel of its own, built for occupancy):
-// the analytic bins of the classes, the buffer hand-off timelines, the per-slot histograms of a table whose
-// column sets do not fit the class scheme.  One launch, workgroups by kind; the kinds a table does not use
-// return at once.
-__global__ __launch_bounds__(1024) void k_tbt_side(TraceView tr, i64 n_tok, int align, const disco_policy* __restrict__ pol,
-                                                   TimelineArgs a, PassGrid g)
-{
-    __shared__ __align__(16) unsigned smem[DISCO_TL_HIST_WORDS];
-    __shared__ TimelineLds lds;
-    const TlPlan& pl = a.S->tl.plan[a.pass + 1];        // (left by the launch that opened the pass)
-    if (pl.width <= 0) return;                          // selection finished
-    unsigned bid = blockIdx.x;
-    if (bid < g.analytic) {
-        const int ncls = a.S->tl.ncls;
-        if (!pl.fallback && (int)bid < ncls) analytic_class(pl, ncls, a.pass, a.ghist, a.ppcnt, a.tau, (int)bid, smem);
-        return;
-    }
-    bid -= g.analytic;
-    if (bid < g.buf) {
-        if (!pl.fallback && *a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), pl, bid, g.buf);
-        return;
-    }
-    bid -= g.buf;
-    if (pl.fallback) timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, &pl, bid, g.general);
-}
 
 // Workgroup = slot: the digit of the slot; SEL_CLEAR workgroups behind them clear the bins of the next pass.
 constexpr int SEL_CLEAR = DISCO_GHIST_WORDS / 4 / 1024;
@@ -424,49 +395,68 @@ __global__ __launch_bounds__(1024) void k_tbt_select(SelState* S, int pass, int 
     else clear_next_bins(S, pass, ns, next, ((int)blockIdx.x - ns) * 1024 + (int)threadIdx.x, SEL_CLEAR * 1024);
 }
 
-// A spare pass (after the passes that normally finish the selection: needed when the window was missed or the
-// digits are narrow) in one launch: every workgroup adds the analytic bins of its classes and walks its share of each kind
-// of timeline; the one that finishes last takes every slot's digit and clears the next pass's bins.  One launch per pass matters
-// more here than speed: normally all of them return at once.
-__global__ __launch_bounds__(1024) void k_tbt_spare(TraceView tr, i64 n_tok, int align, const disco_policy* __restrict__ pol,
-                                                    TimelineArgs a, PassGrid g)
+// A pass: its plan, the analytic bins (a class per workgroup), the pools and what is left of the walk list, or the per-slot
+// histograms of a table whose column sets do not fit the class scheme (then every workgroup walks).
+//   PASS_REGULAR  its digits are taken by k_tbt_select behind it
+//   PASS_SPARE    a pass after those that normally decide every slot (the window was missed, or the digits are narrow): the
+//                 workgroup that finishes last takes every slot's digit and clears the next pass's bins; one launch
+//                 matters more here than speed, as normally all workgroups return at once
+//   PASS_LAST     the last spare pass, which also makes the columns' records
+enum { PASS_REGULAR, PASS_SPARE, PASS_LAST };
+constexpr unsigned TP_ANALYTIC = DISCO_MAX_CLS;
+
+template <int KIND>
+__global__ __launch_bounds__(1024) void k_tbt_pass(TraceView tr, i64 n_tok, int align, const disco_policy* __restrict__ pol,
+                                                   TimelineArgs a, FinalArgs fin)
 {
     __shared__ __align__(16) unsigned smem[DISCO_TL_HIST_WORDS];
     __shared__ TimelineLds lds;
-    __shared__ u64 wsum[DISCO_MAX_CLS];
-    __shared__ int s_digit;
-    __shared__ u64 s_rem;
     __shared__ TlPlan pl;
     SelState* S = a.S;
     const TlSel& tl = S->tl;
-    tbt_open_pass(S, a.pass, a.P, a.nq, pl);
-    if (pl.width <= 0) return;                          // selection finished (the same answer in every workgroup)
     const unsigned bid = blockIdx.x;
-    if (!pl.fallback)                                   // the analytic bins: a class per workgroup
-        for (int c = (int)bid; c < tl.ncls; c += (int)gridDim.x) analytic_class(pl, tl.ncls, a.pass, a.ghist, a.ppcnt, a.tau, c, smem);
-    __syncthreads();
+    tbt_open_pass(S, a.pass, a.P, a.nq, pl);
+    if (pl.width <= 0) {                                // selection finished (the same answer in every workgroup)
+        if (KIND == PASS_LAST && (int)bid < a.P) stats_final((int)bid, fin, *reinterpret_cast<FinalLds*>(smem), &pl);
+        return;
+    }
     if (pl.fallback) {
-        timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, &pl, bid, g.general);
+        timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, &pl, bid, gridDim.x);
+    } else if (bid < TP_ANALYTIC) {
+        if ((int)bid < tl.ncls) analytic_class(pl, tl.ncls, a.pass, a.ghist, a.ppcnt, a.tau, (int)bid, smem);
     } else {
+        const unsigned at = bid - TP_ANALYTIC, of = gridDim.x - TP_ANALYTIC;
         HistArgs h;
         h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass; h.S = a.S; h.ghist = a.ghist; h.desc = a.desc; h.list = a.list; h.runs = a.runs;
-        tl_hist_fast_body(smem, tr, n_tok, align, h, pl, bid, g.fast);
+        tl_hist_fast_body(smem, tr, n_tok, align, h, pl, at, of);
         __syncthreads();                                // the bins are used again
-        if (*a.buffer_flag != 0u) tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), pl, bid, g.buf);
+        tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), pl, at, of);
     }
+    if (KIND == PASS_REGULAR) return;
     if (!take_last_ticket(a.ticket)) return;
+    __shared__ u64 wsum[DISCO_MAX_CLS];
+    __shared__ int s_digit;
+    __shared__ u64 s_rem;
     __syncthreads();
     if (!pl.fallback && pl.width <= SEL_NARROW_BITS) {
         for (int s = threadIdx.x >> 6; s < a.P * a.nq; s += (int)blockDim.x >> 6) select_slot_narrow(S, pl, a.pass, a.nq, a.ghist, s);
-        __syncthreads();
     } else {
         for (int s = 0; s < a.P * a.nq; ++s) {
             select_slot(S, pl, a.pass, a.nq, a.ghist, s, wsum, &s_digit, &s_rem, reinterpret_cast<u64*>(smem), DISCO_TL_HIST_WORDS / 2);
             __syncthreads();
         }
     }
-    clear_next_bins(S, a.pass, a.P * a.nq, a.gclear, (int)threadIdx.x, (int)blockDim.x);
     if (threadIdx.x == 0) *a.ticket = 0u;
+    if (KIND == PASS_SPARE) {
+        clear_next_bins(S, a.pass, a.P * a.nq, a.gclear, (int)threadIdx.x, (int)blockDim.x);
+    } else {
+        __threadfence_block();                          // (the slots' digits are read back)
+        __syncthreads();
+        for (int c = 0; c < a.P; ++c) {
+            stats_final(c, fin, *reinterpret_cast<FinalLds*>(smem), &pl);
+            __syncthreads();
+        }
+    }
 }
 
 }  // namespace
@@ -483,24 +473,23 @@ void disco_launch_tl_classify(const TraceView& v, const disco_policy* pol, int P
                        (const BufSummary*)bufsum, price_tag(bc), S);
 }
 
-// One pass of the TBT selection over everything but the streaming kinds' walk in the regular passes (that walk:
-// disco_launch_tl_hist_fast, before this), then the step to the next pass.
-void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a, hipStream_t stream)
+// One pass of the TBT selection and the step to the next one.
+void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a, const FinalArgs& fin,
+                           hipStream_t stream)
 {
     const int align = (int)(((uintptr_t)v.arr >> 2) & 3);
+    // one workgroup per CU: more of them make an empty launch dearer
     const i64 per_wave = (v.n_req + 15) / 16;                    // workgroups if every wave took one request
-    auto cap = [&](i64 c) { return (unsigned)(per_wave < 1 ? 1 : (per_wave > c ? c : per_wave)); };
-    PassGrid g;
+    i64 walkers = per_wave < 1 ? 1 : (per_wave > 256 - (i64)TP_ANALYTIC ? 256 - (i64)TP_ANALYTIC : per_wave);
+    walkers /= disco_grid_divisor();
+    const dim3 grid(TP_ANALYTIC + (unsigned)(walkers < 1 ? 1 : walkers));
     if (a.pass < DISCO_TBT_REGULAR_PASS) {
-        g.analytic = DISCO_MAX_CLS; g.fast = 0; g.buf = cap(512); g.general = cap(512);
-        hipLaunchKernelGGL(k_tbt_side, dim3(g.analytic + g.buf + g.general), dim3(1024), 0, stream, v, n_tok, align, pol, a, g);
+        hipLaunchKernelGGL(k_tbt_pass<PASS_REGULAR>, grid, dim3(1024), 0, stream, v, n_tok, align, pol, a, fin);
         hipLaunchKernelGGL(k_tbt_select, dim3((unsigned)(a.P * a.nq + SEL_CLEAR)), dim3(1024), 0, stream, a.S, a.pass, a.P, a.nq, a.ghist,
                            a.gclear);
+    } else if (a.pass + 1 < DISCO_TBT_MAX_PASS) {
+        hipLaunchKernelGGL(k_tbt_pass<PASS_SPARE>, grid, dim3(1024), 0, stream, v, n_tok, align, pol, a, fin);
     } else {
-        // one workgroup per CU: more of them make an empty launch dearer.  (A workgroup per kind and 64 of each, all slots
-        // and analytic bins left to the last workgroup: 194 us for the one remaining bit of 10^5 requests x 12 wait
-        // columns, now 50.)
-        g.analytic = 0; g.fast = g.buf = g.general = cap(256);
-        hipLaunchKernelGGL(k_tbt_spare, dim3(g.general), dim3(1024), 0, stream, v, n_tok, align, pol, a, g);
+        hipLaunchKernelGGL(k_tbt_pass<PASS_LAST>, grid, dim3(1024), 0, stream, v, n_tok, align, pol, a, fin);
     }
 }

@@ -858,6 +858,14 @@ void launch_hist(const TraceView& v, const disco_policy* pol, int P, int nq, int
 
 }  // namespace
 
+// Passes that can be needed: three where the buckets of the second one (two values per request at most) or the list of the
+// third (a value per request, column and quantile at most) are sure to fit.  An empty pass is two launches, 8 - 9 us.
+int disco_ttft_passes(i64 n_req, int P, int nq)
+{
+    const u64 cap = TG_CAP - 4u * DISCO_MAX_SLOTS;         // (buckets start at multiples of four entries)
+    return 2ull * (u64)n_req <= cap && (u64)n_req * (u64)(P * nq) <= cap ? 3 : 4;
+}
+
 void disco_launch_ttft_pass(const TraceView& v, const disco_policy* pol, int P, int nq, int pass, SelState* S,
                             unsigned* slices, unsigned* rowsum, unsigned char* ubytes, u64* masks, hipStream_t stream)
 {
