@@ -690,7 +690,8 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
     if (n_steps < 1 || n_steps > DISCO_MAX_STEPS) return DISCO_ERR_SHAPE;
     SpecTable t;
     memset(&t, 0, sizeof(t));
-    for (int j = 0; j < n_search && !is_device_pointer(templ); ++j)           // the stochastic baselines have no searched parameter
+    const bool host_templ = !is_device_pointer(templ);
+    for (int j = 0; j < n_search && host_templ; ++j)                          // the stochastic baselines have no searched parameter
         if (templ[j].mode >= DISCO_MODE_STOCH_SERVER) return DISCO_ERR_RANGE;
     for (int j = 0; j < n_search; ++j) {
         if (spec[j].n_steps != n_steps) return DISCO_ERR_SHAPE;
@@ -713,7 +714,7 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
     // Length thresholds of server-constrained columns against a prompt-token budget: the accumulator is a
     // function of the threshold alone and is tabulated once (Alg. 3's sorted running totals); all bisection
     // steps then read the table.  Needs a host-resident template table (its modes are inspected here).
-    bool tabulated = v.n_req > 0 && !is_device_pointer(templ);
+    bool tabulated = v.n_req > 0 && host_templ;
     double max_hi = 0.0;
     for (int j = 0; j < n_search && tabulated; ++j) {
         tabulated = templ[j].mode == DISCO_MODE_SERVER_CONSTRAINED && spec[j].which_param == DISCO_PARAM_L_TH &&
@@ -744,7 +745,7 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
     // Waits and ramp slopes of device-constrained columns: the outcomes of a request are step functions of the
     // parameter, a pass takes eight bisection steps (disco_search.hip), where that is the faster way.  The bounds are such
     // that no midpoint overflows and no ramp is infinity times zero.
-    bool binned = !tabulated && !is_device_pointer(templ) && disco_search_bins_bytes(n_search) <= L.total - L.slices &&
+    bool binned = !tabulated && host_templ && disco_search_bins_bytes(n_search) <= L.total - L.slices &&
                   disco_search_bins_pays(v.n_req, n_search, n_steps, need != 0);
     for (int j = 0; j < n_search && binned; ++j)
         binned = templ[j].mode == DISCO_MODE_DEVICE_CONSTRAINED && spec[j].which_param != DISCO_PARAM_L_TH &&
