@@ -333,8 +333,10 @@ __device__ __forceinline__ void batch_pairs_need(const Staged* __restrict__ st, 
 
 template <int G>
 __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const disco_policy* __restrict__ pol, int P,
-                                                           u64* __restrict__ part, DispFin fin)
+                                                           u64* __restrict__ part, DispFin fin, int nacc, PairOut out)
 {
+    // the workgroups behind the first nacc write the per-pair outputs
+    if ((int)blockIdx.x >= nacc) { mat_body(tr, pol, P, out, (int)blockIdx.x - nacc, (int)gridDim.x - nacc); return; }
     __shared__ __align__(16) unsigned char smem[DP_BLOCK * sizeof(DispPartial)];    // 64 KB: staging, then folds
     Staged* stage = reinterpret_cast<Staged*>(smem);
     u64* sh = reinterpret_cast<u64*>(smem);
@@ -348,7 +350,7 @@ __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const d
     StagedRace* sr = reinterpret_cast<StagedRace*>(smem + DP_BLOCK * sizeof(Staged)) + wave * 64;
     unsigned* pnr = reinterpret_cast<unsigned*>(smem + DP_BLOCK * (sizeof(Staged) + sizeof(StagedRace))) + wave * 64;
     const i64 nbatch = (tr.n_req + 63) >> 6;
-    const i64 bstride = (i64)gridDim.x * DP_WAVES;
+    const i64 bstride = (i64)nacc * DP_WAVES;
     // one batch ahead: the loads of the next batch (at first: of the first one, together with the policy
     // record) are in flight while the current one is evaluated
     int lv_n = 0, nv_n = 0;
@@ -458,8 +460,9 @@ __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const d
 // iteration (16-byte loads when VEC, i.e. all arrays 16-byte aligned).
 template <bool VEC>
 __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc1(TraceView tr, const disco_policy* __restrict__ pol,
-                                                            u64* __restrict__ part, DispFin fin)
+                                                            u64* __restrict__ part, DispFin fin, int nacc, PairOut out)
 {
+    if ((int)blockIdx.x >= nacc) { mat_body(tr, pol, 1, out, (int)blockIdx.x - nacc, (int)gridDim.x - nacc); return; }
     __shared__ __align__(16) unsigned char smem[DP_BLOCK * sizeof(DispPartial)];
     u64* sh = reinterpret_cast<u64*>(smem);
     const disco_policy p = pol[0];
@@ -467,7 +470,7 @@ __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc1(TraceView tr, const 
     ColTotals t{0, 0, 0, 0, 0, 0.0, 0xFFFFFFFFu, 0u};
     u64 tot_n = 0;
     const i64 ngroups = (tr.n_req + 3) >> 2;
-    const i64 stride = (i64)gridDim.x * DP_BLOCK;
+    const i64 stride = (i64)nacc * DP_BLOCK;
     for (i64 g4 = (i64)blockIdx.x * DP_BLOCK + threadIdx.x; g4 < ngroups; g4 += stride) {
         int l[4], n[4];
         float s[4], k[4];
@@ -535,28 +538,6 @@ __global__ __launch_bounds__(512) void k_dispatch_fin(u64* __restrict__ part, in
 {
     __shared__ u64 sh[8 * 64];
     finish_columns(part, P, fin, sh);
-}
-
-// Materialised per-pair outputs, lane = request so that every column is
-// written coalesced.
-__global__ __launch_bounds__(256) void k_dispatch_mat(TraceView tr, const disco_policy* __restrict__ pol, int P,
-                                                      uint8_t* __restrict__ decision, float* __restrict__ ttft)
-{
-    __shared__ disco_policy sp[DISCO_MAX_COLS];
-    if ((int)threadIdx.x < P) sp[threadIdx.x] = pol[threadIdx.x];
-    __syncthreads();
-    for (i64 i = (i64)blockIdx.x * blockDim.x + threadIdx.x; i < tr.n_req; i += (i64)gridDim.x * blockDim.x) {
-        const int l = tr.l[i];
-        const float s = tr.s[i];
-        const float k = tr.k ? tr.k[i] : tr.k_s;
-        const float d = __fmaf_rn((float)l, k, tr.c);
-        for (int j = 0; j < P; ++j) {
-            unsigned dec; float t;
-            dispatch_pair(sp[j], l, s, d, i, dec, t);
-            if (decision) decision[(size_t)j * tr.n_req + i] = (uint8_t)dec;
-            if (ttft) ttft[(size_t)j * tr.n_req + i] = t;
-        }
-    }
 }
 
 // ---------------------------------------------- threshold search, Alg. 3 ----
@@ -682,12 +663,26 @@ unsigned dispatch_blocks(i64 units, i64 per_block)
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
+// Workgroups of a pass: those of the totals, and behind them those of the per-pair outputs.  The former are bound by issue, the
+// latter by the writes: with a workgroup on every CU for the totals first, 10^6 requests x 64 columns took 27 + 72 us one after
+// the other.
+constexpr unsigned BOTH_ACC_BLOCKS = 96;
+struct AccGrid { unsigned acc, all; };
+AccGrid acc_grid(const TraceView& v, int P, unsigned acc, const PairOut& out)
+{
+    if (!out.decision && !out.ttft) return AccGrid{acc, acc};
+    if (acc > BOTH_ACC_BLOCKS) acc = BOTH_ACC_BLOCKS;
+    i64 m = (v.n_req + 4 * DP_BLOCK - 1) / (4 * DP_BLOCK) * ((P + MAT_COLS - 1) / MAT_COLS);
+    if (m > 2048) m = 2048;
+    return AccGrid{acc, acc + (unsigned)m};
+}
+
 template <int G>
-void launch_acc(const TraceView& v, const disco_policy* pol, int P, u64* part, const DispFin& fin,
+void launch_acc(const TraceView& v, const disco_policy* pol, int P, u64* part, const DispFin& fin, const PairOut& out,
                 hipStream_t stream)
 {
-    const unsigned blocks = dispatch_blocks((v.n_req + 63) / 64, DP_WAVES);
-    hipLaunchKernelGGL(k_dispatch_acc<G>, dim3(blocks), dim3(DP_BLOCK), 0, stream, v, pol, P, part, fin);
+    const AccGrid g = acc_grid(v, P, dispatch_blocks((v.n_req + 63) / 64, DP_WAVES), out);
+    hipLaunchKernelGGL(k_dispatch_acc<G>, dim3(g.all), dim3(DP_BLOCK), 0, stream, v, pol, P, part, fin, (int)g.acc, out);
     hipLaunchKernelGGL(k_dispatch_fin, dim3(1), dim3(512), 0, stream, part, P, fin);
 }
 
@@ -701,33 +696,25 @@ int pow2_cols(int P)
 }  // namespace
 
 void disco_launch_dispatch_acc(const TraceView& v, const disco_policy* pol, int P, u64* part, const DispFin& fin,
-                               hipStream_t stream)
+                               hipStream_t stream, uint8_t* decision, float* ttft)
 {
+    const PairOut out{decision, ttft};
     switch (pow2_cols(P)) {
     case 1: {
-        const unsigned blocks = dispatch_blocks((v.n_req + 3) / 4, DP_BLOCK);
+        const AccGrid g = acc_grid(v, P, dispatch_blocks((v.n_req + 3) / 4, DP_BLOCK), out);
         const bool vec = aligned16(v.l) && aligned16(v.n) && aligned16(v.s) && (!v.k || aligned16(v.k));
-        if (vec) hipLaunchKernelGGL(k_dispatch_acc1<true>, dim3(blocks), dim3(DP_BLOCK), 0, stream, v, pol, part, fin);
-        else hipLaunchKernelGGL(k_dispatch_acc1<false>, dim3(blocks), dim3(DP_BLOCK), 0, stream, v, pol, part, fin);
+        if (vec) hipLaunchKernelGGL(k_dispatch_acc1<true>, dim3(g.all), dim3(DP_BLOCK), 0, stream, v, pol, part, fin, (int)g.acc, out);
+        else hipLaunchKernelGGL(k_dispatch_acc1<false>, dim3(g.all), dim3(DP_BLOCK), 0, stream, v, pol, part, fin, (int)g.acc, out);
         hipLaunchKernelGGL(k_dispatch_fin, dim3(1), dim3(512), 0, stream, part, 1, fin);
         break;
     }
-    case 2: launch_acc<2>(v, pol, P, part, fin, stream); break;
-    case 4: launch_acc<4>(v, pol, P, part, fin, stream); break;
-    case 8: launch_acc<8>(v, pol, P, part, fin, stream); break;
-    case 16: launch_acc<16>(v, pol, P, part, fin, stream); break;
-    case 32: launch_acc<32>(v, pol, P, part, fin, stream); break;
-    default: launch_acc<64>(v, pol, P, part, fin, stream); break;
+    case 2: launch_acc<2>(v, pol, P, part, fin, out, stream); break;
+    case 4: launch_acc<4>(v, pol, P, part, fin, out, stream); break;
+    case 8: launch_acc<8>(v, pol, P, part, fin, out, stream); break;
+    case 16: launch_acc<16>(v, pol, P, part, fin, out, stream); break;
+    case 32: launch_acc<32>(v, pol, P, part, fin, out, stream); break;
+    default: launch_acc<64>(v, pol, P, part, fin, out, stream); break;
     }
-}
-
-void disco_launch_dispatch_mat(const TraceView& v, const disco_policy* pol, int P, uint8_t* decision, float* ttft,
-                               hipStream_t stream)
-{
-    i64 b = (v.n_req + 255) / 256;
-    if (b > 4096) b = 4096;
-    if (b < 1) b = 1;
-    hipLaunchKernelGGL(k_dispatch_mat, dim3((unsigned)b), dim3(256), 0, stream, v, pol, P, decision, ttft);
 }
 
 // Prompt tokens by length in blocks (disco_len.h); `scratch` holds the workgroup slices.  Returns their number.

@@ -213,31 +213,23 @@ int small_table(const disco_policy* pol, int P, PolTable& host, const disco_poli
 int eval_dispatch(const TraceView& v, const disco_policy* pol, int P, const disco_pair_out* out, disco_accum* acc, char* ws,
                   const WsLayout& L, hipStream_t stream)
 {
-    const bool pairs = out && (out->decision || out->ttft) && v.n_req > 0;
-    const bool small = disco_small(v.n_req);
-    const disco_policy* staged = (const disco_policy*)(ws + L.pol);
-    if (small && !pairs) {
+    uint8_t* decision = out && v.n_req > 0 ? out->decision : nullptr;
+    float* ttft = out && v.n_req > 0 ? out->ttft : nullptr;
+    if (disco_small(v.n_req)) {
         PolTable t;
         const disco_policy* device;
         const int rc = small_table(pol, P, t, &device);
         if (rc) return rc;
-        disco_launch_small_dispatch(v, t, device, P, acc, stream);
+        disco_launch_small_dispatch(v, t, device, P, acc, decision, ttft, stream);
     } else {
         const int rc = stage_policies(pol, P, ws, L, stream);        // also puts the flag words and the totals at their identity
         if (rc) return rc;
-        if (small) {
-            PolTable none;
-            memset(&none, 0, sizeof(none));
-            disco_launch_small_dispatch(v, none, staged, P, acc, stream);
-        } else {
-            DispFin fin;
-            memset(&fin, 0, sizeof(fin));
-            fin.kind = 0;
-            fin.need = 2;
-            fin.acc = acc;
-            disco_launch_dispatch_acc(v, staged, P, (u64*)(ws + L.part), fin, stream);
-        }
-        if (pairs) disco_launch_dispatch_mat(v, staged, P, out->decision, out->ttft, stream);
+        DispFin fin;
+        memset(&fin, 0, sizeof(fin));
+        fin.kind = 0;
+        fin.need = 2;
+        fin.acc = acc;
+        disco_launch_dispatch_acc(v, (const disco_policy*)(ws + L.pol), P, (u64*)(ws + L.part), fin, stream, decision, ttft);
     }
     DISCO_HIP(hipGetLastError());
     return DISCO_OK;

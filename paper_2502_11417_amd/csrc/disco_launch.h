@@ -82,7 +82,7 @@ struct SmallSearch { double target; int lo, hi, which_acc, pad; };
 struct SmallSearches { SmallSearch s[DISCO_MAX_COLS]; };
 // Table from device memory, or from `host` where `device` is null.
 void disco_launch_small_dispatch(const TraceView& v, const PolTable& host, const disco_policy* device, int P, disco_accum* acc,
-                                 hipStream_t stream);
+                                 uint8_t* decision, float* ttft, hipStream_t stream);
 // Tabulated threshold searches (templates: server-constrained columns), with the evaluation at the answers.
 int disco_small_search_max_bins(void);
 void disco_launch_small_search(const TraceView& v, const PolTable& templ, const SmallSearches& sp, int n_search, int n_steps, int nbins,
@@ -96,8 +96,9 @@ void disco_launch_small_begin(const TraceView& v, const PolTable& host, const di
 // Levels of the bisection tree one pass can evaluate for n searches (64 columns per pass).
 inline int disco_search_depth(int n) { return n <= 9 ? 3 : (n <= 21 ? 2 : 1); }
 
+// decision, ttft: per-pair outputs, nullable.
 void disco_launch_dispatch_acc(const TraceView& v, const disco_policy* pol, int P, u64* part, const DispFin& fin,
-                               hipStream_t stream);
+                               hipStream_t stream, uint8_t* decision = nullptr, float* ttft = nullptr);
 // Threshold search of server-constrained columns from a table of prompt-token sums by length.
 void disco_launch_search_table(const TraceView& v, const SpecTable& spec, int n_search, int nbins, unsigned* scratch,
                                size_t scratch_bytes, u64* table, SearchState* st, disco_policy* pol, disco_search_out* sout,
@@ -135,8 +136,6 @@ void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n,
 int disco_ttft_passes(i64 n_req, int P, int nq);
 void disco_launch_ttft_pass(const TraceView& v, const disco_policy* pol, int P, int nq, int pass, SelState* S,
                             unsigned* slices, unsigned* rowsum, unsigned char* ubytes, u64* masks, hipStream_t stream);
-void disco_launch_dispatch_mat(const TraceView& v, const disco_policy* pol, int P, uint8_t* decision, float* ttft,
-                               hipStream_t stream);
 // Token timelines.  Statistics pass (a.pass = -1): streaming kernel, or the general kernel when the
 // per-token deliveries of a column are wanted.  TBT selection: classification and assignment once; then per regular pass (a.pass < DISCO_TBT_REGULAR_PASS) the walk of the
 // streaming kinds (disco_launch_tl_hist_fast) followed by disco_launch_tbt_pass (the other histogram work of the

@@ -136,4 +136,69 @@ __device__ __forceinline__ int table_mode(const disco_policy& p, bool colv)
     return any_x ? 2 : (any_d ? (any_s ? 2 : 1) : 0);
 }
 
+// --------------------------------------------------- per-pair outputs ----
+
+struct PairOut { uint8_t* decision; float* ttft; };      // policy-major, nullable
+
+// Four consecutive elements of a row that starts anywhere (gfx950 stores them in one instruction).
+typedef float PairFloats __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned PairBytes __attribute__((aligned(1)));
+
+// Workgroup `bid` of `nblk`: four consecutive requests per lane, so that a wave writes 1 KB of a TTFT row and 256 B of a decision
+// row at a time; a task is a block of requests and MAT_COLS columns.
+constexpr int MAT_COLS = 8;
+__device__ __forceinline__ void mat_body(const TraceView& tr, const disco_policy* pol, int P, const PairOut& out, int bid, int nblk)
+{
+    const i64 blocks = (tr.n_req + 4 * DP_BLOCK - 1) / (4 * DP_BLOCK);
+    const int chunks = (P + MAT_COLS - 1) / MAT_COLS;
+    for (i64 task = bid; task < blocks * chunks; task += nblk) {
+        const i64 i0 = (task / chunks) * (4 * DP_BLOCK) + 4 * (int)threadIdx.x;
+        const int j0 = (int)(task % chunks) * MAT_COLS, j1 = j0 + MAT_COLS < P ? j0 + MAT_COLS : P;
+        if (i0 >= tr.n_req) continue;
+        const int cnt = tr.n_req - i0 < 4 ? (int)(tr.n_req - i0) : 4;
+        int l[4];
+        float s[4], d[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const i64 i = i0 + (q < cnt ? q : 0);
+            l[q] = tr.l[i]; s[q] = tr.s[i];
+            d[q] = __fmaf_rn((float)l[q], tr.k ? tr.k[i] : tr.k_s, tr.c);
+        }
+        // a race that starts both endpoints at once (Alg. 3): the same for every column; ties go to the server
+        unsigned race[4];
+        float first[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { race[q] = d[q] < s[q] ? 7u : 3u; first[q] = d[q] < s[q] ? d[q] : s[q]; }
+#pragma unroll 1
+        for (int j = j0; j < j1; ++j) {
+            const disco_policy p = pol[j];                       // (the same for all lanes, as is its kind)
+            unsigned dec[4];
+            float t[4];
+            if (p.mode == DISCO_MODE_SERVER_CONSTRAINED) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bool dev_only = l[q] < p.l_th;         // strict: Alg. 3
+                    dec[q] = dev_only ? 6u : race[q];
+                    t[q] = dev_only ? d[q] : first[q];
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) dispatch_pair(p, l[q], s[q], d[q], i0 + q, dec[q], t[q]);
+            }
+            const size_t at = (size_t)j * tr.n_req + i0;
+            if (cnt == 4) {
+                if (out.ttft) *reinterpret_cast<PairFloats*>(out.ttft + at) = PairFloats{t[0], t[1], t[2], t[3]};
+                if (out.decision) *reinterpret_cast<PairBytes*>(out.decision + at) = dec[0] | (dec[1] << 8) | (dec[2] << 16) | (dec[3] << 24);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (q < cnt) {
+                        if (out.ttft) out.ttft[at + q] = t[q];
+                        if (out.decision) out.decision[at + q] = (uint8_t)dec[q];
+                    }
+            }
+        }
+    }
+}
+
 }  // namespace

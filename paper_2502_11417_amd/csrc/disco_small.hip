@@ -12,10 +12,14 @@ namespace {
 // Bound by latency, like all of this file: 6 us for 2000 requests, 13 for 32 000 (11 and 14 in the two kernels of the
 // general pass).
 __global__ __launch_bounds__(SM_BLOCK) void k_small_dispatch(TraceView tr, PolTable host, const disco_policy* __restrict__ device,
-                                                             disco_accum* __restrict__ acc)
+                                                             int P, disco_accum* __restrict__ acc, PairOut out)
 {
     __shared__ ColumnLds lds;
     const int c = blockIdx.x;
+    if (c >= P) {                                            // the workgroups behind the columns write the per-pair outputs
+        mat_body(tr, device ? device : host.p, P, out, c - P, (int)gridDim.x - P);
+        return;
+    }
     const disco_policy p = device ? device[c] : host.p[c];
     ColumnSums sums;
     for_outcomes<true>(tr, p, [&](int, int l, int n, const PairResult& e) { sums.add(l, n, e); });
@@ -108,9 +112,11 @@ __global__ __launch_bounds__(SM_BLOCK) void k_small_begin(TraceView tr, PolTable
 }  // namespace
 
 void disco_launch_small_dispatch(const TraceView& v, const PolTable& host, const disco_policy* device, int P, disco_accum* acc,
-                                 hipStream_t stream)
+                                 uint8_t* decision, float* ttft, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_small_dispatch, dim3((unsigned)P), dim3(SM_BLOCK), 0, stream, v, host, device, acc);
+    const PairOut out{decision, ttft};
+    const i64 tasks = decision || ttft ? (v.n_req + 4 * DP_BLOCK - 1) / (4 * DP_BLOCK) * ((P + MAT_COLS - 1) / MAT_COLS) : 0;
+    hipLaunchKernelGGL(k_small_dispatch, dim3((unsigned)(P + tasks)), dim3(SM_BLOCK), 0, stream, v, host, device, P, acc, out);
 }
 
 int disco_small_search_max_bins(void) { return SL_BINS; }

@@ -416,3 +416,15 @@ def test_gaps_beyond_the_pools(B, oracle):
     assert tr["n_tok"] * 4 < 1 << 30
     specs = [dict(mode=0, l_th=0, mig_mode=0), dict(mode=0, l_th=0, mig_mode=1)]
     check_stats(B, oracle, tr, specs, DI.COST_S, tau=DI.TAU, kappa=DI.KAPPA_LAG)
+
+
+# per-pair outputs: four requests per lane, rows that start anywhere, chunks of eight columns, next to the totals of small traces
+# and of large ones
+@pytest.mark.parametrize("n_req", [1, 2, 3, 5, 4095, 4097, 32_768, 32_769, 36_866])
+@pytest.mark.parametrize("cols", [1, 8, 9, 17])
+def test_per_pair_outputs(B, oracle, n_req, cols):
+    print(f"per-pair outputs: n_req={n_req} cols={cols}", flush=True)
+    tr = DI.handmade_trace(700 + n_req, n_req, tokens=False, ties=True)
+    specs = [dict(mode=0, l_th=170 * j) if j % 4 < 2 else
+             (dict(mode=1, l_th=100 * (j % 3), w_tail=DI.f32(0.07 * j)) if j % 4 == 2 else dict(mode=2 + j % 2, beta=DI.f32(0.1 + 0.05 * j), l_mid=j)) for j in range(cols)]
+    check_dispatch(B, oracle, tr, specs)
