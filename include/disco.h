@@ -554,7 +554,7 @@ typedef struct disco_search_out {
  * so there is no host round trip between steps.  When every search is a wait
  * or a ramp slope of a host-resident device-constrained template with
  * -1e37 <= lo and hi <= 1e37, and the number of searches, of steps and of
- * requests make it the faster way, a pass takes up to eight steps of each
+ * requests make it the faster way, a pass takes up to ten steps of each
  * search from the changes of the requests' outcomes between the midpoints;
  * results and recorded history are the same.  When every search is a length threshold of a
  * server-constrained template (Alg. 3) against a prompt-token accumulator,

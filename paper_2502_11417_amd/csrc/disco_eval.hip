@@ -728,20 +728,34 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
         DISCO_HIP(hipGetLastError());
         return DISCO_OK;
     }
-    rc = stage_policies(templ, n_search, ws, L, stream);
-    if (rc) return rc;
     // bisection passes only need the totals their accumulators are made of
     int need = 0;
     for (int j = 0; j < n_search; ++j)
         if (spec[j].which_acc != DISCO_ACC_SERVER_PREFILL_TOK && spec[j].which_acc != DISCO_ACC_DEVICE_PREFILL_TOK) need = 1;
     // Waits and ramp slopes of device-constrained columns: the outcomes of a request are step functions of the
-    // parameter, a pass takes eight bisection steps (disco_search.hip), where that is the faster way.  The bounds are such
+    // parameter, a pass takes ten bisection steps (disco_search.hip), where that is the faster way.  The bounds are such
     // that no midpoint overflows and no ramp is infinity times zero.
-    bool binned = !tabulated && host_templ && disco_search_bins_bytes(n_search) <= L.total - L.slices &&
-                  disco_search_bins_pays(v.n_req, n_search, n_steps, need != 0);
-    for (int j = 0; j < n_search && binned; ++j)
-        binned = templ[j].mode == DISCO_MODE_DEVICE_CONSTRAINED && spec[j].which_param != DISCO_PARAM_L_TH &&
+    bool waits = !tabulated && host_templ;
+    for (int j = 0; j < n_search && waits; ++j)
+        waits = templ[j].mode == DISCO_MODE_DEVICE_CONSTRAINED && spec[j].which_param != DISCO_PARAM_L_TH &&
                  spec[j].lo >= -1e37 && spec[j].hi <= 1e37;
+    const bool small_waits = waits && disco_small(v.n_req) && v.n_req <= WAIT_SMALL_REQ;
+    const bool binned = waits && !small_waits && disco_search_bins_bytes(n_search) <= L.total - L.slices &&
+                        disco_search_bins_pays(v.n_req, n_search, n_steps, need != 0);
+    PolTable host;
+    if (small_waits || binned) {
+        memset(&host, 0, sizeof(host));
+        rc = check_policies(templ, n_search);
+        if (rc == DISCO_OK) memcpy(host.p, templ, sizeof(disco_policy) * (size_t)n_search);
+    } else {
+        rc = stage_policies(templ, n_search, ws, L, stream);
+    }
+    if (rc) return rc;
+    if (small_waits) {
+        disco_launch_small_wait_search(v, host, n_search, n_steps, t, *cost, out, pol_out, acc_out, stream);
+        DISCO_HIP(hipGetLastError());
+        return DISCO_OK;
+    }
     DispFin fin;
     memset(&fin, 0, sizeof(fin));
     fin.kind = 1;
@@ -757,8 +771,8 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
         disco_launch_search_table(v, t, n_search, (int)max_hi + 2, (unsigned*)(ws + L.slices), L.total - L.slices,
                                   (u64*)(ws + L.ppcnt), fin.st, fin.pol_rw, out, stream);
     } else if (binned) {
-        disco_launch_search_bins(v, n_search, n_steps, t, *cost, ws + L.slices, (SearchState*)(ws + L.search), fin.pol_rw,
-                                 (disco_policy*)(ws + L.templ), out, stream);
+        disco_launch_search_bins(v, host, n_search, n_steps, t, *cost, ws + L.slices, L.total - L.slices, (SearchState*)(ws + L.search),
+                                 fin.pol_rw, (disco_policy*)(ws + L.templ), (unsigned*)(ws + L.ticket), (u64*)(ws + L.part), out, stream);
     } else {
         // Every pass evaluates the next `depth` levels of each search's bisection tree as columns of their own and so
         // takes `depth` bisection steps; the recorded steps are those of the plain bisection.

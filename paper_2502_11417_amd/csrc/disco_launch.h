@@ -103,13 +103,21 @@ void disco_launch_dispatch_acc(const TraceView& v, const disco_policy* pol, int 
 void disco_launch_search_table(const TraceView& v, const SpecTable& spec, int n_search, int nbins, unsigned* scratch,
                                size_t scratch_bytes, u64* table, SearchState* st, disco_policy* pol, disco_search_out* sout,
                                hipStream_t stream);
-// Search of w_tail or beta over device-constrained templates (in `pol`; the answers end there too), eight steps per pass.
+// Search of w_tail or beta over device-constrained templates (the answers end in `pol`), ten steps per pass.
 // `scratch`: disco_search_bins_bytes(n_search) bytes.
 size_t disco_search_bins_bytes(int n_search);
 bool disco_search_bins_pays(i64 n_req, int n_search, int n_steps, bool decode);
-void disco_launch_search_bins(const TraceView& v, int n_search, int n_steps, const SpecTable& spec, const disco_cost_params& cost,
-                              void* scratch, SearchState* st, disco_policy* pol, disco_policy* templ, disco_search_out* sout,
-                              hipStream_t stream);
+// (`host`: the templates, staged in `pol`, with the totals cleared, by the first launch)
+void disco_launch_search_bins(const TraceView& v, const PolTable& host, int n_search, int n_steps, const SpecTable& spec,
+                              const disco_cost_params& cost, void* scratch, size_t scratch_bytes, SearchState* st, disco_policy* pol,
+                              disco_policy* templ, unsigned* tickets, u64* totals, disco_search_out* sout, hipStream_t stream);
+// The same on a trace of up to WAIT_SMALL_REQ requests, with the evaluation at the answers: one launch.  2000 requests: 16, 25
+// and 38 us for 4, 16 and 32 steps, the fused passes and the ones above 41, 93 and 157; 32 000: 70, 79 and 98 us against 29, 46
+// and 62 of the passes above (one workgroup: 1.8 us more per 1000 requests).
+constexpr int WAIT_SMALL_REQ = 8192;
+void disco_launch_small_wait_search(const TraceView& v, const PolTable& host, int n_search, int n_steps, const SpecTable& spec,
+                                    const disco_cost_params& cost, disco_search_out* sout, disco_policy* pol_out, disco_accum* acc,
+                                    hipStream_t stream);
 int disco_search_table_max_bins(void);
 int disco_launch_len_table(const TraceView& v, int nbins, unsigned* scratch, size_t scratch_bytes, u64* table, hipStream_t stream);
 // Pairs with the buffer hand-off in class mode: their per-request summaries (a.bufsum), from the summaries of the

@@ -103,7 +103,7 @@ def test_server_tails_of_wait_columns(B, oracle, n_req, max_out, stall_p):
     check_stats(B, oracle, tr, specs, DI.COST_D, tau=DI.TAU, kappa=DI.KAPPA_LAG)
 
 
-# eight bisection steps per pass: step counts around the passes, one to several searches of both parameters at once,
+# ten bisection steps per pass: step counts around the passes, one to several searches of both parameters at once,
 # arrays on and off 16-byte boundaries, exact ties at the searched wait, brackets that run out of floats
 @pytest.mark.parametrize("n_req,n_steps,shift", [(0, 9, 0), (1, 1, 0), (5, 8, 0), (777, 9, 1), (4099, 32, 0), (4096, 64, 3)])
 def test_wait_and_slope_searches(B, oracle, n_req, n_steps, shift):
@@ -219,7 +219,7 @@ def test_a_nan_law_is_not_hidden(B, oracle, law, field):
     assert B.disco_validate_trace(got) == B.ERR["range"]
 
 
-# many wait searches at once: few steps on many requests take the fused passes, the others eight steps per pass
+# many wait searches at once: few steps on many requests take the fused passes, the others ten steps per pass
 @pytest.mark.parametrize("n_req,n_search,n_steps", [(300_011, 10, 1), (300_011, 64, 3), (300_011, 64, 9), (900_001, 32, 4)])
 def test_many_wait_searches(B, oracle, n_req, n_search, n_steps):
     print(f"many wait searches: n_req={n_req} n_search={n_search} n_steps={n_steps}", flush=True)
@@ -428,3 +428,35 @@ def test_per_pair_outputs(B, oracle, n_req, cols):
     specs = [dict(mode=0, l_th=170 * j) if j % 4 < 2 else
              (dict(mode=1, l_th=100 * (j % 3), w_tail=DI.f32(0.07 * j)) if j % 4 == 2 else dict(mode=2 + j % 2, beta=DI.f32(0.1 + 0.05 * j), l_mid=j)) for j in range(cols)]
     check_dispatch(B, oracle, tr, specs)
+
+
+# wait and slope searches behind their second pass: all steps in one launch (8192 requests, the last size, and one more), the rest
+# from the list of the requests that still change (none, a few, some that all change at one wait) and further passes where that
+# list is too long (all of them at one wait); step counts at the ends of the passes
+@pytest.mark.parametrize("n_req,same", [(8191, 0.4), (8192, 1.0), (8193, 0.0), (20_011, 0.4), (40_003, 1.0), (300_011, 0.0)])
+@pytest.mark.parametrize("n_steps", [10, 11, 20, 21, 31, 64])
+def test_searches_behind_the_second_pass(B, oracle, n_req, same, n_steps):
+    print(f"searches behind the second pass: n_req={n_req} same={same} n_steps={n_steps}", flush=True)
+    tr = DI.handmade_trace(700 + n_req, n_req, tokens=False, ties=False)
+    at = np.arange(n_req) % 100 < 100 * same
+    tr["srv_ttft"][at] = np.float32(0.7)
+    total = float(tr["prompt_len"].sum(dtype=np.int64))
+    below = float(tr["prompt_len"][tr["srv_ttft"] > np.float32(0.7)].sum(dtype=np.int64))
+    middle = 0.5 * (below + float(tr["prompt_len"][tr["srv_ttft"] >= np.float32(0.7)].sum(dtype=np.int64)))
+    searches = [  # template, parameter, accumulator, lo, hi, target
+        (dict(mode=1, l_th=-1), B.PARAM_W_TAIL, "device_prefill_tok", 0.0, 4.0, middle),
+        (dict(mode=1, l_th=60), B.PARAM_W_TAIL, "total_cost", 0.1, 3.0, 0.4 * DI.COST_D["cs_pre"] * total),
+        (dict(mode=1, l_th=-1, w_tail=DI.f32(1.5)), B.PARAM_BETA, "device_prefill_tok", 0.0, 0.02, 0.3 * total),
+    ]
+    out = B.disco_budget_search(B.upload_trace(tr), DI.COST_D, [B.Policy(**s[0]) for s in searches],
+                                [dict(which_param=p, which_acc=acc, n_steps=n_steps, lo=lo, hi=hi, target=target)
+                                 for _, p, acc, lo, hi, target in searches])
+    so = B.search_to_host(out["out"], len(searches))
+    pol = B.policies_to_host(out["pol_out"], len(searches))
+    for j, (templ, p, acc, lo, hi, target) in enumerate(searches):
+        find = oracle.search_wait if p == B.PARAM_W_TAIL else oracle.search_slope
+        x, hp, ha = find(tr, oracle.Policy(**templ), lo, hi, n_steps, acc, DI.COST_D, target)
+        same_bits(so["hist_param"][j][:n_steps].astype(np.float32), hp, f"hist_param {j}")
+        same_bits(so["hist_acc"][j][:n_steps], ha, f"hist_acc {j}")
+        got = pol[j].w_tail if p == B.PARAM_W_TAIL else pol[j].beta
+        assert np.float32(got) == np.float32(x) == np.float32(so["param"][j]), j

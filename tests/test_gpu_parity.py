@@ -596,7 +596,7 @@ def test_wait_searches_side_by_side(B, oracle, n_search, n_steps, where):
     """Many wait-time searches in one call, the recorded history is that of the plain bisection for every one of them.
     Templates on the device take the fused passes, where the number of searches decides how many levels of the bisection a
     pass evaluates (three for up to 9 searches, two for up to 21, else one) and the steps need not fill the last pass;
-    templates on the host take passes of up to eight steps at this size."""
+    templates on the host take passes of up to ten steps at this size."""
     print(f"search parity {n_search} searches x {n_steps} steps, templates on the {where}", flush=True)
     tr = DI.handmade_trace(79, 20_011, tokens=False)
     dt = B.upload_trace(tr)
