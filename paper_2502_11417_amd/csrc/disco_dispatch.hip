@@ -10,7 +10,7 @@
 // loads.  With a single column (G = 1) lane = request and four consecutive
 // requests are fetched per lane with 16-byte loads.  Per-column totals stay
 // in registers (32-bit inside a batch, 64-bit across batches) until the end
-// of the kernel, are folded over the workgroup and added into a few copies
+// of the kernel (long tables of threshold columns: per-bucket sums in LDS, disco_buckets.h), are folded over the workgroup and added into a few copies
 // of the device-wide totals; a one-workgroup kernel behind the pass
 // (k_dispatch_fin) folds the copies in a fixed order and, for a budget
 // search, advances the bisection on the device.
@@ -19,6 +19,7 @@
 
 #include <type_traits>
 
+#include "disco_buckets.h"
 #include "disco_launch.h"
 #include "disco_len.h"
 #include "disco_pair.h"
@@ -130,6 +131,16 @@ __device__ __forceinline__ bool word_needed(int f, int need) { return f < 2 || (
 // wave f folds word f over the waves and adds it into one of the copies with
 // one atomic instruction (exact integer atomics; the fp64 TTFT sum is
 // order-dependent in its last bits).
+__device__ __forceinline__ void add_word(u64* tot, int f, int c, u64 x)
+{
+    u64* dst = &tot[(f * DISCO_NCOPY + (int)(blockIdx.x % DISCO_NCOPY)) * 64 + c];
+    if (f < 6) atomicAdd((unsigned long long*)dst, (unsigned long long)x);
+    else if (f == 6) unsafeAtomicAdd(reinterpret_cast<double*>(dst), __longlong_as_double((long long)x));   // hardware fp64 add (the workspace is ordinary device memory)
+    else {
+        atomicMin(reinterpret_cast<unsigned*>(dst), (unsigned)x);
+        atomicMax(reinterpret_cast<unsigned*>(dst) + 1, (unsigned)(x >> 32));
+    }
+}
 template <int G>
 __device__ __forceinline__ void add_to_totals(const u64* sh, u64* tot, int P, int need)
 {
@@ -138,14 +149,7 @@ __device__ __forceinline__ void add_to_totals(const u64* sh, u64* tot, int P, in
     u64 x = sh[f * DP_BLOCK + c];
 #pragma unroll
     for (int w = 1; w < DP_WAVES; ++w) x = fold_word(f, x, sh[f * DP_BLOCK + w * G + c]);
-    if (c >= P) return;
-    u64* dst = &tot[(f * DISCO_NCOPY + (int)(blockIdx.x % DISCO_NCOPY)) * 64 + c];
-    if (f < 6) atomicAdd((unsigned long long*)dst, (unsigned long long)x);
-    else if (f == 6) unsafeAtomicAdd(reinterpret_cast<double*>(dst), __longlong_as_double((long long)x));   // hardware fp64 add (the workspace is ordinary device memory)
-    else {
-        atomicMin(reinterpret_cast<unsigned*>(dst), (unsigned)x);
-        atomicMax(reinterpret_cast<unsigned*>(dst) + 1, (unsigned)(x >> 32));
-    }
+    if (c < P) add_word(tot, f, c, x);
 }
 
 // After the pass (k_dispatch_fin): wave f reads the copies of word f, puts them back to their
@@ -331,6 +335,14 @@ __device__ __forceinline__ void batch_pairs_need(const Staged* __restrict__ st, 
     }
 }
 
+// Batches per wave up to which a table of threshold columns takes every pair for itself rather than the buckets of
+// disco_buckets.h, whose cost hardly depends on the columns (sorting, clearing and folding: 3 us more than a pass of one batch).
+// Replayed calls on 256 workgroups, pairs against buckets: 64 columns, 2 10^5 requests (one batch) 17.1 / 18.4 us, 3 10^5 23.2 / 18.5,
+// 10^6 31.7 / 19.3, 4 10^6 90.8 / 29.3; 32 columns 15.3 / 17.4, 18.9 / 17.5, 23.3 / 17.9, 57.1 / 27.8; 16 columns 14.4 / 16.7,
+// 16.5 / 17.0, 19.8 / 17.2, 41.3 / 27.3; 8 columns 10^6 17.6 / 16.8, 4 10^6 31.6 / 26.2; 4 columns 16.8 / 16.9 and 27.9 / 26.2.
+template <int G>
+constexpr i64 pair_batches() { return G >= 32 ? 1 : (G == 16 ? 2 : 4); }
+
 template <int G>
 __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const disco_policy* __restrict__ pol, int P,
                                                            u64* __restrict__ part, DispFin fin, int nacc, PairOut out)
@@ -344,6 +356,14 @@ __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const d
     const int col = lane & (G - 1), sub = lane / G;
     const bool colv = col < P;
     const disco_policy p = pol[colv ? col : 0];
+    if (G >= 4 && tr.n_req > pair_batches<G>() * nacc * DP_BLOCK && table_mode(p, colv) == 0) {
+        u64* words = sh + sizeof(Buckets) / sizeof(u64);
+        static_assert(sizeof(Buckets) % sizeof(u64) == 0 && sizeof(Buckets) + 8 * 64 * sizeof(u64) <= sizeof(smem), "buckets and words");
+        if (!threshold_buckets<G>(tr, pol, P, fin.need, (int)blockIdx.x, nacc, *reinterpret_cast<Buckets*>(smem), words)) return;
+        const int f = threadIdx.x >> 6, c = threadIdx.x & 63;
+        if (f < 8 && c < P && word_needed(f, fin.need)) add_word(part, f, c, words[f * 64 + c]);
+        return;
+    }
     ColTotals t{0, 0, 0, 0, 0, 0.0, 0xFFFFFFFFu, 0u};
     u64 tot_l = 0, tot_n = 0, tot_c = 0;      // column-independent sums, kept by the loading lane
     Staged* st = stage + wave * 64;

@@ -460,3 +460,38 @@ def test_searches_behind_the_second_pass(B, oracle, n_req, same, n_steps):
         same_bits(so["hist_acc"][j][:n_steps], ha, f"hist_acc {j}")
         got = pol[j].w_tail if p == B.PARAM_W_TAIL else pol[j].beta
         assert np.float32(got) == np.float32(x) == np.float32(so["param"][j]), j
+
+
+# tables of threshold columns from their sorted thresholds (workgroups with more than one batch per wave: one workgroup here): the
+# fewest and most columns of each width, thresholds below, between, at and above all lengths, equal ones, lengths and tokens
+# beyond 2^24, server TTFTs of infinity, arrays on and off 16-byte boundaries, pairs beside the totals
+@pytest.mark.parametrize("n_req,P,shift", [(1025, 64, 0), (1030, 33, 1), (5003, 64, 2), (2049, 16, 0), (4097, 5, 3), (20_011, 8, 0), (4098, 3, 0)])
+@pytest.mark.parametrize("equal", [False, True])
+def test_threshold_tables_by_bucket(B, oracle, n_req, P, shift, equal):
+    print(f"threshold buckets: n_req={n_req} P={P} shift={shift} equal={equal}", flush=True)
+    tr = DI.handmade_trace(800 + n_req, n_req, tokens=False, ties=True)
+    tr["srv_ttft"][5] = np.inf
+    tr["prompt_len"][7], tr["prompt_len"][n_req - 1] = (1 << 24) + 5, 2**31 - 1
+    tr["output_len"][9] = (1 << 24) + 7
+    at = np.sort(tr["prompt_len"])[np.arange(P) * n_req // P]
+    th = np.full(P, at[P // 2]) if equal else np.random.default_rng(P).permutation(at + np.arange(P) % 2)
+    th = [int(x) for x in th]
+    if not equal:
+        th[0], th[P - 1], th[P // 2] = -5, 2**31 - 1, 0
+    specs = [dict(mode=0, l_th=x) for x in th]
+    try:
+        assert B._lib.disco_set_grid_divisor(64) == 0
+        dt, acc = check_dispatch(B, oracle, tr, specs)
+        check_dispatch(B, oracle, tr, specs, materialise=False)
+        for name in ("prompt_len", "output_len", "srv_ttft", "dev_pre_spt"):
+            x = getattr(dt, name)
+            buf = torch.zeros(x.numel() + shift, dtype=x.dtype, device="cuda")[shift:]
+            buf.copy_(x)
+            setattr(dt, name, buf)
+        moved = B.accum_to_host(B.disco_eval_dispatch(dt, [B.Policy(**s) for s in specs])["acc"], P)
+        torch.cuda.synchronize()
+    finally:
+        assert B._lib.disco_set_grid_divisor(1) == 0
+    for f in ("s_pre", "s_dec", "d_pre", "d_dec", "n_dev_started", "n_dev_win", "ttft_min_bits", "ttft_max_bits"):
+        assert (moved[f] == acc[f]).all(), f
+    assert np.allclose(moved["ttft_sum"], acc["ttft_sum"], rtol=1e-12, atol=0)       # fp64 sums in another order
