@@ -34,20 +34,26 @@ __device__ void select_init(const SelInit& si, int which, int P, const disco_pol
     __shared__ unsigned smin, smax;
     __shared__ int all_thresholds;
     if (threadIdx.x == 0) { smin = 0xFFFFFFFFu; smax = 0u; all_thresholds = 1; }
-    __syncthreads();
     if (which == 0) {
         // a table of length-threshold columns (Alg. 3) is selected by classes: thresholds in ascending order
         const int t = threadIdx.x;
-        __shared__ int lth_s[DISCO_MAX_COLS];
-        if (t < P) {
-            if (pol[t].mode != DISCO_MODE_SERVER_CONSTRAINED) all_thresholds = 0;
-            lth_s[t] = pol[t].l_th;
-        }
+        __shared__ __align__(16) int lth_s[DISCO_MAX_COLS];
+        unsigned lo = 0u, hi = 0u;
+        int mode = 0, lth = 0;
+        if (t < P) { mode = pol[t].mode; lth = pol[t].l_th; lo = acc[t].ttft_min_bits; hi = acc[t].ttft_max_bits; }
+        if (t < DISCO_MAX_COLS) lth_s[t] = t < P ? lth : 0x7FFFFFFF;
         __syncthreads();
         if (t < P) {
-            const int lth = lth_s[t];
+            if (mode != DISCO_MODE_SERVER_CONSTRAINED) all_thresholds = 0;
+            atomicMin(&smin, lo);
+            atomicMax(&smax, hi);
             int rank = 0;
-            for (int k = 0; k < P; ++k) rank += (lth_s[k] < lth || (lth_s[k] == lth && k < t)) ? 1 : 0;
+#pragma unroll
+            for (int k = 0; k < DISCO_MAX_COLS; k += 4) {          // (the ones behind the table are never in front)
+                const int4 x = *reinterpret_cast<const int4*>(&lth_s[k]);
+                rank += (x.x < lth || (x.x == lth && k < t)) + (x.y < lth || (x.y == lth && k + 1 < t)) +
+                        (x.z < lth || (x.z == lth && k + 2 < t)) + (x.w < lth || (x.w == lth && k + 3 < t));
+            }
             S->tc.sorted_lth[rank] = lth;
             S->tc.col_of_pos[rank] = (unsigned char)t;
             S->tc.pos_of_col[t] = (unsigned char)rank;
@@ -55,10 +61,6 @@ __device__ void select_init(const SelInit& si, int which, int P, const disco_pol
         __syncthreads();
         if (t == 0) { S->tc.on = all_thresholds; S->tb.on = 0; S->tb.pad = 0; }
         if (t < DISCO_MAX_SLOTS) { S->tb.fill[t] = 0u; S->tb.of_slot[t] = -1; }
-    }
-    if (which == 0 && (int)threadIdx.x < P) {
-        atomicMin(&smin, acc[threadIdx.x].ttft_min_bits);
-        atomicMax(&smax, acc[threadIdx.x].ttft_max_bits);
     }
     __syncthreads();
     if (which == 0 && threadIdx.x < DISCO_MAX_PASS) {

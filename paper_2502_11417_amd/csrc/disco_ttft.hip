@@ -430,24 +430,38 @@ __device__ __forceinline__ void cls_body(const TraceView& tr, int P, int nq, int
         unsigned* psum = hist;                              // the bins are idle
         const int w0 = g.plan.width[0];
         {
+            constexpr int PARTS = DP_BLOCK / DISCO_MAX_SLOTS, PER = (TH_ROWS + PARTS - 1) / PARTS;
             const int f = t & (DISCO_MAX_SLOTS - 1), part = t / DISCO_MAX_SLOTS;
+            const bool on = T.slive[f] && T.first_of[f] == f;
+            const unsigned* src = rowsum + (on ? T.sprefix[f] : 0u);
             unsigned a = 0u;
-            if (T.slive[f] && T.first_of[f] == f)
-                for (int row = part; row < 2 * (P + 1); row += DP_BLOCK / DISCO_MAX_SLOTS)
-                    a += rowsum[((size_t)row << w0) + T.sprefix[f]];
-            psum[t] = a;
+#pragma unroll
+            for (int z = 0; z < PER; ++z) {                 // (all reads in flight: one after the other they cost 8 us)
+                const int row = part + z * PARTS;
+                const unsigned x = src[(size_t)(row < 2 * (P + 1) ? row : 0) << w0];
+                a += row < 2 * (P + 1) ? x : 0u;
+            }
+            psum[t] = on ? a : 0u;
         }
         __syncthreads();
-        if (t < DISCO_MAX_SLOTS) {
-            unsigned a = 0u;
-            for (int part = 0; part < DP_BLOCK / DISCO_MAX_SLOTS; ++part) a += psum[part * DISCO_MAX_SLOTS + t];
-            T.bcnt[t] = a;
-        }
-        __syncthreads();
-        if (t < DISCO_MAX_SLOTS) {
-            u64 at = 0;
-            for (int z = 0; z < t; ++z) at += ((u64)T.bcnt[z] + 3ull) & ~3ull;      // buckets start at multiples of four entries
-            const u64 end = at + T.bcnt[t];
+        if (t < DISCO_MAX_SLOTS) {                          // two waves, the second adds up the slots of the first too
+            static_assert(DISCO_MAX_SLOTS == 128, "two waves");
+            auto count = [&](int slot) {
+                unsigned a = 0u;
+#pragma unroll
+                for (int part = 0; part < DP_BLOCK / DISCO_MAX_SLOTS; ++part) a += psum[part * DISCO_MAX_SLOTS + slot];
+                return a;
+            };
+            auto room = [](unsigned a) { return ((u64)a + 3ull) & ~3ull; };         // buckets start at multiples of four entries
+            const unsigned mine = count(t);
+            u64 incl = room(mine);
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const u64 y = __shfl_up((unsigned long long)incl, d, 64);
+                if ((t & 63) >= d) incl += y;
+            }
+            if (t >= 64) incl += wave_sum_u64(room(count(t - 64)));
+            const u64 at = incl - room(mine), end = at + mine;
             T.bbase[t] = (unsigned)(at < TG_CAP ? at : TG_CAP);
             T.bend[t] = (unsigned)(end < TG_CAP ? end : TG_CAP);
             if (t == DISCO_MAX_SLOTS - 1) T.scatter = end <= (u64)TG_CAP;
@@ -821,7 +835,13 @@ __global__ __launch_bounds__(1024) void k_ttft_select(SelState* S, int pass, int
             if (q == 0) mine = rowsum[((size_t)col << width) + t];
         } else {                                           // device rows ub <= p, race rows ub > p
             const int p = S->tc.pos_of_col[col];
-            for (int ub = q; ub <= P; ub += 4) mine += rowsum[((size_t)(ub <= p ? ub : P + 1 + ub) << width) + t];
+            constexpr int PER = (DISCO_MAX_COLS + 4) / 4;
+#pragma unroll
+            for (int z = 0; z < PER; ++z) {                // (all reads in flight)
+                const int ub = q + 4 * z;
+                const unsigned x = rowsum[((size_t)(ub <= p ? ub : (ub <= P ? P + 1 + ub : 0)) << width) + t];
+                mine += ub <= P ? x : 0u;
+            }
         }
     }
     part[threadIdx.x] = mine;
