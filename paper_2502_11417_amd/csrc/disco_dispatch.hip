@@ -10,8 +10,9 @@
 // loads.  With a single column (G = 1) lane = request and four consecutive
 // requests are fetched per lane with 16-byte loads.  Per-column totals stay
 // in registers (32-bit inside a batch, 64-bit across batches) until the end
-// of the kernel (long tables of threshold columns: per-bucket sums in LDS, disco_buckets.h), are folded over the workgroup and added into a few copies
-// of the device-wide totals; a one-workgroup kernel behind the pass
+// of the kernel, are folded over the workgroup and added into a few copies
+// of the device-wide totals (long tables of threshold columns on many
+// requests: sums per bucket of the sorted thresholds, disco_buckets.h); a one-workgroup kernel behind the pass
 // (k_dispatch_fin) folds the copies in a fixed order and, for a budget
 // search, advances the bisection on the device.
 #include <math.h>

@@ -9,11 +9,12 @@
 //   k_pp_reduce  per-workgroup count slices -> counts per class and length
 //   k_tl_runs    the listed timelines' gaps, counted per value once
 //                (disco_tl_runs.h)
-//   k_tl_hist    one pass over these and what is left of the walk list (workgroup body and walker in
-//                disco_tl_hist_fast.h): a wave walks one request at a time in
-//                chunks of 256 tokens, four consecutive tokens per lane (one
-//                16-byte load per lane and chunk, the next chunk's load
-//                issued before the current one is used)
+//
+// A pass over these and what is left of the walk list is k_tbt_pass (the
+// selection's own file; workgroup body and walker in disco_tl_hist_fast.h): a
+// wave walks one request at a time in chunks of 256 tokens, four consecutive
+// tokens per lane (one 16-byte load per lane and chunk, the next chunk's
+// load issued before the current one is used).
 //
 // The delivery recurrence delta_t = max(r_t, delta_{t-1} + tau) is evaluated
 // in the shifted domain u_t = r_t - t tau, where it is a running maximum M_t
