@@ -41,8 +41,14 @@ constexpr int SB_MAX_BLOCKS = 512;                // two workgroups per CU
 constexpr int SB_HEAD = 4, SB_WORDS = SB_HEAD + 2 * SB_CAND, SB_COPIES = 4;
 // The list: up to this many requests one workgroup takes all remaining steps (1 us per 1000 of them and round, where all of them
 // change between the same two candidates); longer ones take further passes (empty ones are two launches each, 4 to 5 us).
-constexpr unsigned LIST_MAX = 32768;
+// The workgroups of several searches walk their lists side by side, where further passes cost every search its own.  10^6
+// requests, 32 steps, with a limit of 8192 and of 32 768: one search 85 / 86 us, server TTFTs of whole milliseconds (thousands
+// at one value) 87 / 105; four searches 142 / 117, 16 276 / 215, 64 791 / 698.
+constexpr unsigned LIST_MAX = 32768, LIST_MAX_FEW = 8192;
+constexpr int LIST_FEW = 2;
 constexpr unsigned LIST_LDS = 2048;               // entries that a workgroup can add (one with more of them ends the list)
+// Requests of one interval that the walk holds in LDS; with more of them its rounds go over the whole list.
+constexpr unsigned WALK_LDS = 8192;
 
 struct BinSpec { double target; float lo, hi; int which_param, which_acc; };
 struct BinSpecs { BinSpec s[DISCO_MAX_COLS]; };
@@ -254,7 +260,7 @@ struct WalkLds {
     u64 head[SB_HEAD], wsum[SB_BLOCK / 64], wave[4][SB_BLOCK / 64];
     float sc[SB_CAND];
     SearchState st;
-    unsigned kept[LIST_LDS], nkept;
+    unsigned kept[WALK_LDS], nkept;
     int chosen;                    // interval between candidates that the steps have led to
 };
 
@@ -314,7 +320,7 @@ __device__ __forceinline__ void keep_open(WalkLds& w, unsigned count, Of&& of, W
         const unsigned x = where(e);
         if ((x & 0xFFFFu) == k || (x >> 16) == k) {
             const unsigned at = atomicAdd(&w.nkept, 1u);
-            if (at < LIST_LDS) w.kept[at] = of(e);
+            if (at < WALK_LDS) w.kept[at] = of(e);
         }
     }
     __syncthreads();
@@ -387,7 +393,7 @@ __device__ __forceinline__ void rounds(const TraceView& tr, const uint2* __restr
         take_steps(w, depth, cost, o);
         if (ALL && !from_lds) {
             keep_open(w, count, [&](unsigned e) { return e; }, [&](unsigned e) { return where[e]; });
-            if (w.nkept <= LIST_LDS) {
+            if (w.nkept <= WALK_LDS) {
                 from_lds = true;
                 count = w.nkept;
                 const int at = known_end(w);
@@ -436,7 +442,7 @@ __global__ __launch_bounds__(SB_BLOCK) void k_search_walk(TraceView tr, SearchSt
     if (rest) {
         const uint2* mylist = list + (size_t)j * cap;
         keep_open(w, count, [&](unsigned e) { return mylist[e].x; }, [&](unsigned e) { return mylist[e].y; });
-        const bool few = w.nkept <= LIST_LDS;                // (else all of the list, against the first candidate)
+        const bool few = w.nkept <= WALK_LDS;                // (else all of the list, against the first candidate)
         const int at = few ? known_end(w) : 0;
         const float x_base = w.sc[at];
         if (t == 0) { w.head[2] = w.tot[at]; w.head[3] = w.tot[SB_CAND + at]; }
@@ -541,7 +547,8 @@ void disco_launch_search_bins(const TraceView& v, const PolTable& host, int n_se
     unsigned* listed = (unsigned*)(cand + (size_t)n_search * SB_CAND);
     uint2* list = (uint2*)((char*)scratch + disco_search_bins_bytes(n_search));
     const size_t room = (scratch_bytes - disco_search_bins_bytes(n_search)) / sizeof(uint2) / (size_t)n_search;
-    const unsigned cap = (unsigned)(room < LIST_MAX ? room : LIST_MAX);
+    const size_t limit = n_search <= LIST_FEW ? LIST_MAX_FEW : LIST_MAX;
+    const unsigned cap = (unsigned)(room < limit ? room : limit);
     // one pass, two passes that share the steps out evenly, or two full ones and the rest from the list of the second; passes
     // behind those for searches whose list is too long
     const bool rest = n_steps > 2 * SB_DEPTH;

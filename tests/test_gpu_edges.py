@@ -453,6 +453,10 @@ def test_searches_behind_the_second_pass(B, oracle, n_req, same, n_steps):
                                  for _, p, acc, lo, hi, target in searches])
     so = B.search_to_host(out["out"], len(searches))
     pol = B.policies_to_host(out["pol_out"], len(searches))
+    alone = B.disco_budget_search(B.upload_trace(tr), DI.COST_D, [B.Policy(**searches[0][0])],       # (a shorter list)
+                                  [dict(which_param=searches[0][1], which_acc=searches[0][2], n_steps=n_steps, lo=searches[0][3],
+                                        hi=searches[0][4], target=searches[0][5])])
+    same_bits(B.search_to_host(alone["out"], 1)["hist_acc"][0][:n_steps], so["hist_acc"][0][:n_steps], "one search")
     for j, (templ, p, acc, lo, hi, target) in enumerate(searches):
         find = oracle.search_wait if p == B.PARAM_W_TAIL else oracle.search_slope
         x, hp, ha = find(tr, oracle.Policy(**templ), lo, hi, n_steps, acc, DI.COST_D, target)
