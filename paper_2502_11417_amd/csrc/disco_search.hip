@@ -26,26 +26,19 @@
 #include <string.h>
 
 #include "disco_launch.h"
+#include "disco_search_plan.h"
 #include "disco_small.h"
 #include "disco_stage.h"
 #include "disco_state.h"
 
 namespace {
 
-constexpr int SB_DEPTH = 10;                      // bisection steps per pass, at most
 constexpr int SB_CAND = 1 << SB_DEPTH;            // (2^SB_DEPTH - 1 candidates)
 constexpr int SB_BLOCK = 1024;
 constexpr int SB_MAX_BLOCKS = 512;                // two workgroups per CU
 // Device-wide bins of a search, SB_COPIES copies: prompt tokens, output tokens, device prompt tokens and device
 // output tokens at the first candidate, then the changes of the latter two by candidate.
 constexpr int SB_HEAD = 4, SB_WORDS = SB_HEAD + 2 * SB_CAND, SB_COPIES = 4;
-// The list: up to this many requests one workgroup takes all remaining steps (1 us per 1000 of them and round, where all of them
-// change between the same two candidates); longer ones take further passes (empty ones are two launches each, 4 to 5 us).
-// The workgroups of several searches walk their lists side by side, where further passes cost every search its own.  10^6
-// requests, 32 steps, with a limit of 8192 and of 32 768: one search 85 / 86 us, server TTFTs of whole milliseconds (thousands
-// at one value) 87 / 105; four searches 142 / 117, 16 276 / 215, 64 791 / 698.
-constexpr unsigned LIST_MAX = 32768, LIST_MAX_FEW = 8192;
-constexpr int LIST_FEW = 2;
 constexpr unsigned LIST_LDS = 2048;               // entries that a workgroup can add (one with more of them ends the list)
 // Requests of one interval that the walk holds in LDS; with more of them its rounds go over the whole list.
 constexpr unsigned WALK_LDS = 8192;
@@ -547,17 +540,7 @@ void disco_launch_search_bins(const TraceView& v, const PolTable& host, int n_se
     unsigned* listed = (unsigned*)(cand + (size_t)n_search * SB_CAND);
     uint2* list = (uint2*)((char*)scratch + disco_search_bins_bytes(n_search));
     const size_t room = (scratch_bytes - disco_search_bins_bytes(n_search)) / sizeof(uint2) / (size_t)n_search;
-    const size_t limit = n_search <= LIST_FEW ? LIST_MAX_FEW : LIST_MAX;
-    const unsigned cap = (unsigned)(room < limit ? room : limit);
-    // one pass, two passes that share the steps out evenly, or two full ones and the rest from the list of the second; passes
-    // behind those for searches whose list is too long
-    const bool rest = n_steps > 2 * SB_DEPTH;
-    int depth[DISCO_MAX_STEPS + 1], npass = 0;
-    if (n_steps <= SB_DEPTH) depth[npass++] = n_steps;
-    else if (!rest) { depth[npass++] = (n_steps + 1) / 2; depth[npass++] = n_steps / 2; }
-    else
-        for (int left = n_steps; left > 0; left -= SB_DEPTH) depth[npass++] = left < SB_DEPTH ? left : SB_DEPTH;
-    depth[npass] = 0;
+    const SearchPlan s = search_plan(v.n_req, n_search, n_steps, room);
     i64 b = (v.n_req + 4 * SB_BLOCK - 1) / (4 * SB_BLOCK);
     const i64 most = SB_MAX_BLOCKS / n_search > 8 ? SB_MAX_BLOCKS / n_search : 8;      // (every workgroup adds up to 2048 bins)
     if (b > most) b = most;
@@ -566,15 +549,15 @@ void disco_launch_search_bins(const TraceView& v, const PolTable& host, int n_se
     auto a16 = [](const void* q) { return ((uintptr_t)q & 15u) == 0; };
     const bool vec = a16(v.l) && a16(v.n) && a16(v.s) && (!v.k || a16(v.k));
     hipLaunchKernelGGL(k_bins_init, dim3((unsigned)n_search + 1u), dim3(SB_BLOCK), 0, stream, host, bin_specs(spec, n_search), n_search, n_steps, st,
-                       templ, bins, cand, listed, depth[0], pol, tickets, totals);
+                       templ, bins, cand, listed, s.depth[0], pol, tickets, totals);
     int from = 0;
-    for (int pass = 0; pass < npass; ++pass) {
-        const int M = (1 << depth[pass]) - 1;
-        uint2* mylist = rest && pass == 1 ? list : nullptr;
-        if (vec) hipLaunchKernelGGL(k_search_bins<true>, dim3((unsigned)b, (unsigned)n_search), dim3(SB_BLOCK), 0, stream, v, st, templ, cand, bins, M, from, mylist, cap, listed);
-        else hipLaunchKernelGGL(k_search_bins<false>, dim3((unsigned)b, (unsigned)n_search), dim3(SB_BLOCK), 0, stream, v, st, templ, cand, bins, M, from, mylist, cap, listed);
+    for (int pass = 0; pass < s.npass; ++pass) {
+        const int M = (1 << s.depth[pass]) - 1;
+        uint2* mylist = s.list && pass == 1 ? list : nullptr;
+        if (vec) hipLaunchKernelGGL(k_search_bins<true>, dim3((unsigned)b, (unsigned)n_search), dim3(SB_BLOCK), 0, stream, v, st, templ, cand, bins, M, from, mylist, s.cap, listed);
+        else hipLaunchKernelGGL(k_search_bins<false>, dim3((unsigned)b, (unsigned)n_search), dim3(SB_BLOCK), 0, stream, v, st, templ, cand, bins, M, from, mylist, s.cap, listed);
         hipLaunchKernelGGL(k_search_walk, dim3((unsigned)n_search), dim3(SB_BLOCK), 0, stream, v, st, templ, pol, cand, bins, sout, cost,
-                           depth[pass], depth[pass + 1], from, mylist, cap, listed);
-        from += depth[pass];
+                           s.depth[pass], s.depth[pass + 1], from, mylist, s.cap, listed);
+        from += s.depth[pass];
     }
 }

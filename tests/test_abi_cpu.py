@@ -194,3 +194,36 @@ def test_policy_type_agrees_with_the_oracle(B, oracle):
     for cs_pre, cs_dec, e_pre, e_dec, lam in itertools.product(vals, vals, vals, vals, (0.5, 1.0, 1.5)):
         cost = {"cs_pre": cs_pre, "cs_dec": cs_dec, "e_pre": e_pre, "e_dec": e_dec, "lam": lam}
         assert B.disco_policy_type(cost) == oracle.policy_type(cost), cost
+
+
+def test_passes_of_a_search(tmp_path):
+    """Every step in a pass of at most ten; no list of 32-bit request indices beyond 2^32 requests."""
+    import subprocess
+    src = tmp_path / "plan.cpp"
+    src.write_text("""#include <stdio.h>
+#include <initializer_list>
+#include "disco_search_plan.h"
+int main() {
+    const int64_t reqs[] = {8193, ((int64_t)1 << 32) - 1, (int64_t)1 << 32, ((int64_t)1 << 32) + 1, (int64_t)1 << 40};
+    for (int64_t n : reqs)
+        for (int k : {1, 2, 3, 64})
+            for (int steps = 1; steps <= DISCO_MAX_STEPS; ++steps)
+                for (size_t room : {(size_t)0, (size_t)9000, (size_t)1 << 40}) {
+                    const SearchPlan s = search_plan(n, k, steps, room);
+                    int sum = 0, most = 0;
+                    for (int p = 0; p < s.npass; ++p) { sum += s.depth[p]; most = s.depth[p] > most ? s.depth[p] : most; }
+                    printf("%lld %d %d %zu %d %d %d %d %u %d\\n", (long long)n, k, steps, room, s.npass, sum, most, (int)s.list, s.cap, s.depth[s.npass]);
+                }
+    return 0;
+}
+""")
+    exe = tmp_path / "plan"
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_11417_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    rows = [[int(x) for x in line.split()] for line in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()]
+    assert len(rows) == 5 * 4 * 64 * 3
+    for n, k, steps, room, npass, total, most, listed, cap, behind in rows:
+        assert total == steps and 1 <= most <= 10 and behind == 0
+        assert npass == -(-steps // 10)
+        assert bool(listed) == (steps > 20 and n - 1 <= 0xFFFFFFFF)
+        assert cap == min(room, 8192 if k <= 2 else 32768)

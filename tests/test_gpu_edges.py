@@ -466,6 +466,43 @@ def test_searches_behind_the_second_pass(B, oracle, n_req, same, n_steps):
         assert np.float32(got) == np.float32(x) == np.float32(so["param"][j]), j
 
 
+# more than 2^32 requests: those that still change behind the second pass are the last ones.  All the others are over before the
+# brackets begin and take no device, so that the histories are those of the same searches on the last ones alone
+def test_searches_of_more_than_2_to_the_32_requests(B):
+    n_req, tail, n_steps = (1 << 32) + 4099, 3001, 40
+    print(f"searches of {n_req} requests", flush=True)
+    rng = np.random.default_rng(32)
+    few = dict(prompt_len=rng.integers(1, 4, tail).astype(np.int32), output_len=rng.integers(1, 300, tail).astype(np.int32),
+               srv_ttft=rng.uniform(0.6, 7.4, tail).astype(np.float32))
+    rest = dict(prompt_len=1, output_len=1, srv_ttft=0.25)
+
+    def trace(n):
+        arrays = {}
+        for name, x in few.items():
+            arrays[name] = torch.full((n,), rest[name], dtype=torch.float32 if name == "srv_ttft" else torch.int32, device="cuda")
+            arrays[name][n - tail:] = torch.from_numpy(x).cuda()
+        return B.Trace(n_req=n, n_tok=0, srv_tbt=None, dev_pre_spt=None, dev_dec_spt=None, tok_off=None, tok_arr=None,
+                       dev_pre_spt_s=DI.f32(0.01), dev_dec_spt_s=DI.f32(0.05), dev_ttft_c=0.0, **arrays)
+
+    templ = [dict(mode=1, l_th=-1), dict(mode=1, l_th=-1, w_tail=float("inf"))]
+    specs = [dict(which_param=B.PARAM_W_TAIL, which_acc="device_prefill_tok", n_steps=n_steps, lo=0.5, hi=8.0, target=2500.0),
+             dict(which_param=B.PARAM_BETA, which_acc="device_cost", n_steps=n_steps, lo=0.5, hi=8.0, target=1000 * DI.COST_D["lam"] * DI.COST_D["e_pre"])]
+    res = []
+    for n in (tail, n_req):
+        t = trace(n)
+        assert t.srv_ttft.numel() == n
+        out = B.disco_budget_search(t, DI.COST_D, [B.Policy(**x) for x in templ], specs, ws=B.workspace(0, 2))
+        res.append(B.search_to_host(out["out"], 2).copy())
+        del t, out
+    torch.cuda.empty_cache()
+    alone, among = res
+    for f in ("hist_param", "hist_acc", "param", "acc_at_param", "lo", "hi"):
+        same_bits(among[f], alone[f], f)
+    for f in ("d_pre", "d_dec", "n_dev_started", "n_dev_win"):
+        assert (among["at_param"][f] == alone["at_param"][f]).all(), f
+    assert (among["at_param"]["s_pre"] == int(few["prompt_len"].sum()) + n_req - tail).all()
+
+
 # tables of threshold columns from their sorted thresholds (workgroups with more than one batch per wave: one workgroup here): the
 # fewest and most columns of each width, thresholds below, between, at and above all lengths, equal ones, lengths and tokens
 # beyond 2^24, server TTFTs of infinity, arrays on and off 16-byte boundaries, pairs beside the totals
