@@ -117,7 +117,8 @@ struct TlPlan {
     int window;                    // key bits of the window, 0 = raw 31-bit keys
     unsigned key_lo;
     int fallback;                  // 1: one histogram per (column, quantile) slot instead of per class
-    int reset;                     // the slots start over with this pass (empty prefix, full rank)
+    short reset;                   // the slots start over with this pass (empty prefix, full rank)
+    short walks;                   // listed timelines are left to be walked: bit 0 of the streaming kinds, bit 1 of the buffer hand-off kinds
     unsigned grp_prefix[DISCO_MAX_GRP];
     signed char slot_grp[DISCO_MAX_SLOTS];       // prefix group of each live slot, -1 otherwise
 };
@@ -128,7 +129,7 @@ struct TlSel {
     int error;                     // a column set could not be placed (never expected)
     unsigned nlist;                // requests with a timeline whose tokens are walked: entries at the front of the walk list
     unsigned nlist_back;           // ... and entries at its back (the short requests, see walk_list_entry)
-    unsigned left_fast, left_buf;  // listed timelines whose tokens the passes walk: streaming kinds, buffer hand-off kinds
+    unsigned left_fast, left_buf;  // not 0: there are listed timelines whose tokens the passes walk (see TlPlan)
     TlPlan plan[DISCO_TBT_MAX_PASS + 1];         // [0]: where the selection starts; [1 + p]: pass p
     int restart[DISCO_TBT_MAX_PASS];             // pass p missed the window
     // device-wide hash table of the column sets (classification): every workgroup enters its distinct sets, those of

@@ -110,7 +110,7 @@ __device__ __forceinline__ void tl_hist_buf_body(unsigned* smem, const TraceView
     const HistArgs& a = ba.h;
     const TlSel* tl = &a.S->tl;
     const int width = __builtin_amdgcn_readfirstlane(pl.width);
-    if (*ba.buffer_flag == 0u || tl->left_buf == 0u || width <= 0 || pl.fallback) return;
+    if (*ba.buffer_flag == 0u || (__builtin_amdgcn_readfirstlane(pl.walks) & 2) == 0 || width <= 0 || pl.fallback) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ncls = tl->ncls, nwalk = tl->nwalk;
     const HistCtx h = hist_ctx(smem, pl, nwalk);

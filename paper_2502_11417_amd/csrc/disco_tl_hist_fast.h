@@ -27,7 +27,7 @@ __device__ __forceinline__ void tbt_plan(const SelState* S, int pass, int P, int
     const TlSel& tl = S->tl;
     const TlPlan& prev = tl.plan[pass];
     const int lane = threadIdx.x & 63, ns = P * nq;
-    const int ncls = tl.ncls, nwalk = tl.nwalk;
+    const int ncls = tl.ncls, nwalk = tl.nwalk, walks = (tl.left_fast != 0u ? 1 : 0) | (tl.left_buf != 0u ? 2 : 0);
     unsigned p0 = 0u, p1 = 0u;
     bool live0 = false, live1 = false;
     if (lane < ns) { p0 = S->slot[1][lane].prefix; live0 = !S->slot[1][lane].done; }
@@ -88,7 +88,7 @@ __device__ __forceinline__ void tbt_plan(const SelState* S, int pass, int P, int
     if (G == 0 || done) w = 0;                 // nothing left to select
     if (lane == 0) {
         out.left = left; out.shift = left - w; out.width = w; out.G = G; out.window = window; out.key_lo = key_lo;
-        out.fallback = fallback; out.reset = reset;
+        out.fallback = fallback; out.reset = (short)reset; out.walks = (short)walks;
 #pragma unroll
         for (int k = 0; k < DISCO_MAX_GRP; ++k) out.grp_prefix[k] = grp[k];
     }
@@ -256,7 +256,7 @@ __device__ __forceinline__ void tl_hist_fast_body(unsigned* smem, const TraceVie
     const TlSel* tl = &a.S->tl;
     const int width = __builtin_amdgcn_readfirstlane(pl.width);
     // (a pass over the pools alone takes fewer workgroups: each one clears its bins and adds them to the device-wide ones)
-    const bool walks = tl->left_fast != 0u;
+    const bool walks = (__builtin_amdgcn_readfirstlane(pl.walks) & 1) != 0;
     if (!walks && nblk > HIST_POOL_BLOCKS) nblk = HIST_POOL_BLOCKS;
     if (bid >= nblk) return;
     if (width <= 0 || pl.fallback) return;        // selection finished, or per-slot histograms (other kernel)

@@ -398,16 +398,23 @@ __global__ __launch_bounds__(1024) void k_tbt_select(SelState* S, int pass, int 
 // A pass: its plan, the analytic bins (a class per workgroup), the pools and what is left of the walk list, or the per-slot
 // histograms of a table whose column sets do not fit the class scheme (then every workgroup walks).
 //   PASS_REGULAR  its digits are taken by k_tbt_select behind it
+//   PASS_DENSE    the same from DENSE_REQ requests on: two workgroups per CU, for the timelines that no pool holds (those of a
+//                 source slower than the reader; a wave's walk waits for its LDS atomics and loads).  In 64 registers it
+//                 spills, which costs the other passes 0.6 us each, more than it gains on fewer requests.  Statistics of
+//                 threshold columns with such sources, PASS_DENSE against PASS_REGULAR: 10^6 requests x 8 columns 3452 / 3551 us
+//                 (lag), 5598 / 5762 (buffer), x 1 column 3259 / 3452; 10^5 requests 713 / 713, 998 / 995, 551 / 562
 //   PASS_SPARE    a pass after those that normally decide every slot (the window was missed, or the digits are narrow): the
 //                 workgroup that finishes last takes every slot's digit and clears the next pass's bins; one launch
 //                 matters more here than speed, as normally all workgroups return at once
 //   PASS_LAST     the last spare pass, which also makes the columns' records
-enum { PASS_REGULAR, PASS_SPARE, PASS_LAST };
+enum { PASS_REGULAR, PASS_DENSE, PASS_SPARE, PASS_LAST };
+constexpr i64 DENSE_REQ = 1 << 18;
 constexpr unsigned TP_ANALYTIC = DISCO_MAX_CLS;
 
 template <int KIND>
-__global__ __launch_bounds__(1024) void k_tbt_pass(TraceView tr, i64 n_tok, int align, const disco_policy* __restrict__ pol,
-                                                   TimelineArgs a, FinalArgs fin)
+__global__ __launch_bounds__(1024, KIND == PASS_DENSE ? 8 : 4) void k_tbt_pass(TraceView tr, i64 n_tok, int align,
+                                                                               const disco_policy* __restrict__ pol,
+                                                                               TimelineArgs a, FinalArgs fin)
 {
     __shared__ __align__(16) unsigned smem[DISCO_TL_HIST_WORDS];
     __shared__ TimelineLds lds;
@@ -422,17 +429,25 @@ __global__ __launch_bounds__(1024) void k_tbt_pass(TraceView tr, i64 n_tok, int 
     }
     if (pl.fallback) {
         timeline_body<true>(smem, lds, tr, n_tok, align, pol, a, &pl, bid, gridDim.x);
-    } else if (bid < TP_ANALYTIC) {
-        if ((int)bid < tl.ncls) analytic_class(pl, tl.ncls, a.pass, a.ghist, a.ppcnt, a.tau, (int)bid, smem);
     } else {
-        const unsigned at = bid - TP_ANALYTIC, of = gridDim.x - TP_ANALYTIC;
-        HistArgs h;
-        h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass; h.S = a.S; h.ghist = a.ghist; h.desc = a.desc; h.list = a.list; h.runs = a.runs;
-        tl_hist_fast_body(smem, tr, n_tok, align, h, pl, at, of);
-        __syncthreads();                                // the bins are used again
-        tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), pl, at, of);
+        // with timelines left to walk the workgroups of the classes take a share of them too (192 of 256 workgroups walking, 1.3
+        // times the time); the last one, as the long requests are dealt first
+        const bool walks = pl.walks != 0;
+        if (bid < TP_ANALYTIC && (int)bid < tl.ncls) {
+            analytic_class(pl, tl.ncls, a.pass, a.ghist, a.ppcnt, a.tau, (int)bid, smem);
+            __syncthreads();                            // the bins are used again
+        }
+        if (walks || bid >= TP_ANALYTIC) {
+            const unsigned others = gridDim.x - TP_ANALYTIC, at = bid >= TP_ANALYTIC ? bid - TP_ANALYTIC : bid + others;
+            const unsigned of = walks ? gridDim.x : others;
+            HistArgs h;
+            h.tau = a.tau; h.kt = a.kt; h.P = a.P; h.nq = a.nq; h.pass = a.pass; h.S = a.S; h.ghist = a.ghist; h.desc = a.desc; h.list = a.list; h.runs = a.runs;
+            tl_hist_fast_body(smem, tr, n_tok, align, h, pl, at, of);
+            __syncthreads();
+            tl_hist_buf_body(smem, tr, n_tok, align, buf_hist_args(a), pl, at, of);
+        }
     }
-    if (KIND == PASS_REGULAR) return;
+    if (KIND == PASS_REGULAR || KIND == PASS_DENSE) return;
     if (!take_last_ticket(a.ticket)) return;
     __shared__ u64 wsum[DISCO_MAX_CLS];
     __shared__ int s_digit;
@@ -478,13 +493,16 @@ void disco_launch_tbt_pass(const TraceView& v, i64 n_tok, const disco_policy* po
                            hipStream_t stream)
 {
     const int align = (int)(((uintptr_t)v.arr >> 2) & 3);
-    // one workgroup per CU: more of them make an empty launch dearer
+    // all workgroups resident at once: more of them make an empty launch dearer
     const i64 per_wave = (v.n_req + 15) / 16;                    // workgroups if every wave took one request
-    i64 walkers = per_wave < 1 ? 1 : (per_wave > 256 - (i64)TP_ANALYTIC ? 256 - (i64)TP_ANALYTIC : per_wave);
+    const bool dense = a.pass < DISCO_TBT_REGULAR_PASS && v.n_req >= DENSE_REQ;
+    const i64 most = (dense ? 512 : 256) - (i64)TP_ANALYTIC;
+    i64 walkers = per_wave < 1 ? 1 : (per_wave > most ? most : per_wave);
     walkers /= disco_grid_divisor();
     const dim3 grid(TP_ANALYTIC + (unsigned)(walkers < 1 ? 1 : walkers));
     if (a.pass < DISCO_TBT_REGULAR_PASS) {
-        hipLaunchKernelGGL(k_tbt_pass<PASS_REGULAR>, grid, dim3(1024), 0, stream, v, n_tok, align, pol, a, fin);
+        if (dense) hipLaunchKernelGGL(k_tbt_pass<PASS_DENSE>, grid, dim3(1024), 0, stream, v, n_tok, align, pol, a, fin);
+        else hipLaunchKernelGGL(k_tbt_pass<PASS_REGULAR>, grid, dim3(1024), 0, stream, v, n_tok, align, pol, a, fin);
         hipLaunchKernelGGL(k_tbt_select, dim3((unsigned)(a.P * a.nq + SEL_CLEAR)), dim3(1024), 0, stream, a.S, a.pass, a.P, a.nq, a.ghist,
                            a.gclear);
     } else if (a.pass + 1 < DISCO_TBT_MAX_PASS) {

@@ -418,6 +418,53 @@ def test_gaps_beyond_the_pools(B, oracle):
     check_stats(B, oracle, tr, specs, DI.COST_S, tau=DI.TAU, kappa=DI.KAPPA_LAG)
 
 
+# timelines of sources slower than the reader, which no pool holds: all of them walked in the passes, with every kind of hand-off,
+# by more and fewer workgroups than there are classes, and (a few workgroups) by waves that stop trying to count their gaps
+@pytest.mark.parametrize("n_req,max_out,tau,tokens,divisor", [(1, 40, 0.02, True, 1), (700, 300, 0.02, True, 1), (2500, 120, 0.05, False, 1),
+                                                              (3100, 90, 0.01, True, 64), (33_001, 40, 0.03, True, 1), (33_001, 40, 0.03, True, 128)])
+def test_sources_slower_than_the_reader(B, oracle, n_req, max_out, tau, tokens, divisor):
+    print(f"slow sources: n_req={n_req} max_out={max_out} tau={tau} tokens={tokens} divisor={divisor}", flush=True)
+    tr = slow_prefill(DI.handmade_trace(540 + n_req, n_req, tokens=tokens, max_out=max_out, stall_p=0.1), 16.0)
+    if not tokens:
+        tr["srv_tbt"] = (tr["srv_tbt"] * np.float32(4)).astype(np.float32)
+    try:
+        assert B._lib.disco_set_grid_divisor(divisor) == 0
+        for mode in (0, 1):
+            specs = [dict(mode=mode, l_th=x, w_tail=DI.f32(0.1 * j), mig_mode=(2, 1, 0, 2)[j]) for j, x in enumerate((-1, 16, 30, 40))]
+            check_stats(B, oracle, tr, specs, DI.COST_D if mode else DI.COST_S, tau=DI.f32(tau), kappa=DI.KAPPA_LAG,
+                        quantiles=((1, 100), (50, 100), (99, 100)))
+    finally:
+        assert B._lib.disco_set_grid_divisor(1) == 0
+
+
+# the passes with two workgroups per CU begin at 2^18 requests: the gaps of as many and of one fewer, the last one of which has a
+# single token and so no gap, have the same order statistics; sources slower and faster than the reader
+@pytest.mark.parametrize("tau", [0.02, 0.1, 0.2])
+def test_passes_of_many_requests(B, tau):
+    print(f"passes of many requests: tau={tau}", flush=True)
+    n = 1 << 18
+    t = B.disco_gen_trace(dict(DI.config(4, n_req=n, seed=11)["gen"], out_hi=200))
+    keep = int(t.tok_off[n - 1].item())
+    t.output_len[n - 1] = 1
+    t.tok_off[n] = keep + 1
+    t.n_tok = keep + 1
+    for table in ([dict(mode=0, l_th=x, mig_mode=m) for x, m in ((0, 1), (200, 2), (700, 0))],
+                  [dict(mode=1, l_th=-1, w_tail=DI.f32(w), mig_mode=2) for w in (0.1, 0.4)]):
+        pols = [B.Policy(**x) for x in table]
+        P, got = len(pols), []
+        for k in (n, n - 1):
+            x = B.Trace(**{**{f: getattr(t, f) for f in ("prompt_len", "output_len", "srv_ttft", "srv_tbt", "dev_pre_spt", "dev_dec_spt", "tok_off", "tok_arr",
+                                                        "dev_pre_spt_s", "dev_dec_spt_s", "dev_ttft_c")}, "n_req": k, "n_tok": keep + 1})
+            ws = B.workspace(k, P)
+            acc = B.disco_eval_dispatch(x, pols, ws=ws)["acc"]
+            B.disco_eval_migration(x, DI.f32(tau), DI.KAPPA_LAG, pols, ws=ws, acc=acc, cost=DI.COST_D)
+            got.append(B.stats_to_host(B.disco_reduce_stats(x, DI.COST_D, pols, acc, ((1, 100), (50, 100), (99, 100)), tau=DI.f32(tau), kappa=DI.KAPPA_LAG,
+                                                            ws=ws, mig_cost=DI.COST_D, reuse_walk=True), P).copy())
+        assert (got[0]["tbt_count"] == got[1]["tbt_count"]).all() and (got[0]["tbt_count"] > 0).all()
+        for f in ("tbt_rank", "tbt_q"):
+            same_bits(got[0][f], got[1][f], f)
+
+
 # per-pair outputs: four requests per lane, rows that start anywhere, chunks of eight columns, next to the totals of small traces
 # and of large ones
 @pytest.mark.parametrize("n_req", [1, 2, 3, 5, 4095, 4097, 32_768, 32_769, 36_866])
