@@ -344,12 +344,28 @@ __device__ __forceinline__ void batch_pairs_need(const Staged* __restrict__ st, 
 template <int G>
 constexpr i64 pair_batches() { return G >= 32 ? 1 : (G == 16 ? 2 : 4); }
 
+// Workgroups of a pass: `acc` for the totals, `all` - `acc` for the per-pair outputs.
+struct AccGrid { int acc, all; };
+
+// With per-pair outputs those of the totals that the kind of the table leaves (kind: table_mode): they are bound by issue, the
+// others by the writes.  Threshold tables that go by bucket (or take a batch or two) are cheap, mixed ones take every pair
+// through all modes.  10^6 requests, 96 / 128 / 160 / 192 / 256 workgroups for the totals: 64 thresholds 75.8 us with 96 (99 one
+// after the other), 16 waits 47 / 45 / 45 / 46 / 44, 8 waits 35 / 29 / 34 / 32 / 31, 64 columns of all modes
+// 410 / 304 / 269 / 233 / 236, 8 stochastic ones 53 / 44 / 49 / 47 / 43, 2 thresholds 21.5 / 19.8 / 21.5 / 21.8 / 21.5.
+template <int G>
+__device__ __forceinline__ int acc_workgroups(const AccGrid& g, int kind, bool stochastic)
+{
+    if (g.acc == g.all) return g.acc;
+    const int most = kind == 0 && G >= 4 ? 96 : (kind == 2 && !stochastic ? 192 : 128);
+    return g.acc < most ? g.acc : most;
+}
+
 template <int G>
 __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const disco_policy* __restrict__ pol, int P,
-                                                           u64* __restrict__ part, DispFin fin, int nacc, PairOut out)
+                                                           u64* __restrict__ part, DispFin fin, AccGrid grid, PairOut out)
 {
-    // the workgroups behind the first nacc write the per-pair outputs
-    if ((int)blockIdx.x >= nacc) { mat_body(tr, pol, P, out, (int)blockIdx.x - nacc, (int)gridDim.x - nacc); return; }
+    // the workgroups behind those of the totals write the per-pair outputs
+    if ((int)blockIdx.x >= grid.acc) { mat_body(tr, pol, P, out, (int)blockIdx.x - grid.acc, grid.all - grid.acc); return; }
     __shared__ __align__(16) unsigned char smem[DP_BLOCK * sizeof(DispPartial)];    // 64 KB: staging, then folds
     Staged* stage = reinterpret_cast<Staged*>(smem);
     u64* sh = reinterpret_cast<u64*>(smem);
@@ -357,7 +373,9 @@ __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const d
     const int col = lane & (G - 1), sub = lane / G;
     const bool colv = col < P;
     const disco_policy p = pol[colv ? col : 0];
-    if (G >= 4 && tr.n_req > pair_batches<G>() * nacc * DP_BLOCK && table_mode(p, colv) == 0) {
+    const int kind = table_mode(p, colv), nacc = acc_workgroups<G>(grid, kind, all_stochastic(p, colv));
+    if ((int)blockIdx.x >= nacc) return;
+    if (G >= 4 && tr.n_req > pair_batches<G>() * nacc * DP_BLOCK && kind == 0) {
         u64* words = sh + sizeof(Buckets) / sizeof(u64);
         static_assert(sizeof(Buckets) % sizeof(u64) == 0 && sizeof(Buckets) + 8 * 64 * sizeof(u64) <= sizeof(smem), "buckets and words");
         if (!threshold_buckets<G>(tr, pol, P, fin.need, (int)blockIdx.x, nacc, *reinterpret_cast<Buckets*>(smem), words)) return;
@@ -481,9 +499,11 @@ __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc(TraceView tr, const d
 // iteration (16-byte loads when VEC, i.e. all arrays 16-byte aligned).
 template <bool VEC>
 __global__ __launch_bounds__(DP_BLOCK) void k_dispatch_acc1(TraceView tr, const disco_policy* __restrict__ pol,
-                                                            u64* __restrict__ part, DispFin fin, int nacc, PairOut out)
+                                                            u64* __restrict__ part, DispFin fin, AccGrid grid, PairOut out)
 {
-    if ((int)blockIdx.x >= nacc) { mat_body(tr, pol, 1, out, (int)blockIdx.x - nacc, (int)gridDim.x - nacc); return; }
+    if ((int)blockIdx.x >= grid.acc) { mat_body(tr, pol, 1, out, (int)blockIdx.x - grid.acc, grid.all - grid.acc); return; }
+    const int nacc = acc_workgroups<1>(grid, 0, false);      // (no kind of a single column is dear)
+    if ((int)blockIdx.x >= nacc) return;
     __shared__ __align__(16) unsigned char smem[DP_BLOCK * sizeof(DispPartial)];
     u64* sh = reinterpret_cast<u64*>(smem);
     const disco_policy p = pol[0];
@@ -684,18 +704,12 @@ unsigned dispatch_blocks(i64 units, i64 per_block)
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-// Workgroups of a pass: those of the totals, and behind them those of the per-pair outputs.  The former are bound by issue, the
-// latter by the writes: with a workgroup on every CU for the totals first, 10^6 requests x 64 columns took 27 + 72 us one after
-// the other.
-constexpr unsigned BOTH_ACC_BLOCKS = 96;
-struct AccGrid { unsigned acc, all; };
 AccGrid acc_grid(const TraceView& v, int P, unsigned acc, const PairOut& out)
 {
-    if (!out.decision && !out.ttft) return AccGrid{acc, acc};
-    if (acc > BOTH_ACC_BLOCKS) acc = BOTH_ACC_BLOCKS;
+    if (!out.decision && !out.ttft) return AccGrid{(int)acc, (int)acc};
     i64 m = (v.n_req + 4 * DP_BLOCK - 1) / (4 * DP_BLOCK) * ((P + MAT_COLS - 1) / MAT_COLS);
     if (m > 2048) m = 2048;
-    return AccGrid{acc, acc + (unsigned)m};
+    return AccGrid{(int)acc, (int)acc + (int)m};
 }
 
 template <int G>
@@ -703,7 +717,7 @@ void launch_acc(const TraceView& v, const disco_policy* pol, int P, u64* part, c
                 hipStream_t stream)
 {
     const AccGrid g = acc_grid(v, P, dispatch_blocks((v.n_req + 63) / 64, DP_WAVES), out);
-    hipLaunchKernelGGL(k_dispatch_acc<G>, dim3(g.all), dim3(DP_BLOCK), 0, stream, v, pol, P, part, fin, (int)g.acc, out);
+    hipLaunchKernelGGL(k_dispatch_acc<G>, dim3((unsigned)g.all), dim3(DP_BLOCK), 0, stream, v, pol, P, part, fin, g, out);
     hipLaunchKernelGGL(k_dispatch_fin, dim3(1), dim3(512), 0, stream, part, P, fin);
 }
 
@@ -724,8 +738,8 @@ void disco_launch_dispatch_acc(const TraceView& v, const disco_policy* pol, int 
     case 1: {
         const AccGrid g = acc_grid(v, P, dispatch_blocks((v.n_req + 3) / 4, DP_BLOCK), out);
         const bool vec = aligned16(v.l) && aligned16(v.n) && aligned16(v.s) && (!v.k || aligned16(v.k));
-        if (vec) hipLaunchKernelGGL(k_dispatch_acc1<true>, dim3(g.all), dim3(DP_BLOCK), 0, stream, v, pol, part, fin, (int)g.acc, out);
-        else hipLaunchKernelGGL(k_dispatch_acc1<false>, dim3(g.all), dim3(DP_BLOCK), 0, stream, v, pol, part, fin, (int)g.acc, out);
+        if (vec) hipLaunchKernelGGL(k_dispatch_acc1<true>, dim3((unsigned)g.all), dim3(DP_BLOCK), 0, stream, v, pol, part, fin, g, out);
+        else hipLaunchKernelGGL(k_dispatch_acc1<false>, dim3((unsigned)g.all), dim3(DP_BLOCK), 0, stream, v, pol, part, fin, g, out);
         hipLaunchKernelGGL(k_dispatch_fin, dim3(1), dim3(512), 0, stream, part, 1, fin);
         break;
     }

@@ -477,6 +477,17 @@ def test_per_pair_outputs(B, oracle, n_req, cols):
     check_dispatch(B, oracle, tr, specs)
 
 
+# totals beside the per-pair outputs: by 96, 128 or 192 of their workgroups by the kind of the table, the others leave
+@pytest.mark.parametrize("kind,cols", [("threshold", 1), ("threshold", 2), ("threshold", 5), ("wait", 3), ("stochastic", 1), ("stochastic", 3), ("all", 4)])
+def test_totals_beside_per_pair_outputs(B, oracle, kind, cols):
+    print(f"totals beside per-pair outputs: kind={kind} cols={cols}", flush=True)
+    tr = DI.handmade_trace(720, 263_003, tokens=False, ties=True)
+    of = {"threshold": lambda j: dict(mode=0, l_th=300 * j + 100), "wait": lambda j: dict(mode=1, l_th=100 * j, w_tail=DI.f32(0.2 * j)),
+          "stochastic": lambda j: dict(mode=2 + j % 2, beta=DI.f32(0.2 + 0.2 * j), l_mid=j)}
+    kinds = list(of) if kind == "all" else [kind]
+    check_dispatch(B, oracle, tr, [of[kinds[j % len(kinds)]](j) for j in range(cols)])
+
+
 # wait and slope searches behind their second pass: all steps in one launch (8192 requests, the last size, and one more), the rest
 # from the list of the requests that still change (none, a few, some that all change at one wait) and further passes where that
 # list is too long (all of them at one wait); step counts at the ends of the passes
