@@ -563,10 +563,14 @@ __global__ __launch_bounds__(TW_BLOCK) void k_tl_walk_rest(TraceView tr, i64 n_t
 }
 
 // Small traces (disco_small): the policy table staged, the flags, and every walk with the exact walker, in one launch of a
-// few requests per wave.  What counts there is the longest request's walk: 512 tokens per iteration.
-constexpr int SW_NV = 2;
+// few requests per wave.  What counts there is the longest request's walk: 512 tokens per iteration, 1024 (in 128 registers) where the
+// requests have more than 512 on average.  Whole calls, 512 / 1024 per iteration, threshold columns: 24 000 requests of 333 tokens
+// 25.5 / 28.2 us, 16 384 of 488 31.4 / 31.4, 500 of 600 11.6 / 11.0, 8192 of 3900 96 / 75, 16 384 of 6000 169 / 129 (the streaming walk of larger
+// traces 90 and 151); of 12 000 tokens 255 / 192 (192).
+constexpr int SMALL_LONG_TOKENS = 512;
 
-__global__ __launch_bounds__(TW_BLOCK) void k_small_walk(TraceView tr, i64 n_tok, PolTable host, const disco_policy* __restrict__ device,
+template <int NV>
+__global__ __launch_bounds__(TW_BLOCK, 4) void k_small_walk(TraceView tr, i64 n_tok, PolTable host, const disco_policy* __restrict__ device,
                                                          int P, int rb, float tau, float kt, TlSummary* __restrict__ summary,
                                                          disco_policy* __restrict__ staged, unsigned* __restrict__ tickets,
                                                          u64* __restrict__ totals)
@@ -597,7 +601,7 @@ __global__ __launch_bounds__(TW_BLOCK) void k_small_walk(TraceView tr, i64 n_tok
         f = walks_needed(m, tr.arr != nullptr, gap, gd, tau);
     }
     TlSummary s{0.0f, -1, 0.0f, 0.0f};
-    walk_batch<SW_NV>(tr, n_tok, first, il, f, (f & (WF_LAG | WF_PLAIN)) != 0u, tau, kt, lc, rows[wave], s);
+    walk_batch<NV>(tr, n_tok, first, il, f, (f & (WF_LAG | WF_PLAIN)) != 0u, tau, kt, lc, rows[wave], s);
     if (valid) summary[il] = s;
 }
 
@@ -882,8 +886,12 @@ void disco_launch_small_walk(const TraceView& v, i64 n_tok, const PolTable& host
     while ((v.n_req + (i64)TW_WAVES * rb - 1) / ((i64)TW_WAVES * rb) > 2048) rb <<= 1;
     i64 b = (v.n_req + (i64)TW_WAVES * rb - 1) / ((i64)TW_WAVES * rb);
     if (b < 1) b = 1;
-    hipLaunchKernelGGL(k_small_walk, dim3((unsigned)b), dim3(TW_BLOCK), 0, stream, v, n_tok, host, device, P, rb, tau, kt,
-                       (TlSummary*)summary, staged, tickets, (u64*)totals);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)b), dim3(TW_BLOCK), 0, stream, v, n_tok, host, device, P, rb, tau, kt,
+                           (TlSummary*)summary, staged, tickets, (u64*)totals);
+    };
+    if (v.arr != nullptr && n_tok > SMALL_LONG_TOKENS * v.n_req) launch(k_small_walk<4>);
+    else launch(k_small_walk<2>);
 }
 
 static void launch_accum(const TraceView& v, const disco_policy* pol, const TimelineArgs& a, MigPartial* totals, hipStream_t stream)

@@ -378,6 +378,31 @@ def test_timelines_of_small_traces(B, oracle, n_req, max_out, tokens):
         check_stats(B, oracle, tr, specs, cost, tau=DI.TAU, kappa=DI.KAPPA_LAG)
 
 
+# small traces whose requests have more than 512 tokens on average: 1024 per iteration; lengths around its vectors and its ends, stalls
+# (hand-offs) in every one of them
+@pytest.mark.parametrize("n_req,stall_p", [(1, 0.0), (13, 0.004), (260, 0.001), (260, 0.05)])
+def test_long_requests_of_small_traces(B, oracle, n_req, stall_p):
+    print(f"long requests of small traces: n_req={n_req} stall_p={stall_p}", flush=True)
+    tr = DI.handmade_trace(620 + n_req, n_req, tokens=False, max_out=3)
+    n = np.array([1025, 255, 257, 513, 769, 1023, 1024, 2047, 2049, 3073, 4097, 1, 5000])[np.arange(n_req) % 13]
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    rng = np.random.default_rng(n_req)
+    gap = rng.lognormal(-3.5, 0.6, int(off[-1])).astype(np.float32)
+    stall = rng.random(len(gap)) < stall_p
+    gap[stall] = rng.uniform(0.5, 400.0, int(stall.sum())).astype(np.float32)       # (some beyond what a reader of 5000 tokens has buffered)
+    arr = np.zeros(len(gap), np.float32)
+    for i in range(n_req):
+        arr[off[i] + 1:off[i + 1]] = np.cumsum(gap[off[i] + 1:off[i + 1]], dtype=np.float32)
+    assert off[-1] > 512 * n_req
+    tr.update(n_tok=len(arr), output_len=n.astype(np.int32), tok_off=off, tok_arr=arr)
+    tr = slow_prefill(tr, 16.0)
+    for mode in (0, 1):
+        specs = [dict(mode=mode, l_th=x, w_tail=DI.f32(0.05 * j), mig_mode=j % 3) for j, x in enumerate((-1, 300, 900, 1500, 2900))]
+        cost = DI.COST_D if mode else DI.COST_S
+        check_migration(B, oracle, tr, specs, DI.TAU, DI.KAPPA_LAG, delivered_col=None, cost=cost)
+        check_stats(B, oracle, tr, specs, cost, tau=DI.TAU, kappa=DI.KAPPA_LAG)
+
+
 # stretches of tokens that do not move the running maximum are counted by binade of the delivery: pacing intervals whose ratio to
 # the spacing of the floats is an integer or not, maxima on and off half spacings, stretches over one to twenty binades, more
 # of them in a request than wait together, stalls on both sides of a chunk's ends
