@@ -296,10 +296,10 @@ __global__ __launch_bounds__(1024) void k_pp_reduce(const SelState* S, int nslic
 constexpr int TR_BLOCK = 512, TR_WAVES = TR_BLOCK / 64;
 constexpr int TR_MAX_BLOCKS = 768;           // what the chip holds at once (six waves per SIMD)
 // An attempt at a timeline of too many moves, or at a full pool, is made in vain; one that succeeds spares every pass a walk.  A
-// wave stops trying when its pool is full, and when RUNS_VAIN more of its attempts were in vain than RUNS_WORTH times those
-// that were not: sources slower than the reader, 10^6 requests x 1 column 3.05 ms of order statistics, 3.37 without the rule; gaps
+// wave stops trying when its pool is full, and after RUNS_VAIN attempts in vain one behind the other (where fewer than one in eight
+// succeeds): sources slower than the reader, 10^6 requests x 1 column 3.05 ms of order statistics, 3.37 without the rule; gaps
 // of many stalls, which fill the pools, 0.87 and 1.20.
-constexpr int RUNS_WORTH = 15, RUNS_VAIN = 8;
+constexpr int RUNS_VAIN = 12;
 
 __global__ __launch_bounds__(TR_BLOCK, 6) void k_tl_runs(TraceView tr, i64 n_tok, int align, float tau, float kt, SelState* S,
                                                       u64* __restrict__ desc_rw, const unsigned* __restrict__ list,
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(TR_BLOCK, 6) void k_tl_runs(TraceView tr, i64 n_tok
     if (threadIdx.x == 0) used = 0u;
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int vain = 0;                                            // the wave's attempts in vain, less RUNS_WORTH times the others
+    int vain = 0;                                            // the wave's last attempts that were in vain
     bool some_fast = false, some_buf = false;
     const i64 nfront = (i64)tl.nlist, nlist = tl.plan[0].fallback ? 0 : nfront + (i64)tl.nlist_back;
     const i64 nwaves = (i64)gridDim.x * (TR_WAVES);
@@ -388,10 +388,14 @@ __global__ __launch_bounds__(TR_BLOCK, 6) void k_tl_runs(TraceView tr, i64 n_tok
                 int ns, n1;
                 const bool done = walk_runs(rl[wave], ns, n1, kind, n, tr.arr, off, n_tok, align, chunk, gap, gd, l, k, tr.c, m, ho, tau, kt, lane) &&
                                   emit_runs(rl[wave], ns, n1, row, tau, pool, runs.cap, &used, lane);
-                if (done) kinds |= lane == rq ? 0x100u << kind : 0u;
-                vain = done ? vain - RUNS_WORTH : (*(volatile unsigned*)&used >= runs.cap ? RUNS_VAIN : vain + 1);
+                if (done) {
+                    kinds |= lane == rq ? 0x100u << kind : 0u;
+                    vain = 0;
+                } else {
+                    vain = *(volatile unsigned*)&used >= runs.cap ? RUNS_VAIN : vain + 1;
+                    if (vain >= RUNS_VAIN) walkers = 0ull;
+                }
             }
-            if (vain >= RUNS_VAIN) break;
         }
         u64 left = desc;
 #pragma unroll
