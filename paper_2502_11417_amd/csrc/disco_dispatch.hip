@@ -591,13 +591,11 @@ __global__ __launch_bounds__(512) void k_dispatch_fin(u64* __restrict__ part, in
 // table instead of passing over the requests.  The steps, their order and the
 // recorded history are those of the generic search.
 
-constexpr int LH_MAX_BINS = 32772;          // 128 KB of LDS counts: prompt lengths 0 .. 32771
-
 // Requests per prompt length, one slice of `nbins` counts per workgroup, and the
 // sum of the lengths of its requests beyond the table.
 __global__ __launch_bounds__(DP_BLOCK) void k_len_hist(TraceView tr, int nbins, unsigned* __restrict__ slices, u64* __restrict__ table)
 {
-    __shared__ unsigned cnt[LH_MAX_BINS];
+    __shared__ unsigned cnt[LEN_MAX_BINS];
     __shared__ u64 wout[DP_WAVES];
     for (int i = threadIdx.x; i < nbins; i += DP_BLOCK) cnt[i] = 0u;
     __syncthreads();
@@ -775,4 +773,4 @@ void disco_launch_search_table(const TraceView& v, const SpecTable& spec, int n_
     hipLaunchKernelGGL(k_len_search, dim3(1), dim3(1024), 0, stream, nbins, nslices, table, spec, n_search, st, pol, sout);
 }
 
-int disco_search_table_max_bins(void) { return LH_MAX_BINS; }
+int disco_search_table_max_bins(void) { return LEN_MAX_BINS; }

@@ -714,7 +714,7 @@ extern "C" int32_t disco_budget_search(const disco_trace* trace, const disco_cos
                     spec[j].lo >= 0.0 && spec[j].hi + 2.0 <= (double)disco_search_table_max_bins();
         if (spec[j].hi > max_hi) max_hi = spec[j].hi;
     }
-    if (tabulated && disco_small(v.n_req) && (int)max_hi + 2 <= disco_small_search_max_bins()) {
+    if (tabulated && disco_small(v.n_req)) {
         rc = check_policies(templ, n_search);
         if (rc) return rc;
         PolTable pt;

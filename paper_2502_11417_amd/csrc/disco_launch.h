@@ -84,7 +84,6 @@ struct SmallSearches { SmallSearch s[DISCO_MAX_COLS]; };
 void disco_launch_small_dispatch(const TraceView& v, const PolTable& host, const disco_policy* device, int P, disco_accum* acc,
                                  uint8_t* decision, float* ttft, hipStream_t stream);
 // Tabulated threshold searches (templates: server-constrained columns), with the evaluation at the answers.
-int disco_small_search_max_bins(void);
 void disco_launch_small_search(const TraceView& v, const PolTable& templ, const SmallSearches& sp, int n_search, int n_steps, int nbins,
                                const disco_cost_params& cost, disco_search_out* sout, disco_policy* pol_out, disco_accum* acc,
                                hipStream_t stream);

@@ -9,6 +9,8 @@
 
 namespace {
 
+// Lengths 0 .. LEN_MAX_BINS - 1 of the largest table (128 KB of LDS counts where it is made, and where a small trace's lies).
+constexpr int LEN_MAX_BINS = 32772;
 constexpr int LEN_BLOCK = 64;
 constexpr int LEN_MAX_BLOCKS = 1024;                    // of a table (threads of the workgroup that adds them up)
 

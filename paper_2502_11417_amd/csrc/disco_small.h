@@ -5,6 +5,7 @@
 // memory, barriers, tickets): what counts is how few of them there are.
 #pragma once
 #include "disco_launch.h"
+#include "disco_len.h"
 #include "disco_pair.h"
 
 namespace {
@@ -202,7 +203,7 @@ __device__ __forceinline__ void store_dispatch_accum(disco_accum* o, const disco
 
 // A(L) = prompt tokens of the requests of length >= L, for lengths 0 .. nbins - 1 in LDS (and `beyond`, those of longer
 // prompts): SMALL_REQ requests of less than 2^15 tokens add up to less than 2^32.
-constexpr int SL_BINS = 32772, SL_PER = (SL_BINS + SM_BLOCK - 1) / SM_BLOCK;
+constexpr int SL_BINS = LEN_MAX_BINS, SL_PER = (SL_BINS + SM_BLOCK - 1) / SM_BLOCK;
 static_assert((u64)SMALL_REQ * SL_BINS < (1ull << 32), "sums of 32 bits");
 struct SmallLenLds { unsigned a[SL_PER * SM_BLOCK]; unsigned wsum[SM_WAVES]; u64 beyond[SM_WAVES]; };
 

@@ -119,8 +119,6 @@ void disco_launch_small_dispatch(const TraceView& v, const PolTable& host, const
     hipLaunchKernelGGL(k_small_dispatch, dim3((unsigned)(P + tasks)), dim3(SM_BLOCK), 0, stream, v, host, device, P, acc, out);
 }
 
-int disco_small_search_max_bins(void) { return SL_BINS; }
-
 void disco_launch_small_search(const TraceView& v, const PolTable& templ, const SmallSearches& sp, int n_search, int n_steps, int nbins,
                                const disco_cost_params& cost, disco_search_out* sout, disco_policy* pol_out, disco_accum* acc,
                                hipStream_t stream)

@@ -323,7 +323,6 @@ void disco_launch_solve(const TraceView& v, const disco_solve_spec* spec, int n,
     memset(&t, 0, sizeof(t));
     memcpy(t.s, spec, sizeof(disco_solve_spec) * (size_t)n);
     if (disco_small(v.n_req)) {
-        static_assert(SL_BINS >= 32772, "the table of the general solve");
         hipLaunchKernelGGL(k_small_solve, dim3((unsigned)n), dim3(SM_BLOCK), 0, stream, v, t, nbins, pol_out, out);
         return;
     }
