@@ -323,8 +323,8 @@ __device__ __forceinline__ int known_end(const WalkLds& w) { return w.chosen > 0
 
 // All remaining steps by one workgroup, SB_DEPTH of them per round over its requests: all of the trace (ALL), of a list in
 // device memory, or (from_lds) those in w.kept.  Of a list w.head holds the totals of all requests at x_base, with these
-// ones' outcomes there.  ALL: `where` takes a word per request; once those whose outcome changes in the chosen interval fit
-// w.kept the rounds go on with them.
+// ones' outcomes there.  ALL: `where` takes a word per request, and the rounds behind the first go on with those whose outcome
+// changes in the chosen interval.
 template <bool ALL>
 __device__ __forceinline__ void rounds(const TraceView& tr, const uint2* __restrict__ list, unsigned count, bool from_lds, const disco_policy& p,
                                        float x_base, const disco_cost_params& cost, WalkLds& w, unsigned* where, disco_search_out* o)
@@ -386,13 +386,12 @@ __device__ __forceinline__ void rounds(const TraceView& tr, const uint2* __restr
         take_steps(w, depth, cost, o);
         if (ALL && !from_lds) {
             keep_open(w, count, [&](unsigned e) { return e; }, [&](unsigned e) { return where[e]; });
-            if (w.nkept <= WALK_LDS) {
-                from_lds = true;
-                count = w.nkept;
-                const int at = known_end(w);
-                x_base = w.sc[at];
-                all_pre = w.tot[at]; all_dec = w.tot[SB_CAND + at];
-            }
+            static_assert(WAIT_SMALL_REQ <= WALK_LDS, "all of the trace fits w.kept");
+            from_lds = true;
+            count = w.nkept;
+            const int at = known_end(w);
+            x_base = w.sc[at];
+            all_pre = w.tot[at]; all_dec = w.tot[SB_CAND + at];
             __syncthreads();
         }
     }
