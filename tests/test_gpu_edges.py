@@ -515,8 +515,10 @@ def test_totals_beside_per_pair_outputs(B, oracle, kind, cols):
 
 # wait and slope searches behind their second pass: all steps in one launch (8192 requests, the last size, and one more), the rest
 # from the list of the requests that still change (none, a few, some that all change at one wait) and further passes where that
-# list is too long (all of them at one wait); step counts at the ends of the passes
-@pytest.mark.parametrize("n_req,same", [(8191, 0.4), (8192, 1.0), (8193, 0.0), (20_011, 0.4), (40_003, 1.0), (300_011, 0.0)])
+# list is too long (all of them at one wait: already a workgroup's share); 16 000 of 40 003 at one wait: more than the walk holds in
+# LDS, so that its rounds go over the list in device memory, and for a single search too long by its total alone; step counts
+# at the ends of the passes
+@pytest.mark.parametrize("n_req,same", [(8191, 0.4), (8192, 1.0), (8193, 0.0), (20_011, 0.4), (40_003, 1.0), (300_011, 0.0), (40_003, 0.4)])
 @pytest.mark.parametrize("n_steps", [10, 11, 20, 21, 31, 64])
 def test_searches_behind_the_second_pass(B, oracle, n_req, same, n_steps):
     print(f"searches behind the second pass: n_req={n_req} same={same} n_steps={n_steps}", flush=True)
