@@ -236,9 +236,15 @@ class Trace:
                       self.dev_pre_spt_s, self.dev_dec_spt_s, self.dev_ttft_c, 0.0)
 
 
+# the handle of the current stream without the wrapper object of torch.cuda.current_stream() (3 us a call); not a public name of
+# torch's, so looked up
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the current stream's handle without the wrapper object of torch.cuda.current_stream() (3 us a call)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())        # (initialises the device where nothing has yet)
 
 
 def _check(rc: int, where: str):

@@ -227,3 +227,15 @@ int main() {
         assert npass == -(-steps // 10)
         assert bool(listed) == (steps > 20 and n - 1 <= 0xFFFFFFFF)
         assert cap == min(room, 8192 if k <= 2 else 32768)
+
+
+def test_stream_handle_without_torchs_private_function(B, monkeypatch):
+    """Where this torch has no raw handle the public call gives it; where it has one, the device is asked for first."""
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(B, "_raw_stream", None)
+    assert B._stream() == 77
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 100 + device)
+    assert B._stream() == 103

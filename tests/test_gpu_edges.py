@@ -18,6 +18,14 @@ def same_bits(got, want, what):
     assert bad.size == 0, f"{what}: {bad.size} bytes differ, first at {bad[:5]}"
 
 
+# the handle that the calls get is that of torch's current stream
+def test_the_current_streams_handle(B):
+    side = torch.cuda.Stream()
+    assert B._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert B._stream() == side.cuda_stream
+
+
 # requests per wave of the token generator: 1 below 8192 requests, 4 below 32768, then 16; pieces of 64, 256 and 1024
 # tokens from multiples of 32 on, or all of a wave's requests in one stretch where they have at most 1024 tokens; the stall
 # test at both ends of its range
