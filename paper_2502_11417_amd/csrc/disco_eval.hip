@@ -35,12 +35,6 @@ __global__ __launch_bounds__(STAGE_THREADS) void k_copy_policies(const disco_pol
     stage_table(src, P, dst, tickets, totals, si, (int)blockIdx.x, (int)gridDim.x);
 }
 
-// ----------------------------------------------------------------- select --
-// TTFT: key = bits - min_bits over nb = bit length of (max_bits - min_bits)
-// bits, 8 bits per pass (up to 128 (column, quantile) slots of 256 bins in
-// LDS).  TBT: the plan comes from the host (raw 31-bit keys).
-
-
 // ------------------------------------------------------------ final stats --
 
 __global__ __launch_bounds__(FINAL_THREADS) void k_stats_final(FinalArgs f)

@@ -53,7 +53,7 @@ struct TimelineArgs {
     RunPool runs;                  // gaps of the timelines that need no walk (histogram passes)
 };
 
-// How the last workgroup of a dispatch pass hands on the column totals.
+// How the kernel behind a dispatch pass hands on the column totals.
 struct DispFin {
     int kind;                     // 0: write disco_accum, 1: advance a budget search
     int need;                     // totals wanted: 0 prefill tokens, 1 + decode split, 2 + TTFT sum and range
@@ -144,10 +144,10 @@ int disco_ttft_passes(i64 n_req, int P, int nq);
 void disco_launch_ttft_pass(const TraceView& v, const disco_policy* pol, int P, int nq, int pass, SelState* S,
                             unsigned* slices, unsigned* rowsum, unsigned char* ubytes, u64* masks, hipStream_t stream);
 // Token timelines.  Statistics pass (a.pass = -1): streaming kernel, or the general kernel when the
-// per-token deliveries of a column are wanted.  TBT selection: classification and assignment once; then per regular pass (a.pass < DISCO_TBT_REGULAR_PASS) the walk of the
-// streaming kinds (disco_launch_tl_hist_fast) followed by disco_launch_tbt_pass (the other histogram work of the
-// pass, the digits, the plan of the next pass); a spare pass is disco_launch_tbt_pass alone, one launch that
-// normally returns at once.
+// per-token deliveries of a column are wanted.  TBT selection: classification, assignment and gap pools once; then
+// disco_launch_tbt_pass for every pass: two launches in a regular one (a.pass < DISCO_TBT_REGULAR_PASS: plan and
+// histograms, then the digits), one in a spare one, which normally returns at once; the last one also makes the
+// records.
 void disco_launch_tl_stats_fast(const TraceView& v, i64 n_tok, const disco_policy* pol, const TimelineArgs& a,
                                 MigPartial* totals, hipStream_t stream);
 // The token walk alone (flags, then one 16-byte summary per request), for a statistics call that was not handed

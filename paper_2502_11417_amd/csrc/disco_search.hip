@@ -7,8 +7,9 @@
 // bisection steps can reach are sorted by construction (the in-order walk of the bisection tree), so a request's
 // share of all of them is: its share of the first one, plus one change at the candidate where it starts to differ.
 // A request that is the same at the first and the last candidate (nearly all of them from the second pass on: the
-// bracket is down to 1/1024) is added to two sums in registers; another one finds its two candidates by bisection,
-// with the operations of the dispatch pass itself, and adds its tokens to their LDS bins.  Prefix sums over the bins
+// bracket is down to 1/1024) is added to two sums in registers; another one finds its two candidates (a guess from their
+// spacing, corrected by bisection where it is not the answer or next to it), with the operations of the dispatch pass
+// itself, and adds its tokens to their LDS bins.  Prefix sums over the bins
 // give every candidate's totals, exact integers, and the walk down the tree records the steps of the plain bisection.
 //
 //   k_bins_init     states, templates, candidates of the first pass; clears the device-wide bins; stages the table

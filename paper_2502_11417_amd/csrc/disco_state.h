@@ -1,5 +1,5 @@
 // Device-resident state shared by the passes of libdisco and the helpers that
-// advance it at the end of a pass (last-ticket workgroup).
+// advance it (between passes, where one opens, or by the workgroup that ends it).
 #pragma once
 #include "disco_common.h"
 #include "disco_device.h"

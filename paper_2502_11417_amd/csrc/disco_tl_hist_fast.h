@@ -8,7 +8,10 @@
 namespace {
 
 constexpr int TH_BLOCK = 1024;               // histogram workgroups: 16 waves share 64 KB of bins
-constexpr unsigned HIST_POOL_BLOCKS = 128;   // (512: 18 and 23 us for the two passes of 10^6 requests x 8 columns, 128: 13 and 14)
+// Workgroups of a pass over the pools alone: each one clears its bins and adds them to the device-wide ones.  Little depends on
+// their number: order statistics with 48 / 128 / as many as walk, at most 256, of 10^4 requests x 8 columns 101 / 99 / 99 us, 10^5 x 8
+// 158 / 152 / 154, 10^5 x 12 waits 239 / 227 / 226, 4 10^5 x 8 204 / 196 / 197, 10^6 x 8 263 / 248 / 249, 10^6 x 12 waits 720 / 686 / 686.
+constexpr unsigned HIST_POOL_BLOCKS = 128;
 
 // ------------------------------------------------------------------ plan ---
 
@@ -255,7 +258,7 @@ __device__ __forceinline__ void tl_hist_fast_body(unsigned* smem, const TraceVie
 {
     const TlSel* tl = &a.S->tl;
     const int width = __builtin_amdgcn_readfirstlane(pl.width);
-    // (a pass over the pools alone takes fewer workgroups: each one clears its bins and adds them to the device-wide ones)
+    // (a pass over the pools alone takes fewer workgroups)
     const bool walks = (__builtin_amdgcn_readfirstlane(pl.walks) & 1) != 0;
     if (!walks && nblk > HIST_POOL_BLOCKS) nblk = HIST_POOL_BLOCKS;
     if (bid >= nblk) return;
